@@ -62,8 +62,8 @@ enum {
      * LDS when it fits; when it does not, large batches are binned by groups of tasks whose part of
      * the index fits and looked up group by group, small ones read it from global memory.  Queries the index cannot decide
      * (its per-slice capacity was exceeded) are finished by a rank-ordered scan inside the same
-     * kernel, so results never depend on the engine.  If more than half of the slices exceed the
-     * capacity when the table is loaded, the exhaustive scan is used instead. */
+     * kernel, so results never depend on the engine.  While more than half of the slices exceed the
+     * capacity, slices are searched in rank order through levels of running extremes instead. */
     INFAAS_SEL_ENGINE_AUTO = 0,
     /* Exhaustive scan only: queries bucketed by (task, batch) slice, slice staged in LDS,
      * feasibility filter and wavefront min-reduction over every variant of the slice. */
@@ -467,7 +467,8 @@ enum {
     INFAAS_SEL_K_HISTOGRAM = 1,  /* scan engine: queries per slice */
     INFAAS_SEL_K_PLAN = 2,       /* scan engine: prefix sums and tile plan */
     INFAAS_SEL_K_SCATTER = 3,    /* scan engine: bucket the queries */
-    INFAAS_SEL_K_SCAN_LDS = 4,   /* scan engine: LDS-staged filter + argmin */
+    INFAAS_SEL_K_SCAN_LDS = 4,   /* scan engine: LDS-staged filter + argmin; automatic mode on a table that the
+                                  * index cannot hold: search of the slices in rank order */
     INFAAS_SEL_K_SCAN_WIDE = 5,  /* scan engine: device-wide path for large slices */
     INFAAS_SEL_K_FINISH_WIDE = 6,/* scan engine: decode the device-wide minima */
     INFAAS_SEL_K_INDEX_BUILD = 7,/* staircase index (re)build */

@@ -100,6 +100,121 @@ __device__ __forceinline__ void body_store(uint8_t *body, int g0, int kb, int la
 
 constexpr int kBuildWaves = 4;                    // slices (wavefronts) per workgroup
 
+// Highest accuracy and lowest latency-plus-queue over entries [lo, hi) of a slice (hi - lo > 0; lo a multiple
+// of 4), for every lane of the wavefront.
+__device__ __forceinline__ void range_extremes(const int32_t *acc, const uint32_t *tot, int32_t lo, int32_t hi, int lane,
+                                               int32_t &mx, uint32_t &mn)
+{
+    mx = INT32_MIN;
+    mn = 0xFFFFFFFFu;
+    for (int32_t i = lo + 4 * lane; i < hi; i += 256) {   // (the entries that pad a slice to a multiple of 4 change nothing)
+        const v4i a = *(const v4i *)(acc + i);
+        const uint4 t = *(const uint4 *)(tot + i);
+        const int32_t a01 = a.x > a.y ? a.x : a.y, a23 = a.z > a.w ? a.z : a.w, m4 = a01 > a23 ? a01 : a23;
+        const uint32_t t01 = t.x < t.y ? t.x : t.y, t23 = t.z < t.w ? t.z : t.w, n4 = t01 < t23 ? t01 : t23;
+        mx = m4 > mx ? m4 : mx;
+        mn = n4 < mn ? n4 : mn;
+    }
+    for (int o = 32; o; o >>= 1) {
+        const int32_t om = __shfl_xor(mx, o);
+        const uint32_t on = __shfl_xor(mn, o);
+        mx = om > mx ? om : mx;
+        mn = on < mn ? on : mn;
+    }
+}
+// 256 keys in ascending order by one wavefront, four per lane (key 4 * lane + j is k[j]).
+__device__ __forceinline__ void sort_keys(unsigned long long (&k)[4], int lane)
+{
+#pragma unroll
+    for (int size = 2; size <= 256; size *= 2) {
+#pragma unroll
+        for (int stride = size / 2; stride > 0; stride /= 2) {
+            if (stride >= 4) {
+                const bool keep_min = ((4 * lane & stride) == 0) == ((4 * lane & size) == 0);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const unsigned long long o = __shfl_xor(k[j], stride / 4);
+                    k[j] = ((o < k[j]) == keep_min) ? o : k[j];
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (j & stride) continue;
+                    const bool up = size >= 4 ? (4 * lane & size) == 0 : (j & size) == 0;
+                    const bool swap = (k[j + stride] < k[j]) == up;
+                    const unsigned long long a = k[j], b = k[j + stride];
+                    k[j] = swap ? b : a;
+                    k[j + stride] = swap ? a : b;
+                }
+            }
+        }
+    }
+}
+// TableView::rank_nodes (`nodes`: the slice's first) of entries [lo, hi) of a slice of L by one wavefront; lo is
+// a multiple of 256, hi too unless it is L; (mx, mn): what entries [0, lo) come to.  Four consecutive
+// entries per lane, so that the scan over the lanes is done once per 256 entries.
+__device__ __forceinline__ void write_rank_nodes(const int32_t *acc, const uint32_t *tot, uint4 *nodes, int32_t L, int32_t lo,
+                                                 int32_t hi, int lane, int32_t mx, uint32_t mn)
+{
+    uint2 *out = (uint2 *)nodes;   // pairs
+    uint4 *sorted = nodes + (int64_t)all_level_nodes(L) * 8;
+    for (int32_t c = lo; c < hi; c += kRankBlock) {
+        const int32_t i = c + 4 * lane;
+        const bool in = i < hi;
+        const v4i a = *(const v4i *)(acc + (in ? i : lo));
+        const uint4 t = *(const uint4 *)(tot + (in ? i : lo));
+        const int32_t a01 = a.x > a.y ? a.x : a.y, a23 = a.z > a.w ? a.z : a.w;
+        const uint32_t t01 = t.x < t.y ? t.x : t.y, t23 = t.z < t.w ? t.z : t.w;
+        int32_t m = in ? (a01 > a23 ? a01 : a23) : INT32_MIN;
+        uint32_t n = in ? (t01 < t23 ? t01 : t23) : 0xFFFFFFFFu;
+        m = m > mx ? m : mx;
+        n = n < mn ? n : mn;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int32_t om = __shfl_up(m, d);
+            const uint32_t on = __shfl_up(n, d);
+            m = (lane >= d && om > m) ? om : m;
+            n = (lane >= d && on < n) ? on : n;
+        }
+        // level 1: the last lane of every four, where the four begin inside the slice
+        if ((lane & 3) == 3 && c + 4 * (lane - 3) < hi) out[(uint32_t)(c >> 4) + (lane >> 2)] = make_uint2((uint32_t)m, n);
+        mx = __builtin_amdgcn_readlane(m, 63);
+        mn = (uint32_t)__builtin_amdgcn_readlane((int)n, 63);
+        if (lane == 0) {   // the levels above, where one of their places ends with this chunk
+            uint32_t at = 0;
+            for (int level = 2; level_nodes(L, level - 1) > 1; ++level) {
+                at += 16u * (uint32_t)level_nodes(L, level - 1);
+                const int64_t end = (int64_t)c + kRankBlock, size = (int64_t)1 << (4 * level);
+                if (end % size == 0 || end >= L) out[at + (uint32_t)((int64_t)c / size)] = make_uint2((uint32_t)mx, mn);
+            }
+        }
+        if (L <= kRankBlock) return;
+        // the block by falling accuracy (equal ones by rising latency), entries past the end of the slice last
+        auto key = [&](int32_t x, uint32_t y) {
+            return in ? ((unsigned long long)(~((uint32_t)x ^ 0x80000000u)) << 32) | y : ~0ull;
+        };
+        unsigned long long k[4] = {key(a.x, t.x), key(a.y, t.y), key(a.z, t.z), key(a.w, t.w)};
+        sort_keys(k, lane);
+        uint32_t low[4];   // the lowest latency up to each of them
+        low[0] = (uint32_t)k[0];
+#pragma unroll
+        for (int j = 1; j < 4; ++j) low[j] = (uint32_t)k[j] < low[j - 1] ? (uint32_t)k[j] : low[j - 1];
+        n = low[3];
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t on = __shfl_up(n, d);
+            n = (lane >= d && on < n) ? on : n;
+        }
+        uint32_t before = __shfl_up(n, 1);
+        before = lane ? before : 0xFFFFFFFFu;
+        uint2 pair[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            pair[j] = make_uint2(~(uint32_t)(k[j] >> 32) ^ 0x80000000u, low[j] < before ? low[j] : before);
+        uint4 *blk = sorted + (int64_t)(c / kRankBlock) * kRankBlockNodes * 8;
+        blk[8 + 2 * lane] = make_uint4(pair[0].x, pair[0].y, pair[1].x, pair[1].y);
+        blk[8 + 2 * lane + 1] = make_uint4(pair[2].x, pair[2].y, pair[3].x, pair[3].y);
+        if ((lane & 3) == 3) ((uint2 *)blk)[lane >> 2] = pair[3];
+    }
+}
 // One wavefront per slice, kBuildWaves slices per workgroup.  An entry of the slice is a step exactly
 // when no entry ranked before it has at least its accuracy and at most its latency-plus-queue; that
 // relation is transitive, so it is enough to test an entry against the earlier STEPS.  The wavefront
@@ -439,6 +554,23 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView tv, 
             if (wave == 0) body_store(body0, 0, k0, lane, st_acc, st_tot, tv.acc_base, r);
             else body_store(body0 + size0, k0, k1, lane, st_acc, st_tot, tv.acc_base, r);
         }
+        if (has && (trunc || !fits)) {   // (the whole workgroup) queries of this slice may go through its entries in rank order
+            const int32_t quarter = (((L + kBuildWaves - 1) / kBuildWaves) + 255) & ~255;
+            const int32_t from = wave * quarter, to = from + quarter < L ? from + quarter : L;
+            int32_t mx = INT32_MIN;
+            uint32_t mn = 0xFFFFFFFFu;
+            range_extremes(accc, totc, from, to, lane, mx, mn);
+            lds_barrier();   // (the parts of the bodies have been read)
+            if (lane == 0) { parts[wave][0][0] = (uint32_t)mx; parts[wave][0][1] = mn; }
+            lds_barrier();
+            mx = INT32_MIN;
+            mn = 0xFFFFFFFFu;
+            for (int w = 0; w < wave; ++w) {
+                mx = (int32_t)parts[w][0][0] > mx ? (int32_t)parts[w][0][0] : mx;
+                mn = parts[w][0][1] < mn ? parts[w][0][1] : mn;
+            }
+            write_rank_nodes(accc, totc, tv.rank_nodes + (uint64_t)tv.rank_hdr[s].z * 8, L, from, to, lane, mx, mn);
+        }
         if (wave != 0) return;   // (no barrier follows)
         if (fits && lane < K) {
             ix.step_row[rec + lane] = row;
@@ -546,6 +678,8 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView tv, 
                 *(uint16_t *)(body0 - 2 - 2 * lane) = (uint16_t)row;
         }
     }
+    if (has && (trunc || !fits))   // (the wavefront) queries of this slice may go through its entries in rank order
+        write_rank_nodes(accc, totc, tv.rank_nodes + (uint64_t)tv.rank_hdr[s].z * 8, L, 0, L, lane, INT32_MIN, 0xFFFFFFFFu);
     if (lane == 0 && inside) {
         if (fits) {
             const uint32_t y = (re0 << kHdrK0Shift) | (re1 << kHdrK1Shift) | (trunc ? kHdrTrunc : 0u) |
@@ -762,6 +896,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
     const int32_t open_n = kSecond ? q.open_count[blockIdx.x] : 0;
     if (kSecond && open_n == 0) {   // the whole workgroup: nothing was left open in its share
         if (tid < kLookupStats) ix.stats[blockIdx.x * kLookupStats + tid] = 0u;
+        if (blockIdx.x == 0 && tid == 0) *ix.stat_used = gridDim.x;
         return;
     }
     const int32_t nunits = ((kSecond ? open_n : q.n) + kUnit - 1) / kUnit;
@@ -1254,6 +1389,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
     }
     __syncthreads();
     if (tid < kLookupStats) ix.stats[blockIdx.x * kLookupStats + tid] = lds_w[4 + tid];
+    if (blockIdx.x == 0 && tid == 0) *ix.stat_used = gridDim.x;
     if (kFirst && tid == 0) q.open_count[blockIdx.x] = (int32_t)s_open;
 }
 
@@ -1275,6 +1411,7 @@ hipError_t launch_index_build(const TableView &tv, const IndexView &ix, hipStrea
 }
 
 int index_select_blocks(int num_cus) { return num_cus; }
+int index_stat_blocks(int num_cus) { return kStatShare * num_cus; }
 
 // Records per workgroup of the lists a first-tier pass over n queries may write: every query of
 // the workgroup's share of the units.

@@ -32,6 +32,20 @@ struct TableView {
     const int32_t *lat_r;       // [B][Vp]
     const int32_t *orig_r;      // [B][Vp] caller row
     const int32_t *gpos;        // [B][Vp] slot -> its entry in the rank-ordered column b
+    // Two search structures over the entries, in rank order, of a slice that the index cannot hold completely,
+    // written by the index build for those slices.  Both are made of nodes of 16 pairs {accuracy,
+    // latency-plus-queue} (128 bytes); rank_hdr names a slice's first.
+    // 1. Levels: how high the accuracy and how low the latency have come from the start of the slice to the
+    //    end of every 16 entries (level 1), of every 256 (level 2), of every 4096, ..., as many levels as it
+    //    takes to get to one node; level 1's nodes come first.  Places past the end of a level hold a pair
+    //    that meets every requirement.
+    // 2. Behind the levels, for slices of more than 256 entries, 17 nodes per 256 entries: the entries by
+    //    falling accuracy, each with the lowest latency so far (nodes 1..16), and the last pair of each of
+    //    those nodes (node 0).
+    // Null without an index.
+    uint4 *rank_nodes;          // [B][rank_stride][8]
+    const uint4 *rank_hdr;      // [S + 1] {first entry of the slice in the rank-ordered columns, divided by 4; its entries; its first
+                                //         node in rank_nodes; unused}; entry S stands for no slice (0 entries)
     int32_t acc_base;           // smallest accuracy in the table; index keys are acc - acc_base + 1
     // State-aware selection: a table serves one state (Active or Inactive).  Variants in another
     // state are masked in the rank-ordered columns (accuracy = acc_base, latency-plus-queue =
@@ -88,6 +102,7 @@ constexpr uint32_t kHdrDeep = 1u << 31;      // a miss in the first body is not 
 constexpr uint32_t kLdsHdrBytes = 8;         // per slice in the lookup kernel's LDS: {body address, y | first step}
 constexpr uint32_t kLdsCtrlBytes = 48;       // control words at the start of the lookup kernel's LDS: 2 next unit, 3 records
                                              // in the open list, 4..8 the statistics below
+constexpr int kStatShare = 8;                // entries of the statistics per compute unit: k_direct_select has that many workgroups on each
 constexpr int kLookupStats = 5;              // per launch and workgroup: queries parked; of those, answered by a second body,
                                              // by a first body read from global memory, sent through the rank-ordered
                                              // scan, and left without an answer
@@ -122,7 +137,8 @@ struct IndexView {
     const uint16_t *task_group;   // [T] group of every task; null when num_groups == 1
     const int32_t *group_task0;   // [num_groups + 1]
     uint32_t *gctrl;              // [2 num_groups] per group: bytes of its region and steps handed out
-    uint32_t *stats;     // [workgroups of the lookup kernel][kLookupStats] what the most recent lookup launch did
+    uint32_t *stats;     // [kStatShare x compute units][kLookupStats] what the most recent lookup launch did
+    uint32_t *stat_used; // entries of `stats` that launch has written
 };
 // Counters of the index build.  Every slice takes its room with one 64-bit add on the pair
 // (kCtlPool, kCtlSteps) and waits for the answer; the statistics live on a cache line of their
@@ -137,6 +153,16 @@ constexpr int kCtlTrunc = 33;     // slices with more steps than the index keeps
 constexpr int kCtlNoBody = 34;    // slices without a body
 constexpr int kCtlMaxK = 35;      // most steps in a slice
 constexpr int kCtlWords = 64;
+// TableView::rank_nodes of a slice of L entries: nodes of a level, of all levels, and of everything.
+constexpr int kRankBlock = 256, kRankBlockNodes = 17;
+__host__ __device__ inline int32_t level_nodes(int32_t L, int level) { return (int32_t)(((int64_t)L + ((int64_t)16 << (4 * level)) - 1) >> (4 * level + 4)); }
+__host__ __device__ inline int32_t all_level_nodes(int32_t L)
+{
+    int32_t sum = 0, n = 2;
+    for (int level = 1; n > 1; ++level) { n = level_nodes(L, level); sum += n; }
+    return sum;
+}
+__host__ __device__ inline int32_t rank_blocks(int32_t L) { return L > kRankBlock ? (int32_t)(((int64_t)L + kRankBlock - 1) / kRankBlock) : 0; }
 // Called by every thread of the first kernel of a selection.
 __device__ __forceinline__ void publish_index_stats(const TableView &tv)
 {
@@ -228,6 +254,11 @@ hipError_t launch_index_build(const TableView &tv, const IndexView &ix, hipStrea
 hipError_t launch_index_select(const TableView &tv, const IndexView &ix, const QueryView &q,
                                int32_t *park_mem, uint32_t lds_bytes, int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
 int index_select_blocks(int num_cus);
+// One lane per query, everything read from global memory (L2): for calls too small to pay for the LDS
+// mirror, and (ranked) for tables most of whose slices the index cannot hold.  Selection only (q.pass 0).
+hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int num_cus,
+                                hipStream_t st, const LaunchEvents *ev = nullptr);
+int index_stat_blocks(int num_cus);               // entries of IndexView::stats
 int32_t index_open_cap(int32_t n, int num_cus);   // records per workgroup of QueryView::open for a pass over n queries
 size_t index_park_bytes(int num_cus);
 

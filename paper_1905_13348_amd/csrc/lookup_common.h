@@ -125,6 +125,151 @@ __device__ __forceinline__ int32_t closest_by_scan(const TableView &tv, int32_t 
     return b_missed < 3 ? tv.orig_r[col + b_pos] : -1;
 }
 
+// The first entry, in rank order, of the slice with rank_hdr entry `rh` that fits (min_acc, bound), as the
+// caller's row or -1; one query per lane (entry S: no query), for slices whose TableView::rank_nodes the index build has written.
+// "The accuracy has come up to min_acc and the latency down to bound" turns true once along a slice and
+// stays true, so the first 16 entries that can hold the answer are found by descending the levels, one
+// node each.  Four lanes read a query's node together (64 bytes at a time, which is what the L1 delivers in
+// a cycle), so that a level costs one line of memory where a bisection by the lane itself would cost up to
+// four.  Those 16 entries are tried in the same manner.  Where accuracy rises and latency falls with the
+// rank the answer is among them.  What is still open goes on from there, the whole wavefront on one query
+// after the other: the rest of the block of 256 entries, then the sorted blocks, eight at a time, which tell
+// exactly whether they hold an entry that fits, then the first one that does.
+// 16M queries on 50 tasks of 2000 variants none of which dominates another: 0.69 ms; the same with the lane's own
+// bisection over a running extreme per entry 1.32 ms, with eight lanes to a node instead of four 0.68 (and 41 us
+// instead of 25 for 1.4M queries on tasks of 81 variants).  Without the sorted blocks the two families of
+// use_ranked() (api.hip) took 3.09 ms per 4M queries instead of 1.33.  What bounds it is scattered reads of L2 lines,
+// two levels, two columns, a row and two headers per query.
+__device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const uint4 &rh, int32_t min_acc, uint32_t bound)
+{
+    const int lane = threadIdx.x & 63, sub = lane & 3, round = lane >> 4;
+    const int back = 4 * (lane & 15);            // where this lane's query is answered in its round
+    const int32_t L = (int32_t)rh.y;
+    int32_t am[4];       // of the query this lane works for in round r
+    uint32_t bd[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        am[r] = __shfl(min_acc, 16 * r + (lane >> 2));
+        bd[r] = (uint32_t)__shfl((int)bound, 16 * r + (lane >> 2));
+    }
+    auto quad = [](int v, int o) {   // the value of the lane 1 or 2 away inside the four
+        return o == 1 ? __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true) : __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);
+    };
+    int top = 1;   // this lane's highest level
+    while (level_nodes(L, top) > 1) ++top;
+    bool open = L > 0;
+    int32_t node = 0;
+    int level = 1;
+    while (__ballot(open && top > level)) ++level;   // the highest of all lanes
+    for (; level >= 1; --level) {
+        const bool here = open && level <= top;
+        uint32_t at = rh.z;
+        for (int i = 1; i < level; ++i) at += (uint32_t)level_nodes(L, i);
+        at = here ? at + (uint32_t)node : 0u;
+        int cnt = 0;   // pairs of the node that do not meet the requirements yet: they come first
+        uint4 v[4][2];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint4 *p = tv.rank_nodes + (uint64_t)(uint32_t)__shfl((int)at, 16 * r + (lane >> 2)) * 8u + (uint32_t)sub;
+            v[r][0] = p[0];
+            v[r][1] = p[4];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            int c = 0;
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                c += (int)((int32_t)v[r][k].x < am[r] || v[r][k].y > bd[r]) + (int)((int32_t)v[r][k].z < am[r] || v[r][k].w > bd[r]);
+            c += quad(c, 1);
+            c += quad(c, 2);
+            c = __shfl(c, back);
+            cnt = round == r ? c : cnt;
+        }
+        if (here) {
+            node = node * 16 + cnt;
+            open = level == 1 ? (int64_t)node * 16 < L : (cnt < 16 && node < level_nodes(L, level - 1));
+        }
+    }
+    int32_t found = -1, from = node * 16;
+    {   // the 16 entries
+        const uint32_t at = open ? rh.x + ((uint32_t)from >> 2) : 0u;
+        const int32_t left = open ? L - from : 0;
+        uint4 a[4], w[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint64_t p = (uint64_t)(uint32_t)__shfl((int)at, 16 * r + (lane >> 2)) + (uint32_t)sub;
+            a[r] = ((const uint4 *)tv.acc_r)[p];
+            w[r] = ((const uint4 *)tv.tot_r)[p];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            uint32_t m = 0x10000u;
+            m |= ((int32_t)a[r].x >= am[r] && w[r].x <= bd[r]) ? 1u : 0u;
+            m |= ((int32_t)a[r].y >= am[r] && w[r].y <= bd[r]) ? 2u : 0u;
+            m |= ((int32_t)a[r].z >= am[r] && w[r].z <= bd[r]) ? 4u : 0u;
+            m |= ((int32_t)a[r].w >= am[r] && w[r].w <= bd[r]) ? 8u : 0u;
+            int f = 4 * sub + __builtin_ctz(m), o = quad(f, 1);   // 16 or more: none of this lane's four
+            f = o < f ? o : f;
+            o = quad(f, 2);
+            f = o < f ? o : f;
+            f = __shfl(f, back);
+            if (round == r && f < 16 && f < left) found = from + f;
+        }
+        open = open && found < 0 && left > 16;
+        from += 16;
+    }
+    uint64_t todo = __ballot(open);
+    while (todo) {
+        const int l = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int32_t lo = __builtin_amdgcn_readlane(from, l), len = __builtin_amdgcn_readlane(L, l);
+        const int32_t qa = __builtin_amdgcn_readlane(min_acc, l);
+        const uint32_t qb = (uint32_t)__builtin_amdgcn_readlane((int)bound, l);
+        const int64_t c = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)rh.x, l) * 4;
+        // the first entry of [lo, hi) that fits, or -1; at most 256 entries, lo a multiple of 4.  (Slices
+        // start at multiples of 4 and are padded to multiples of 4 with entries that never fit.)
+        auto try_block = [&](int32_t first, int32_t hi) -> int32_t {
+            const int32_t pos = first + 4 * lane;
+            const bool in = pos < hi;
+            const uint4 a = *(const uint4 *)(tv.acc_r + c + (in ? pos : 0)), w = *(const uint4 *)(tv.tot_r + c + (in ? pos : 0));
+            uint32_t m = 0;
+            m |= ((int32_t)a.x >= qa && w.x <= qb) ? 1u : 0u;
+            m |= ((int32_t)a.y >= qa && w.y <= qb) ? 2u : 0u;
+            m |= ((int32_t)a.z >= qa && w.z <= qb) ? 4u : 0u;
+            m |= ((int32_t)a.w >= qa && w.w <= qb) ? 8u : 0u;
+            m = in ? m : 0u;
+            const uint64_t any = __ballot(m != 0u);
+            if (!any) return -1;
+            const int f = __builtin_ctzll(any);
+            return first + 4 * f + __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)m, f));
+        };
+        int32_t end = (lo + kRankBlock - 1) & ~(kRankBlock - 1);
+        int32_t hit = lo < end ? try_block(lo, end < len ? end : len) : -1;
+        const int32_t nblk = rank_blocks(len);
+        const uint32_t sorted = (uint32_t)__builtin_amdgcn_readlane((int)rh.z, l) + (uint32_t)all_level_nodes(len);
+        for (int32_t b0 = end / kRankBlock; hit < 0 && b0 < nblk; b0 += 8) {
+            const int32_t blk = b0 + (lane >> 3);
+            const bool in = blk < nblk;
+            const uint4 *p = tv.rank_nodes + ((uint64_t)sorted + (uint64_t)(in ? blk : b0) * kRankBlockNodes) * 8u + (uint32_t)(lane & 7);
+            const uint4 v = *p;   // of the last pair of each node: is the node altogether accurate enough?
+            const bool k0 = (int32_t)v.x >= qa, k1 = (int32_t)v.z >= qa;
+            const uint64_t n0 = __ballot(k0), n1 = __ballot(k1);
+            const int whole = __builtin_popcount((uint32_t)(n0 >> (lane & 56)) & 0xFFu) + __builtin_popcount((uint32_t)(n1 >> (lane & 56)) & 0xFFu);
+            const uint4 u = p[8 * (whole < 16 ? 1 + whole : 16)];
+            bool fits = (k0 && v.y <= qb) || (k1 && v.w <= qb);
+            fits = fits || ((int32_t)u.x >= qa && u.y <= qb) || ((int32_t)u.z >= qa && u.w <= qb);
+            const uint64_t any = __ballot(fits && in);
+            if (any) {
+                const int32_t first = (b0 + (__builtin_ctzll(any) >> 3)) * kRankBlock;
+                hit = try_block(first, first + kRankBlock < len ? first + kRankBlock : len);
+                break;
+            }
+        }
+        if (lane == l) found = hit;
+    }
+    return found >= 0 ? tv.orig_r[(int64_t)rh.x * 4 + found] : -1;
+}
+
 // Accuracy bound in key space: keys are acc - acc_base + 1 >= 1, so the bound is
 // min_acc - acc_base + 1 limited to [1, 65536] (65536 is above every key).
 __device__ __forceinline__ uint32_t acc_threshold(int32_t min_acc, int32_t acc_base_m1)
