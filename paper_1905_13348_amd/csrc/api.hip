@@ -179,8 +179,8 @@ struct infaas_sel {
     void free_index()
     {
         (void)hipFree(ix.pool); (void)hipFree(ix.step_row); (void)hipFree(ix.ctrl);  // hdr lives in pool's allocation
-        (void)hipFree(ix.stats); (void)hipFree(ix.slice_room); (void)hipFree(tv.rank_nodes); (void)hipFree((void *)tv.rank_hdr);
-        tv.rank_nodes = nullptr;
+        (void)hipFree(ix.stats); (void)hipFree(ix.slice_room);
+        tv.rank_nodes = nullptr;   // (in pool's allocation, like rank_hdr)
         tv.rank_hdr = nullptr;
         (void)hipFree((void *)ix.task_group); (void)hipFree((void *)ix.group_task0); (void)hipFree(ix.gctrl);
         (void)hipFree(ix.step_worker); (void)hipFree(ix.hot_worker);
@@ -367,38 +367,39 @@ int create_index(infaas_sel *h)
     // room for the regions of a grouped layout in front of what an ungrouped one needs
     ix.pool_bytes = (uint32_t)std::min<int64_t>(regions + kDummyBodyBytes + S * worst + 64, (int64_t)3 << 30);
     ix.step_cap = (uint32_t)std::min<int64_t>(region_steps + 1 + S * kIndexCap, (int64_t)1 << 29);
-    // one allocation: the pool, then the headers, so that one 32-bit offset reaches both
-    ix.pool_bytes &= ~15u;
-    const size_t nstats = (size_t)index_stat_blocks(h->num_cus) * kLookupStats + 1;   // (the last word: how many entries are in use)
-    bool ok = dev_alloc(&ix.pool, (size_t)ix.pool_bytes + (size_t)(S + 1) * 16) == hipSuccess &&
-              dev_alloc(&ix.step_row, ix.step_cap) == hipSuccess && dev_alloc(&ix.ctrl, kCtlWords) == hipSuccess &&
-              dev_alloc(&ix.stats, nstats) == hipSuccess && dev_alloc(&ix.gctrl, 2 * (size_t)kGroupMaxGroups) == hipSuccess &&
-              dev_alloc(&ix.slice_room, (size_t)S) == hipSuccess;
-    // nodes over the entries of the slices the index cannot hold (TableView::rank_nodes): every place holds a pair
-    // that meets every requirement until a build writes it
-    std::vector<uint32_t> rank_hdr(((size_t)S + 1) * 4, 0u);
+    // the header of an empty slice, and the slices as the search in rank order sees them (TableView::rank_hdr)
+    std::vector<uint32_t> hdrs{0u, kEmptyHdrY, 0u, 4u + body_bytes(2)};
+    hdrs.resize(4 + ((size_t)S + 1) * 4, 0u);
     int64_t nodes = 0;
     {
         std::vector<int32_t> len((size_t)h->T, 0);
         for (int32_t t : h->h_task) len[(size_t)t] += 1;
         int64_t seg = 0;
         for (int32_t t = 0; t < h->T; ++t) {
-            const int32_t L = len[(size_t)t];
-            for (int32_t b = 0; b < h->B; ++b) {
-                uint32_t *e = &rank_hdr[((size_t)t * h->B + b) * 4];
+            const int32_t L = len[(size_t)t], n = all_level_nodes(L) + rank_blocks(L) * kRankBlockNodes;
+            for (int32_t b = 0; b < h->B; ++b, nodes += n) {
+                uint32_t *e = &hdrs[4 + ((size_t)t * h->B + b) * 4];
                 e[0] = (uint32_t)(((int64_t)b * h->Vp + seg) / 4); e[1] = (uint32_t)L; e[2] = (uint32_t)nodes;
-                nodes += all_level_nodes(L) + (int64_t)rank_blocks(L) * kRankBlockNodes;
             }
             seg += (L + 3) & ~3;
         }
     }
-    std::vector<int32_t> pairs((size_t)std::max<int64_t>(nodes, 1) * 32, 0);
-    for (size_t i = 0; i < pairs.size(); i += 2) pairs[i] = INT32_MAX;
-    uint4 *d_rank_hdr = nullptr;
-    ok = ok && dev_alloc(&h->tv.rank_nodes, pairs.size() / 4) == hipSuccess && dev_alloc(&d_rank_hdr, (size_t)S + 1) == hipSuccess;
-    h->tv.rank_hdr = d_rank_hdr;
-    ix.hdr = ok ? (uint4 *)(ix.pool + ix.pool_bytes) : nullptr;
-    ix.stat_used = ok ? ix.stats + nstats - 1 : nullptr;
+    // one allocation: the pool, then the headers, so that one 32-bit offset reaches both; behind them rank_hdr and,
+    // at a multiple of their size, the nodes of TableView::rank_nodes
+    ix.pool_bytes &= ~15u;
+    const size_t rank_at = (size_t)ix.pool_bytes + (size_t)(S + 1) * 16;
+    const size_t nodes_at = (rank_at + (size_t)(S + 1) * 16 + 127) & ~(size_t)127;
+    const size_t nstats = (size_t)index_stat_blocks(h->num_cus) * kLookupStats;   // and one word: how many entries are in use
+    bool ok = dev_alloc(&ix.pool, nodes_at + (size_t)std::max<int64_t>(nodes, 1) * 128) == hipSuccess &&
+              dev_alloc(&ix.step_row, ix.step_cap) == hipSuccess && dev_alloc(&ix.ctrl, kCtlWords) == hipSuccess &&
+              dev_alloc(&ix.stats, nstats + 1) == hipSuccess && dev_alloc(&ix.gctrl, 2 * (size_t)kGroupMaxGroups) == hipSuccess &&
+              dev_alloc(&ix.slice_room, (size_t)S) == hipSuccess;
+    if (ok) {
+        ix.hdr = (uint4 *)(ix.pool + ix.pool_bytes);
+        h->tv.rank_hdr = (const uint4 *)(ix.pool + rank_at);
+        h->tv.rank_nodes = (uint4 *)(ix.pool + nodes_at);
+        ix.stat_used = ix.stats + nstats;
+    }
     h->ix = ix;
     const size_t park = index_park_bytes(h->num_cus);
     ok = ok && dev_alloc(&h->d_park, park / 4) == hipSuccess;
@@ -412,13 +413,10 @@ int create_index(infaas_sel *h)
     uint8_t dummy[kDummyBodyBytes] = {0};
     for (uint32_t i = 8; i < 16; ++i) dummy[i] = 0xFF;  // latency sentinels of the empty body (Re = 2)
     const int32_t none = -1;
-    const uint32_t empty_hdr[4] = {0u, kEmptyHdrY, 0u, 4u + body_bytes(2)};
-    if (!HIP_OK(hipMemset(ix.stats, 0, nstats * 4)) ||
-        !HIP_OK(hipMemcpy(h->tv.rank_nodes, pairs.data(), pairs.size() * 4, hipMemcpyHostToDevice)) ||
-        !HIP_OK(hipMemcpy(d_rank_hdr, rank_hdr.data(), rank_hdr.size() * 4, hipMemcpyHostToDevice)) ||
+    if (!HIP_OK(hipMemset(ix.stat_used, 0, 4)) ||
         !HIP_OK(hipMemcpy(ix.pool, dummy, sizeof(dummy), hipMemcpyHostToDevice)) ||
         !HIP_OK(hipMemcpy(ix.step_row, &none, 4, hipMemcpyHostToDevice)) ||
-        !HIP_OK(hipMemcpy(&ix.hdr[S], empty_hdr, sizeof(empty_hdr), hipMemcpyHostToDevice)) ||
+        !HIP_OK(hipMemcpy(&ix.hdr[S], hdrs.data(), hdrs.size() * 4, hipMemcpyHostToDevice)) ||
         build_index_now(h) != INFAAS_SEL_OK) {
         h->free_index();
         return INFAAS_SEL_ERR_HIP;
@@ -1670,7 +1668,7 @@ int infaas_sel_get_info(infaas_sel_t *h, infaas_sel_info *out)
         out->index_bytes = pool_now + (int64_t)h->T * h->B * 16 + (steps_now + 1) * 4;
         out->index_steps = steps_now;
         // what the most recent lookup launch did with the queries its first probe could not decide
-        std::vector<uint32_t> st((size_t)index_stat_blocks(h->num_cus) * kLookupStats + 1, 0u);
+        std::vector<uint32_t> st((size_t)index_stat_blocks(h->num_cus) * kLookupStats + 1, 0u);   // (its last word: entries in use)
         DeviceGuard g(h->device);
         if (h->last_stats &&
             (!g.ok || !HIP_OK(hipMemcpy(st.data(), h->last_stats, st.size() * 4, hipMemcpyDeviceToHost)))) return INFAAS_SEL_ERR_HIP;

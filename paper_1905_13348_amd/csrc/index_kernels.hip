@@ -187,7 +187,7 @@ __device__ __forceinline__ void write_rank_nodes(const int32_t *acc, const uint3
                 if (end % size == 0 || end >= L) out[at + (uint32_t)((int64_t)c / size)] = make_uint2((uint32_t)mx, mn);
             }
         }
-        if (L <= kRankBlock) return;
+        if (L <= kRankBlock) break;
         // the block by falling accuracy (equal ones by rising latency), entries past the end of the slice last
         auto key = [&](int32_t x, uint32_t y) {
             return in ? ((unsigned long long)(~((uint32_t)x ^ 0x80000000u)) << 32) | y : ~0ull;
@@ -213,6 +213,16 @@ __device__ __forceinline__ void write_rank_nodes(const int32_t *acc, const uint3
         blk[8 + 2 * lane] = make_uint4(pair[0].x, pair[0].y, pair[1].x, pair[1].y);
         blk[8 + 2 * lane + 1] = make_uint4(pair[2].x, pair[2].y, pair[3].x, pair[3].y);
         if ((lane & 3) == 3) ((uint2 *)blk)[lane >> 2] = pair[3];
+    }
+    if (lo < hi && hi == L && lane < 15) {   // the places past the end of every level
+        uint32_t at = 0;
+        for (int level = 1;; ++level) {
+            const int32_t n = level_nodes(L, level);
+            const int64_t place = (((int64_t)L + ((int64_t)1 << (4 * level)) - 1) >> (4 * level)) + lane;
+            if (place < (int64_t)n * 16) out[at + (uint32_t)place] = make_uint2(0x7FFFFFFFu, 0u);
+            if (n <= 1) break;
+            at += 16u * (uint32_t)n;
+        }
     }
 }
 // One wavefront per slice, kBuildWaves slices per workgroup.  An entry of the slice is a step exactly
