@@ -518,10 +518,29 @@ int ensure_open(infaas_sel *h, int64_t n, bool side)
     return INFAAS_SEL_OK;
 }
 
+// Up to this many queries a selection is answered straight from global memory, one lane per query, rather than
+// through an LDS mirror of the index.  The mirror costs its fill (2-4 us, more with many slices) and pays with 4
+// ps per query against 40 (measured, us for 10,000 / 80,000 / 150,000 / 300,000 queries; config 2's table, whole
+// index in LDS: 4.5 / 6.5 / 8.7 / 14.7 direct, 7.7 / 8.0 / 8.1 / 8.2 mirrored; config 1's, 92% of it: 4.2 / 5.8 / 8.1 /
+// 14.3 and 8.8 / 9.0 / 9.7 / 9.4; config 3's, 7%: 4.3 / 7.0 / 9.8 / 17.4 and 16.0 / 17.2 / 17.6 / 20.7).  The less of the
+// index the mirror holds, the later it pays.
+constexpr int64_t kDirectQueries = 100000;
+bool use_direct(const infaas_sel *h, int64_t n)
+{
+    if (h->index_lds_bytes == 0) return n <= kDirectQueries;   // (no mirror, four interleaved queries per lane)
+    const int64_t room = (int64_t)h->index_lds_bytes - kLdsCtrlBytes - lds_header_bytes(h->tv.S);
+    const int64_t pool = h->ix.num_groups > 1 ? h->ix_bytes : h->host_stats ? ((volatile uint32_t *)h->host_stats)[4] : h->ix_stats[kCtlPool];
+    return n <= (pool <= room ? kDirectQueries : kDirectQueries * pool / room);
+}
+
 // One pass of the index engine over n <= 2^28 queries.
 int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
+    if (q.pass == 0 && use_direct(h, q.n)) {
+        if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
+        return INFAAS_SEL_OK;
+    }
     if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->d_park, h->index_lds_bytes, h->num_cus, st, t.ev())))
         return INFAAS_SEL_ERR_HIP;
     return INFAAS_SEL_OK;
@@ -1392,7 +1411,9 @@ int infaas_sel_select_noalloc(infaas_sel_t *h, int64_t N, const int32_t *d_task,
     q.task = d_task; q.slo = d_slo_us; q.min_acc = d_min_acc_bp; q.bidx = d_batch_idx; q.out = d_out_variant;
     q.pass = 0;
     // no event pair even when timing is on: taking one may create it
-    if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->static_park, h->index_lds_bytes, h->num_cus,
+    if (use_direct(h, q.n)) {
+        if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
+    } else if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->static_park, h->index_lds_bytes, h->num_cus,
                                     (hipStream_t)hip_stream, nullptr)))
         return INFAAS_SEL_ERR_HIP;
     h->last_stats = h->ix.stats;
