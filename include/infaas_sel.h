@@ -473,15 +473,15 @@ enum {
     INFAAS_SEL_K_FINISH_WIDE = 6,/* scan engine: decode the device-wide minima */
     INFAAS_SEL_K_INDEX_BUILD = 7,/* staircase index (re)build */
     INFAAS_SEL_K_INDEX_SELECT = 8,/* staircase index lookup, one lane per query */
-    INFAAS_SEL_K_UPDATE_STATE = 9,/* state report: masks of the rank-ordered columns */
+    INFAAS_SEL_K_UPDATE_STATE = 9,/* state report (given, or derived from the instances' states): masks of the rank-ordered columns */
     INFAAS_SEL_K_WORKER_REPORT = 10,/* utilisation and instance-load report */
-    INFAAS_SEL_K_WORKER_TABLES = 11,/* worker of every variant (two kernels) */
+    INFAAS_SEL_K_WORKER_TABLES = 11,/* worker of every variant */
     INFAAS_SEL_K_STEP_WORKERS = 12,/* worker of every step of an index */
     INFAAS_SEL_K_SCALE = 13,     /* scaling decisions */
     INFAAS_SEL_K_GROUP_BIN = 14, /* grouped index: queries binned by group of tasks */
     INFAAS_SEL_K_GROUP_LOOKUP = 15,/* grouped index: lookup, one group's bodies in LDS per workgroup */
     INFAAS_SEL_K_GROUP_FINISH = 16,/* grouped index: answers back into query order */
-    INFAAS_SEL_K_INSTANCE_STATES = 17,/* instance state report and the variants' states derived from it */
+    INFAAS_SEL_K_INSTANCE_STATES = 17,/* instance state report */
     INFAAS_SEL_K_CLOSEST_SCAN = 18,/* closest-variant suggestions by exhaustive scan (no index) */
     INFAAS_SEL_K_SCALE_DOWN = 19,/* scaling-down decisions */
     INFAAS_SEL_K_COUNT = 20

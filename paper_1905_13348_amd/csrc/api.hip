@@ -877,7 +877,7 @@ int infaas_sel_load_variants(infaas_sel_t *h, int32_t V, const int32_t *task_id,
     h->wide_segments = wide;
     h->table_bytes = (int64_t)Vp * 4 * (3 + 8 * (int64_t)B) + ((int64_t)2 * T + 1 + std::max(V, 1)) * 4;
     TableView tv{};
-    tv.T = T; tv.B = B; tv.S = T * B; tv.V = V; tv.Vp = Vp; tv.lds_limit = h->lds_limit;
+    tv.T = T; tv.B = B; tv.S = T * B; tv.V = V; tv.Vp = Vp; tv.lds_limit = h->lds_limit; tv.max_len = max_seg;
     tv.acc = h->d_acc; tv.queue = h->d_queue; tv.orig = h->d_orig; tv.lat = h->d_lat;
     tv.rank = h->d_rank; tv.perm = h->d_perm; tv.seg_off = h->d_seg_off; tv.seg_len = h->d_seg_len;
     tv.slot_of = h->d_slot_of;
@@ -928,13 +928,19 @@ int infaas_sel_update_load(infaas_sel_t *h, int32_t n, const int32_t *d_variant_
 
 namespace {
 
-// Gives the table of `h` the states (device copy of the caller's [V] array) and rebuilds its index.
-int apply_states(infaas_sel *h, const int32_t *d_states, hipStream_t st)
+// A state report (idx null: of all rows) on the tables of both tiers, whose indexes are rebuilt behind it.
+// derive: the states are those the instances' states give.
+int apply_states(infaas_sel *h, infaas_sel *sub, bool derive, int32_t n, const int32_t *d_idx, const int32_t *d_states, hipStream_t st)
 {
-    if (!HIP_OK(launch_update_state(h->tv, h->V, nullptr, d_states, h->have_index ? &h->ix : nullptr, st)))
-        return INFAAS_SEL_ERR_HIP;
-    h->steps_stale = true;
-    if (h->have_index && !HIP_OK(launch_index_build(h->tv, h->ix, st))) return INFAAS_SEL_ERR_HIP;
+    {
+        LaunchTimer t(h, INFAAS_SEL_K_UPDATE_STATE, st);
+        const hipError_t e = derive ? launch_derive_states(h->wv, h->tv, h->ix, sub->tv, sub->ix, st, t.ev())
+                                    : launch_update_state(h->tv, h->ix, sub->tv, sub->ix, n, d_idx, d_states, st, t.ev());
+        if (!HIP_OK(e)) return INFAAS_SEL_ERR_HIP;
+    }
+    h->steps_stale = sub->steps_stale = true;
+    LaunchTimer t(h, INFAAS_SEL_K_INDEX_BUILD, st);
+    if (!HIP_OK(launch_index_build(h->tv, h->ix, sub->tv, sub->ix, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
     return INFAAS_SEL_OK;
 }
 
@@ -986,8 +992,7 @@ int infaas_sel_load_states(infaas_sel_t *h, const int32_t *state, const int32_t 
     if (rc == INFAAS_SEL_OK) {
         h->tv.state = h->d_state; h->tv.want_state = 1;       // Active
         sub->tv.state = sub->d_state; sub->tv.want_state = 0; // Inactive
-        rc = apply_states(h, d_states, nullptr);
-        if (rc == INFAAS_SEL_OK) rc = apply_states(sub, d_states, nullptr);
+        rc = apply_states(h, sub, false, V, nullptr, d_states, nullptr);
         if (rc == INFAAS_SEL_OK && !HIP_OK(hipDeviceSynchronize())) rc = INFAAS_SEL_ERR_HIP;
     }
     (void)hipFree(d_states);
@@ -1014,18 +1019,7 @@ int infaas_sel_update_state(infaas_sel_t *h, int32_t n, const int32_t *d_variant
     if (!d_variant_idx || !d_state) return INFAAS_SEL_ERR_INVALID_ARG;
     DeviceGuard g(h->device);
     if (!g.ok) return INFAAS_SEL_ERR_HIP;
-    hipStream_t st = (hipStream_t)hip_stream;
-    for (infaas_sel *t : {h, h->inactive}) {
-        {
-            LaunchTimer tm(t, INFAAS_SEL_K_UPDATE_STATE, st);
-            if (!HIP_OK(launch_update_state(t->tv, n, d_variant_idx, d_state, &t->ix, st, tm.ev())))
-                return INFAAS_SEL_ERR_HIP;
-        }
-        t->steps_stale = true;
-        LaunchTimer tm(t, INFAAS_SEL_K_INDEX_BUILD, st);
-        if (!HIP_OK(launch_index_build(t->tv, t->ix, st, tm.ev()))) return INFAAS_SEL_ERR_HIP;
-    }
-    return INFAAS_SEL_OK;
+    return apply_states(h, h->inactive, false, n, d_variant_idx, d_state, (hipStream_t)hip_stream);
 }
 
 namespace {
@@ -1105,25 +1099,19 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     if (rc != INFAAS_SEL_OK) return rc;
     if (workers) {
         // bring the worker of every variant, then of every step of both indexes, up to date
-        if (h->workers_dirty) {
-            {
-                LaunchTimer t(h, INFAAS_SEL_K_WORKER_TABLES, st);
-                if (!HIP_OK(launch_best_per_class(h->wv, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
-            }
+        infaas_sel *sub = h->inactive;
+        const bool rows = h->workers_dirty;
+        if (rows) {
             LaunchTimer t(h, INFAAS_SEL_K_WORKER_TABLES, st);
             if (!HIP_OK(launch_worker_tables(h->wv, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
-            h->workers_dirty = false;
-            h->steps_stale = h->inactive->steps_stale = true;
+            h->steps_stale = sub->steps_stale = true;
         }
-        infaas_sel *tables[2] = {h, h->inactive};
-        for (int tier = 0; tier < 2; ++tier) {
-            infaas_sel *t = tables[tier];
-            if (!t->steps_stale) continue;
-            LaunchTimer tm(h, INFAAS_SEL_K_STEP_WORKERS, st);
-            if (!HIP_OK(launch_step_workers(t->ix, h->wv.row_worker + (int64_t)tier * h->V, h->V, st, tm.ev())))
+        if (h->steps_stale || sub->steps_stale) {
+            LaunchTimer t(h, INFAAS_SEL_K_STEP_WORKERS, st);
+            if (!HIP_OK(launch_step_workers(h->wv, h->steps_stale ? &h->ix : nullptr, sub->steps_stale ? &sub->ix : nullptr,
+                                            h->T * h->B, rows, st, t.ev())))
                 return INFAAS_SEL_ERR_HIP;
-            if (!HIP_OK(launch_hot_workers(t->ix, t->T * t->B, st))) return INFAAS_SEL_ERR_HIP;
-            t->steps_stale = false;
+            h->workers_dirty = h->steps_stale = sub->steps_stale = false;
         }
     }
     // The Active tier's lookup writes all result arrays and lists the valid queries it could not
@@ -1308,22 +1296,9 @@ namespace {
 // rebuilt behind it (as after a state report).
 int apply_instance_states(infaas_sel *h, hipStream_t st)
 {
-    {
-        LaunchTimer t(h, INFAAS_SEL_K_INSTANCE_STATES, st);
-        if (!HIP_OK(launch_derive_states(h->wv, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
-    }
-    for (infaas_sel *t : {h, h->inactive}) {
-        {
-            LaunchTimer tm(t, INFAAS_SEL_K_UPDATE_STATE, st);
-            if (!HIP_OK(launch_update_state(t->tv, h->V, nullptr, h->wv.derived, &t->ix, st, tm.ev())))
-                return INFAAS_SEL_ERR_HIP;
-        }
-        t->steps_stale = true;
-        LaunchTimer tm(t, INFAAS_SEL_K_INDEX_BUILD, st);
-        if (!HIP_OK(launch_index_build(t->tv, t->ix, st, tm.ev()))) return INFAAS_SEL_ERR_HIP;
-    }
-    h->workers_dirty = true;
-    return INFAAS_SEL_OK;
+    const int rc = apply_states(h, h->inactive, true, 0, nullptr, nullptr, st);
+    if (rc == INFAAS_SEL_OK) h->workers_dirty = true;
+    return rc;
 }
 
 }  // namespace
@@ -1344,13 +1319,13 @@ int infaas_sel_load_instance_states(infaas_sel_t *h, const int32_t *inst_state)
     if (I > 0 && !HIP_OK(hipMemcpy(pos.data(), h->wv.inst_pos, (size_t)I * 4, hipMemcpyDeviceToHost))) return INFAAS_SEL_ERR_HIP;
     for (int32_t i = 0; i < I; ++i) grouped[(size_t)pos[(size_t)i]] = inst_state[i];
     if (!h->wv.inst_state) {
-        int32_t *d_st = nullptr, *d_der = nullptr;
-        if (dev_alloc(&d_st, (size_t)std::max(I, 1)) != hipSuccess || dev_alloc(&d_der, (size_t)std::max(h->V, 1)) != hipSuccess) {
-            (void)hipFree(d_st); (void)hipFree(d_der); (void)hipGetLastError();
+        int32_t *d_st = nullptr;
+        if (dev_alloc(&d_st, (size_t)std::max(I, 1)) != hipSuccess) {
+            (void)hipGetLastError();
             return INFAAS_SEL_ERR_OOM;
         }
-        h->worker_mem.push_back(d_st); h->worker_mem.push_back(d_der);
-        h->wv.inst_state = d_st; h->wv.derived = d_der;
+        h->worker_mem.push_back(d_st);
+        h->wv.inst_state = d_st;
     }
     if (I > 0 && !HIP_OK(hipMemcpy(h->wv.inst_state, grouped.data(), (size_t)I * 4, hipMemcpyHostToDevice))) return INFAAS_SEL_ERR_HIP;
     h->instance_states = true;

@@ -193,7 +193,9 @@ __device__ __forceinline__ void write_rank_nodes(const int32_t *acc, const uint3
             return in ? ((unsigned long long)(~((uint32_t)x ^ 0x80000000u)) << 32) | y : ~0ull;
         };
         unsigned long long k[4] = {key(a.x, t.x), key(a.y, t.y), key(a.z, t.z), key(a.w, t.w)};
-        sort_keys(k, lane);
+        int ln = lane;
+        asm volatile("" : "+v"(ln));   // (the masks of the sort's stages are made here, every time: before the loop there are too many to keep)
+        sort_keys(k, ln);
         uint32_t low[4];   // the lowest latency up to each of them
         low[0] = (uint32_t)k[0];
 #pragma unroll
@@ -225,6 +227,27 @@ __device__ __forceinline__ void write_rank_nodes(const int32_t *acc, const uint3
         }
     }
 }
+// What write_rank_nodes needs of slice s = (t, b), taken from the kernel's arguments (ta, ia, tb, ib, in this
+// order) where it is needed: kept from the start of the kernel, for the few slices that have a use for it, it
+// pushes other scalars out of their registers.
+struct SliceColumns {
+    const int32_t *acc;
+    const uint32_t *tot;
+    uint4 *nodes;
+    int32_t L;
+};
+template <bool kTwo>
+__device__ __forceinline__ SliceColumns slice_columns(int32_t s, int32_t t, int32_t b)
+{
+    static_assert(sizeof(TableView) % alignof(IndexView) == 0 && sizeof(IndexView) % alignof(TableView) == 0, "no gaps between the arguments");
+    const __attribute__((address_space(4))) char *args = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));   // (reads of the arguments are not moved in front of this)
+    if (kTwo && blockIdx.y) args += sizeof(TableView) + sizeof(IndexView);
+    const __attribute__((address_space(4))) TableView *tv = (const __attribute__((address_space(4))) TableView *)args;
+    const int64_t col = (int64_t)b * tv->Vp + tv->seg_off[t];
+    return SliceColumns{tv->acc_r + col, tv->tot_r + col, tv->rank_nodes + (uint64_t)tv->rank_hdr[s].z * 8, tv->seg_len[t]};
+}
+
 // One wavefront per slice, kBuildWaves slices per workgroup.  An entry of the slice is a step exactly
 // when no entry ranked before it has at least its accuracy and at most its latency-plus-queue; that
 // relation is transitive, so it is enough to test an entry against the earlier STEPS.  The wavefront
@@ -251,9 +274,13 @@ __device__ __forceinline__ void write_rank_nodes(const int32_t *acc, const uint3
 // dependent steps): ONE slice per workgroup.  Its first wavefront finds the steps as above; then all
 // four share the bodies -- each counts and collects over a quarter of the steps, the parts are put
 // together through LDS -- while one of them asks for the room in the pool.
-template <int kBuildPer, bool kShare>
-__global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView tv, IndexView ix)
+// kTwo: workgroups (x, 0) build the index of `ta`, (x, 1) that of `tb` (the two tables of a state-aware handle);
+// otherwise there is only `ta`.
+template <int kBuildPer, bool kShare, bool kTwo>
+__global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, IndexView ia, TableView tb, IndexView ib)
 {
+    const TableView tv = kTwo && blockIdx.y ? tb : ta;
+    const IndexView ix = kTwo && blockIdx.y ? ib : ia;
     constexpr int kBuildChunk = 64 * kBuildPer;   // entries of a slice taken in at a time
     constexpr int kLists = kShare ? 1 : kBuildWaves;   // wavefronts that look for steps
     __shared__ int32_t c_acc_all[kLists][kBuildChunk];    // candidates: accuracy,
@@ -564,12 +591,13 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView tv, 
             if (wave == 0) body_store(body0, 0, k0, lane, st_acc, st_tot, tv.acc_base, r);
             else body_store(body0 + size0, k0, k1, lane, st_acc, st_tot, tv.acc_base, r);
         }
-        if (has && (trunc || !fits)) {   // (the whole workgroup) queries of this slice may go through its entries in rank order
-            const int32_t quarter = (((L + kBuildWaves - 1) / kBuildWaves) + 255) & ~255;
-            const int32_t from = wave * quarter, to = from + quarter < L ? from + quarter : L;
+        if (__builtin_expect(has && (trunc || !fits), 0)) {   // (the whole workgroup) queries of this slice may go through its entries in rank order
+            const SliceColumns sc = slice_columns<kTwo>(s, t, b);
+            const int32_t quarter = (((sc.L + kBuildWaves - 1) / kBuildWaves) + 255) & ~255;
+            const int32_t from = wave * quarter, to = from + quarter < sc.L ? from + quarter : sc.L;
             int32_t mx = INT32_MIN;
             uint32_t mn = 0xFFFFFFFFu;
-            range_extremes(accc, totc, from, to, lane, mx, mn);
+            range_extremes(sc.acc, sc.tot, from, to, lane, mx, mn);
             lds_barrier();   // (the parts of the bodies have been read)
             if (lane == 0) { parts[wave][0][0] = (uint32_t)mx; parts[wave][0][1] = mn; }
             lds_barrier();
@@ -579,7 +607,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView tv, 
                 mx = (int32_t)parts[w][0][0] > mx ? (int32_t)parts[w][0][0] : mx;
                 mn = parts[w][0][1] < mn ? parts[w][0][1] : mn;
             }
-            write_rank_nodes(accc, totc, tv.rank_nodes + (uint64_t)tv.rank_hdr[s].z * 8, L, from, to, lane, mx, mn);
+            write_rank_nodes(sc.acc, sc.tot, sc.nodes, sc.L, from, to, lane, mx, mn);
         }
         if (wave != 0) return;   // (no barrier follows)
         if (fits && lane < K) {
@@ -688,8 +716,10 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView tv, 
                 *(uint16_t *)(body0 - 2 - 2 * lane) = (uint16_t)row;
         }
     }
-    if (has && (trunc || !fits))   // (the wavefront) queries of this slice may go through its entries in rank order
-        write_rank_nodes(accc, totc, tv.rank_nodes + (uint64_t)tv.rank_hdr[s].z * 8, L, 0, L, lane, INT32_MIN, 0xFFFFFFFFu);
+    if (__builtin_expect(has && (trunc || !fits), 0)) {   // (the wavefront) queries of this slice may go through its entries in rank order
+        const SliceColumns sc = slice_columns<kTwo>(s, t, b);
+        write_rank_nodes(sc.acc, sc.tot, sc.nodes, sc.L, 0, sc.L, lane, INT32_MIN, 0xFFFFFFFFu);
+    }
     if (lane == 0 && inside) {
         if (fits) {
             const uint32_t y = (re0 << kHdrK0Shift) | (re1 << kHdrK1Shift) | (trunc ? kHdrTrunc : 0u) |
@@ -1407,17 +1437,40 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
 
 // ---------------------------------------------------------------- launchers
 
-hipError_t launch_index_build(const TableView &tv, const IndexView &ix, hipStream_t st, const LaunchEvents *ev)
+namespace {
+
+template <bool kTwo>
+hipError_t launch_build(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, hipStream_t st,
+                        const LaunchEvents *ev)
 {
-    if (tv.S <= 0) return hipSuccess;
+    constexpr unsigned tables = kTwo ? 2 : 1;
+    if (ta.S <= 0) return hipSuccess;
     const dim3 block(64 * kBuildWaves);
     // few slices of many variants each: one slice per workgroup, its wavefronts share the bodies
-    if (tv.S <= 512 && (int64_t)tv.Vp >= 512 * (int64_t)tv.T)
-        return launch_kernel(ev, k_index_build<32, true>, dim3((unsigned)tv.S), block, 0, st, tv, ix);
-    const dim3 grid((unsigned)((tv.S + kBuildWaves - 1) / kBuildWaves));
+    if (ta.S <= 512 && (int64_t)ta.Vp >= 512 * (int64_t)ta.T)
+        return launch_kernel(ev, k_index_build<32, true, kTwo>, dim3((unsigned)ta.S, tables), block, 0, st, ta, ia, tb, ib);
+    const dim3 grid((unsigned)((ta.S + kBuildWaves - 1) / kBuildWaves), tables);
+    // no slice longer than one chunk: a chunk of that size, whose loops have no idle rounds (us, two tables of 100
+    // tasks of 200 variants x 8: 13.5 with chunks of 4 x 64 entries, 13.7 with 8, 14.7 with 16, 24.8 with 32; one
+    // table of 100 x 500: 21.9, 17.5, 17.8, 19.2)
+    if (ta.max_len <= 256) return launch_kernel(ev, k_index_build<4, false, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
+    if (ta.max_len <= 512) return launch_kernel(ev, k_index_build<8, false, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
     // up to 1024 slices every workgroup is resident at once whatever its size: the larger chunk
-    if (tv.S <= 1024) return launch_kernel(ev, k_index_build<32, false>, grid, block, 0, st, tv, ix);
-    return launch_kernel(ev, k_index_build<16, false>, grid, block, 0, st, tv, ix);
+    if ((int64_t)ta.S * tables <= 1024) return launch_kernel(ev, k_index_build<32, false, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
+    return launch_kernel(ev, k_index_build<16, false, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
+}
+
+}  // namespace
+
+hipError_t launch_index_build(const TableView &tv, const IndexView &ix, hipStream_t st, const LaunchEvents *ev)
+{
+    return launch_build<false>(tv, ix, tv, ix, st, ev);
+}
+
+hipError_t launch_index_build(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, hipStream_t st,
+                              const LaunchEvents *ev)
+{
+    return launch_build<true>(ta, ia, tb, ib, st, ev);
 }
 
 int index_select_blocks(int num_cus) { return num_cus; }

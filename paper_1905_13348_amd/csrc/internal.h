@@ -16,6 +16,7 @@ constexpr int kLdsHistMaxSlices = 8192;   // per-workgroup LDS histogram up to t
 struct TableView {
     int32_t T, B, S, V, Vp;
     int32_t lds_limit;          // variants per staged chunk; segments above it take the wide path
+    int32_t max_len;            // most variants of a task
     const int32_t *acc;         // [Vp]
     int32_t *queue;             // [Vp]
     const int32_t *orig;        // [Vp] caller row of each slot
@@ -227,9 +228,10 @@ inline hipError_t launch_kernel(const LaunchEvents *ev, void (*kernel)(P...), di
 // index: the index that is rebuilt afterwards (its allocator counters are rewound), or null.
 hipError_t launch_update_load(const TableView &tv, int32_t n, const int32_t *idx,
                               const int32_t *val, const IndexView *index, hipStream_t st, const LaunchEvents *ev = nullptr);
-// State report: state of row idx[i] := val[i] (idx null: row i, all V rows), masks refreshed.
-hipError_t launch_update_state(const TableView &tv, int32_t n, const int32_t *idx,
-                               const int32_t *val, const IndexView *index, hipStream_t st, const LaunchEvents *ev = nullptr);
+// State report on the two tables of a state-aware handle (Active tier, Inactive tier): the state of row idx[i]
+// becomes val[i] (idx null: of row i), masks refreshed, both indexes rewound.
+hipError_t launch_update_state(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, int32_t n,
+                               const int32_t *idx, const int32_t *val, hipStream_t st, const LaunchEvents *ev = nullptr);
 hipError_t launch_histogram(const TableView &tv, const QueryView &q, const ScanScratch &sc,
                             hipStream_t st, const LaunchEvents *ev = nullptr);
 hipError_t launch_plan(const TableView &tv, const ScanScratch &sc, hipStream_t st, const LaunchEvents *ev = nullptr);
@@ -248,6 +250,9 @@ hipError_t launch_closest_scan(const TableView &tv, const QueryView &q, int num_
 
 // Kernel launchers (staircase index).
 hipError_t launch_index_build(const TableView &tv, const IndexView &ix, hipStream_t st, const LaunchEvents *ev = nullptr);
+// Both tables of a state-aware handle in one launch.
+hipError_t launch_index_build(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, hipStream_t st,
+                              const LaunchEvents *ev = nullptr);
 // lds_bytes: dynamic LDS of the lookup kernel when the index is mirrored in LDS, 0 to read it
 // from global memory.  park_mem: index_park_bytes() of device memory (16-byte aligned) for the
 // queues of parked queries; its size does not depend on the number of queries.
@@ -293,7 +298,6 @@ struct WorkerView {
     const int32_t *inst_worker;   // [I]     ... their workers
     int32_t *inst_load;           // [I]     ... their loads
     int32_t *inst_state;          // [I]     ... their states (Active, Overloaded, Interfered), or null: all Active
-    int32_t *derived;             // [V] with instance states: the state of every variant as its instances give it
     const int32_t *inst_pos;      // [I] caller's instance number -> position in the grouped arrays
     int32_t *best_cls;            // [H] least-utilised worker of every class
     int32_t *row_worker;          // [2 V] worker by caller row: for an Active answer, then for an Inactive one
@@ -306,17 +310,16 @@ hipError_t launch_worker_report(const WorkerView &wv, int32_t n, const int32_t *
 // code that is not Active, Overloaded or Interfered are skipped.
 hipError_t launch_instance_state_report(const WorkerView &wv, int32_t n, const int32_t *inst_idx, const int32_t *state,
                                         hipStream_t st, const LaunchEvents *ev = nullptr);
-// wv.derived from wv.inst_state: Inactive without instances, Active with an Active one, else Overloaded if
-// some instance is, else Interfered.
-hipError_t launch_derive_states(const WorkerView &wv, hipStream_t st, const LaunchEvents *ev = nullptr);
-// best_cls, then row_worker, from the current utilisations and loads (in this order).
-hipError_t launch_best_per_class(const WorkerView &wv, hipStream_t st, const LaunchEvents *ev = nullptr);
+// As launch_update_state for all rows, with the states that the instances' states give: Inactive without
+// instances, Active with an Active one, else Overloaded if some instance is, else Interfered.
+hipError_t launch_derive_states(const WorkerView &wv, const TableView &ta, const IndexView &ia, const TableView &tb,
+                                const IndexView &ib, hipStream_t st, const LaunchEvents *ev = nullptr);
+// best_cls and the Active half of row_worker from the current utilisations and loads.
 hipError_t launch_worker_tables(const WorkerView &wv, hipStream_t st, const LaunchEvents *ev = nullptr);
-// ix.step_worker[j] = row_worker[ix.step_row[j]] for every step of the index (row_worker: num_rows entries).
-hipError_t launch_step_workers(const IndexView &ix, const int32_t *row_worker, int32_t num_rows, hipStream_t st,
-                               const LaunchEvents *ev = nullptr);
-// ix.hot_worker from ix.step_worker (num_slices = S of the table the index belongs to); no-op without hot_worker.
-hipError_t launch_hot_workers(const IndexView &ix, int32_t num_slices, hipStream_t st, const LaunchEvents *ev = nullptr);
+// Behind it: the worker of every step of the two tables' indexes (ia, ib; null: that one is left alone) and the
+// hot_worker copies (num_slices = S of the tables); rows: also the Inactive half of row_worker.
+hipError_t launch_step_workers(const WorkerView &wv, const IndexView *ia, const IndexView *ib, int32_t num_slices, bool rows,
+                               hipStream_t st, const LaunchEvents *ev = nullptr);
 
 // Scaling decision on a change in load (Section 4.2.2).
 // Everything a request reads sits in ONE 128-byte block per (batch size, caller row) -- 32 words:

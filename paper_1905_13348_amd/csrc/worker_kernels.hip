@@ -6,8 +6,11 @@
 // The worker depends on the variant and its tier only, not on the query.  So these kernels keep a
 // worker per variant up to date (k_worker_tables, from the reports applied by k_worker_report) and
 // copy it next to every step of the staircase indexes (k_step_workers); the lookup kernel then
-// fetches the worker of an answer with the same gather that fetches its row.
+// fetches the worker of an answer with the same gather that fetches its row.  All of it is bound by
+// launches and latency (a few hundred KB), hence two launches, as many as there are dependencies.
 #include "internal.h"
+
+#include <algorithm>
 
 namespace infaas {
 
@@ -42,23 +45,6 @@ __global__ __launch_bounds__(kThreads) void k_instance_state_report(WorkerView w
     if ((uint32_t)j < (uint32_t)wv.I && c >= 1 && c <= 3) wv.inst_state[wv.inst_pos[j]] = c;
 }
 
-// One lane per variant: its state as its instances give it (Section 4 keeps the state machine per
-// variant instance): Inactive when it runs nowhere, Active when some instance is, else Overloaded when
-// some instance is, else Interfered.
-__global__ __launch_bounds__(kThreads) void k_derive_states(WorkerView wv)
-{
-    const int32_t v = (int32_t)(blockIdx.x * kThreads + threadIdx.x);
-    if (v >= wv.V) return;
-    const int32_t lo = wv.inst_off[v], hi = wv.inst_off[v + 1];
-    bool active = false, overloaded = false;
-    for (int32_t i = lo; i < hi; ++i) {
-        const int32_t c = wv.inst_state[i];
-        active = active || c == 1;
-        overloaded = overloaded || c == 2;
-    }
-    wv.derived[v] = hi == lo ? 0 : (active ? 1 : (overloaded ? 2 : 3));
-}
-
 __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v)
 {
 #pragma unroll
@@ -69,79 +55,80 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v)
     return v;
 }
 
-// One workgroup per hardware class: the worker with the smallest (utilisation, number).
-__global__ __launch_bounds__(kThreads) void k_best_per_class(WorkerView wv)
-{
-    __shared__ uint64_t s_best[kThreads / 64];
-    const int32_t c = (int32_t)blockIdx.x;
-    const int32_t lo = wv.cls_off[c], hi = wv.cls_off[c + 1];
-    uint64_t best = ~0ull;
-    for (int32_t i = lo + (int32_t)threadIdx.x; i < hi; i += kThreads) {
-        const int32_t w = wv.cls_worker[i];
-        const uint64_t key = ((uint64_t)(uint32_t)wv.util[w] << 32) | (uint32_t)w;   // utilisation is never negative
-        best = key < best ? key : best;
-    }
-    best = wave_min_u64(best);
-    if ((threadIdx.x & 63) == 0) s_best[threadIdx.x >> 6] = best;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 1; k < kThreads / 64; ++k) best = s_best[k] < best ? s_best[k] : best;
-        wv.best_cls[c] = hi > lo ? (int32_t)(uint32_t)best : -1;
-    }
-}
-
-// One lane per variant: the worker of its instance with the smallest (load, worker) -- of its Active
-// instances, when the instances carry states -- and the best worker of its hardware class.
+// The first H workgroups, one per hardware class: the worker with the smallest (utilisation, number).
+// The others, one lane per variant: the worker of its instance with the smallest (load, worker) -- of its
+// Active instances, when the instances carry states.
 __global__ __launch_bounds__(kThreads) void k_worker_tables(WorkerView wv)
 {
-    const int32_t v = (int32_t)(blockIdx.x * kThreads + threadIdx.x);
-    if (v >= wv.V) return;
+    __shared__ uint64_t s_best[kThreads / 64];
     uint64_t best = ~0ull;
+    if ((int32_t)blockIdx.x < wv.H) {
+        const int32_t c = (int32_t)blockIdx.x;
+        const int32_t lo = wv.cls_off[c], hi = wv.cls_off[c + 1];
+        for (int32_t i = lo + (int32_t)threadIdx.x; i < hi; i += kThreads) {
+            const int32_t w = wv.cls_worker[i];
+            const uint64_t key = ((uint64_t)(uint32_t)wv.util[w] << 32) | (uint32_t)w;   // utilisation is never negative
+            best = key < best ? key : best;
+        }
+        best = wave_min_u64(best);
+        if ((threadIdx.x & 63) == 0) s_best[threadIdx.x >> 6] = best;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int k = 1; k < kThreads / 64; ++k) best = s_best[k] < best ? s_best[k] : best;
+            wv.best_cls[c] = hi > lo ? (int32_t)(uint32_t)best : -1;
+        }
+        return;
+    }
+    const int32_t v = (int32_t)((blockIdx.x - (uint32_t)wv.H) * kThreads + threadIdx.x);
+    if (v >= wv.V) return;
     for (int32_t i = wv.inst_off[v]; i < wv.inst_off[v + 1]; ++i) {
         if (wv.inst_state && wv.inst_state[i] != 1) continue;
         const uint64_t key = ((uint64_t)(uint32_t)wv.inst_load[i] << 32) | (uint32_t)wv.inst_worker[i];
         best = key < best ? key : best;
     }
     wv.row_worker[v] = best != ~0ull ? (int32_t)(uint32_t)best : -1;
-    const int32_t c = wv.var_cls[v];
-    wv.row_worker[wv.V + v] = c >= 0 ? wv.best_cls[c] : -1;
 }
 
-// Entries of step_row that a slice reserved but could not fill hold no row: anything outside
-// 0..num_rows-1 gets no worker.
-__global__ __launch_bounds__(kThreads) void k_step_workers(IndexView ix, const int32_t *__restrict__ row_worker,
-                                                           int32_t num_rows)
+// Workgroups (x, 0) serve the Active tier's index, (x, 1) the Inactive tier's (step_worker null: left alone):
+// the worker of every step in use, and of the hot steps once more in 16 bits, as the lookup kernel keeps them
+// in LDS.  Entries of step_row that a slice reserved but could not fill hold no row: anything outside 0..V-1
+// gets no worker.  Places past a slice's last step are never read by the lookup.  rows: the second half of
+// row_worker as well, the best worker of every variant's hardware class.
+__global__ __launch_bounds__(kThreads) void k_step_workers(WorkerView wv, IndexView ia, IndexView ib, int32_t num_slices, int rows)
 {
-    const uint32_t j = blockIdx.x * kThreads + threadIdx.x;
-    const uint32_t steps = ix.ctrl[kCtlSteps];   // entries of step_row in use (entry 0 included)
-    if (j >= steps || j >= ix.step_cap) return;
-    const int32_t row = ix.step_row[j];
-    ix.step_worker[j] = (uint32_t)row < (uint32_t)num_rows ? row_worker[row] : -1;
-}
-
-// One lane per (slice, hot step): the 16-bit copy of the step's worker that the lookup kernel keeps
-// in LDS.  Places past the slice's last step are never read by the lookup.
-__global__ __launch_bounds__(kThreads) void k_hot_workers(IndexView ix, int32_t num_slices)
-{
-    const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
-    if (i >= (uint32_t)num_slices * ix.hot_rows) return;
-    const uint32_t s = i / ix.hot_rows, step = i - s * ix.hot_rows;
-    const uint4 hdr = ix.hdr[s];
-    const uint32_t at = hdr.z + step;   // the slice's first entry in step_row / step_worker, plus the step
-    const int32_t w = ((hdr.y & kHdrPark) || at >= ix.step_cap) ? -1 : ix.step_worker[at];
-    ix.hot_worker[i] = (uint32_t)w < 0xFFFFu ? (uint16_t)w : (uint16_t)0xFFFFu;
+    const bool second = blockIdx.y != 0;
+    const uint32_t *ctrl = second ? ib.ctrl : ia.ctrl;
+    const int32_t *step_row = second ? ib.step_row : ia.step_row;
+    int32_t *step_worker = second ? ib.step_worker : ia.step_worker;
+    uint16_t *hot_worker = second ? ib.hot_worker : ia.hot_worker;
+    const uint4 *hdr = second ? ib.hdr : ia.hdr;
+    const uint32_t cap = second ? ib.step_cap : ia.step_cap, hot_rows = second ? ib.hot_rows : ia.hot_rows;
+    const uint32_t first = blockIdx.x * kThreads + threadIdx.x, stride = gridDim.x * kThreads;
+    auto class_worker = [&](int32_t row) {
+        const int32_t c = wv.var_cls[row];
+        return c >= 0 ? wv.best_cls[c] : -1;
+    };
+    auto worker = [&](uint32_t at) {
+        const int32_t row = step_row[at];
+        return (uint32_t)row >= (uint32_t)wv.V ? -1 : second ? class_worker(row) : wv.row_worker[row];
+    };
+    if (second && rows)
+        for (uint32_t v = first; v < (uint32_t)wv.V; v += stride) wv.row_worker[wv.V + v] = class_worker((int32_t)v);
+    if (!step_worker) return;
+    const uint32_t used = ctrl[kCtlSteps];   // entries of step_row in use (entry 0 included)
+    for (uint32_t j = first; j < used && j < cap; j += stride) step_worker[j] = worker(j);
+    if (!hot_worker) return;
+    for (uint32_t i = first; i < (uint32_t)num_slices * hot_rows; i += stride) {
+        const uint32_t s = i / hot_rows, step = i - s * hot_rows;
+        const uint4 h = hdr[s];
+        const uint32_t at = h.z + step;   // the slice's first entry in step_row / step_worker, plus the step
+        const int32_t w = ((h.y & kHdrPark) || at >= cap) ? -1 : worker(at);
+        hot_worker[i] = (uint32_t)w < 0xFFFFu ? (uint16_t)w : (uint16_t)0xFFFFu;
+    }
 }
 
 }  // namespace
-
-hipError_t launch_hot_workers(const IndexView &ix, int32_t num_slices, hipStream_t st, const LaunchEvents *ev)
-{
-    const int64_t n = (int64_t)num_slices * ix.hot_rows;
-    if (!ix.hot_worker || n <= 0) return hipSuccess;
-    return launch_kernel(ev, k_hot_workers, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, ix,
-                         num_slices);
-}
 
 hipError_t launch_worker_report(const WorkerView &wv, int32_t n, const int32_t *worker_idx, const int32_t *util,
                                 int32_t m, const int32_t *inst_idx, const int32_t *load, hipStream_t st,
@@ -161,30 +148,21 @@ hipError_t launch_instance_state_report(const WorkerView &wv, int32_t n, const i
                          wv, n, inst_idx, state);
 }
 
-hipError_t launch_derive_states(const WorkerView &wv, hipStream_t st, const LaunchEvents *ev)
-{
-    if (wv.V <= 0 || !wv.inst_state || !wv.derived) return hipSuccess;
-    return launch_kernel(ev, k_derive_states, dim3((unsigned)((wv.V + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, wv);
-}
-
-hipError_t launch_best_per_class(const WorkerView &wv, hipStream_t st, const LaunchEvents *ev)
-{
-    if (wv.H <= 0) return hipSuccess;
-    return launch_kernel(ev, k_best_per_class, dim3((unsigned)wv.H), dim3(kThreads), 0, st, wv);
-}
-
 hipError_t launch_worker_tables(const WorkerView &wv, hipStream_t st, const LaunchEvents *ev)
 {
-    if (wv.V <= 0) return hipSuccess;
-    return launch_kernel(ev, k_worker_tables, dim3((unsigned)((wv.V + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, wv);
+    const int64_t blocks = (int64_t)wv.H + ((int64_t)wv.V + kThreads - 1) / kThreads;
+    if (blocks <= 0) return hipSuccess;
+    return launch_kernel(ev, k_worker_tables, dim3((unsigned)blocks), dim3(kThreads), 0, st, wv);
 }
 
-hipError_t launch_step_workers(const IndexView &ix, const int32_t *row_worker, int32_t num_rows, hipStream_t st,
-                               const LaunchEvents *ev)
+hipError_t launch_step_workers(const WorkerView &wv, const IndexView *ia, const IndexView *ib, int32_t num_slices, bool rows,
+                               hipStream_t st, const LaunchEvents *ev)
 {
-    // the number of steps in use is known on the device only: one lane per entry there is room for
-    return launch_kernel(ev, k_step_workers, dim3((ix.step_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, st, ix,
-                         row_worker, num_rows);
+    // the number of steps in use is known on the device only; a slice has at most kIndexCap
+    const int64_t work = std::max<int64_t>((int64_t)num_slices * kIndexCap, wv.V);
+    const int64_t blocks = std::min<int64_t>((work + kThreads - 1) / kThreads, 1024);
+    return launch_kernel(ev, k_step_workers, dim3((unsigned)std::max<int64_t>(blocks, 1), 2), dim3(kThreads), 0, st, wv,
+                         ia ? *ia : IndexView{}, ib ? *ib : IndexView{}, num_slices, rows ? 1 : 0);
 }
 
 }  // namespace infaas

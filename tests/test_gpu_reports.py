@@ -1,0 +1,56 @@
+"""State reports applied to both tiers' tables in one launch (64 / B entries of a report per wavefront) and
+both indexes built in one: batch-size counts that divide 64 and that do not, slices around the sizes of the
+build's chunks (256, 512, 1024, 2048 entries), reports that change a state, repeat it, or must be
+skipped; every element of variant, tier and worker against the CPU oracle."""
+import numpy as np
+import pytest
+
+from gpu_util import make_selector, table_args, to_dev
+from test_gpu_instances import _check as check_instances
+from test_gpu_parity import _random_queries, _random_table, _table
+from test_gpu_workers import _check as check_workers, _random_cluster, load_cluster
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,sizes", [(1, (255, 256, 3)), (3, (257, 0, 40)), (5, (511, 512)), (7, (513, 1, 90)), (8, (64, 65, 1)),
+                                     (33, (20, 31)), (64, (5, 33)), (2, (1024, 1025)), (2, (2048, 2049))],
+                         ids=lambda v: str(v).replace(" ", ""))
+def test_state_reports(oracle_lib, B, sizes):
+    rng = np.random.default_rng(B * 1000 + sum(sizes))
+    T = len(sizes)
+    tb = _random_table(rng, T, np.asarray(sizes), min(B, 8))
+    if B > 8:   # more batch sizes than the generator has: its columns over again, a little slower every time
+        again = np.arange(B)
+        tb = _table(T, list(range(1, B + 1)), tb.task_id, tb.acc_bp, tb.lat_us[:, again % 8] + again // 8, tb.cost[:, again % 8], tb.queue_us)
+    state, load = rng.integers(0, 4, tb.V).astype(np.int32), rng.integers(0, 40_000, tb.V).astype(np.int32)
+    cl = _random_cluster(rng, tb.V, state, 1000)
+    qs = _random_queries(rng, T, B, 6000)
+    sel = make_selector(tb, engine=0)
+    sel.load_states(state, load)
+    load_cluster(sel, cl)
+    state, queue = state.copy(), tb.queue_us.copy()
+    for rnd in range(3):
+        n = int(rng.integers(1, tb.V + 1))
+        rows, vals = rng.choice(tb.V, n, replace=False).astype(np.int32), rng.integers(0, 4, n).astype(np.int32)
+        keep = rng.random(n) < 0.3
+        vals[keep] = state[rows[keep]]                      # reported, but not changed
+        if n > 3:
+            rows[:2], vals[2] = (-1, tb.V), 4               # skipped
+        sel.update_state(to_dev(rows), to_dev(vals))
+        oracle_lib.update_state(state, rows, vals)
+        up, q = rng.choice(tb.V, tb.V // 2 + 1, replace=False).astype(np.int32), rng.integers(0, 50_000, tb.V // 2 + 1).astype(np.int32)
+        sel.update_load(to_dev(up), to_dev(q))
+        oracle_lib.update_load(queue, up, q)
+        check_workers(oracle_lib, sel, tb, state, load, cl, qs, f"B={B} {sizes} states {rnd}", queue)
+    ist = rng.choice([1, 2, 3], max(len(cl[3]), 1))[:len(cl[3])].astype(np.int32)
+    sel.load_instance_states(ist)
+    for rnd in range(2):
+        check_instances(oracle_lib, sel, tb, load, cl, ist, qs, f"B={B} {sizes} instances {rnd}", queue)
+        if not len(ist):
+            break
+        idx, val = rng.choice(len(ist), len(ist) // 3 + 1, replace=False).astype(np.int32), rng.integers(0, 4, len(ist) // 3 + 1).astype(np.int32)
+        sel.update_instance_states(to_dev(idx), to_dev(val))
+        ok = val >= 1
+        ist[idx[ok]] = val[ok]
+    sel.destroy()
