@@ -20,6 +20,8 @@
 #include "internal.h"
 #include "lookup_common.h"
 
+#include <type_traits>
+
 namespace infaas {
 
 namespace {
@@ -251,7 +253,7 @@ __device__ __forceinline__ SliceColumns slice_columns(int32_t s, int32_t t, int3
 // One wavefront per slice, kBuildWaves slices per workgroup.  An entry of the slice is a step exactly
 // when no entry ranked before it has at least its accuracy and at most its latency-plus-queue; that
 // relation is transitive, so it is enough to test an entry against the earlier STEPS.  The wavefront
-// takes in a chunk of the rank-ordered columns, kBuildPer (32 or 16) entries per lane, in registers.  Then
+// takes in a chunk of the rank-ordered columns, kBuildPer (4, 8 or 16) entries per lane, in registers.  Then
 //   1. (first chunk) the steps among the first 64 entries: the first of them is a step (nothing
 //      earlier is left), it retires what it dominates among the 64, the next one left is a step, ...;
 //   2. a coarse filter: from the steps known so far, a table over ~32 accuracy buckets of the lowest
@@ -266,40 +268,30 @@ __device__ __forceinline__ SliceColumns slice_columns(int32_t s, int32_t t, int3
 // Steps come out in rank order, so when a slice has more than the index keeps, the ones kept are
 // its first ones.  The steps sit one per lane (and in LDS); the same wavefront computes the bodies.
 // Room in the pool is taken by ONE 64-bit add per workgroup (with one per slice, every slice waited
-// microseconds for its turn at the counter).  The larger chunk is faster for slices of thousands of
-// variants; the smaller one takes half the LDS and registers, so that twice as many workgroups run
-// at a time when there are thousands of slices.
-//
-// kShare (few slices of thousands of variants each, where the time is one slice's chain of
-// dependent steps): ONE slice per workgroup.  Its first wavefront finds the steps as above; then all
-// four share the bodies -- each counts and collects over a quarter of the steps, the parts are put
-// together through LDS -- while one of them asks for the room in the pool.
+// microseconds for its turn at the counter).
 // kTwo: workgroups (x, 0) build the index of `ta`, (x, 1) that of `tb` (the two tables of a state-aware handle);
 // otherwise there is only `ta`.
-template <int kBuildPer, bool kShare, bool kTwo>
+template <int kBuildPer, bool kTwo>
 __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, IndexView ia, TableView tb, IndexView ib)
 {
     const TableView tv = kTwo && blockIdx.y ? tb : ta;
     const IndexView ix = kTwo && blockIdx.y ? ib : ia;
     constexpr int kBuildChunk = 64 * kBuildPer;   // entries of a slice taken in at a time
-    constexpr int kLists = kShare ? 1 : kBuildWaves;   // wavefronts that look for steps
-    __shared__ int32_t c_acc_all[kLists][kBuildChunk];    // candidates: accuracy,
-    __shared__ uint32_t c_tot_all[kLists][kBuildChunk];   //   latency + queue,
-    __shared__ uint16_t c_pos_all[kLists][kBuildChunk];   //   position in the chunk
-    __shared__ int32_t p_acc_all[kLists][64];             // steps, in rank order
-    __shared__ uint32_t p_tot_all[kLists][64];
-    __shared__ int32_t p_pos_all[kLists][64];
-    __shared__ uint32_t f_tab_all[kLists][64];            // the coarse filter's table
-    __shared__ int32_t ranks_all[kLists][128];            // scratch of body_compute; kShare: the steps' places in their bodies
-    __shared__ uint32_t parts[kShare ? kBuildWaves : 1][4][64];   // kShare: what each wavefront found over its quarter of the steps
+    __shared__ int32_t c_acc_all[kBuildWaves][kBuildChunk];    // candidates: accuracy,
+    __shared__ uint32_t c_tot_all[kBuildWaves][kBuildChunk];   //   latency + queue,
+    __shared__ uint16_t c_pos_all[kBuildWaves][kBuildChunk];   //   position in the chunk
+    __shared__ int32_t p_acc_all[kBuildWaves][64];             // steps, in rank order
+    __shared__ uint32_t p_tot_all[kBuildWaves][64];
+    __shared__ int32_t p_pos_all[kBuildWaves][64];
+    __shared__ uint32_t f_tab_all[kBuildWaves][64];            // the coarse filter's table
+    __shared__ int32_t ranks_all[kBuildWaves][128];            // scratch of body_compute
     __shared__ uint32_t s_size[kBuildWaves], s_steps[kBuildWaves], s_stat[4];
     __shared__ uint32_t s_group[kBuildWaves], s_off[kBuildWaves], s_rec[kBuildWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int mine = kShare ? 0 : wave;                   // the lists this wavefront works on
-    int32_t *c_acc = c_acc_all[mine], *p_acc = p_acc_all[mine], *p_pos = p_pos_all[mine];
-    uint32_t *c_tot = c_tot_all[mine], *p_tot = p_tot_all[mine], *f_tab = f_tab_all[mine];
-    uint16_t *c_pos = c_pos_all[mine];
-    const int32_t s = kShare ? (int32_t)blockIdx.x : (int32_t)blockIdx.x * kBuildWaves + wave;
+    int32_t *c_acc = c_acc_all[wave], *p_acc = p_acc_all[wave], *p_pos = p_pos_all[wave];
+    uint32_t *c_tot = c_tot_all[wave], *p_tot = p_tot_all[wave], *f_tab = f_tab_all[wave];
+    uint16_t *c_pos = c_pos_all[wave];
+    const int32_t s = (int32_t)blockIdx.x * kBuildWaves + wave;
     const bool inside = s < tv.S;
     const int32_t t = inside ? s / tv.B : 0, b = inside ? s - t * tv.B : 0;
     const int32_t seg = tv.seg_off[t], L = inside ? tv.seg_len[t] : 0;
@@ -334,7 +326,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
         st_tot = lane < K ? p_tot[lane] : 0u;
         st_pos = lane < K ? p_pos[lane] : 0;
     };
-    for (int32_t c0 = 0; c0 < L && !trunc && (!kShare || wave == 0); c0 += kBuildChunk) {
+    for (int32_t c0 = 0; c0 < L && !trunc; c0 += kBuildChunk) {
         const int32_t n = L - c0 < kBuildChunk ? L - c0 : kBuildChunk;
         int32_t va[kBuildPer];
         uint32_t vt[kBuildPer];
@@ -453,192 +445,6 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
         }
     }
 
-    if constexpr (kShare) {
-        // ---- phase B with one slice per workgroup: the steps are in LDS (p_acc / p_tot / p_pos);
-        // wavefront w counts and collects over steps [w q, w q + q), q = K / 4 rounded up
-        if (wave == 0 && lane == 0) { s_steps[0] = (uint32_t)K; s_size[0] = trunc ? 1u : 0u; }
-        lds_barrier();
-        K = (int32_t)s_steps[0];
-        trunc = s_size[0] != 0u;
-        st_acc = lane < K ? p_acc[lane] : 0;
-        st_tot = lane < K ? p_tot[lane] : 0u;
-        st_pos = lane < K ? p_pos[lane] : 0;
-        const int k0 = K < kBodySteps ? K : kBodySteps, k1 = K - k0;
-        const uint32_t r0 = (uint32_t)k0 < ix.hot_rows ? (uint32_t)k0 : ix.hot_rows;
-        const uint32_t re0 = body_re(k0), re1 = k1 ? body_re(k1) : 0u;
-        const uint32_t rows = (2u * r0 + 3u) & ~3u, size0 = body_bytes(re0);
-        const uint32_t size = L > 0 ? rows + size0 + body_bytes(re1) : 0u;   // (a multiple of 4)
-        const bool has = L > 0;
-        // requested now, used at the end: the caller rows of the steps and the two maxima of the statistics
-        const int32_t row = (wave == 0 && lane < K) ? tv.orig_r[(int64_t)b * tv.Vp + seg + st_pos] : 0;
-        uint32_t stat_now = 0u;
-        if (wave == 0 && lane < 2)
-            stat_now = __hip_atomic_load(&ix.ctrl[lane == 0 ? kCtlMaxK0 : kCtlMaxK], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // Room in the pool and in step_row.  Without groups the slices are placed in the order of their
-        // numbers, so that the layout does not depend on which workgroup was quicker: when the bodies
-        // outgrow the LDS mirror of the lookup kernel, the slices it leaves out are always those of the
-        // last tasks.  Every slice publishes what it needs; the last wavefront adds up what the slices
-        // before its own need, once they have all said so (below).  With groups: one add on the
-        // group's counter pair, asked for now by one lane and looked at after the sets.
-        const bool grouped = ix.num_groups > 1;
-        const unsigned long long add = ((unsigned long long)(uint32_t)K << 32) | size;
-        const uint32_t epoch = ix.ctrl[kCtlEpoch];
-        if (!grouped && threadIdx.x == 0)
-            __hip_atomic_store(ix.slice_room + s, add | ((unsigned long long)epoch << 20), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool asks = grouped && threadIdx.x == 192 && size != 0u;
-        const uint32_t grp = grouped ? (uint32_t)ix.task_group[t] : 0u;
-        unsigned long long *whole = (unsigned long long *)(ix.ctrl + kCtlPool);
-        unsigned long long old = 0;
-        if (asks) old = atomicAdd((unsigned long long *)(ix.gctrl + 2 * grp), add);
-        const int q = (K + kBuildWaves - 1) / kBuildWaves, j_lo = wave * q, j_hi = j_lo + q < K ? j_lo + q : K;
-        const bool second = lane >= k0;   // this lane's step belongs to the second body
-        // 1. the place of every step among the keys of its body: how many steps of the body come before it
-        uint32_t before = 0;              // by accuracy (low half) and by latency-plus-queue (high half)
-        for (int j0 = j_lo; j0 < j_hi; j0 += 4) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int j = j0 + u < j_hi ? j0 + u : j_hi - 1;
-                const bool in = (j0 + u < j_hi) & ((j >= k0) == second);
-                const int32_t aj = p_acc[j];
-                const uint32_t tj = p_tot[j];
-                before += (uint32_t)(in & ((aj > st_acc) | ((aj == st_acc) & (j < lane))));   // (no short-circuit: no branches)
-                before += (uint32_t)(in & ((tj < st_tot) | ((tj == st_tot) & (j < lane)))) << 16;
-            }
-        }
-        parts[wave][0][lane] = before;
-        lds_barrier();
-        before = parts[0][0][lane] + parts[1][0][lane] + parts[2][0][lane] + parts[3][0][lane];
-        const int32_t pa = (int32_t)(before & 0xFFFFu), ps = (int32_t)(before >> 16);
-        int32_t *ranks = ranks_all[0];
-        if (wave == 0) { ranks[lane] = pa; ranks[64 + lane] = ps; }
-        lds_barrier();
-        // 2. the sets: lane p collects A[p] and S[p] of both bodies
-        uint32_t ma0 = 0u, ms0 = 0u, ma1 = 0u, ms1 = 0u;
-        for (int j0 = j_lo; j0 < j_hi; j0 += 4) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int j = j0 + u < j_hi ? j0 + u : j_hi - 1;
-                const bool in = j0 + u < j_hi, first = j < k0;
-                const uint32_t bit = in ? 1u << (first ? j : j - k0) : 0u;
-                const bool a_in = ranks[j] < lane, s_in = ranks[64 + j] < lane;
-                ma0 |= (first & a_in) ? bit : 0u;
-                ms0 |= (first & s_in) ? bit : 0u;
-                ma1 |= (!first & a_in) ? bit : 0u;
-                ms1 |= (!first & s_in) ? bit : 0u;
-            }
-        }
-        parts[wave][0][lane] = ma0; parts[wave][1][lane] = ms0; parts[wave][2][lane] = ma1; parts[wave][3][lane] = ms1;
-        if (asks) {
-            uint32_t off = (uint32_t)old, rec = (uint32_t)(old >> 32);
-            if (off + size <= ix.region_bytes && rec + (uint32_t)K <= ix.group_step_cap) {
-                off += grp * ix.region_bytes; rec += grp * ix.group_step_cap;
-            } else {   // the group's region has no room: behind the regions
-                const unsigned long long o2 = atomicAdd(whole, add);
-                off = (uint32_t)o2; rec = (uint32_t)(o2 >> 32);
-            }
-            s_off[0] = off; s_rec[0] = rec;
-        }
-        if (!grouped && wave == 3) {
-            // What the slices before this one need, lane by lane.  An entry counts once it carries this
-            // build's number.  The wait is bounded: every slice publishes as soon as it knows its steps,
-            // whatever the others do, and workgroups start in the order of their numbers; should the
-            // entries still not be there after kRoomPolls rounds, the slice goes without a body and
-            // its queries are answered by the scan.
-            constexpr int kRoomPolls = 1 << 16;
-            unsigned long long sum = 0;
-            bool got = false;
-            for (int poll = 0; poll < kRoomPolls && !got; ++poll) {
-                bool ok = true;
-                sum = 0;
-                for (int32_t i = lane; i < s; i += 64) {
-                    const unsigned long long v = __hip_atomic_load(ix.slice_room + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    ok = ok && (((uint32_t)v >> 20) == epoch);
-                    sum += v & 0xFFFFFFFF000FFFFFull;
-                }
-                got = __ballot(!ok) == 0ull;
-                if (!got) __builtin_amdgcn_s_sleep(16);
-            }
-            for (int o = 32; o; o >>= 1) sum += __shfl_xor(sum, o);
-            if (lane == 0) {
-                s_off[0] = got ? ix.ctrl[kCtlPool0] + (uint32_t)sum : 0xFFFFFFFFu;
-                s_rec[0] = got ? ix.ctrl[kCtlSteps0] + (uint32_t)(sum >> 32) : 0xFFFFFFFFu;
-            }
-        }
-        if (wave == 2) {   // do the accuracies fit 16-bit keys?
-            int32_t hi = __builtin_amdgcn_readfirstlane(st_acc), lo = hi;   // (of lane 0, a step whenever the slice has variants)
-            for (int32_t j0 = 1; j0 < K; j0 += 8) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int32_t aj = p_acc[j0 + u < K ? j0 + u : 0];
-                    hi = aj > hi ? aj : hi;
-                    lo = aj < lo ? aj : lo;
-                }
-            }
-            if (lane == 0) s_group[0] = ((int64_t)hi - (int64_t)tv.acc_base <= 65533 && lo >= tv.acc_base) ? 1u : 0u;
-        }
-        lds_barrier();   // (also: the room and the verdict on the accuracies are in LDS)
-        const uint32_t off = s_off[0], rec = s_rec[0];
-        const bool fits = has && (uint64_t)off + size <= ix.pool_bytes && (uint64_t)rec + K <= ix.step_cap && s_group[0] != 0u;
-        uint8_t *body0 = ix.pool + off + rows;
-        if (!grouped && s == tv.S - 1 && threadIdx.x == 0 && off != 0xFFFFFFFFu) {   // the totals, for the statistics
-            ix.ctrl[kCtlPool] = off + size;
-            ix.ctrl[kCtlSteps] = rec + (uint32_t)K;
-        }
-        if (wave <= 1 && fits && (wave == 0 || k1)) {   // wavefront 0 writes the first body, wavefront 1 the second
-            const int h = 2 * wave;
-            BodyRegs r{pa, ps, parts[0][h][lane] | parts[1][h][lane] | parts[2][h][lane] | parts[3][h][lane],
-                       parts[0][h + 1][lane] | parts[1][h + 1][lane] | parts[2][h + 1][lane] | parts[3][h + 1][lane]};
-            if (wave == 0) body_store(body0, 0, k0, lane, st_acc, st_tot, tv.acc_base, r);
-            else body_store(body0 + size0, k0, k1, lane, st_acc, st_tot, tv.acc_base, r);
-        }
-        if (__builtin_expect(has && (trunc || !fits), 0)) {   // (the whole workgroup) queries of this slice may go through its entries in rank order
-            const SliceColumns sc = slice_columns<kTwo>(s, t, b);
-            const int32_t quarter = (((sc.L + kBuildWaves - 1) / kBuildWaves) + 255) & ~255;
-            const int32_t from = wave * quarter, to = from + quarter < sc.L ? from + quarter : sc.L;
-            int32_t mx = INT32_MIN;
-            uint32_t mn = 0xFFFFFFFFu;
-            range_extremes(sc.acc, sc.tot, from, to, lane, mx, mn);
-            lds_barrier();   // (the parts of the bodies have been read)
-            if (lane == 0) { parts[wave][0][0] = (uint32_t)mx; parts[wave][0][1] = mn; }
-            lds_barrier();
-            mx = INT32_MIN;
-            mn = 0xFFFFFFFFu;
-            for (int w = 0; w < wave; ++w) {
-                mx = (int32_t)parts[w][0][0] > mx ? (int32_t)parts[w][0][0] : mx;
-                mn = parts[w][0][1] < mn ? parts[w][0][1] : mn;
-            }
-            write_rank_nodes(sc.acc, sc.tot, sc.nodes, sc.L, from, to, lane, mx, mn);
-        }
-        if (wave != 0) return;   // (no barrier follows)
-        if (fits && lane < K) {
-            ix.step_row[rec + lane] = row;
-            if ((uint32_t)lane < r0)   // in reverse in front of the body
-                *(uint16_t *)(body0 - 2 - 2 * lane) = (uint16_t)row;
-        }
-        uint32_t row_hi = 0;   // of the first steps' rows the bits above the low 16 go into the header
-        for (uint32_t j = 0; j < r0; ++j)
-            row_hi |= ((uint32_t)__builtin_amdgcn_readlane(row, (int)j) >> 16) << (j * ix.row_hi_bits);
-        if (lane == 0) {
-            if (fits) {
-                const uint32_t y = (re0 << kHdrK0Shift) | (re1 << kHdrK1Shift) | (trunc ? kHdrTrunc : 0u) |
-                                   ((k1 || trunc) ? kHdrDeep : 0u) | row_hi;
-                ix.hdr[s] = make_uint4(off + rows - 4u, y, rec, off + size);
-            } else if (has) {   // no body: every query of this slice goes to the rank-ordered scan
-                ix.hdr[s] = make_uint4(0u, kEmptyHdrY | kHdrPark | kHdrTrunc | kHdrDeep, 0u, 0u);
-            } else {            // no variants: the empty dummy body at offset 0 answers "nothing feasible"
-                ix.hdr[s] = make_uint4(0u, kEmptyHdrY, 0u, 4u + body_bytes(2));
-            }
-        }
-        // statistics: lanes 0..3 one word each; the maxima only where they raise what was read above
-        if (lane < 4) {
-            constexpr int word[4] = {kCtlMaxK0, kCtlMaxK, kCtlTrunc, kCtlNoBody};
-            const uint32_t v = lane == 0 ? (fits ? (uint32_t)k0 : 0u) : lane == 1 ? (fits ? (uint32_t)K : 0u)
-                             : lane == 2 ? ((fits && trunc) ? 1u : 0u) : ((has && !fits) ? 1u : 0u);
-            if (lane >= 2) { if (v) atomicAdd(&ix.ctrl[word[lane]], v); }
-            else if (v > stat_now) atomicMax(&ix.ctrl[word[lane]], v);
-        }
-        return;
-    }
     // ---- phase B: one or two bodies of sorted keys and bit sets, computed while the workgroup's
     // request for room in the pool is under way
     const int k0 = K < kBodySteps ? K : kBodySteps, k1 = K - k0;
@@ -748,6 +554,417 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
         if (threadIdx.x >= 2) atomicAdd(g, v);
         else if (v > __hip_atomic_load(g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(g, v);   // (mostly not)
     }
+}
+
+// Few slices, one per workgroup: the time is one slice's chain of dependent steps, so its four wavefronts take
+// every stage together and meet at barriers that order LDS traffic only.  Entries come in chunks of 256 kPer, a
+// quarter to each wavefront, kPer per lane in registers.  Then
+//   1. (first chunk) the steps among the first 64 entries, every pair of them tested, a quarter of the pairs by
+//      each wavefront;
+//   2. the coarse filter of k_index_build, its table from a quarter of the steps per wavefront; what passes is
+//      compacted into the candidate list, in rank order;
+//   3. the list in batches of 256: every candidate against the steps known so far and against every candidate
+//      before it in the batch (that a non-step dominates it is enough: whatever dominates that one is a
+//      step), a quarter of the tests by each wavefront; the survivors are the batch's steps.
+// The four then share the bodies: each counts and collects over a quarter of the steps, the parts are put
+// together through LDS, while one of them asks for the room in the pool.
+// Bound by latency: a few hundred dependent LDS reads and compares on a lone wavefront per SIMD.  Measured (us,
+// config 2's 400 slices of 2000 entries): 21.0 with one wavefront looking for the steps round by round, 15.9 so.
+template <int kPer, bool kTwo>
+__global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableView ta, IndexView ia, TableView tb, IndexView ib)
+{
+    const TableView tv = kTwo && blockIdx.y ? tb : ta;
+    const IndexView ix = kTwo && blockIdx.y ? ib : ia;
+    constexpr int kChunk = 64 * kBuildWaves * kPer;       // entries of a slice taken in at a time
+    constexpr int kBatch = 256;
+    __shared__ int2 c_pair[kChunk < 64 ? 64 : kChunk];    // candidates: accuracy, latency + queue
+    __shared__ uint16_t c_pos[kChunk];                    //   position in the chunk
+    __shared__ int32_t p_acc[64], p_pos[64];              // steps, in rank order
+    __shared__ uint32_t p_tot[64];
+    __shared__ uint32_t f_part[kBuildWaves][64], f_tab[kBuildWaves][64];   // the coarse filter's table (one copy per wavefront)
+    __shared__ unsigned long long s_alive[kBuildWaves][kBatch / 64];
+    __shared__ int32_t s_cnt[kBuildWaves];
+    __shared__ int32_t ranks[128];                        // the steps' places in their bodies
+    __shared__ uint32_t parts[kBuildWaves][4][64];        // what each wavefront found over its quarter of the steps
+    __shared__ uint32_t s_off[1], s_rec[1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t s = (int32_t)blockIdx.x;
+    const int32_t t = s / tv.B, b = s - t * tv.B;
+    const int32_t seg = tv.seg_off[t], L = tv.seg_len[t];
+    const int32_t *__restrict__ accc = tv.acc_r + (int64_t)b * tv.Vp + seg;
+    const uint32_t *__restrict__ totc = tv.tot_r + (int64_t)b * tv.Vp + seg;
+
+    // ---- phase A: the steps, in rank order; p_acc / p_tot / p_pos hold all of them
+    int32_t K = 0;
+    bool trunc = false;
+    // After a barrier: which of the 64 candidates of block u every wavefront has found alive.
+    auto survivors = [&](int u) { return s_alive[0][u] & s_alive[1][u] & s_alive[2][u] & s_alive[3][u]; };
+    auto grow = [&](int32_t k_new) {   // more steps than the index keeps: its first ones stay
+        trunc = K + k_new > kIndexCap;
+        K = trunc ? kIndexCap : K + k_new;
+    };
+    for (int32_t c0 = 0; c0 < L && !trunc; c0 += kChunk) {
+        const int32_t n = L - c0 < kChunk ? L - c0 : kChunk;
+        int ln = lane;
+        asm volatile("" : "+v"(ln));   // (masks made from it stay where they are needed: in front of the loop there are too many to keep)
+        int32_t va[kPer];
+        uint32_t vt[kPer];
+        uint32_t dead = 0u;   // bit k: entry k of this lane is outside the chunk, dominated, or taken care of
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {   // unconditional loads (clamped), so that they overlap
+            const int32_t i = (wave * kPer + k) * 64 + lane;
+            const int32_t j = c0 + (i < n ? i : n - 1);
+            va[k] = accc[j];
+            vt[k] = totc[j];
+            dead |= i >= n ? 1u << k : 0u;
+        }
+        if (c0 == 0) {   // 1. the first 64 entries
+            if (wave == 0) c_pair[lane] = make_int2(va[0], (int32_t)vt[0]);
+            lds_barrier();
+            const int2 me = c_pair[lane];
+            bool gone = lane >= n;
+#pragma unroll
+            for (int x = 0; x < 64 / kBuildWaves; ++x) {
+                const int j = wave * (64 / kBuildWaves) + x;
+                const int2 o = c_pair[j];
+                gone = gone | ((j < ln) & (o.x >= me.x) & ((uint32_t)o.y <= (uint32_t)me.y));
+            }
+            const uint64_t m = __ballot(!gone);
+            if (lane == 0) s_alive[wave][0] = m;
+            lds_barrier();
+            const uint64_t ok = survivors(0);
+            const int32_t at = (int32_t)lanes_below(ok);
+            if (wave == 0 && ((ok >> lane) & 1u) && at < kIndexCap) { p_acc[at] = me.x; p_tot[at] = (uint32_t)me.y; p_pos[at] = lane; }
+            if (wave == 0) dead |= 1u;
+            grow((int32_t)__builtin_popcountll(ok));
+            lds_barrier();
+            if (trunc) break;
+        }
+        int32_t vp[kPer];   // where in the chunk
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) vp[k] = (wave * kPer + k) * 64 + lane;
+        for (int round = 0;; ++round) {
+            // 2. coarse filter (see k_index_build): accuracies from the lowest (mn) to the highest (mx) of the steps
+            // in buckets of 2^sh; entry 0 is for entries below mn, entry 1 + q for bucket q, entry 33 for those above mx
+            {
+                int32_t mn = p_acc[lane < K ? lane : 0], mx = mn;
+                for (int o = 32; o; o >>= 1) {
+                    const int32_t x = __shfl_xor(mn, o), y = __shfl_xor(mx, o);
+                    mn = x < mn ? x : mn;
+                    mx = y > mx ? y : mx;
+                }
+                const uint32_t range = (uint32_t)mx - (uint32_t)mn;
+                const int bits = 32 - __builtin_clz(range | 1u);
+                const uint32_t sh = bits > 5 ? (uint32_t)(bits - 5) : 0u;   // range >> sh < 32
+                uint32_t f = 0xFFFFFFFFu;
+                for (int j0 = wave; j0 < K; j0 += 4 * kBuildWaves) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int j = j0 + kBuildWaves * u < K ? j0 + kBuildWaves * u : 0;   // (step 0 again: harmless)
+                        const uint64_t uj = (uint64_t)((uint32_t)p_acc[j] - (uint32_t)mn) + 1u;
+                        const uint32_t tj = p_tot[j];
+                        const bool covers = (uint32_t)(uj >> sh) >= (uint32_t)lane;
+                        f = (covers & (tj < f)) ? tj : f;
+                    }
+                }
+                f_part[wave][lane] = f;
+                lds_barrier();
+                uint32_t g = f_part[0][lane];
+#pragma unroll
+                for (int w = 1; w < kBuildWaves; ++w) g = f_part[w][lane] < g ? f_part[w][lane] : g;
+                f_tab[wave][lane] = lane <= 32 ? g : 0xFFFFFFFFu;   // (entry 33, above every step: never dominated)
+                wave_sync();
+#pragma unroll
+                for (int k = 0; k < kPer; ++k) {
+                    const uint32_t u = (uint32_t)va[k] - (uint32_t)mn;
+                    uint32_t idx = 1u + (u >> sh);
+                    idx = idx > 33u ? 33u : idx;
+                    idx = va[k] < mn ? 0u : idx;
+                    const uint32_t fv = f_tab[wave][idx];
+                    dead |= ((fv != 0xFFFFFFFFu) & (fv <= vt[k])) ? 1u << k : 0u;
+                }
+            }
+            // what is left becomes the candidate list
+            int32_t mine = 0;
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) mine += (int32_t)__builtin_popcountll(__ballot(!((dead >> k) & 1u)));
+            if (lane == 0) s_cnt[wave] = mine;
+            lds_barrier();
+            int32_t at = 0, num = 0;
+#pragma unroll
+            for (int w = 0; w < kBuildWaves; ++w) { at += w < wave ? s_cnt[w] : 0; num += s_cnt[w]; }
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const bool live = !((dead >> k) & 1u);
+                const uint64_t m = __ballot(live);
+                const int32_t to = at + (int32_t)lanes_below(m);
+                if (live) { c_pair[to] = make_int2(va[k], (int32_t)vt[k]); c_pos[to] = (uint16_t)vp[k]; }
+                at += (int32_t)__builtin_popcountll(m);
+            }
+            lds_barrier();
+            if (num == 0) break;
+            // 3. a batch from the front of the list: all of it if there is not much, else so few that the filter,
+            // made anew from the steps found, takes most of the rest
+            const int32_t m = num <= 160 ? num : round == 0 ? 64 : num < kBatch ? num : kBatch;
+            const int blocks = (m + 63) >> 6;
+            auto test = [&](auto count) __attribute__((always_inline)) {
+                constexpr int kU = decltype(count)::value;   // blocks of 64 candidates
+                int2 me[kU];
+                bool gone[kU];
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    gone[u] = u * 64 + lane >= m;
+                    me[u] = c_pair[(gone[u] ? 0 : u * 64 + lane)];
+                }
+                for (int j0 = wave; j0 < K; j0 += 4 * kBuildWaves) {
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const int j = j0 + kBuildWaves * x < K ? j0 + kBuildWaves * x : 0;   // (step 0 again: harmless)
+                        const int32_t aj = p_acc[j];
+                        const uint32_t tj = p_tot[j];
+#pragma unroll
+                        for (int u = 0; u < kU; ++u) gone[u] = gone[u] | ((aj >= me[u].x) & (tj <= (uint32_t)me[u].y));
+                    }
+                }
+                for (int j0 = wave; j0 < m; j0 += 4 * kBuildWaves) {
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const int j = j0 + kBuildWaves * x;   // (at or behind m: in front of no candidate)
+                        const int2 o = c_pair[(j < m ? j : 0)];
+#pragma unroll
+                        for (int u = 0; u < kU; ++u)
+                            gone[u] = gone[u] | ((j < u * 64 + ln) & (j < m) & (o.x >= me[u].x) & ((uint32_t)o.y <= (uint32_t)me[u].y));
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const uint64_t alive = __ballot(!gone[u]);
+                    if (lane == 0) s_alive[wave][u] = alive;
+                }
+            };
+            if (blocks == 1) test(std::integral_constant<int, 1>{});
+            else if (blocks == 2) test(std::integral_constant<int, 2>{});
+            else test(std::integral_constant<int, 4>{});
+            lds_barrier();
+            int32_t to = K, k_new = 0;   // wavefront w appends the survivors of block w
+#pragma unroll
+            for (int u = 0; u < kBatch / 64; ++u) {
+                if (u >= blocks) continue;
+                const int32_t c = (int32_t)__builtin_popcountll(survivors(u));
+                to += u < wave ? c : 0;
+                k_new += c;
+            }
+            if (wave < blocks) {
+                const uint64_t ok = survivors(wave);
+                to += (int32_t)lanes_below(ok);
+                if (((ok >> lane) & 1u) && to < kIndexCap) {
+                    const int2 me = c_pair[wave * 64 + lane];
+                    p_acc[to] = me.x; p_tot[to] = (uint32_t)me.y; p_pos[to] = c0 + (int32_t)c_pos[wave * 64 + lane];
+                }
+            }
+            grow(k_new);
+            lds_barrier();
+            if (trunc || m == num) break;
+            // the rest of the list, in rank order: a quarter to each wavefront, as the entries were
+            const int32_t rest = num - m, share = (((rest + kBuildWaves - 1) / kBuildWaves) + 63) & ~63;   // (at most 64 kPer)
+            dead = 0u;
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const int32_t i = wave * share + k * 64 + lane;
+                const bool in = k * 64 < share && i < rest;
+                const int2 e = c_pair[m + (in ? i : 0)];
+                va[k] = e.x; vt[k] = (uint32_t)e.y; vp[k] = (int32_t)c_pos[m + (in ? i : 0)];
+                dead |= in ? 0u : 1u << k;
+            }
+            lds_barrier();
+        }
+    }
+
+    // ---- phase B: wavefront w counts and collects over steps [w q, w q + q), q = K / 4 rounded up
+    const int32_t st_acc = lane < K ? p_acc[lane] : 0, st_pos = lane < K ? p_pos[lane] : 0;
+    const uint32_t st_tot = lane < K ? p_tot[lane] : 0u;
+    const int k0 = K < kBodySteps ? K : kBodySteps, k1 = K - k0;
+    const uint32_t r0 = (uint32_t)k0 < ix.hot_rows ? (uint32_t)k0 : ix.hot_rows;
+    const uint32_t re0 = body_re(k0), re1 = k1 ? body_re(k1) : 0u;
+    const uint32_t rows = (2u * r0 + 3u) & ~3u, size0 = body_bytes(re0);
+    const bool has = L > 0;
+    // accuracies that do not fit 16-bit keys: no bodies, and no room asked for
+    const bool narrow = __ballot(lane < K && (st_acc < tv.acc_base || (int64_t)st_acc - (int64_t)tv.acc_base > 65533)) == 0ull;
+    const uint32_t size = has && narrow ? rows + size0 + body_bytes(re1) : 0u;   // (a multiple of 4)
+    // requested now, used at the end: the caller rows of the steps
+    const int32_t row = (wave == 0 && lane < K) ? tv.orig_r[(int64_t)b * tv.Vp + seg + st_pos] : 0;
+    // Room in the pool and in step_row.  Without groups the slices are placed in the order of their
+    // numbers, so that the layout does not depend on which workgroup was quicker: when the bodies
+    // outgrow the LDS mirror of the lookup kernel, the slices it leaves out are always those of the
+    // last tasks.  Every slice publishes what it needs; the last wavefront adds up what the slices
+    // before its own need, once they have all said so (below), and that of the last slice leaves the
+    // statistics (as a maximum per slice in one word of global memory, every slice waited for its turn there).
+    // With groups: room by one add on the group's counter pair, asked for now by one lane and looked at after the sets.
+    const bool grouped = ix.num_groups > 1;
+    const unsigned long long add = size ? ((unsigned long long)(uint32_t)K << 32) | size : 0ull;
+    const unsigned long long published = add | ((size && trunc) ? 1ull << kRoomTrunc : 0ull);
+    const uint32_t epoch = ix.ctrl[kCtlEpoch];
+    if (threadIdx.x == 0)
+        __hip_atomic_store(ix.slice_room + s, published | ((unsigned long long)epoch << 20), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool asks = grouped && threadIdx.x == 192 && size != 0u;
+    const uint32_t grp = grouped ? (uint32_t)ix.task_group[t] : 0u;
+    unsigned long long *whole = (unsigned long long *)(ix.ctrl + kCtlPool);
+    unsigned long long old = 0;
+    if (asks) old = atomicAdd((unsigned long long *)(ix.gctrl + 2 * grp), add);
+    const int q = (K + kBuildWaves - 1) / kBuildWaves, j_lo = wave * q, j_hi = j_lo + q < K ? j_lo + q : K;
+    const bool second = lane >= k0;   // this lane's step belongs to the second body
+    // 1. the place of every step among the keys of its body: how many steps of the body come before it
+    uint32_t before = 0;              // by accuracy (low half) and by latency-plus-queue (high half)
+    for (int j0 = j_lo; j0 < j_hi; j0 += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = j0 + u < j_hi ? j0 + u : j_hi - 1;
+            const bool in = (j0 + u < j_hi) & ((j >= k0) == second);
+            const int32_t aj = p_acc[j];
+            const uint32_t tj = p_tot[j];
+            before += (uint32_t)(in & ((aj > st_acc) | ((aj == st_acc) & (j < lane))));   // (no short-circuit: no branches)
+            before += (uint32_t)(in & ((tj < st_tot) | ((tj == st_tot) & (j < lane)))) << 16;
+        }
+    }
+    parts[wave][0][lane] = before;
+    lds_barrier();
+    before = parts[0][0][lane] + parts[1][0][lane] + parts[2][0][lane] + parts[3][0][lane];
+    const int32_t pa = (int32_t)(before & 0xFFFFu), ps = (int32_t)(before >> 16);
+            if (wave == 0) { ranks[lane] = pa; ranks[64 + lane] = ps; }
+    lds_barrier();
+    // 2. the sets: lane p collects A[p] and S[p] of both bodies
+    uint32_t ma0 = 0u, ms0 = 0u, ma1 = 0u, ms1 = 0u;
+    for (int j0 = j_lo; j0 < j_hi; j0 += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = j0 + u < j_hi ? j0 + u : j_hi - 1;
+            const bool in = j0 + u < j_hi, first = j < k0;
+            const uint32_t bit = in ? 1u << (first ? j : j - k0) : 0u;
+            const bool a_in = ranks[j] < lane, s_in = ranks[64 + j] < lane;
+            ma0 |= (first & a_in) ? bit : 0u;
+            ms0 |= (first & s_in) ? bit : 0u;
+            ma1 |= (!first & a_in) ? bit : 0u;
+            ms1 |= (!first & s_in) ? bit : 0u;
+        }
+    }
+    parts[wave][0][lane] = ma0; parts[wave][1][lane] = ms0; parts[wave][2][lane] = ma1; parts[wave][3][lane] = ms1;
+    if (asks) {
+        uint32_t off = (uint32_t)old, rec = (uint32_t)(old >> 32);
+        if (off + size <= ix.region_bytes && rec + (uint32_t)K <= ix.group_step_cap) {
+            off += grp * ix.region_bytes; rec += grp * ix.group_step_cap;
+        } else {   // the group's region has no room: behind the regions
+            const unsigned long long o2 = atomicAdd(whole, add);
+            off = (uint32_t)o2; rec = (uint32_t)(o2 >> 32);
+        }
+        s_off[0] = off; s_rec[0] = rec;
+    }
+    if (wave == 3 && (!grouped || s == tv.S - 1)) {
+        // What the slices before this one need, lane by lane (with groups only for the statistics).  An entry counts once it carries this
+        // build's number.  The wait is bounded: every slice publishes as soon as it knows its steps,
+        // whatever the others do, and workgroups start in the order of their numbers; should the
+        // entries still not be there after kRoomPolls rounds, the slice goes without a body and
+        // its queries are answered by the scan.
+        constexpr int kRoomPolls = 1 << 18, kAtOnce = 8;
+        unsigned long long sum = 0;
+        int32_t most = 0;   // steps of the slice that has most
+        bool got = true;
+        int polls = 0;
+        for (int32_t first = 0; first < s && got; first += 64 * kAtOnce) {   // (a batch of entries is read until all of it is there)
+            unsigned long long part;
+            int32_t part_most;
+            do {
+                part = 0;
+                part_most = 0;
+                bool ok = true;
+#pragma unroll
+                for (int u = 0; u < kAtOnce; ++u) {
+                    const int32_t i = first + 64 * u + lane;
+                    const unsigned long long v = __hip_atomic_load(ix.slice_room + (i < s ? i : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int32_t k = i < s ? (int32_t)((uint32_t)(v >> 32) & kRoomSteps) : 0;
+                    ok = ok && (i >= s || ((uint32_t)v >> 20) == epoch);
+                    part += i < s ? v & 0xFFFFFFFF000FFFFFull : 0ull;
+                    part_most = k > part_most ? k : part_most;
+                }
+                got = __ballot(!ok) == 0ull;
+                if (!got) __builtin_amdgcn_s_sleep(2);
+            } while (!got && ++polls < kRoomPolls);
+            sum += part;
+            most = part_most > most ? part_most : most;
+        }
+        for (int o = 32; o; o >>= 1) sum += __shfl_xor(sum, o);
+        if (lane == 0 && !grouped) {
+            s_off[0] = got ? ix.ctrl[kCtlPool0] + (uint32_t)sum : 0xFFFFFFFFu;
+            s_rec[0] = got ? ix.ctrl[kCtlSteps0] + ((uint32_t)(sum >> 32) & kRoomSteps) : 0xFFFFFFFFu;
+        }
+        if (s == tv.S - 1) {   // the totals and the statistics
+            most = (size && K > most) ? K : most;
+            for (int o = 32; o; o >>= 1) {
+                const int32_t x = __shfl_xor(most, o);
+                most = x > most ? x : most;
+            }
+            most = got ? most : kIndexCap;   // (should the wait have run out: the most there can be)
+            sum += published;
+            if (lane == 0) {
+                if (!grouped) {
+                    ix.ctrl[kCtlPool] = ix.ctrl[kCtlPool0] + (uint32_t)sum;
+                    ix.ctrl[kCtlSteps] = ix.ctrl[kCtlSteps0] + ((uint32_t)(sum >> 32) & kRoomSteps);
+                }
+                ix.ctrl[kCtlTrunc] = (uint32_t)(sum >> kRoomTrunc);
+                ix.ctrl[kCtlMaxK] = (uint32_t)most;
+                ix.ctrl[kCtlMaxK0] = (uint32_t)(most < 1 ? 1 : most < kBodySteps ? most : kBodySteps);
+            }
+        }
+    }
+    lds_barrier();   // (also: the room is in LDS)
+    const uint32_t off = s_off[0], rec = s_rec[0];
+    const bool fits = has && (uint64_t)off + size <= ix.pool_bytes && (uint64_t)rec + K <= ix.step_cap && narrow;
+    uint8_t *body0 = ix.pool + off + rows;
+    if (wave <= 1 && fits && (wave == 0 || k1)) {   // wavefront 0 writes the first body, wavefront 1 the second
+        const int h = 2 * wave;
+        BodyRegs r{pa, ps, parts[0][h][lane] | parts[1][h][lane] | parts[2][h][lane] | parts[3][h][lane],
+                   parts[0][h + 1][lane] | parts[1][h + 1][lane] | parts[2][h + 1][lane] | parts[3][h + 1][lane]};
+        if (wave == 0) body_store(body0, 0, k0, lane, st_acc, st_tot, tv.acc_base, r);
+        else body_store(body0 + size0, k0, k1, lane, st_acc, st_tot, tv.acc_base, r);
+    }
+    if (__builtin_expect(has && (trunc || !fits), 0)) {   // (the whole workgroup) queries of this slice may go through its entries in rank order
+        const SliceColumns sc = slice_columns<kTwo>(s, t, b);
+        const int32_t quarter = (((sc.L + kBuildWaves - 1) / kBuildWaves) + 255) & ~255;
+        const int32_t from = wave * quarter, to = from + quarter < sc.L ? from + quarter : sc.L;
+        int32_t mx = INT32_MIN;
+        uint32_t mn = 0xFFFFFFFFu;
+        range_extremes(sc.acc, sc.tot, from, to, lane, mx, mn);
+        lds_barrier();   // (the parts of the bodies have been read)
+        if (lane == 0) { parts[wave][0][0] = (uint32_t)mx; parts[wave][0][1] = mn; }
+        lds_barrier();
+        mx = INT32_MIN;
+        mn = 0xFFFFFFFFu;
+        for (int w = 0; w < wave; ++w) {
+            mx = (int32_t)parts[w][0][0] > mx ? (int32_t)parts[w][0][0] : mx;
+            mn = parts[w][0][1] < mn ? parts[w][0][1] : mn;
+        }
+        write_rank_nodes(sc.acc, sc.tot, sc.nodes, sc.L, from, to, lane, mx, mn);
+    }
+    if (wave != 0) return;   // (no barrier follows)
+    if (fits && lane < K) {
+        ix.step_row[rec + lane] = row;
+        if ((uint32_t)lane < r0)   // in reverse in front of the body
+            *(uint16_t *)(body0 - 2 - 2 * lane) = (uint16_t)row;
+    }
+    uint32_t row_hi = 0;   // of the first steps' rows the bits above the low 16 go into the header
+    for (uint32_t j = 0; j < r0; ++j)
+        row_hi |= ((uint32_t)__builtin_amdgcn_readlane(row, (int)j) >> 16) << (j * ix.row_hi_bits);
+    if (lane == 0) {
+        if (fits) {
+            const uint32_t y = (re0 << kHdrK0Shift) | (re1 << kHdrK1Shift) | (trunc ? kHdrTrunc : 0u) |
+                               ((k1 || trunc) ? kHdrDeep : 0u) | row_hi;
+            ix.hdr[s] = make_uint4(off + rows - 4u, y, rec, off + size);
+        } else if (has) {   // no body: every query of this slice goes to the rank-ordered scan
+            ix.hdr[s] = make_uint4(0u, kEmptyHdrY | kHdrPark | kHdrTrunc | kHdrDeep, 0u, 0u);
+        } else {            // no variants: the empty dummy body at offset 0 answers "nothing feasible"
+            ix.hdr[s] = make_uint4(0u, kEmptyHdrY, 0u, 4u + body_bytes(2));
+        }
+    }
+    if (lane == 0 && has && !fits) atomicAdd(&ix.ctrl[kCtlNoBody], 1u);
 }
 
 // ---------------------------------------------------------------- lookup
@@ -1446,18 +1663,23 @@ hipError_t launch_build(const TableView &ta, const IndexView &ia, const TableVie
     constexpr unsigned tables = kTwo ? 2 : 1;
     if (ta.S <= 0) return hipSuccess;
     const dim3 block(64 * kBuildWaves);
-    // few slices of many variants each: one slice per workgroup, its wavefronts share the bodies
-    if (ta.S <= 512 && (int64_t)ta.Vp >= 512 * (int64_t)ta.T)
-        return launch_kernel(ev, k_index_build<32, true, kTwo>, dim3((unsigned)ta.S, tables), block, 0, st, ta, ia, tb, ib);
+    // One slice per workgroup as long as all of them are on the device at once (five workgroups of these registers
+    // to a compute unit; the sums over the slices before are short, too).  us for one slice per workgroup / per
+    // wavefront: 160 slices of 45 entries 7.3 / 9.9, 800 of 200 11.5 / 15.1, of 500 12.4 / 16.5, of 1000 16.5 / 21.4,
+    // 400 of 2000 15.9 / 21; two tables of 800 slices of 200 20.3 / 12.7; 1600 of 60 16.0 / 13.5
+    if ((int64_t)ta.S * tables <= 1024) {
+        const dim3 each((unsigned)ta.S, tables);
+        if (ta.max_len <= 256) return launch_kernel(ev, k_index_build_shared<1, kTwo>, each, block, 0, st, ta, ia, tb, ib);
+        if (ta.max_len <= 512) return launch_kernel(ev, k_index_build_shared<2, kTwo>, each, block, 0, st, ta, ia, tb, ib);
+        if (ta.max_len <= 1024) return launch_kernel(ev, k_index_build_shared<4, kTwo>, each, block, 0, st, ta, ia, tb, ib);
+        return launch_kernel(ev, k_index_build_shared<8, kTwo>, each, block, 0, st, ta, ia, tb, ib);
+    }
     const dim3 grid((unsigned)((ta.S + kBuildWaves - 1) / kBuildWaves), tables);
     // no slice longer than one chunk: a chunk of that size, whose loops have no idle rounds (us, two tables of 100
-    // tasks of 200 variants x 8: 13.5 with chunks of 4 x 64 entries, 13.7 with 8, 14.7 with 16, 24.8 with 32; one
-    // table of 100 x 500: 21.9, 17.5, 17.8, 19.2)
-    if (ta.max_len <= 256) return launch_kernel(ev, k_index_build<4, false, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
-    if (ta.max_len <= 512) return launch_kernel(ev, k_index_build<8, false, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
-    // up to 1024 slices every workgroup is resident at once whatever its size: the larger chunk
-    if ((int64_t)ta.S * tables <= 1024) return launch_kernel(ev, k_index_build<32, false, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
-    return launch_kernel(ev, k_index_build<16, false, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
+    // tasks of 200 variants x 8: 13.5 with chunks of 4 x 64 entries, 13.7 with 8, 14.7 with 16)
+    if (ta.max_len <= 256) return launch_kernel(ev, k_index_build<4, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
+    if (ta.max_len <= 512) return launch_kernel(ev, k_index_build<8, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
+    return launch_kernel(ev, k_index_build<16, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
 }
 
 }  // namespace

@@ -127,7 +127,7 @@ struct IndexView {
     uint32_t row_hi_bits;// bits of a row number above its low 16
     uint32_t *ctrl;      // [kCtlWords] counters of the build, see kCtl*
     unsigned long long *slice_room;   // [S] what slice s needs, published by the build that places the slices in the
-                         // order of their numbers: steps << 32 | build number (12 bits) << 20 | bytes
+                         // order of their numbers: bytes (20 bits) | build number (12) | steps (20) | truncated (12)
     // Groups.  When the bodies of all slices do not fit one compute unit's LDS, the tasks are dealt, in
     // order, to num_groups groups whose bodies do: group g owns the tasks [group_task0[g],
     // group_task0[g + 1]), the bytes [g * region_bytes, (g + 1) * region_bytes) of the pool (every region
@@ -154,6 +154,8 @@ constexpr int kCtlTrunc = 33;     // slices with more steps than the index keeps
 constexpr int kCtlNoBody = 34;    // slices without a body
 constexpr int kCtlMaxK = 35;      // most steps in a slice
 constexpr int kCtlWords = 64;
+constexpr uint32_t kRoomSteps = 0xFFFFFu;   // entries of slice_room, shifted down by 32: the steps
+constexpr int kRoomTrunc = 52;              //   the flag of a truncated slice (both fields hold the sum over 4095 slices)
 // TableView::rank_nodes of a slice of L entries: nodes of a level, of all levels, and of everything.
 constexpr int kRankBlock = 256, kRankBlockNodes = 17;
 __host__ __device__ inline int32_t level_nodes(int32_t L, int level) { return (int32_t)(((int64_t)L + ((int64_t)16 << (4 * level)) - 1) >> (4 * level + 4)); }
