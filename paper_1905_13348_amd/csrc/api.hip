@@ -99,7 +99,8 @@ struct infaas_sel {
     int32_t *d_acc = nullptr, *d_queue = nullptr, *d_orig = nullptr, *d_lat = nullptr;
     uint32_t *d_rank = nullptr, *d_perm = nullptr;
     int32_t *d_seg_off = nullptr, *d_seg_len = nullptr, *d_slot_of = nullptr;
-    int32_t *d_acc_r = nullptr, *d_lat_r = nullptr, *d_orig_r = nullptr, *d_gpos = nullptr;
+    int32_t *d_acc_r = nullptr, *d_orig_r = nullptr;
+    int2 *d_row_entry = nullptr;
     uint32_t *d_tot_r = nullptr;
     int64_t table_bytes = 0;
     int32_t max_segment = 0, max_lds_segment = 0, wide_segments = 0;
@@ -107,7 +108,7 @@ struct infaas_sel {
     // state-aware selection: this table then serves the Active variants, `inactive` (a handle of
     // its own, built from the same rows) the Inactive ones
     std::vector<int32_t> h_task, h_acc, h_lat;   // host copies of the static columns, for building `inactive`
-    int32_t *d_state = nullptr;                  // [Vp] state per slot (see TableView::state)
+    int32_t *d_state = nullptr;                  // [V] state per row (see TableView::state)
     infaas_sel *inactive = nullptr;
     int32_t *d_open = nullptr;                   // lists of the queries the Active tier leaves open (grows)
     int32_t *d_open_count = nullptr;             // [workgroups of the lookup kernel]
@@ -158,10 +159,11 @@ struct infaas_sel {
         (void)hipFree(d_acc); (void)hipFree(d_queue); (void)hipFree(d_orig); (void)hipFree(d_lat);
         (void)hipFree(d_rank); (void)hipFree(d_perm); (void)hipFree(d_seg_off);
         (void)hipFree(d_seg_len); (void)hipFree(d_slot_of);
-        (void)hipFree(d_acc_r); (void)hipFree(d_lat_r); (void)hipFree(d_orig_r); (void)hipFree(d_gpos);
+        (void)hipFree(d_acc_r); (void)hipFree(d_orig_r); (void)hipFree(d_row_entry);
         (void)hipFree(d_tot_r);
         d_acc = d_queue = d_orig = d_lat = d_seg_off = d_seg_len = d_slot_of = nullptr;
-        d_acc_r = d_lat_r = d_orig_r = d_gpos = nullptr;
+        d_acc_r = d_orig_r = nullptr;
+        d_row_entry = nullptr;
         d_tot_r = nullptr;
         d_rank = d_perm = nullptr;
         (void)hipFree(d_state);
@@ -790,8 +792,7 @@ int infaas_sel_load_variants(infaas_sel_t *h, int32_t V, const int32_t *task_id,
     std::vector<int32_t> acc(Vp, INT32_MIN), queue(Vp, INT32_MAX), orig(Vp, -1), slot_of(std::max(V, 1), 0);
     std::vector<int32_t> lat((size_t)B * Vp, INT32_MAX);
     std::vector<uint32_t> rank((size_t)B * Vp, kNoRank), perm((size_t)B * Vp, 0u);
-    std::vector<int32_t> acc_r((size_t)B * Vp, INT32_MIN), lat_r((size_t)B * Vp, 0), orig_r((size_t)B * Vp, -1);
-    std::vector<int32_t> gpos((size_t)B * Vp, 0);
+    std::vector<int32_t> acc_r((size_t)B * Vp, INT32_MIN), orig_r((size_t)B * Vp, -1);
     std::vector<uint32_t> tot_r((size_t)B * Vp, 0xFFFFFFFFu);
     {
         std::vector<int32_t> fill(T, 0);
@@ -827,10 +828,8 @@ int infaas_sel_load_variants(infaas_sel_t *h, int32_t V, const int32_t *task_id,
                     perm[g] = (uint32_t)ord[r];
                     rank[sl] = (uint32_t)r;
                     acc_r[g] = acc[seg + ord[r]];
-                    lat_r[g] = lat[sl];
                     tot_r[g] = (uint32_t)lat[sl] + (uint32_t)queue[seg + ord[r]];
                     orig_r[g] = orig[seg + ord[r]];
-                    gpos[sl] = seg + r;
                 }
             }
         }
@@ -847,8 +846,8 @@ int infaas_sel_load_variants(infaas_sel_t *h, int32_t V, const int32_t *task_id,
               dev_alloc(&h->d_perm, (size_t)B * Vp) == hipSuccess &&
               dev_alloc(&h->d_seg_off, (size_t)T + 1) == hipSuccess && dev_alloc(&h->d_seg_len, T) == hipSuccess &&
               dev_alloc(&h->d_slot_of, std::max(V, 1)) == hipSuccess &&
-              dev_alloc(&h->d_acc_r, (size_t)B * Vp) == hipSuccess && dev_alloc(&h->d_lat_r, (size_t)B * Vp) == hipSuccess &&
-              dev_alloc(&h->d_orig_r, (size_t)B * Vp) == hipSuccess && dev_alloc(&h->d_gpos, (size_t)B * Vp) == hipSuccess &&
+              dev_alloc(&h->d_acc_r, (size_t)B * Vp) == hipSuccess && dev_alloc(&h->d_orig_r, (size_t)B * Vp) == hipSuccess &&
+              dev_alloc(&h->d_row_entry, (size_t)std::max(V, 1) * B) == hipSuccess &&
               dev_alloc(&h->d_tot_r, (size_t)B * Vp) == hipSuccess;
     if (!ok) {
         h->free_table();
@@ -863,8 +862,8 @@ int infaas_sel_load_variants(infaas_sel_t *h, int32_t V, const int32_t *task_id,
          up(h->d_rank, rank.data(), (size_t)B * Vp * 4) && up(h->d_perm, perm.data(), (size_t)B * Vp * 4) &&
          up(h->d_seg_off, seg_off.data(), ((size_t)T + 1) * 4) && up(h->d_seg_len, seg_len.data(), (size_t)T * 4) &&
          up(h->d_slot_of, slot_of.data(), (size_t)std::max(V, 1) * 4) &&
-         up(h->d_acc_r, acc_r.data(), (size_t)B * Vp * 4) && up(h->d_lat_r, lat_r.data(), (size_t)B * Vp * 4) &&
-         up(h->d_orig_r, orig_r.data(), (size_t)B * Vp * 4) && up(h->d_gpos, gpos.data(), (size_t)B * Vp * 4) &&
+         up(h->d_acc_r, acc_r.data(), (size_t)B * Vp * 4) && up(h->d_orig_r, orig_r.data(), (size_t)B * Vp * 4) &&
+        
          up(h->d_tot_r, tot_r.data(), (size_t)B * Vp * 4);
     if (!ok) {
         h->free_table();
@@ -875,20 +874,24 @@ int infaas_sel_load_variants(infaas_sel_t *h, int32_t V, const int32_t *task_id,
     h->max_segment = max_seg;
     h->max_lds_segment = max_lds_seg;
     h->wide_segments = wide;
-    h->table_bytes = (int64_t)Vp * 4 * (3 + 8 * (int64_t)B) + ((int64_t)2 * T + 1 + std::max(V, 1)) * 4;
+    h->table_bytes = (int64_t)Vp * 4 * (3 + 6 * (int64_t)B) + (int64_t)std::max(V, 1) * B * 8 + ((int64_t)2 * T + 1 + std::max(V, 1)) * 4;
     TableView tv{};
     tv.T = T; tv.B = B; tv.S = T * B; tv.V = V; tv.Vp = Vp; tv.lds_limit = h->lds_limit; tv.max_len = max_seg;
     tv.acc = h->d_acc; tv.queue = h->d_queue; tv.orig = h->d_orig; tv.lat = h->d_lat;
     tv.rank = h->d_rank; tv.perm = h->d_perm; tv.seg_off = h->d_seg_off; tv.seg_len = h->d_seg_len;
     tv.slot_of = h->d_slot_of;
-    tv.acc_r = h->d_acc_r; tv.tot_r = h->d_tot_r; tv.lat_r = h->d_lat_r; tv.orig_r = h->d_orig_r;
-    tv.gpos = h->d_gpos;
+    tv.acc_r = h->d_acc_r; tv.tot_r = h->d_tot_r; tv.orig_r = h->d_orig_r;
+    tv.row_entry = h->d_row_entry;
     tv.acc_base = 0;
     for (int64_t v = 0; v < V; ++v) tv.acc_base = (v == 0 || acc_bp[v] < tv.acc_base) ? acc_bp[v] : tv.acc_base;
     // the lookup forms acc_base - 1; a slice that holds the one accuracy below this base is not indexed
     if (tv.acc_base == INT32_MIN) tv.acc_base = INT32_MIN + 1;
     tv.state = nullptr;
     tv.want_state = 1;
+    if (!HIP_OK(launch_row_entries(tv, nullptr))) {
+        h->free_table();
+        return INFAAS_SEL_ERR_HIP;
+    }
     h->tv = tv;
     h->h_task.swap(keep_task); h->h_acc.swap(keep_acc); h->h_lat.swap(keep_lat);
     h->loaded = true;
@@ -898,6 +901,10 @@ int infaas_sel_load_variants(infaas_sel_t *h, int32_t V, const int32_t *task_id,
             h->free_table();
             return rc;
         }
+    }
+    if (!h->have_index && !HIP_OK(hipDeviceSynchronize())) {   // (the index build has waited for row_entry)
+        h->free_table();
+        return INFAAS_SEL_ERR_HIP;
     }
     return INFAAS_SEL_OK;
 }
@@ -977,15 +984,15 @@ int infaas_sel_load_states(infaas_sel_t *h, const int32_t *state, const int32_t 
     if (rc == INFAAS_SEL_OK && !sub->have_index) rc = INFAAS_SEL_ERR_INVALID_ARG;
     int32_t *d_states = nullptr;
     if (rc == INFAAS_SEL_OK) {
-        const size_t vp = (size_t)h->Vp;
-        if (!h->d_state && dev_alloc(&h->d_state, vp) != hipSuccess) rc = INFAAS_SEL_ERR_OOM;
-        if (rc == INFAAS_SEL_OK && dev_alloc(&sub->d_state, vp) != hipSuccess) rc = INFAAS_SEL_ERR_OOM;
-        if (rc == INFAAS_SEL_OK && dev_alloc(&d_states, (size_t)std::max(V, 1)) != hipSuccess) rc = INFAAS_SEL_ERR_OOM;
+        const size_t rows = (size_t)std::max(V, 1);
+        if (!h->d_state && dev_alloc(&h->d_state, rows) != hipSuccess) rc = INFAAS_SEL_ERR_OOM;
+        if (rc == INFAAS_SEL_OK && dev_alloc(&sub->d_state, rows) != hipSuccess) rc = INFAAS_SEL_ERR_OOM;
+        if (rc == INFAAS_SEL_OK && dev_alloc(&d_states, rows) != hipSuccess) rc = INFAAS_SEL_ERR_OOM;
         if (rc == INFAAS_SEL_ERR_OOM) (void)hipGetLastError();
     }
     if (rc == INFAAS_SEL_OK) {
-        // padding slots get a state no table serves
-        if (!HIP_OK(hipMemset(h->d_state, 0x7F, (size_t)h->Vp * 4)) || !HIP_OK(hipMemset(sub->d_state, 0x7F, (size_t)h->Vp * 4)) ||
+        // a state that is none, so that every row's is seen to change
+        if (!HIP_OK(hipMemset(h->d_state, 0x7F, (size_t)V * 4)) || !HIP_OK(hipMemset(sub->d_state, 0x7F, (size_t)V * 4)) ||
             (V > 0 && !HIP_OK(hipMemcpy(d_states, state, (size_t)V * 4, hipMemcpyHostToDevice))))
             rc = INFAAS_SEL_ERR_HIP;
     }

@@ -27,12 +27,13 @@ struct TableView {
     const int32_t *seg_len;     // [T]
     const int32_t *slot_of;     // [V] caller row -> slot
     // The same slices once more, stored in rank order: entry seg_off[t] + r of column b is the
-    // variant of rank r in slice (t, b).  tot_r = lat_r + queue is kept current by load updates.
+    // variant of rank r in slice (t, b).  tot_r = latency + queue is kept current by load updates.
     int32_t *acc_r;             // [B][Vp]
     uint32_t *tot_r;            // [B][Vp]
-    const int32_t *lat_r;       // [B][Vp]
     const int32_t *orig_r;      // [B][Vp] caller row
-    const int32_t *gpos;        // [B][Vp] slot -> its entry in the rank-ordered column b
+    // By caller row, so that what a report reads of a row is one or two lines of memory: its entry in the
+    // rank-ordered column b and its latency there, side by side.
+    int2 *row_entry;            // [V][B] {entry, latency}
     // Two search structures over the entries, in rank order, of a slice that the index cannot hold completely,
     // written by the index build for those slices.  Both are made of nodes of 16 pairs {accuracy,
     // latency-plus-queue} (128 bytes); rank_hdr names a slice's first.
@@ -51,7 +52,7 @@ struct TableView {
     // State-aware selection: a table serves one state (Active or Inactive).  Variants in another
     // state are masked in the rank-ordered columns (accuracy = acc_base, latency-plus-queue =
     // 0xFFFFFFFF): nothing selects them and every entry ranked before them dominates them.
-    int32_t *state;             // [Vp] state of each slot, or null when the table is not state-aware
+    int32_t *state;             // [V] state of each caller row, or null when the table is not state-aware
     int32_t want_state;         // the state this table serves
     // Six counters of the latest build of the table's index (kCtlMaxK0 .. kCtlMaxK, kCtlPool, kCtlSteps) and
     // where the first kernel of every selection copies them for the host to see (pinned host memory); null: nowhere.
@@ -230,6 +231,8 @@ inline hipError_t launch_kernel(const LaunchEvents *ev, void (*kernel)(P...), di
 // index: the index that is rebuilt afterwards (its allocator counters are rewound), or null.
 hipError_t launch_update_load(const TableView &tv, int32_t n, const int32_t *idx,
                               const int32_t *val, const IndexView *index, hipStream_t st, const LaunchEvents *ev = nullptr);
+// tv.row_entry of a table as loaded (tot_r = latency + queue everywhere).
+hipError_t launch_row_entries(const TableView &tv, hipStream_t st);
 // State report on the two tables of a state-aware handle (Active tier, Inactive tier): the state of row idx[i]
 // becomes val[i] (idx null: of row i), masks refreshed, both indexes rewound.
 hipError_t launch_update_state(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, int32_t n,
