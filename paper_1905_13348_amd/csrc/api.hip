@@ -527,21 +527,23 @@ int ensure_open(infaas_sel *h, int64_t n, bool side)
 // 14.3 and 8.8 / 9.0 / 9.7 / 9.4; config 3's, 7%: 4.3 / 7.0 / 9.8 / 17.4 and 16.0 / 17.2 / 17.6 / 20.7).  The less of the
 // index the mirror holds, the later it pays.
 constexpr int64_t kDirectQueries = 100000;
-bool use_direct(const infaas_sel *h, int64_t n)
+int64_t direct_limit(const infaas_sel *h)
 {
-    if (h->index_lds_bytes == 0) return n <= kDirectQueries;   // (no mirror, four interleaved queries per lane)
+    if (h->index_lds_bytes == 0) return kDirectQueries;   // (no mirror, four interleaved queries per lane)
     const int64_t room = (int64_t)h->index_lds_bytes - kLdsCtrlBytes - lds_header_bytes(h->tv.S);
     const int64_t pool = h->ix.num_groups > 1 ? h->ix_bytes : h->host_stats ? ((volatile uint32_t *)h->host_stats)[4] : h->ix_stats[kCtlPool];
-    return n <= (pool <= room ? kDirectQueries : kDirectQueries * pool / room);
+    return pool <= room ? kDirectQueries : kDirectQueries * pool / room;
 }
+bool use_direct(const infaas_sel *h, int64_t n) { return n <= direct_limit(h); }
 
 // One pass of the index engine over n <= 2^28 queries.
 int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
-    if (q.pass == 0 && use_direct(h, q.n)) {
-        if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
-        return INFAAS_SEL_OK;
+    if (q.pass <= 1 && use_direct(h, q.n)) {
+        const hipError_t e = q.pass == 0 ? launch_direct_select(h->tv, h->ix, q, false, h->num_cus, st, t.ev())
+                                         : launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, h->num_cus, st, t.ev());
+        return HIP_OK(e) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
     }
     if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->d_park, h->index_lds_bytes, h->num_cus, st, t.ev())))
         return INFAAS_SEL_ERR_HIP;
@@ -1102,7 +1104,12 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     DeviceGuard g(h->device);
     if (!g.ok) return INFAAS_SEL_ERR_HIP;
     hipStream_t st = (hipStream_t)hip_stream;
-    int rc = ensure_open(h, std::min(N, kMaxTierPass), closest);
+    // Two mirrors and two launches against one kernel: the sum of the tables' limits.  (us for 10,000 / 100,000 / 200,000 /
+    // 400,000 queries on 100 tasks of 200 variants: two tiers 7.8 / 8.2 / 12.8 / 21.4 direct, 13.9 / 14.9 / 14.9 / 15.9
+    // mirrored; with workers 8.8 / 8.7 / 13.8 / 22.8 and 16.9 / 17.9 / 18.4 / 20.2; complete Case I with workers 11.3 / 13.6 /
+    // 19.0 / 34.7 and 21.7 / 23.3 / 26.8 / 30.7)
+    const bool direct = N <= direct_limit(h) + direct_limit(h->inactive);
+    int rc = direct ? INFAAS_SEL_OK : ensure_open(h, std::min(N, kMaxTierPass), closest);
     if (rc != INFAAS_SEL_OK) return rc;
     if (workers) {
         // bring the worker of every variant, then of every step of both indexes, up to date
@@ -1133,6 +1140,12 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
         q.open_cap = index_open_cap(q.n, h->num_cus);
         if (workers) { q.worker = d_out_worker + done; q.row_worker = h->wv.row_worker; }
         if (closest) q.closest = d_out_closest + done;
+        if (direct) {
+            LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
+            if (!HIP_OK(launch_direct_modes(h->tv, h->ix, h->inactive->tv, h->inactive->ix, q, true, h->num_cus, st, t.ev())))
+                return INFAAS_SEL_ERR_HIP;
+            continue;
+        }
         q.pass = workers ? (closest ? 8 : 4) : closest ? 6 : 2;
         rc = index_pass(h, q, st);
         if (rc != INFAAS_SEL_OK) return rc;

@@ -9,8 +9,112 @@ namespace {
 
 constexpr int kDirThreads = 256;
 
-// kRanked: slices whose steps are not all in their bodies go through their entries in rank order at once (for
-// tables that consist mostly of such slices); otherwise only with what the bodies leave open.
+// The slice of one query per lane and what the lookups of all modes need of it.
+struct Query {
+    int32_t task, bidx, slo, min_acc;
+    bool inside, valid;   // names a slice of the table; and has a bound that anything can meet
+    uint32_t s;           // its slice, or the empty one
+};
+__device__ __forceinline__ Query load_query(const TableView &tv, const QueryView &q, int64_t i)
+{
+    const bool in = i < q.n;
+    Query u;
+    u.task = in ? q.task[i] : -1; u.slo = in ? q.slo[i] : -1; u.min_acc = in ? q.min_acc[i] : 0; u.bidx = in ? q.bidx[i] : -1;
+    u.inside = (uint32_t)u.task < (uint32_t)tv.T && (uint32_t)u.bidx < (uint32_t)tv.B;
+    u.valid = u.inside && u.slo >= 0;
+    u.s = u.inside ? (uint32_t)u.task * (uint32_t)tv.B + (uint32_t)u.bidx : (uint32_t)tv.S;
+    return u;
+}
+
+// The selection for the lanes in `want` (of valid queries), -1 elsewhere.  kRanked: slices whose steps are not all
+// in their bodies go through their entries in rank order at once; otherwise only with what the bodies leave
+// open.  Counts in st what became of the queries, as the lookup kernel does; no query is decided by an
+// LDS copy here, so all count as parked.
+template <bool kRanked>
+__device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want,
+                                                      uint32_t (&st)[kLookupStats])
+{
+    auto count = [&](int what, bool yes) { st[what] += (uint32_t)__builtin_popcountll(__ballot(yes)); };
+    const uint32_t max_k = ix.ctrl[kCtlMaxK0];
+    const int nit = 32 - __builtin_clz(max_k | 1u);    // <= 5
+    const GlobalMem gmem{ix.pool};
+    const uint32_t s = want ? u.s : (uint32_t)tv.S;
+    const uint4 h = ix.hdr[s], rh = tv.rank_hdr[s];
+    int32_t ans = -1;
+    const bool body = want && !(h.y & kHdrPark) && !(kRanked && (h.y & kHdrTrunc));
+    if (__ballot(body)) {
+        const uint32_t keys0 = (h.y >> kHdrK0Shift) & 0x3Fu, keys1 = (h.y >> kHdrK1Shift) & 0x3Fu;
+        const uint32_t dd[1] = {acc_threshold(u.min_acc, tv.acc_base - 1)}, lim[1] = {(uint32_t)u.slo};
+        const uint32_t bd[1] = {body ? h.x : 0u}, ks[1] = {body ? keys0 : 2u};
+        uint32_t m[1];
+        search_bodies<1>(gmem, nit, bd, ks, dd, lim, m);
+        const bool hit0 = body && m[0] != 0u;
+        uint32_t at = hit0 ? h.z + (uint32_t)__builtin_ctz(m[0]) : 0u;   // (entry 0 of step_row is -1)
+        count(2, hit0);
+        const bool more = body && !hit0 && keys1 != 0u;
+        if (__ballot(more)) {
+            const uint32_t bd1[1] = {more ? h.x + body_bytes(keys0) : 0u}, ks1[1] = {more ? keys1 : 2u};
+            search_bodies<1>(gmem, nit, bd1, ks1, dd, lim, m);
+            const bool hit1 = more && m[0] != 0u;
+            if (hit1) at = h.z + kBodySteps + (uint32_t)__builtin_ctz(m[0]);
+            count(1, hit1);
+        }
+        ans = ix.step_row[at];
+    }
+    const bool scan = want && ans < 0 && (h.y & kHdrTrunc);
+    if (__ballot(scan)) {
+        const int32_t row = ranked_first_fit(tv, scan ? rh : make_uint4(0u, 0u, 0u, 0u), u.min_acc, (uint32_t)u.slo);
+        if (scan) ans = row;
+        count(3, scan);
+    }
+    count(0, want);
+    count(4, want && ans < 0);
+    return ans;
+}
+
+// The closest variant of the table for the lanes in `want` (queries inside the table that nothing satisfies),
+// and how far it is from the requirements: from the bodies, or where they are not all of the slice's steps
+// by the wavefront over the whole slice.
+__device__ __forceinline__ int32_t closest_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want, HowFar &how)
+{
+    how = HowFar{3, 0, 0};
+    int32_t sug = -1;
+    const uint32_t s = want ? u.s : (uint32_t)tv.S;
+    const uint4 h = ix.hdr[s];
+    const bool by_index = want && !(h.y & (kHdrPark | kHdrTrunc));
+    if (__ballot(by_index)) {
+        const uint32_t max_k = ix.ctrl[kCtlMaxK0];
+        const ClosestStep c = closest_step(GlobalMem{ix.pool}, 32 - __builtin_clz(max_k | 1u), by_index ? h.x : 0u,
+                                           by_index ? (h.y >> kHdrK0Shift) & 0x3Fu : 2u, by_index ? (h.y >> kHdrK1Shift) & 0x3Fu : 0u,
+                                           acc_threshold(u.min_acc, tv.acc_base - 1), u.slo, u.min_acc, tv.acc_base - 1);
+        if (by_index && c.step >= 0) { sug = ix.step_row[h.z + (uint32_t)c.step]; how = c.how; }
+    }
+    uint64_t rest = __ballot(want && !by_index);
+    while (rest) {
+        const int l = __builtin_ctzll(rest);
+        rest &= rest - 1;
+        HowFar far;
+        const int32_t found = closest_by_scan(tv, __builtin_amdgcn_readlane(u.task, l), __builtin_amdgcn_readlane(u.bidx, l),
+                                              __builtin_amdgcn_readlane(u.min_acc, l), __builtin_amdgcn_readlane(u.slo, l),
+                                              (int)(threadIdx.x & 63), &far);
+        if ((int)(threadIdx.x & 63) == l) { sug = found; how = far; }
+    }
+    return sug;
+}
+
+// The workgroup's counts into its entry of the statistics (l_st: kLookupStats words of LDS, cleared before).
+__device__ __forceinline__ void leave_statistics(const IndexView &ix, uint32_t *l_st, const uint32_t (&st)[kLookupStats])
+{
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int k = 0; k < kLookupStats; ++k)
+            if (st[k]) atomicAdd(&l_st[k], st[k]);
+    }
+    __syncthreads();
+    if (threadIdx.x < kLookupStats) ix.stats[blockIdx.x * kLookupStats + threadIdx.x] = l_st[threadIdx.x];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *ix.stat_used = gridDim.x;
+}
+
 // Bound by the rate of scattered reads: 14 per query through a body (header, ten probes, two sets, row), each
 // lane another line.  Sixteen wavefronts per compute unit already saturate that: register caps for 24 to 32
 // (80 to 64 registers instead of 89) were measured 0-25% slower on batches of a million.
@@ -18,64 +122,66 @@ template <bool kRanked>
 __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, IndexView ix, QueryView q)
 {
     __shared__ uint32_t l_st[kLookupStats];
-    const int tid = threadIdx.x, lane = tid & 63;
     publish_index_stats(tv);
-    if (tid < kLookupStats) l_st[tid] = 0u;
+    if (threadIdx.x < kLookupStats) l_st[threadIdx.x] = 0u;
     __syncthreads();
-    const int32_t acc_base_m1 = tv.acc_base - 1;
-    const uint32_t max_k = ix.ctrl[kCtlMaxK0];
-    const int nit = 32 - __builtin_clz(max_k | 1u);    // <= 5
-    const GlobalMem gmem{ix.pool};
-    // as in the lookup kernel; no query is decided by an LDS copy here, so all valid ones count as parked
     uint32_t st[kLookupStats] = {0u, 0u, 0u, 0u, 0u};
-    auto count = [&](int what, bool yes) { st[what] += (uint32_t)__builtin_popcountll(__ballot(yes)); };
-    for (int64_t i0 = (int64_t)blockIdx.x * kDirThreads + (tid & ~63); i0 < q.n; i0 += (int64_t)gridDim.x * kDirThreads) {
-        const int64_t i = i0 + lane;
-        const bool in = i < q.n;
-        const int32_t task = in ? q.task[i] : -1, slo = in ? q.slo[i] : -1, min_acc = in ? q.min_acc[i] : 0;
-        const int32_t bidx = in ? q.bidx[i] : -1;
-        const bool valid = (uint32_t)task < (uint32_t)tv.T && (uint32_t)bidx < (uint32_t)tv.B && slo >= 0;
-        const uint32_t s = valid ? (uint32_t)task * (uint32_t)tv.B + (uint32_t)bidx : (uint32_t)tv.S;
-        const uint4 h = ix.hdr[s], rh = tv.rank_hdr[s];
-        int32_t ans = -1;
-        const bool body = valid && !(h.y & kHdrPark) && !(kRanked && (h.y & kHdrTrunc));
-        if (__ballot(body)) {
-            const uint32_t keys0 = (h.y >> kHdrK0Shift) & 0x3Fu, keys1 = (h.y >> kHdrK1Shift) & 0x3Fu;
-            const uint32_t dd[1] = {acc_threshold(min_acc, acc_base_m1)}, lim[1] = {(uint32_t)slo};
-            const uint32_t bd[1] = {body ? h.x : 0u}, ks[1] = {body ? keys0 : 2u};
-            uint32_t m[1];
-            search_bodies<1>(gmem, nit, bd, ks, dd, lim, m);
-            const bool hit0 = body && m[0] != 0u;
-            uint32_t at = hit0 ? h.z + (uint32_t)__builtin_ctz(m[0]) : 0u;   // (entry 0 of step_row is -1)
-            count(2, hit0);
-            const bool more = body && !hit0 && keys1 != 0u;
-            if (__ballot(more)) {
-                const uint32_t bd1[1] = {more ? h.x + body_bytes(keys0) : 0u}, ks1[1] = {more ? keys1 : 2u};
-                search_bodies<1>(gmem, nit, bd1, ks1, dd, lim, m);
-                const bool hit1 = more && m[0] != 0u;
-                if (hit1) at = h.z + kBodySteps + (uint32_t)__builtin_ctz(m[0]);
-                count(1, hit1);
-            }
-            ans = ix.step_row[at];
-        }
-        const bool scan = valid && ans < 0 && (h.y & kHdrTrunc);
-        if (__ballot(scan)) {
-            const int32_t row = ranked_first_fit(tv, scan ? rh : make_uint4(0u, 0u, 0u, 0u), min_acc, (uint32_t)slo);
-            if (scan) ans = row;
-            count(3, scan);
-        }
-        count(0, valid);
-        count(4, valid && ans < 0);
-        if (in) q.out[i] = ans;
+    for (int64_t i0 = (int64_t)blockIdx.x * kDirThreads; i0 < q.n; i0 += (int64_t)gridDim.x * kDirThreads) {
+        const int64_t i = i0 + threadIdx.x;
+        const Query u = load_query(tv, q, i);
+        const int32_t ans = select_from_memory<kRanked>(tv, ix, u, u.valid, st);
+        if (i < q.n) q.out[i] = ans;
     }
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < kLookupStats; ++k)
-            if (st[k]) atomicAdd(&l_st[k], st[k]);
-    }
+    leave_statistics(ix, l_st, st);
+}
+
+// The other modes of the lookup in one launch: both tiers after one another for the lanes that need them, no lists
+// in between.  kTiers: ta / ia serve the Active variants, tb / ib the Inactive ones (otherwise there is only ta);
+// kSuggest: the closest variant (of both tiers) where there is no answer; kWorker: the worker of every answer.
+// At 1001 to 100,001 queries bound by its launch and the chain of dependent reads, like the two passes of the
+// lookup kernel that it replaces, but once and without the two LDS mirrors.
+template <bool kTiers, bool kSuggest, bool kWorker>
+__global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, IndexView ia, TableView tb, IndexView ib, QueryView q)
+{
+    __shared__ uint32_t l_st[kLookupStats];
+    publish_index_stats(ta);
+    if (kTiers) publish_index_stats(tb);
+    if (threadIdx.x < kLookupStats) l_st[threadIdx.x] = 0u;
     __syncthreads();
-    if (tid < kLookupStats) ix.stats[blockIdx.x * kLookupStats + tid] = l_st[tid];
-    if (blockIdx.x == 0 && tid == 0) *ix.stat_used = gridDim.x;
+    uint32_t st[kLookupStats] = {0u, 0u, 0u, 0u, 0u};
+    for (int64_t i0 = (int64_t)blockIdx.x * kDirThreads; i0 < q.n; i0 += (int64_t)gridDim.x * kDirThreads) {
+        const int64_t i = i0 + threadIdx.x;
+        const Query u = load_query(ta, q, i);
+        int32_t ans = select_from_memory<false>(ta, ia, u, u.valid, st), tier = ans >= 0 ? 1 : 0;
+        if (kTiers) {
+            const bool next = u.valid && ans < 0;
+            if (__ballot(next)) {
+                const int32_t row = select_from_memory<false>(tb, ib, u, next, st);
+                if (next && row >= 0) { ans = row; tier = 2; }
+            }
+        }
+        int32_t closest = ans;
+        if (kSuggest) {
+            const bool none = u.inside && ans < 0;
+            if (__ballot(none)) {
+                HowFar how;
+                int32_t sug = closest_from_memory(ta, ia, u, none, how);
+                if (kTiers) {   // the closer of the two tiers' suggestions, the first tier's at a tie
+                    HowFar how2;
+                    const int32_t sug2 = closest_from_memory(tb, ib, u, none, how2);
+                    if (sug2 >= 0 && !(sug >= 0 && closer_or_equal(how, how2))) sug = sug2;
+                }
+                if (none) closest = sug;
+            }
+        }
+        if (i < q.n) {
+            q.out[i] = ans;
+            if (kTiers) q.tier[i] = tier;
+            if (kSuggest) q.closest[i] = closest;
+            if (kWorker) q.worker[i] = ans >= 0 ? q.row_worker[(tier == 2 ? ta.V : 0) + ans] : -1;
+        }
+    }
+    leave_statistics(kTiers ? ib : ia, l_st, st);
 }
 
 }  // namespace
@@ -85,6 +191,15 @@ hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const 
 {
     const int64_t want = ((int64_t)q.n + kDirThreads - 1) / kDirThreads, most = index_stat_blocks(num_cus);
     return launch_kernel(ev, ranked ? k_direct_select<true> : k_direct_select<false>, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, tv, ix, q);
+}
+
+hipError_t launch_direct_modes(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, const QueryView &q,
+                               bool tiers, int num_cus, hipStream_t st, const LaunchEvents *ev)
+{
+    const int64_t want = ((int64_t)q.n + kDirThreads - 1) / kDirThreads, most = index_stat_blocks(num_cus);
+    auto kernel = !tiers ? k_direct_modes<false, true, false> : q.worker ? (q.closest ? k_direct_modes<true, true, true> : k_direct_modes<true, false, true>)
+                                                              : (q.closest ? k_direct_modes<true, true, false> : k_direct_modes<true, false, false>);
+    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, ta, ia, tb, ib, q);
 }
 
 }  // namespace infaas

@@ -278,5 +278,126 @@ __device__ __forceinline__ uint32_t acc_threshold(int32_t min_acc, int32_t acc_b
     return (uint32_t)(d < 1 ? 1 : (d > 65536 ? 65536 : d));
 }
 
+// ---- closest variant (the suggestion of Section 4.1 for a query that nothing satisfies): the
+// variant of the slice that is first by (requirements missed, latency overshoot, accuracy
+// shortfall, rank).  It is always a step.  If some step fits the latency bound it is the most
+// accurate of those; else if some step is accurate enough, the fastest of those; else the fastest
+// of all, the most accurate among equally fast ones; ties go to the earlier rank throughout.
+
+// Counts of one body: accuracy keys >= dd and latency keys <= lim (none when the bound is negative).
+template <class Mem>
+__device__ __forceinline__ void body_counts(const Mem &mem, int nit, uint32_t body, uint32_t re, uint32_t dd,
+                                            uint32_t lim, bool lim_ok, uint32_t &pa, uint32_t &ps)
+{
+    const uint32_t la = body + 2u * re, lt = la + 4u * re;
+    uint32_t a = body, t = la;
+#pragma unroll
+    for (int it = 4; it >= 0; --it) {
+        if (it < nit) {
+            const uint32_t ca = a + (2u << it), ct = t + (4u << it);
+            const uint32_t ka = mem.ld16(ca < la ? ca : la, 2u);
+            const uint32_t kt = mem.ld32(ct < lt ? ct : lt, 0u);
+            a = ka >= dd ? ca : a;
+            t = kt <= lim ? ct : t;
+        }
+    }
+    pa = (a - body) >> 1;
+    ps = lim_ok ? (t - la) >> 2 : 0u;
+}
+
+// Smallest p in 1..re-1 whose set (tbl = address of entry 0 of A or of S, minus 4) meets `mask`.
+template <class Mem>
+__device__ __forceinline__ uint32_t first_meeting(const Mem &mem, uint32_t tbl, uint32_t re, uint32_t mask)
+{
+    uint32_t p = 0;   // the largest p found so far whose set misses the mask (set 0 is empty)
+#pragma unroll
+    for (uint32_t step = 16; step; step >>= 1) {
+        const uint32_t c = p + step < re - 1u ? p + step : re - 1u;
+        const uint32_t set = mem.ld32(tbl + 4u * c, 4u);
+        p = (p + step <= re - 1u && (set & mask) == 0u) ? p + step : p;
+    }
+    return p + 1u;
+}
+
+// What one body offers: the step, and the keys the bodies are compared by.
+struct Offer {
+    uint32_t tot, acc, step;   // latency-plus-queue key, accuracy key, step number in the body
+};
+// kind 1: most accurate step among those within the latency bound (ps > 0 of them);
+// kind 2: fastest step among those accurate enough (pa > 0 of them);
+// kind 3: fastest step of all, the most accurate of equally fast ones.  The body has >= 1 step.
+template <class Mem>
+__device__ __forceinline__ Offer body_offer(const Mem &mem, int nit, uint32_t body, uint32_t re, int kind,
+                                            uint32_t pa, uint32_t ps)
+{
+    const uint32_t acc_k = body, tot_k = body + 2u * re, a_tbl = body + 6u * re, s_tbl = body + 10u * re;
+    Offer o;
+    if (kind == 2) {
+        const uint32_t mask = mem.ld32(a_tbl + 4u * pa, 4u);
+        const uint32_t p = first_meeting(mem, s_tbl, re, mask);
+        o.tot = mem.ld32(tot_k + 4u * p, 0u);
+        o.acc = 0u;
+        o.step = (uint32_t)__builtin_ctz(mem.ld32(s_tbl + 4u * p, 4u) & mask);
+        return o;
+    }
+    uint32_t fast = ps;   // kind 3: the steps that share the smallest latency key
+    o.tot = mem.ld32(tot_k + 4u, 0u);
+    if (kind == 3) {
+        uint32_t unused;
+        body_counts(mem, nit, body, re, 0x20000u, o.tot, true, unused, fast);
+    }
+    const uint32_t mask = mem.ld32(s_tbl + 4u * fast, 4u);
+    const uint32_t p = first_meeting(mem, a_tbl, re, mask);
+    o.acc = mem.ld16(acc_k + 2u * p, 2u);
+    o.step = (uint32_t)__builtin_ctz(mem.ld32(a_tbl + 4u * p, 4u) & mask);
+    return o;
+}
+
+// Closest step of a slice with one or two bodies (re1 = 0: one): the step number in the slice, or -1
+// when the slice has nothing to suggest, and how far that step is from the requirements (from its keys:
+// no other memory is read).  body1 follows body0 in memory.  min_acc and acc_base_m1 (= accuracy
+// base - 1) turn an accuracy key back into an accuracy.
+struct ClosestStep {
+    int32_t step;
+    HowFar how;
+};
+template <class Mem>
+__device__ __forceinline__ ClosestStep closest_step(const Mem &mem, int nit, uint32_t body0, uint32_t re0, uint32_t re1,
+                                                    uint32_t dd, int32_t slo, int32_t min_acc, int32_t acc_base_m1)
+{
+    const ClosestStep none{-1, HowFar{3, 0, 0}};
+    if (mem.ld32(body0 + 2u * re0 + 4u, 0u) == 0xFFFFFFFFu) return none;   // first latency key is the sentinel: no steps
+    const uint32_t body1 = body0 + body_bytes(re0);
+    const bool lim_ok = slo >= 0;
+    uint32_t pa0, ps0, pa1 = 0, ps1 = 0;
+    body_counts(mem, nit, body0, re0, dd, (uint32_t)slo, lim_ok, pa0, ps0);
+    if (re1) body_counts(mem, nit, body1, re1, dd, (uint32_t)slo, lim_ok, pa1, ps1);
+    const int kind = (ps0 | ps1) ? 1 : ((pa0 | pa1) ? 2 : 3);
+    const bool use0 = kind == 1 ? ps0 > 0 : (kind == 2 ? pa0 > 0 : true);
+    const bool use1 = re1 && (kind == 1 ? ps1 > 0 : (kind == 2 ? pa1 > 0 : true));
+    Offer o0{0, 0, 0}, o1{0, 0, 0};
+    if (use0) o0 = body_offer(mem, nit, body0, re0, kind, pa0, ps0);
+    if (use1) o1 = body_offer(mem, nit, body1, re1, kind, pa1, ps1);
+    bool second = use1 && !use0;
+    if (use0 && use1) {   // ties go to the first body, whose steps rank earlier
+        if (kind == 1) second = o1.acc > o0.acc;
+        else if (kind == 2) second = o1.tot < o0.tot;
+        else second = o1.tot < o0.tot || (o1.tot == o0.tot && o1.acc > o0.acc);
+    }
+    // A table that serves one state keeps the variants of the other states as entries nothing selects
+    // (lowest accuracy key, latency key all ones).  Such an entry can be a step, and it is the closest one
+    // exactly when the slice has no variant of the table's state: then there is nothing to suggest.  (Of
+    // kind 1 the step is within the latency bound, so it is never such an entry.)
+    const Offer o = second ? o1 : o0;
+    if (kind != 1 && o.tot == 0xFFFFFFFFu) return none;
+    // kind 1: within the latency bound, not accurate enough; 2: accurate enough, too slow; 3: neither
+    ClosestStep c;
+    c.step = second ? (int32_t)(kBodySteps + o.step) : (int32_t)o.step;
+    c.how.missed = kind == 3 ? 2 : 1;
+    c.how.over = kind == 1 ? 0 : (int64_t)o.tot - (int64_t)slo;
+    c.how.shortf = kind == 2 ? 0 : (int64_t)min_acc - ((int64_t)o.acc + (int64_t)acc_base_m1);
+    return c;
+}
+
 }  // namespace
 }  // namespace infaas

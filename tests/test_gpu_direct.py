@@ -6,8 +6,13 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_util import make_selector, query_args, table_args
-from test_gpu_parity import _assert_equal_everywhere, _random_table
+from gpu_util import gpu_select_closest, make_selector, query_args, table_args
+from test_gpu_case1 import gpu_case1
+from test_gpu_getvariant import gpu_get_variant
+from test_gpu_parity import (_assert_equal_everywhere, _random_queries, _random_table, _staircase_queries,
+                             _staircase_table)
+from test_gpu_tiered import gpu_select_tiered
+from test_gpu_workers import _random_cluster, gpu_select_workers, load_cluster
 
 pytestmark = pytest.mark.gpu
 
@@ -46,4 +51,49 @@ def test_small_batches(oracle_lib, kind):
                 assert (got[n:] == -7).all()
     info = sel.info()
     assert info["lookup_parked"] >= info["lookup_second_body"] + info["lookup_unanswered"]
+    sel.destroy()
+
+
+@pytest.mark.parametrize("kind", ["ties", "staircase63", "staircase300", "one_tier", "masked"])
+def test_every_mode_below_and_above_the_limit(oracle_lib, kind):
+    """The calls besides the plain selection on tables that make their paths differ: ties, slices with more
+    steps than the index keeps, slices without a variant of one tier or of both.  3001 queries in one call
+    (straight from memory) and the same queries over and over in a call of 300,000 (through the LDS
+    mirrors and, with states, the lists between the tiers); every element against the CPU oracle."""
+    rng = np.random.default_rng(len(kind) * 31)
+    if kind.startswith("staircase"):
+        steps = int(kind[9:])
+        tb, span = _staircase_table(5, steps), None
+        q = _staircase_queries(rng, tb, 3001, steps)
+    else:
+        span = 4 if kind == "ties" else None
+        tb = _random_table(rng, 9, np.asarray([40, 0, 7, 130, 1, 64, 33, 90, 300]), 3, span=span)
+        q = _random_queries(rng, 9, 3, 3001, span=span)
+    vals = span if span else 50_000
+    state = rng.integers(0, 4, tb.V).astype(np.int32)
+    if kind == "one_tier":     # some tasks all Active, some all Inactive
+        state = (tb.task_id % 2).astype(np.int32)
+    if kind == "masked":       # some tasks that nothing of may be selected from
+        state[tb.task_id % 3 == 0] = 2
+    load = rng.integers(0, vals, tb.V).astype(np.int32)
+    cl = _random_cluster(rng, tb.V, state, vals)
+    times = 100
+    many = tuple(np.tile(x, times) for x in q)
+
+    def check(got, want, label):
+        for g, w, what in zip(got, want, ("variant", "second", "third", "fourth")):
+            _assert_equal_everywhere(g, np.tile(w, times) if g.size > w.size else w, f"{kind} {label} {what}")
+
+    sel = make_selector(tb, engine=2)
+    want = oracle_lib.select_closest(*table_args(tb), *q)
+    for qs in (q, many):
+        check(gpu_select_closest(sel, *qs), want, f"closest N={len(qs[0])}")
+    sel.load_states(state, load)
+    load_cluster(sel, cl)
+    for name, call, want in (("tiered", gpu_select_tiered, oracle_lib.select_tiered(*table_args(tb), state, load, *q)),
+                             ("case1", gpu_case1, oracle_lib.select_case1(*table_args(tb), state, load, *q)),
+                             ("workers", gpu_select_workers, oracle_lib.select_workers(*table_args(tb), state, load, *cl, *q)),
+                             ("getvariant", gpu_get_variant, oracle_lib.get_variant(*table_args(tb), state, load, *cl, *q))):
+        for qs in (q, many):
+            check(call(sel, *qs), want, f"{name} N={len(qs[0])}")
     sel.destroy()
