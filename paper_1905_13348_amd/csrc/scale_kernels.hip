@@ -31,10 +31,17 @@ constexpr int kThreads = 256;
 constexpr int kChunk = 4;   // candidates of a list read together
 typedef unsigned __int128 u128;
 
+// 1 / per for 1 <= per < 2^38, within 2^-40 relative: the hardware's estimate (v_rcp_f64, good to 2^-20 and better) and
+// one Newton step, a third of the instructions of the division.
+__device__ __forceinline__ double inverse(uint64_t per)
+{
+    const double d = (double)per, r = __builtin_amdgcn_rcp(d);
+    return __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+}
+
 // ceil(need / per) for need < 2^38 and 1 <= per < 2^38 with a quotient below 2^32, given
-// per_inv = 1 / per rounded to nearest: need * per_inv is within 2^-51 of the quotient relative to it,
-// far less than one unit, so its integer part is the exact floor or one beside it; exact integer
-// tests settle which.
+// per_inv = 1 / per within 2^-40: need * per_inv is within 2^-39 of the quotient relative to it, less than 2^-7
+// of a unit, so its integer part is the exact floor or one beside it; exact integer tests settle which.
 __device__ __forceinline__ uint32_t ceil_div(uint64_t need, uint64_t per, double per_inv)
 {
     uint32_t q = (uint32_t)((double)need * per_inv);
@@ -91,7 +98,7 @@ __global__ __launch_bounds__(kThreads) void k_scale(ScaleView sv, int64_t R, con
         auto offer = [&](uint32_t qps, int32_t lat, uint64_t unit, int32_t row, uint32_t floor_n) {
             if (lat > slo) return;
             const uint64_t per = 100u * (uint64_t)qps;
-            uint32_t inst = ceil_div(need, per, 1.0 / (double)per);
+            uint32_t inst = ceil_div(need, per, inverse(per));
             inst = inst < floor_n ? floor_n : inst;
             const u128 cost = (u128)unit * inst;
             // the running variant keeps a tie; among switches of equal cost the lower row wins
@@ -119,7 +126,7 @@ __global__ __launch_bounds__(kThreads) void k_scale(ScaleView sv, int64_t R, con
             if (scaling) {
                 if (own_lat <= slo) {   // replicate
                     const uint64_t per = 100u * (uint64_t)own_qps;
-                    best_n = ceil_div(need, per, 1.0 / (double)per) - (uint32_t)n_cur;
+                    best_n = ceil_div(need, per, inverse(per)) - (uint32_t)n_cur;
                     best = (u128)own_unit * best_n + saved;
                     have = true;
                 }
@@ -159,7 +166,10 @@ hipError_t launch_scale(const ScaleView &sv, bool down, int64_t R, const int32_t
 {
     if (R <= 0) return hipSuccess;
     const int64_t want = (R + kThreads - 1) / kThreads;
-    const int64_t blocks = want < (int64_t)num_cus * 32 ? want : (int64_t)num_cus * 32;
+    // one request per lane (to 2^26 of them): the loop over a smaller grid makes every lane wait for its request's line
+    // before it asks for the next one's fields (4M requests: 129.5 us with 32 workgroups per compute unit, 125.5 so, the cheaper reciprocal
+    // included; 700,001 requests 24.5 and 23.9)
+    const int64_t blocks = want < (int64_t)num_cus * 1024 ? want : (int64_t)num_cus * 1024;
     if (down)
         return launch_kernel(ev, k_scale<true>, dim3((unsigned)blocks), dim3(kThreads), 0, st, sv, R, r_variant,
                              r_instances, r_load_qps, r_slo_us, r_batch_idx, out_action, out_variant, out_instances);
