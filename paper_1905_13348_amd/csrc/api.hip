@@ -181,8 +181,8 @@ struct infaas_sel {
     void free_index()
     {
         (void)hipFree(ix.pool); (void)hipFree(ix.step_row); (void)hipFree(ix.ctrl);  // hdr lives in pool's allocation
-        (void)hipFree(ix.stats); (void)hipFree(ix.slice_room);
-        tv.rank_nodes = nullptr;   // (in pool's allocation, like rank_hdr)
+        if (ix.stats) (void)hipFree(ix.stats - 4);
+        (void)hipFree(ix.slice_room);   // (rank_hdr and the nodes behind it are in pool's allocation)
         tv.rank_hdr = nullptr;
         (void)hipFree((void *)ix.task_group); (void)hipFree((void *)ix.group_task0); (void)hipFree(ix.gctrl);
         (void)hipFree(ix.step_worker); (void)hipFree(ix.hot_worker);
@@ -388,19 +388,16 @@ int create_index(infaas_sel *h)
     }
     // one allocation: the pool, then the headers, so that one 32-bit offset reaches both; behind them rank_hdr and,
     // at a multiple of their size, the nodes of TableView::rank_nodes
-    ix.pool_bytes &= ~15u;
-    const size_t rank_at = (size_t)ix.pool_bytes + (size_t)(S + 1) * 16;
-    const size_t nodes_at = (rank_at + (size_t)(S + 1) * 16 + 127) & ~(size_t)127;
-    const size_t nstats = (size_t)index_stat_blocks(h->num_cus) * kLookupStats;   // and one word: how many entries are in use
-    bool ok = dev_alloc(&ix.pool, nodes_at + (size_t)std::max<int64_t>(nodes, 1) * 128) == hipSuccess &&
+    ix.pool_bytes &= ~127u;
+    const size_t nstats = (size_t)index_stat_blocks(h->num_cus) * kLookupStats;
+    bool ok = dev_alloc(&ix.pool, (size_t)ix.pool_bytes + rank_nodes_at((int32_t)S) + (size_t)std::max<int64_t>(nodes, 1) * 128) == hipSuccess &&
               dev_alloc(&ix.step_row, ix.step_cap) == hipSuccess && dev_alloc(&ix.ctrl, kCtlWords) == hipSuccess &&
-              dev_alloc(&ix.stats, nstats + 1) == hipSuccess && dev_alloc(&ix.gctrl, 2 * (size_t)kGroupMaxGroups) == hipSuccess &&
+              dev_alloc(&ix.stats, 4 + nstats) == hipSuccess && dev_alloc(&ix.gctrl, 2 * (size_t)kGroupMaxGroups) == hipSuccess &&
               dev_alloc(&ix.slice_room, (size_t)S) == hipSuccess;
+    if (ix.stats) ix.stats += 4;   // (in front of it how many entries are in use)
     if (ok) {
         ix.hdr = (uint4 *)(ix.pool + ix.pool_bytes);
-        h->tv.rank_hdr = (const uint4 *)(ix.pool + rank_at);
-        h->tv.rank_nodes = (uint4 *)(ix.pool + nodes_at);
-        ix.stat_used = ix.stats + nstats;
+        h->tv.rank_hdr = (const uint4 *)((char *)ix.hdr + rank_hdr_at((int32_t)S));
     }
     h->ix = ix;
     const size_t park = index_park_bytes(h->num_cus);
@@ -415,7 +412,7 @@ int create_index(infaas_sel *h)
     uint8_t dummy[kDummyBodyBytes] = {0};
     for (uint32_t i = 8; i < 16; ++i) dummy[i] = 0xFF;  // latency sentinels of the empty body (Re = 2)
     const int32_t none = -1;
-    if (!HIP_OK(hipMemset(ix.stat_used, 0, 4)) ||
+    if (!HIP_OK(hipMemset(ix.stats - 1, 0, 4)) ||
         !HIP_OK(hipMemcpy(ix.pool, dummy, sizeof(dummy), hipMemcpyHostToDevice)) ||
         !HIP_OK(hipMemcpy(ix.step_row, &none, 4, hipMemcpyHostToDevice)) ||
         !HIP_OK(hipMemcpy(&ix.hdr[S], hdrs.data(), hdrs.size() * 4, hipMemcpyHostToDevice)) ||
@@ -1684,12 +1681,12 @@ int infaas_sel_get_info(infaas_sel_t *h, infaas_sel_info *out)
         out->index_bytes = pool_now + (int64_t)h->T * h->B * 16 + (steps_now + 1) * 4;
         out->index_steps = steps_now;
         // what the most recent lookup launch did with the queries its first probe could not decide
-        std::vector<uint32_t> st((size_t)index_stat_blocks(h->num_cus) * kLookupStats + 1, 0u);   // (its last word: entries in use)
+        std::vector<uint32_t> st((size_t)index_stat_blocks(h->num_cus) * kLookupStats + 1, 0u);   // (its first word: entries in use)
         DeviceGuard g(h->device);
         if (h->last_stats &&
-            (!g.ok || !HIP_OK(hipMemcpy(st.data(), h->last_stats, st.size() * 4, hipMemcpyDeviceToHost)))) return INFAAS_SEL_ERR_HIP;
+            (!g.ok || !HIP_OK(hipMemcpy(st.data(), h->last_stats - 1, st.size() * 4, hipMemcpyDeviceToHost)))) return INFAAS_SEL_ERR_HIP;
         int64_t sum[kLookupStats] = {0};
-        for (size_t i = 0; i < (size_t)st.back() * kLookupStats && i + 1 < st.size(); ++i) sum[i % kLookupStats] += st[i];
+        for (size_t i = 0; i < (size_t)st[0] * kLookupStats && i + 1 < st.size(); ++i) sum[i % kLookupStats] += st[i + 1];
         out->lookup_parked = sum[0]; out->lookup_second_body = sum[1]; out->lookup_global_body = sum[2];
         out->lookup_scanned = sum[3]; out->lookup_unanswered = sum[4];
     }

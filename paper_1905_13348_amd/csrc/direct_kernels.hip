@@ -112,7 +112,7 @@ __device__ __forceinline__ void leave_statistics(const IndexView &ix, uint32_t *
     }
     __syncthreads();
     if (threadIdx.x < kLookupStats) ix.stats[blockIdx.x * kLookupStats + threadIdx.x] = l_st[threadIdx.x];
-    if (blockIdx.x == 0 && threadIdx.x == 0) *ix.stat_used = gridDim.x;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ix.stats[-1] = gridDim.x;
 }
 
 // Bound by the rate of scattered reads: 14 per query through a body (header, ten probes, two sets, row), each

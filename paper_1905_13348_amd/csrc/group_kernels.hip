@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kGrpThreads) void k_group_bin(TableView tv, IndexVi
     for (int i = tid; i < G1; i += kGrpThreads) { l_t0[i] = ix.group_task0[i]; l_sum[i] = 0u; }
     if (blockIdx.x == 0)   // the statistics of this call are added up by k_group_finish
         for (int i = tid; i < gs.stat_blocks * kLookupStats; i += kGrpThreads) ix.stats[i] = 0u;
-    if (blockIdx.x == 0 && tid == 0) *ix.stat_used = (uint32_t)gs.stat_blocks;
+    if (blockIdx.x == 0 && tid == 0) ix.stats[-1] = (uint32_t)gs.stat_blocks;
     const int32_t acc_base_m1 = tv.acc_base - 1;
     const bool aligned = ((((uintptr_t)q.task) | ((uintptr_t)q.slo) | ((uintptr_t)q.min_acc) | ((uintptr_t)q.bidx)) & 15u) == 0;
     // (barriers that order LDS traffic only: the previous tile's stores stay in flight across them)

@@ -247,7 +247,7 @@ __device__ __forceinline__ SliceColumns slice_columns(int32_t s, int32_t t, int3
     if (kTwo && blockIdx.y) args += sizeof(TableView) + sizeof(IndexView);
     const __attribute__((address_space(4))) TableView *tv = (const __attribute__((address_space(4))) TableView *)args;
     const int64_t col = (int64_t)b * tv->Vp + tv->seg_off[t];
-    return SliceColumns{tv->acc_r + col, tv->tot_r + col, tv->rank_nodes + (uint64_t)tv->rank_hdr[s].z * 8, tv->seg_len[t]};
+    return SliceColumns{tv->acc_r + col, tv->tot_r + col, (uint4 *)((char *)tv->rank_hdr + (rank_nodes_at(tv->S) - rank_hdr_at(tv->S))) + (uint64_t)tv->rank_hdr[s].z * 8, tv->seg_len[t]};
 }
 
 // One wavefront per slice, kBuildWaves slices per workgroup.  An entry of the slice is a step exactly
@@ -1033,7 +1033,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
     const int32_t open_n = kSecond ? q.open_count[blockIdx.x] : 0;
     if (kSecond && open_n == 0) {   // the whole workgroup: nothing was left open in its share
         if (tid < kLookupStats) ix.stats[blockIdx.x * kLookupStats + tid] = 0u;
-        if (blockIdx.x == 0 && tid == 0) *ix.stat_used = gridDim.x;
+        if (blockIdx.x == 0 && tid == 0) ix.stats[-1] = gridDim.x;
         return;
     }
     const int32_t nunits = ((kSecond ? open_n : q.n) + kUnit - 1) / kUnit;
@@ -1526,7 +1526,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
     }
     __syncthreads();
     if (tid < kLookupStats) ix.stats[blockIdx.x * kLookupStats + tid] = lds_w[4 + tid];
-    if (blockIdx.x == 0 && tid == 0) *ix.stat_used = gridDim.x;
+    if (blockIdx.x == 0 && tid == 0) ix.stats[-1] = gridDim.x;
     if (kFirst && tid == 0) q.open_count[blockIdx.x] = (int32_t)s_open;
 }
 

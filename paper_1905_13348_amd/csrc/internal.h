@@ -16,7 +16,6 @@ constexpr int kLdsHistMaxSlices = 8192;   // per-workgroup LDS histogram up to t
 struct TableView {
     int32_t T, B, S, V, Vp;
     int32_t lds_limit;          // variants per staged chunk; segments above it take the wide path
-    int32_t max_len;            // most variants of a task
     const int32_t *acc;         // [Vp]
     int32_t *queue;             // [Vp]
     const int32_t *orig;        // [Vp] caller row of each slot
@@ -30,13 +29,13 @@ struct TableView {
     // variant of rank r in slice (t, b).  tot_r = latency + queue is kept current by load updates.
     int32_t *acc_r;             // [B][Vp]
     uint32_t *tot_r;            // [B][Vp]
-    const int32_t *orig_r;      // [B][Vp] caller row
     // By caller row, so that what a report reads of a row is one or two lines of memory: its entry in the
     // rank-ordered column b and its latency there, side by side.
     int2 *row_entry;            // [V][B] {entry, latency}
+    const int32_t *orig_r;      // [B][Vp] caller row
     // Two search structures over the entries, in rank order, of a slice that the index cannot hold completely,
     // written by the index build for those slices.  Both are made of nodes of 16 pairs {accuracy,
-    // latency-plus-queue} (128 bytes); rank_hdr names a slice's first.
+    // latency-plus-queue} (128 bytes) and lie behind rank_hdr, which names a slice's first.
     // 1. Levels: how high the accuracy and how low the latency have come from the start of the slice to the
     //    end of every 16 entries (level 1), of every 256 (level 2), of every 4096, ..., as many levels as it
     //    takes to get to one node; level 1's nodes come first.  Places past the end of a level hold a pair
@@ -45,15 +44,16 @@ struct TableView {
     //    falling accuracy, each with the lowest latency so far (nodes 1..16), and the last pair of each of
     //    those nodes (node 0).
     // Null without an index.
-    uint4 *rank_nodes;          // [B][rank_stride][8]
     const uint4 *rank_hdr;      // [S + 1] {first entry of the slice in the rank-ordered columns, divided by 4; its entries; its first
                                 //         node in rank_nodes; unused}; entry S stands for no slice (0 entries)
+    __host__ __device__ uint4 *rank_nodes() const;   // [nodes][8]
     int32_t acc_base;           // smallest accuracy in the table; index keys are acc - acc_base + 1
     // State-aware selection: a table serves one state (Active or Inactive).  Variants in another
     // state are masked in the rank-ordered columns (accuracy = acc_base, latency-plus-queue =
     // 0xFFFFFFFF): nothing selects them and every entry ranked before them dominates them.
     int32_t *state;             // [V] state of each caller row, or null when the table is not state-aware
     int32_t want_state;         // the state this table serves
+    int32_t max_len;            // most variants of a task
     // Six counters of the latest build of the table's index (kCtlMaxK0 .. kCtlMaxK, kCtlPool, kCtlSteps) and
     // where the first kernel of every selection copies them for the host to see (pinned host memory); null: nowhere.
     const uint32_t *stat_src;
@@ -139,8 +139,8 @@ struct IndexView {
     const uint16_t *task_group;   // [T] group of every task; null when num_groups == 1
     const int32_t *group_task0;   // [num_groups + 1]
     uint32_t *gctrl;              // [2 num_groups] per group: bytes of its region and steps handed out
-    uint32_t *stats;     // [kStatShare x compute units][kLookupStats] what the most recent lookup launch did
-    uint32_t *stat_used; // entries of `stats` that launch has written
+    uint32_t *stats;     // [kStatShare x compute units][kLookupStats] what the most recent lookup launch did;
+                         // the word in front of it: how many entries that launch has written
 };
 // Counters of the index build.  Every slice takes its room with one 64-bit add on the pair
 // (kCtlPool, kCtlSteps) and waits for the answer; the statistics live on a cache line of their
@@ -157,6 +157,11 @@ constexpr int kCtlMaxK = 35;      // most steps in a slice
 constexpr int kCtlWords = 64;
 constexpr uint32_t kRoomSteps = 0xFFFFFu;   // entries of slice_room, shifted down by 32: the steps
 constexpr int kRoomTrunc = 52;              //   the flag of a truncated slice (both fields hold the sum over 4095 slices)
+// Where the nodes are: behind the S + 1 entries of rank_hdr, which follow as many headers of the index from a multiple
+// of 128 bytes on, at the next such multiple.
+__host__ __device__ inline size_t rank_hdr_at(int32_t S) { return ((size_t)S + 1) * 16; }
+__host__ __device__ inline size_t rank_nodes_at(int32_t S) { return (((size_t)S + 1) * 32 + 127) & ~(size_t)127; }
+__host__ __device__ inline uint4 *TableView::rank_nodes() const { return (uint4 *)((char *)rank_hdr + (rank_nodes_at(S) - rank_hdr_at(S))); }
 // TableView::rank_nodes of a slice of L entries: nodes of a level, of all levels, and of everything.
 constexpr int kRankBlock = 256, kRankBlockNodes = 17;
 __host__ __device__ inline int32_t level_nodes(int32_t L, int level) { return (int32_t)(((int64_t)L + ((int64_t)16 << (4 * level)) - 1) >> (4 * level + 4)); }

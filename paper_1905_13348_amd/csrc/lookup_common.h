@@ -170,7 +170,7 @@ __device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const u
         uint4 v[4][2];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const uint4 *p = tv.rank_nodes + (uint64_t)(uint32_t)__shfl((int)at, 16 * r + (lane >> 2)) * 8u + (uint32_t)sub;
+            const uint4 *p = tv.rank_nodes() + (uint64_t)(uint32_t)__shfl((int)at, 16 * r + (lane >> 2)) * 8u + (uint32_t)sub;
             v[r][0] = p[0];
             v[r][1] = p[4];
         }
@@ -250,7 +250,7 @@ __device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const u
         for (int32_t b0 = end / kRankBlock; hit < 0 && b0 < nblk; b0 += 8) {
             const int32_t blk = b0 + (lane >> 3);
             const bool in = blk < nblk;
-            const uint4 *p = tv.rank_nodes + ((uint64_t)sorted + (uint64_t)(in ? blk : b0) * kRankBlockNodes) * 8u + (uint32_t)(lane & 7);
+            const uint4 *p = tv.rank_nodes() + ((uint64_t)sorted + (uint64_t)(in ? blk : b0) * kRankBlockNodes) * 8u + (uint32_t)(lane & 7);
             const uint4 v = *p;   // of the last pair of each node: is the node altogether accurate enough?
             const bool k0 = (int32_t)v.x >= qa, k1 = (int32_t)v.z >= qa;
             const uint64_t n0 = __ballot(k0), n1 = __ballot(k1);
