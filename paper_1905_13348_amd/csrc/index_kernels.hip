@@ -1545,9 +1545,12 @@ hipError_t launch_build(const TableView &ta, const IndexView &ia, const TableVie
     const dim3 block(64 * kBuildWaves);
     // One slice per workgroup as long as all of them are on the device at once (five workgroups of these registers
     // to a compute unit; the sums over the slices before are short, too).  us for one slice per workgroup / per
-    // wavefront: 160 slices of 45 entries 7.3 / 9.9, 800 of 200 11.5 / 15.1, of 500 12.4 / 16.5, of 1000 16.5 / 21.4,
-    // 400 of 2000 15.9 / 21; two tables of 800 slices of 200 20.3 / 12.7; 1600 of 60 16.0 / 13.5
-    if ((int64_t)ta.S * tables <= 1024) {
+    // wavefront: 160 slices of 45 entries 7.3 / 9.9, 400 of 2000 15.9 / 21, 600 of 60 on average 15.9 / 24.4; two tables
+    // of 800 slices of 200 20.3 / 12.7; 1600 of 60 16.0 / 13.5.  Without groups only up to 512: an index of more
+    // slices mostly outgrows the lookup's LDS mirror, and in the order of the slices' numbers, not of their arrival (short
+    // staircases first), more slices stay outside (1M queries on 800 slices 13.5 us against 12.7, which the
+    // build's 11.5 against 15.1 does not make up for: there are more batches than reports).
+    if ((int64_t)ta.S * tables <= 1024 && (ta.S <= 512 || ia.num_groups > 1)) {
         const dim3 each((unsigned)ta.S, tables);
         if (ta.max_len <= 256) return launch_kernel(ev, k_index_build_shared<1, kTwo>, each, block, 0, st, ta, ia, tb, ib);
         if (ta.max_len <= 512) return launch_kernel(ev, k_index_build_shared<2, kTwo>, each, block, 0, st, ta, ia, tb, ib);
