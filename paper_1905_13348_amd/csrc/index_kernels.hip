@@ -527,6 +527,9 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
         write_rank_nodes(sc.acc, sc.tot, sc.nodes, sc.L, 0, sc.L, lane, INT32_MIN, 0xFFFFFFFFu);
     }
     if (lane == 0 && inside) {
+        // This build places by arrival and reads nobody's entry.  It leaves its number there all the same: the numbers
+        // come round after 4096 builds, and one of k_index_build_shared must not take an entry of that age for its own.
+        ix.slice_room[s] = (unsigned long long)ix.ctrl[kCtlEpoch] << 20;
         if (fits) {
             const uint32_t y = (re0 << kHdrK0Shift) | (re1 << kHdrK1Shift) | (trunc ? kHdrTrunc : 0u) |
                                ((k1 || trunc) ? kHdrDeep : 0u) | row_hi;

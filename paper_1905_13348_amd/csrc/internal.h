@@ -128,7 +128,8 @@ struct IndexView {
     uint32_t row_hi_bits;// bits of a row number above its low 16
     uint32_t *ctrl;      // [kCtlWords] counters of the build, see kCtl*
     unsigned long long *slice_room;   // [S] what slice s needs, published by the build that places the slices in the
-                         // order of their numbers: bytes (20 bits) | build number (12) | steps (20) | truncated (12)
+                         // order of their numbers: bytes (20 bits) | build number (12) | steps (20) | truncated (12);
+                         // every build leaves its number in every entry, whichever kernel it is
     // Groups.  When the bodies of all slices do not fit one compute unit's LDS, the tasks are dealt, in
     // order, to num_groups groups whose bodies do: group g owns the tasks [group_task0[g],
     // group_task0[g + 1]), the bytes [g * region_bytes, (g + 1) * region_bytes) of the pool (every region

@@ -5,9 +5,9 @@ skipped; every element of variant, tier and worker against the CPU oracle."""
 import numpy as np
 import pytest
 
-from gpu_util import make_selector, table_args, to_dev
+from gpu_util import gpu_select, make_selector, table_args, to_dev
 from test_gpu_instances import _check as check_instances
-from test_gpu_parity import _random_queries, _random_table, _table
+from test_gpu_parity import _assert_equal_everywhere, _random_queries, _random_table, _table
 from test_gpu_workers import _check as check_workers, _random_cluster, load_cluster
 
 pytestmark = pytest.mark.gpu
@@ -53,4 +53,35 @@ def test_state_reports(oracle_lib, B, sizes):
         sel.update_instance_states(to_dev(idx), to_dev(val))
         ok = val >= 1
         ist[idx[ok]] = val[ok]
+    sel.destroy()
+
+
+def test_two_build_kernels_on_one_handle(oracle_lib):
+    """1024 slices in groups with states: a load report builds one table (a slice per workgroup, which reads
+    what every slice publishes under the number of the build), a state report builds two (a slice per
+    wavefront).  A build of the first kind with nothing but the second kind between it and the one 4096
+    builds ago, whose number it carries: staircases of one or no step then, full ones now."""
+    rng = np.random.default_rng(8)
+    T, n, B = 128, 2000, 8
+    tb = _random_table(rng, T, np.full(T, n), B)
+    state = np.zeros(tb.V, np.int32)
+    state[np.unique(tb.task_id, return_index=True)[1]] = 1        # one Active variant per task
+    load = rng.integers(0, 40_000, tb.V).astype(np.int32)
+    sel = make_selector(tb, engine=0)
+    assert sel.info()["index_groups"] > 1
+    sel.load_states(state, load)
+    rows, vals = np.arange(0, tb.V, 7, dtype=np.int32), rng.integers(0, 50_000, (tb.V + 6) // 7).astype(np.int32)
+    queue = tb.queue_us.copy()
+    oracle_lib.update_load(queue, rows, vals)
+    qs = _random_queries(rng, T, B, 200_000)
+    dev = [to_dev(x) for x in (rows, vals)]
+    one, same = to_dev(np.zeros(1, np.int32)), to_dev(state[:1])
+    everything, active = to_dev(np.arange(tb.V, dtype=np.int32)), to_dev(np.ones(tb.V, np.int32))
+    sel.update_load(*dev)
+    for i in range(4094):
+        sel.update_state(one, same)
+    sel.update_state(everything, active)
+    sel.update_load(*dev)
+    got = gpu_select(sel, *qs)
+    _assert_equal_everywhere(got, oracle_lib.select(*table_args(tb, queue), *qs), "after 4096 builds")
     sel.destroy()
