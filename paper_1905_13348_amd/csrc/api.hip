@@ -1106,7 +1106,9 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     // mirrored; with workers 8.8 / 8.7 / 13.8 / 22.8 and 16.9 / 17.9 / 18.4 / 20.2; complete Case I with workers 11.3 / 13.6 /
     // 19.0 / 34.7 and 21.7 / 23.3 / 26.8 / 30.7)
     const bool direct = N <= direct_limit(h) + direct_limit(h->inactive);
-    int rc = direct ? INFAAS_SEL_OK : ensure_open(h, std::min(N, kMaxTierPass), closest);
+    // The lists are allocated for direct calls too: the limits follow the index, and the same call after a report
+    // may need them where nothing can be allocated (under capture, after an eager call to warm up).
+    int rc = ensure_open(h, std::min(N, kMaxTierPass), closest);
     if (rc != INFAAS_SEL_OK) return rc;
     if (workers) {
         // bring the worker of every variant, then of every step of both indexes, up to date

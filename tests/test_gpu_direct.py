@@ -97,3 +97,23 @@ def test_every_mode_below_and_above_the_limit(oracle_lib, kind):
         for qs in (q, many):
             check(call(sel, *qs), want, f"{name} N={len(qs[0])}")
     sel.destroy()
+
+
+def test_a_small_call_leaves_the_scratch_of_its_size(oracle_lib):
+    """One eager call is warm-up enough for a capture of the same size, whichever way a report turns it: after
+    a small call the lists between the tiers are there, and nothing is left for infaas_sel_reserve to do."""
+    rng = np.random.default_rng(3)
+    tb = _random_table(rng, 9, np.full(9, 40), 3)
+    q = _random_queries(rng, 9, 3, 5003)
+    state, load = rng.integers(0, 4, tb.V).astype(np.int32), rng.integers(0, 50_000, tb.V).astype(np.int32)
+    sel = make_selector(tb, engine=0)
+    sel.load_states(state, load)
+    before = sel.info()["scratch_bytes"]
+    for call, want, size in ((gpu_select_tiered, oracle_lib.select_tiered, 16), (gpu_case1, oracle_lib.select_case1, 32)):
+        for g, w in zip(call(sel, *q), want(*table_args(tb), state, load, *q)):
+            _assert_equal_everywhere(g, w, call.__name__)
+        after = sel.info()["scratch_bytes"]
+        assert after >= before + size * len(q[0])
+        sel.reserve(len(q[0]))
+        assert sel.info()["scratch_bytes"] == after
+    sel.destroy()
