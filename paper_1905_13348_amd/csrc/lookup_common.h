@@ -133,13 +133,14 @@ __device__ __forceinline__ int32_t closest_by_scan(const TableView &tv, int32_t 
 // a cycle), so that a level costs one line of memory where a bisection by the lane itself would cost up to
 // four.  Those 16 entries are tried in the same manner.  Where accuracy rises and latency falls with the
 // rank the answer is among them.  What is still open goes on from there, the whole wavefront on one query
-// after the other: the rest of the block of 256 entries, then the sorted blocks, eight at a time, which tell
-// exactly whether they hold an entry that fits, then the first one that does.
-// 16M queries on 50 tasks of 2000 variants none of which dominates another: 0.69 ms; the same with the lane's own
-// bisection over a running extreme per entry 1.32 ms, with eight lanes to a node instead of four 0.68 (and 41 us
+// after the other: all of it where that is 512 entries or fewer, else the rest of the block of 256, then the sorted
+// blocks, eight at a time, which tell exactly whether they hold an entry that fits, then the first one that does.
+// 16M queries on 50 tasks of 2000 variants none of which dominates another: 0.55 ms; the same with the lane's own
+// bisection over a running extreme per entry 1.32 ms, with eight lanes to a node instead of four as fast (and 41 us
 // instead of 25 for 1.4M queries on tasks of 81 variants).  Without the sorted blocks the two families of
-// use_ranked() (api.hip) took 3.09 ms per 4M queries instead of 1.33.  What bounds it is scattered reads of L2 lines,
-// two levels, two columns, a row and two headers per query.
+// use_ranked() (api.hip) took 3.1 ms per 4M queries instead of 1.2.  What bounds it is scattered reads of L2 lines,
+// two levels, two columns, a row and two headers per query.  (Comparisons are combined with & and |: with && the
+// 16-byte reads are split into dwords behind branches, 0.62 ms instead of 0.55.)
 __device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const uint4 &rh, int32_t min_acc, uint32_t bound)
 {
     const int lane = threadIdx.x & 63, sub = lane & 3, round = lane >> 4;
@@ -179,7 +180,7 @@ __device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const u
             int c = 0;
 #pragma unroll
             for (int k = 0; k < 2; ++k)
-                c += (int)((int32_t)v[r][k].x < am[r] || v[r][k].y > bd[r]) + (int)((int32_t)v[r][k].z < am[r] || v[r][k].w > bd[r]);
+                c += (int)(((int32_t)v[r][k].x < am[r]) | (v[r][k].y > bd[r])) + (int)(((int32_t)v[r][k].z < am[r]) | (v[r][k].w > bd[r]));
             c += quad(c, 1);
             c += quad(c, 2);
             c = __shfl(c, back);
@@ -204,10 +205,10 @@ __device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const u
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             uint32_t m = 0x10000u;
-            m |= ((int32_t)a[r].x >= am[r] && w[r].x <= bd[r]) ? 1u : 0u;
-            m |= ((int32_t)a[r].y >= am[r] && w[r].y <= bd[r]) ? 2u : 0u;
-            m |= ((int32_t)a[r].z >= am[r] && w[r].z <= bd[r]) ? 4u : 0u;
-            m |= ((int32_t)a[r].w >= am[r] && w[r].w <= bd[r]) ? 8u : 0u;
+            m |= (((int32_t)a[r].x >= am[r]) & (w[r].x <= bd[r])) ? 1u : 0u;
+            m |= (((int32_t)a[r].y >= am[r]) & (w[r].y <= bd[r])) ? 2u : 0u;
+            m |= (((int32_t)a[r].z >= am[r]) & (w[r].z <= bd[r])) ? 4u : 0u;
+            m |= (((int32_t)a[r].w >= am[r]) & (w[r].w <= bd[r])) ? 8u : 0u;
             int f = 4 * sub + __builtin_ctz(m), o = quad(f, 1);   // 16 or more: none of this lane's four
             f = o < f ? o : f;
             o = quad(f, 2);
@@ -226,23 +227,40 @@ __device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const u
         const int32_t qa = __builtin_amdgcn_readlane(min_acc, l);
         const uint32_t qb = (uint32_t)__builtin_amdgcn_readlane((int)bound, l);
         const int64_t c = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)rh.x, l) * 4;
-        // the first entry of [lo, hi) that fits, or -1; at most 256 entries, lo a multiple of 4.  (Slices
-        // start at multiples of 4 and are padded to multiples of 4 with entries that never fit.)
-        auto try_block = [&](int32_t first, int32_t hi) -> int32_t {
-            const int32_t pos = first + 4 * lane;
-            const bool in = pos < hi;
-            const uint4 a = *(const uint4 *)(tv.acc_r + c + (in ? pos : 0)), w = *(const uint4 *)(tv.tot_r + c + (in ? pos : 0));
+        // the first of the entries first + 4 * lane + {0, 1, 2, 3} below hi that fits, or -1 (first: a multiple of 4).
+        // (Slices start at multiples of 4 and are padded to multiples of 4 with entries that never fit.)
+        auto first_fit = [&](const uint4 &a, const uint4 &w, int32_t first, int32_t hi) -> int32_t {
             uint32_t m = 0;
-            m |= ((int32_t)a.x >= qa && w.x <= qb) ? 1u : 0u;
-            m |= ((int32_t)a.y >= qa && w.y <= qb) ? 2u : 0u;
-            m |= ((int32_t)a.z >= qa && w.z <= qb) ? 4u : 0u;
-            m |= ((int32_t)a.w >= qa && w.w <= qb) ? 8u : 0u;
-            m = in ? m : 0u;
+            m |= (((int32_t)a.x >= qa) & (w.x <= qb)) ? 1u : 0u;
+            m |= (((int32_t)a.y >= qa) & (w.y <= qb)) ? 2u : 0u;
+            m |= (((int32_t)a.z >= qa) & (w.z <= qb)) ? 4u : 0u;
+            m |= (((int32_t)a.w >= qa) & (w.w <= qb)) ? 8u : 0u;
+            m = first + 4 * lane < hi ? m : 0u;
             const uint64_t any = __ballot(m != 0u);
             if (!any) return -1;
             const int f = __builtin_ctzll(any);
             return first + 4 * f + __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)m, f));
         };
+        auto try_block = [&](int32_t first, int32_t hi) -> int32_t {   // at most 256 entries
+            const int64_t at = c + (first + 4 * lane < hi ? first + 4 * lane : 0);
+            return first_fit(*(const uint4 *)(tv.acc_r + at), *(const uint4 *)(tv.tot_r + at), first, hi);
+        };
+        // All that is left at once: two rounds of reads instead of up to four.  (1M queries most of which have no answer,
+        // 300 entries of random accuracy and latency to a slice: 337 us block by block, 111 so, 297 with the scan engine.)
+        if (len - lo <= 256) {
+            const int32_t hit = try_block(lo, len);
+            if (lane == l) found = hit;
+            continue;
+        }
+        if (len - lo <= 512) {
+            const int64_t at0 = c + (lo + 4 * lane < len ? lo + 4 * lane : 0), at1 = c + (lo + 256 + 4 * lane < len ? lo + 256 + 4 * lane : 0);
+            const uint4 a0 = *(const uint4 *)(tv.acc_r + at0), w0 = *(const uint4 *)(tv.tot_r + at0);
+            const uint4 a1 = *(const uint4 *)(tv.acc_r + at1), w1 = *(const uint4 *)(tv.tot_r + at1);
+            int32_t hit = first_fit(a0, w0, lo, len);
+            hit = hit < 0 ? first_fit(a1, w1, lo + 256, len) : hit;
+            if (lane == l) found = hit;
+            continue;
+        }
         int32_t end = (lo + kRankBlock - 1) & ~(kRankBlock - 1);
         int32_t hit = lo < end ? try_block(lo, end < len ? end : len) : -1;
         const int32_t nblk = rank_blocks(len);
@@ -256,8 +274,8 @@ __device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const u
             const uint64_t n0 = __ballot(k0), n1 = __ballot(k1);
             const int whole = __builtin_popcount((uint32_t)(n0 >> (lane & 56)) & 0xFFu) + __builtin_popcount((uint32_t)(n1 >> (lane & 56)) & 0xFFu);
             const uint4 u = p[8 * (whole < 16 ? 1 + whole : 16)];
-            bool fits = (k0 && v.y <= qb) || (k1 && v.w <= qb);
-            fits = fits || ((int32_t)u.x >= qa && u.y <= qb) || ((int32_t)u.z >= qa && u.w <= qb);
+            bool fits = (k0 & (v.y <= qb)) | (k1 & (v.w <= qb));
+            fits = fits | (((int32_t)u.x >= qa) & (u.y <= qb)) | (((int32_t)u.z >= qa) & (u.w <= qb));
             const uint64_t any = __ballot(fits && in);
             if (any) {
                 const int32_t first = (b0 + (__builtin_ctzll(any) >> 3)) * kRankBlock;
