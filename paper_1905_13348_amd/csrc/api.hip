@@ -625,9 +625,10 @@ bool use_index(infaas_sel *h)
 
 // Whether a table that the index engine is not used for is answered in rank order instead of by the exhaustive scan:
 // always when there is an index, whose build writes what the search needs.  4M queries on 50 tasks of 2000 variants, the
-// scan engine's four kernels against this one: every variant a step 2.80 ms against 0.14, accuracies beyond 16 bits 2.79
-// against 0.20, config 2 after the degrading report 2.84 against 0.09, steps in random order 2.80 against 1.74, two
-// interleaved families of variants with most queries asking for the best of both 2.77 against 1.33.
+// scan engine's four kernels against this one: every variant a step 2.80 ms against 0.12, accuracies beyond 16 bits 2.79
+// against 0.16, config 2 after the degrading report 2.84 against 0.06, steps in random order 2.80 against 1.39, two
+// interleaved families of variants with most queries asking for the best of both 2.77 against 1.21.  Slices of 64 to 20,000
+// entries and batches of 101 to 1M queries: faster throughout.
 bool use_ranked(const infaas_sel *h)
 {
     return h->have_index && (h->flags & INFAAS_SEL_ENGINE_MASK) == INFAAS_SEL_ENGINE_AUTO;

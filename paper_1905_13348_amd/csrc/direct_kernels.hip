@@ -15,9 +15,9 @@ struct Query {
     bool inside, valid;   // names a slice of the table; and has a bound that anything can meet
     uint32_t s;           // its slice, or the empty one
 };
-__device__ __forceinline__ Query load_query(const TableView &tv, const QueryView &q, int64_t i)
+__device__ __forceinline__ Query load_query(const TableView &tv, const QueryView &q, int64_t i, bool mine = true)
 {
-    const bool in = i < q.n;
+    const bool in = mine && i < q.n;
     Query u;
     u.task = in ? q.task[i] : -1; u.slo = in ? q.slo[i] : -1; u.min_acc = in ? q.min_acc[i] : 0; u.bidx = in ? q.bidx[i] : -1;
     u.inside = (uint32_t)u.task < (uint32_t)tv.T && (uint32_t)u.bidx < (uint32_t)tv.B;
@@ -119,18 +119,20 @@ __device__ __forceinline__ void leave_statistics(const IndexView &ix, uint32_t *
 // lane another line.  Sixteen wavefronts per compute unit already saturate that: register caps for 24 to 32
 // (80 to 64 registers instead of 89) were measured 0-25% slower on batches of a million.
 template <bool kRanked>
-__global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, IndexView ix, QueryView q)
+__global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, IndexView ix, QueryView q, int32_t per_wave)
 {
+    const int32_t per = kRanked ? per_wave : 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, step = per * (kDirThreads / 64);
     __shared__ uint32_t l_st[kLookupStats];
     publish_index_stats(tv);
     if (threadIdx.x < kLookupStats) l_st[threadIdx.x] = 0u;
     __syncthreads();
     uint32_t st[kLookupStats] = {0u, 0u, 0u, 0u, 0u};
-    for (int64_t i0 = (int64_t)blockIdx.x * kDirThreads; i0 < q.n; i0 += (int64_t)gridDim.x * kDirThreads) {
-        const int64_t i = i0 + threadIdx.x;
-        const Query u = load_query(tv, q, i);
+    for (int64_t i0 = (int64_t)blockIdx.x * step; i0 < q.n; i0 += (int64_t)gridDim.x * step) {
+        const int64_t i = i0 + wave * per + lane;
+        const bool mine = !kRanked || lane < per;
+        const Query u = load_query(tv, q, i, mine);
         const int32_t ans = select_from_memory<kRanked>(tv, ix, u, u.valid, st);
-        if (i < q.n) q.out[i] = ans;
+        if (mine && i < q.n) q.out[i] = ans;
     }
     leave_statistics(ix, l_st, st);
 }
@@ -189,8 +191,15 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
 hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int num_cus,
                                 hipStream_t st, const LaunchEvents *ev)
 {
-    const int64_t want = ((int64_t)q.n + kDirThreads - 1) / kDirThreads, most = index_stat_blocks(num_cus);
-    return launch_kernel(ev, ranked ? k_direct_select<true> : k_direct_select<false>, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, tv, ix, q);
+    // In rank order a wavefront finishes its hard queries one after the other, so a batch too small to give every
+    // SIMD two full wavefronts is spread over as many with fewer queries each.  (us for 1001 / 10,001 / 30,001 queries, 64 to a
+    // wavefront and so: 2000 entries of random accuracy and latency to a slice, most queries without an answer, 75 / 75 / 76 and
+    // 6.1 / 14 / 23, with the scan engine 37 / 63 / 89; every entry a step, nothing hard about it, 6.0 / 6.1 / 6.1 and 6.2 / 6.2 /
+    // 6.2, where four wavefronts per SIMD took 6.1 / 6.6 / 8.1.)
+    int32_t per = 64;
+    while (ranked && per > 1 && ((int64_t)q.n + per / 2 - 1) / (per / 2) <= (int64_t)num_cus * 8) per /= 2;
+    const int64_t step = per * (kDirThreads / 64), want = ((int64_t)q.n + step - 1) / step, most = index_stat_blocks(num_cus);
+    return launch_kernel(ev, ranked ? k_direct_select<true> : k_direct_select<false>, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, tv, ix, q, per);
 }
 
 hipError_t launch_direct_modes(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, const QueryView &q,

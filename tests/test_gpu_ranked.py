@@ -82,3 +82,19 @@ def test_ranked_slices(oracle_lib, kind, lengths):
         _assert_equal_everywhere(got, want, f"{kind} {lengths} round {rnd}")
         assert (want >= 0).sum() > n // 10
     sel.destroy()
+
+
+@pytest.mark.parametrize("kind", ["noisy", "mixed"])
+def test_ranked_batches_and_short_rests(oracle_lib, kind):
+    """Batch sizes around those at which a wavefront takes more queries (powers of two times two wavefronts per
+    SIMD: 2048 on 256 compute units), and slices of which 256 or 512 entries, or a few more or fewer, are left behind
+    the first 16."""
+    rng = np.random.default_rng(17)
+    tb = _ranked_table(kind, (272, 271, 273, 276, 528, 527, 529, 532, 100), 2, rng)
+    qs = _ranked_queries(tb, 131_073, rng)
+    want = oracle_lib.select(*table_args(tb), *qs)
+    sel = make_selector(tb, engine=0)
+    assert sel.info()["index_truncated"] > tb.num_tasks
+    for n in (1, 2, 3, 2047, 2048, 2049, 4095, 4097, 8193, 16385, 32767, 65537, 131_072, 131_073):
+        _assert_equal_everywhere(gpu_select(sel, *(x[:n] for x in qs)), want[:n], f"{kind} N={n}")
+    sel.destroy()
