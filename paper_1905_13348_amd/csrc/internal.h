@@ -129,7 +129,7 @@ struct IndexView {
     uint32_t *ctrl;      // [kCtlWords] counters of the build, see kCtl*
     unsigned long long *slice_room;   // [S] what slice s needs, published by the build that places the slices in the
                          // order of their numbers: bytes (20 bits) | build number (12) | steps (20) | truncated (12);
-                         // every build leaves its number in every entry, whichever kernel it is
+                         // the other build leaves kRoomNone in every entry
     // Groups.  When the bodies of all slices do not fit one compute unit's LDS, the tasks are dealt, in
     // order, to num_groups groups whose bodies do: group g owns the tasks [group_task0[g],
     // group_task0[g + 1]), the bytes [g * region_bytes, (g + 1) * region_bytes) of the pool (every region
@@ -150,12 +150,15 @@ constexpr int kCtlPool = 0;       // bytes of the pool handed out (with groups: 
 constexpr int kCtlSteps = 1;      // entries of step_row handed out (entry 0 is unused)
 constexpr int kCtlPool0 = 8;      // what the two counters above start from at every rebuild
 constexpr int kCtlSteps0 = 9;
-constexpr int kCtlEpoch = 10;     // number of the build (12 bits), so that what earlier builds left in slice_room is told apart
+constexpr int kCtlEpoch = 10;     // number of the build, so that what earlier builds left in slice_room is told apart:
+                                  // 0 .. kRoomNumbers - 1, over and over
 constexpr int kCtlMaxK0 = 32;     // most steps in a first body (sets the probe count of the lookup)
 constexpr int kCtlTrunc = 33;     // slices with more steps than the index keeps
 constexpr int kCtlNoBody = 34;    // slices without a body
 constexpr int kCtlMaxK = 35;      // most steps in a slice
 constexpr int kCtlWords = 64;
+constexpr uint32_t kRoomNumbers = 0xFFFu;
+constexpr unsigned long long kRoomNone = (unsigned long long)kRoomNumbers << 20;   // entry of slice_room: no build's
 constexpr uint32_t kRoomSteps = 0xFFFFFu;   // entries of slice_room, shifted down by 32: the steps
 constexpr int kRoomTrunc = 52;              //   the flag of a truncated slice (both fields hold the sum over 4095 slices)
 // Where the nodes are: behind the S + 1 entries of rank_hdr, which follow as many headers of the index from a multiple

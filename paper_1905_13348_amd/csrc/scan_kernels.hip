@@ -81,7 +81,8 @@ __device__ __forceinline__ void rewind_index(const IndexView &ix, int64_t tid)
     if (tid == 0) {
         ix.ctrl[kCtlPool] = ix.ctrl[kCtlPool0];
         ix.ctrl[kCtlSteps] = ix.ctrl[kCtlSteps0];
-        ix.ctrl[kCtlEpoch] = (ix.ctrl[kCtlEpoch] + 1u) & 0xFFFu;
+        const uint32_t next = ix.ctrl[kCtlEpoch] + 1u;
+        ix.ctrl[kCtlEpoch] = next < kRoomNumbers ? next : 0u;
         ix.ctrl[kCtlMaxK0] = 1;
         ix.ctrl[kCtlTrunc] = 0;
         ix.ctrl[kCtlNoBody] = 0;

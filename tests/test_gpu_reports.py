@@ -59,7 +59,7 @@ def test_state_reports(oracle_lib, B, sizes):
 def test_two_build_kernels_on_one_handle(oracle_lib):
     """1024 slices in groups with states: a load report builds one table (a slice per workgroup, which reads
     what every slice publishes under the number of the build), a state report builds two (a slice per
-    wavefront).  A build of the first kind with nothing but the second kind between it and the one 4096
+    wavefront).  A build of the first kind with nothing but the second kind between it and the one 4095
     builds ago, whose number it carries: staircases of one or no step then, full ones now."""
     rng = np.random.default_rng(8)
     T, n, B = 128, 2000, 8
@@ -78,10 +78,10 @@ def test_two_build_kernels_on_one_handle(oracle_lib):
     one, same = to_dev(np.zeros(1, np.int32)), to_dev(state[:1])
     everything, active = to_dev(np.arange(tb.V, dtype=np.int32)), to_dev(np.ones(tb.V, np.int32))
     sel.update_load(*dev)
-    for i in range(4094):
+    for _ in range(4093):
         sel.update_state(one, same)
     sel.update_state(everything, active)
     sel.update_load(*dev)
     got = gpu_select(sel, *qs)
-    _assert_equal_everywhere(got, oracle_lib.select(*table_args(tb, queue), *qs), "after 4096 builds")
+    _assert_equal_everywhere(got, oracle_lib.select(*table_args(tb, queue), *qs), "after 4095 builds")
     sel.destroy()
