@@ -1567,6 +1567,12 @@ hipError_t launch_build(const TableView &ta, const IndexView &ia, const TableVie
     // tasks of 200 variants x 8: 13.5 with chunks of 4 x 64 entries, 13.7 with 8, 14.7 with 16)
     if (ta.max_len <= 256) return launch_kernel(ev, k_index_build<4, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
     if (ta.max_len <= 512) return launch_kernel(ev, k_index_build<8, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
+    // up to 1024 slices, of which some are longer than that: chunks of twice the size, one round of the filter instead of
+    // two for 2048 entries (us, load report and build: 800 slices of 1100 / 1500 entries 29.5 / 32.7 -> 26.1 / 28.2, 1000 slices
+    // of up to 13,396 entries 102 -> 72).  With more slices, or two tables (of more than 512 slices, or they would not be
+    // here), fewer workgroups at a time cost more than that (two tables of 800 slices of 1500: 30.3 -> 34.2).
+    if constexpr (!kTwo)
+        if (ta.S <= 1024 && ta.max_len > 1024) return launch_kernel(ev, k_index_build<32, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
     return launch_kernel(ev, k_index_build<16, kTwo>, grid, block, 0, st, ta, ia, tb, ib);
 }
 

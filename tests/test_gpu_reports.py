@@ -85,3 +85,25 @@ def test_two_build_kernels_on_one_handle(oracle_lib):
     got = gpu_select(sel, *qs)
     _assert_equal_everywhere(got, oracle_lib.select(*table_args(tb, queue), *qs), "after 4095 builds")
     sel.destroy()
+
+
+@pytest.mark.parametrize("T,B", [(300, 2), (170, 6), (513, 1)])
+def test_build_with_slices_around_the_largest_chunk(oracle_lib, T, B):
+    """More than 512 slices, up to 1024 of them, in one pool: a slice per wavefront, entries 2048 at a time."""
+    rng = np.random.default_rng(T)
+    sizes = rng.integers(0, 30, T)
+    sizes[[0, 3, 7, 50, 51, 100, T - 1]] = (2048, 2047, 2049, 1025, 1024, 4097, 5000)
+    tb = _random_table(rng, T, sizes, B)
+    qs = _random_queries(rng, T, B, 250_000)
+    half = rng.random(250_000) < 0.5
+    qs[0][half] = rng.choice(np.asarray([0, 3, 7, 50, 51, 100, T - 1], np.int32), int(half.sum()))
+    sel = make_selector(tb, engine=0)
+    assert sel.info()["index_groups"] == 1
+    queue = tb.queue_us.copy()
+    for rnd in range(3):
+        if rnd:
+            rows, vals = rng.choice(tb.V, tb.V // 3, replace=False).astype(np.int32), rng.integers(0, 50_000, tb.V // 3).astype(np.int32)
+            sel.update_load(to_dev(rows), to_dev(vals))
+            oracle_lib.update_load(queue, rows, vals)
+        _assert_equal_everywhere(gpu_select(sel, *qs), oracle_lib.select(*table_args(tb, queue), *qs), f"T={T} B={B} round {rnd}")
+    sel.destroy()
