@@ -524,20 +524,29 @@ int ensure_open(infaas_sel *h, int64_t n, bool side)
 // 14.3 and 8.8 / 9.0 / 9.7 / 9.4; config 3's, 7%: 4.3 / 7.0 / 9.8 / 17.4 and 16.0 / 17.2 / 17.6 / 20.7).  The less of the
 // index the mirror holds, the later it pays.
 constexpr int64_t kDirectQueries = 100000;
-int64_t direct_limit(const infaas_sel *h)
+// With suggestions the same holds (us for 65,000 / 100,000 / 300,000 queries: 100 tasks of 200 variants 7.9 / 9.5 / 17.9 direct,
+// 13.4 / 13.3 / 14.9 mirrored; config 3's table 9.4 / 11.2 / 22.5 and 27.6 / 28.6 / 33.4), except where the mirror holds nearly the
+// whole index (it does at 1.3 times its room, not at 1.5) and slices have second bodies, both of which a suggestion
+// searches (config 2's: 9.0 / 10.6 / 18.4 direct, 9.7 / 9.9 / 10.7 mirrored).  Slices that are not completely indexed
+// (their queries cost the lookup kernel more than all others) leave the limit where it is for the selection.
+constexpr int64_t kDirectSuggestions = 75000;
+int64_t direct_limit(const infaas_sel *h, bool closest = false)
 {
     if (h->index_lds_bytes == 0) return kDirectQueries;   // (no mirror, four interleaved queries per lane)
     const int64_t room = (int64_t)h->index_lds_bytes - kLdsCtrlBytes - lds_header_bytes(h->tv.S);
-    const int64_t pool = h->ix.num_groups > 1 ? h->ix_bytes : h->host_stats ? ((volatile uint32_t *)h->host_stats)[4] : h->ix_stats[kCtlPool];
+    const volatile uint32_t *now = h->host_stats;
+    const int64_t pool = h->ix.num_groups > 1 ? h->ix_bytes : now ? now[4] : h->ix_stats[kCtlPool];
+    const uint32_t steps = now ? now[kCtlMaxK - kCtlMaxK0] : h->ix_stats[kCtlMaxK];
+    const uint32_t open = now ? now[kCtlTrunc - kCtlMaxK0] + now[kCtlNoBody - kCtlMaxK0] : h->ix_stats[kCtlTrunc] + h->ix_stats[kCtlNoBody];
+    if (closest && open == 0 && steps > (uint32_t)kBodySteps && 5 * pool <= 7 * room) return kDirectSuggestions;
     return pool <= room ? kDirectQueries : kDirectQueries * pool / room;
 }
-bool use_direct(const infaas_sel *h, int64_t n) { return n <= direct_limit(h); }
 
 // One pass of the index engine over n <= 2^28 queries.
 int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
-    if (q.pass <= 1 && use_direct(h, q.n)) {
+    if (q.pass <= 1 && q.n <= direct_limit(h, q.pass == 1)) {
         const hipError_t e = q.pass == 0 ? launch_direct_select(h->tv, h->ix, q, false, h->num_cus, st, t.ev())
                                          : launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, h->num_cus, st, t.ev());
         return HIP_OK(e) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
@@ -1406,7 +1415,7 @@ int infaas_sel_select_noalloc(infaas_sel_t *h, int64_t N, const int32_t *d_task,
     q.task = d_task; q.slo = d_slo_us; q.min_acc = d_min_acc_bp; q.bidx = d_batch_idx; q.out = d_out_variant;
     q.pass = 0;
     // no event pair even when timing is on: taking one may create it
-    if (use_direct(h, q.n)) {
+    if (q.n <= direct_limit(h)) {
         if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
     } else if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->static_park, h->index_lds_bytes, h->num_cus,
                                     (hipStream_t)hip_stream, nullptr)))

@@ -117,3 +117,21 @@ def test_a_small_call_leaves_the_scratch_of_its_size(oracle_lib):
         sel.reserve(len(q[0]))
         assert sel.info()["scratch_bytes"] == after
     sel.destroy()
+
+
+def test_suggestions_around_their_own_limit(oracle_lib):
+    """An index that the mirror holds nearly completely and that has second bodies: suggestions turn to the lookup
+    kernel above 75,000 queries, the plain selection above more than 100,000."""
+    tb = workloads.make_table(2)
+    sel = make_selector(tb, engine=0)
+    assert sel.info()["index_max_steps"] > 31
+    q = query_args(workloads.make_queries(2, n=75_001, seed=9))
+    want = oracle_lib.select_closest(*table_args(tb), *q)
+    valid = int((q[1] >= 0).sum())
+    parked = []
+    for n in (75_000, 75_001):
+        for g, w in zip(gpu_select_closest(sel, *(x[:n] for x in q)), want):
+            _assert_equal_everywhere(g, w[:n], f"closest N={n}")
+        parked.append(sel.info()["lookup_parked"])
+    assert parked[0] >= valid - 1 and 0 < parked[1] < valid // 2   # (straight from memory every query counts as parked)
+    sel.destroy()
