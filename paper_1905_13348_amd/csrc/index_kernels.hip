@@ -109,13 +109,22 @@ __device__ __forceinline__ void range_extremes(const int32_t *acc, const uint32_
 {
     mx = INT32_MIN;
     mn = 0xFFFFFFFFu;
-    for (int32_t i = lo + 4 * lane; i < hi; i += 256) {   // (the entries that pad a slice to a multiple of 4 change nothing)
-        const v4i a = *(const v4i *)(acc + i);
-        const uint4 t = *(const uint4 *)(tot + i);
-        const int32_t a01 = a.x > a.y ? a.x : a.y, a23 = a.z > a.w ? a.z : a.w, m4 = a01 > a23 ? a01 : a23;
-        const uint32_t t01 = t.x < t.y ? t.x : t.y, t23 = t.z < t.w ? t.z : t.w, n4 = t01 < t23 ? t01 : t23;
-        mx = m4 > mx ? m4 : mx;
-        mn = n4 < mn ? n4 : mn;
+    for (int32_t i0 = lo; i0 < hi; i0 += 1024) {   // (the entries that pad a slice to a multiple of 4 change nothing)
+        v4i a[4];
+        uint4 t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {   // (past the end: the first entries again)
+            const int32_t i = i0 + 256 * k + 4 * lane;
+            a[k] = *(const v4i *)(acc + (i < hi ? i : lo));
+            t[k] = *(const uint4 *)(tot + (i < hi ? i : lo));
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int32_t a01 = a[k].x > a[k].y ? a[k].x : a[k].y, a23 = a[k].z > a[k].w ? a[k].z : a[k].w, m4 = a01 > a23 ? a01 : a23;
+            const uint32_t t01 = t[k].x < t[k].y ? t[k].x : t[k].y, t23 = t[k].z < t[k].w ? t[k].z : t[k].w, n4 = t01 < t23 ? t01 : t23;
+            mx = m4 > mx ? m4 : mx;
+            mn = n4 < mn ? n4 : mn;
+        }
     }
     for (int o = 32; o; o >>= 1) {
         const int32_t om = __shfl_xor(mx, o);
@@ -124,59 +133,107 @@ __device__ __forceinline__ void range_extremes(const int32_t *acc, const uint32_
         mn = on < mn ? on : mn;
     }
 }
-// 256 keys in ascending order by one wavefront, four per lane (key 4 * lane + j is k[j]).
-__device__ __forceinline__ void sort_keys(unsigned long long (&k)[4], int lane)
+// 256 keys of 32 or 64 bits in ascending order by one wavefront, four per lane (key 4 * lane + j is k[j]): a bitonic sort whose
+// exchanges stay inside the vector units but for those 16 and 32 lanes apart.  Of two keys a lane keeps the median of
+// them and all zeros (the lower) or all ones (the higher), one instruction for 32 bits.  bit[i]: all ones in the lanes
+// that hold keys with bit i + 2 in their number.
+template <int kLanes>
+__device__ __forceinline__ uint32_t from_lane_xor(uint32_t v)
 {
+    if constexpr (kLanes == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);           // quad_perm
+    else if constexpr (kLanes == 2) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);
+    else if constexpr (kLanes == 4)                                                     // row_half_mirror (7), quad_perm (3)
+        return (uint32_t)__builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+    else if constexpr (kLanes == 8) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true);     // row_ror:8
+    else if constexpr (kLanes == 16) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);
+    else return (uint32_t)__shfl_xor((int)v, kLanes);
+}
+template <int kLanes>
+__device__ __forceinline__ unsigned long long from_lane_xor(unsigned long long v)
+{
+    return ((unsigned long long)from_lane_xor<kLanes>((uint32_t)(v >> 32)) << 32) | from_lane_xor<kLanes>((uint32_t)v);
+}
+__device__ __forceinline__ uint32_t lower_or_higher(uint32_t x, uint32_t y, uint32_t ones)
+{
+    const uint32_t lo = x < y ? x : y, hi = x < y ? y : x, m = hi < ones ? hi : ones;
+    return lo > m ? lo : m;
+}
+__device__ __forceinline__ unsigned long long lower_or_higher(unsigned long long x, unsigned long long y, uint32_t ones)
+{
+    return ((x < y) != (ones != 0u)) ? x : y;
+}
+constexpr int log2_of(int n) { return n > 1 ? 1 + log2_of(n / 2) : 0; }
+template <int kSize, int kStride, class Key>
+__device__ __forceinline__ void sort_stages(Key (&k)[4], const uint32_t (&bit)[7])
+{
+    if constexpr (kStride >= 4) {
+        const uint32_t ones = bit[log2_of(kStride) - 2] ^ bit[log2_of(kSize) - 2];
 #pragma unroll
-    for (int size = 2; size <= 256; size *= 2) {
+        for (int j = 0; j < 4; ++j) k[j] = lower_or_higher(k[j], from_lane_xor<kStride / 4>(k[j]), ones);
+    } else {
 #pragma unroll
-        for (int stride = size / 2; stride > 0; stride /= 2) {
-            if (stride >= 4) {
-                const bool keep_min = ((4 * lane & stride) == 0) == ((4 * lane & size) == 0);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const unsigned long long o = __shfl_xor(k[j], stride / 4);
-                    k[j] = ((o < k[j]) == keep_min) ? o : k[j];
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (j & stride) continue;
-                    const bool up = size >= 4 ? (4 * lane & size) == 0 : (j & size) == 0;
-                    const bool swap = (k[j + stride] < k[j]) == up;
-                    const unsigned long long a = k[j], b = k[j + stride];
-                    k[j] = swap ? b : a;
-                    k[j + stride] = swap ? a : b;
-                }
-            }
+        for (int j = 0; j < 4; ++j) {
+            if (j & kStride) continue;
+            const uint32_t ones = kSize >= 4 ? bit[(kSize >= 4 ? log2_of(kSize) : 2) - 2] : (j & kSize) ? ~0u : 0u;
+            const Key x = k[j], y = k[j + kStride];
+            k[j] = lower_or_higher(x, y, ones);
+            k[j + kStride] = lower_or_higher(x, y, ~ones);
         }
     }
+    if constexpr (kStride > 1) sort_stages<kSize, kStride / 2>(k, bit);
+    else if constexpr (kSize < 256) sort_stages<kSize * 2, kSize>(k, bit);
+}
+template <class Key>
+__device__ __forceinline__ void sort_keys(Key (&k)[4], int lane)
+{
+    uint32_t bit[7];
+#pragma unroll
+    for (int i = 0; i < 7; ++i) bit[i] = ((lane >> i) & 1) ? ~0u : 0u;   // (bit[6]: no lane)
+    sort_stages<2, 1>(k, bit);
+}
+// Inclusive scan over the lanes (row_shr 1, 2, 4, 8, then row_bcast 15 and 31); `none` changes nothing.
+template <class T, class Op>
+__device__ __forceinline__ T scan_lanes(T v, T none, Op op)
+{
+    v = op(v, (T)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x111, 0xF, 0xF, false));
+    v = op(v, (T)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x112, 0xF, 0xF, false));
+    v = op(v, (T)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x114, 0xF, 0xF, false));
+    v = op(v, (T)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x118, 0xF, 0xF, false));
+    v = op(v, (T)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x142, 0xA, 0xF, false));
+    return op(v, (T)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x143, 0xC, 0xF, false));
 }
 // TableView::rank_nodes (`nodes`: the slice's first) of entries [lo, hi) of a slice of L by one wavefront; lo is
 // a multiple of 256, hi too unless it is L; (mx, mn): what entries [0, lo) come to.  Four consecutive
 // entries per lane, so that the scan over the lanes is done once per 256 entries.
+// Bound by the instructions of the sort, 36 stages in a row, which slices of up to kRankUnsorted entries go without.  Measured
+// (us, load report and build, every slice truncated): 1600 slices of 2000 entries 77 with 64-bit keys exchanged through
+// LDS, 57 so; 1600 of 500, sorted or not, 47 and 37; 8 of 20,000, where a quarter of a slice is one wavefront's, 102 and 48.
+// Without any nodes these builds take 46, 36 and 16; the first selection behind them that finds nodes gets back more.
+// kSort false: for kernels of tables without longer ones.
+template <bool kSort>
 __device__ __forceinline__ void write_rank_nodes(const int32_t *acc, const uint32_t *tot, uint4 *nodes, int32_t L, int32_t lo,
-                                                 int32_t hi, int lane, int32_t mx, uint32_t mn)
+                                                 int32_t hi, int lane, int32_t mx, uint32_t mn, int32_t acc_base)
 {
+    const auto higher = [](int32_t x, int32_t y) { return x > y ? x : y; };
+    const auto lower = [](uint32_t x, uint32_t y) { return x < y ? x : y; };
     uint2 *out = (uint2 *)nodes;   // pairs
     uint4 *sorted = nodes + (int64_t)all_level_nodes(L) * 8;
+    if (lo >= hi) return;
+    int32_t at_next = lo + 4 * lane < hi ? lo + 4 * lane : lo;
+    v4i a_next = *(const v4i *)(acc + at_next);   // (the next chunk's entries are requested a chunk ahead)
+    uint4 t_next = *(const uint4 *)(tot + at_next);
     for (int32_t c = lo; c < hi; c += kRankBlock) {
         const int32_t i = c + 4 * lane;
         const bool in = i < hi;
-        const v4i a = *(const v4i *)(acc + (in ? i : lo));
-        const uint4 t = *(const uint4 *)(tot + (in ? i : lo));
-        const int32_t a01 = a.x > a.y ? a.x : a.y, a23 = a.z > a.w ? a.z : a.w;
-        const uint32_t t01 = t.x < t.y ? t.x : t.y, t23 = t.z < t.w ? t.z : t.w;
-        int32_t m = in ? (a01 > a23 ? a01 : a23) : INT32_MIN;
-        uint32_t n = in ? (t01 < t23 ? t01 : t23) : 0xFFFFFFFFu;
-        m = m > mx ? m : mx;
-        n = n < mn ? n : mn;
-        for (int d = 1; d < 64; d <<= 1) {
-            const int32_t om = __shfl_up(m, d);
-            const uint32_t on = __shfl_up(n, d);
-            m = (lane >= d && om > m) ? om : m;
-            n = (lane >= d && on < n) ? on : n;
-        }
+        const v4i a = a_next;
+        const uint4 t = t_next;
+        at_next = i + kRankBlock < hi ? i + kRankBlock : lo;
+        a_next = *(const v4i *)(acc + at_next);
+        t_next = *(const uint4 *)(tot + at_next);
+        int32_t m = in ? higher(higher(a.x, a.y), higher(a.z, a.w)) : INT32_MIN;
+        uint32_t n = in ? lower(lower(t.x, t.y), lower(t.z, t.w)) : 0xFFFFFFFFu;
+        m = higher(scan_lanes(m, INT32_MIN, higher), mx);
+        n = lower(scan_lanes(n, 0xFFFFFFFFu, lower), mn);
         // level 1: the last lane of every four, where the four begin inside the slice
         if ((lane & 3) == 3 && c + 4 * (lane - 3) < hi) out[(uint32_t)(c >> 4) + (lane >> 2)] = make_uint2((uint32_t)m, n);
         mx = __builtin_amdgcn_readlane(m, 63);
@@ -186,39 +243,59 @@ __device__ __forceinline__ void write_rank_nodes(const int32_t *acc, const uint3
             for (int level = 2; level_nodes(L, level - 1) > 1; ++level) {
                 at += 16u * (uint32_t)level_nodes(L, level - 1);
                 const int64_t end = (int64_t)c + kRankBlock, size = (int64_t)1 << (4 * level);
-                if (end % size == 0 || end >= L) out[at + (uint32_t)((int64_t)c / size)] = make_uint2((uint32_t)mx, mn);
+                if ((end & (size - 1)) == 0 || end >= L) out[at + (uint32_t)(c >> (4 * level))] = make_uint2((uint32_t)mx, mn);
             }
         }
-        if (L <= kRankBlock) break;
-        // the block by falling accuracy (equal ones by rising latency), entries past the end of the slice last
-        auto key = [&](int32_t x, uint32_t y) {
-            return in ? ((unsigned long long)(~((uint32_t)x ^ 0x80000000u)) << 32) | y : ~0ull;
-        };
-        unsigned long long k[4] = {key(a.x, t.x), key(a.y, t.y), key(a.z, t.z), key(a.w, t.w)};
+        if (!kSort || L <= kRankUnsorted) continue;
+        // The block by falling accuracy.  Entries that nothing selects (masked, past the end of the slice) come last, as
+        // the lowest accuracy there is; among equal ones any order will do, as the search looks at the last of them.
         int ln = lane;
         asm volatile("" : "+v"(ln));   // (the masks of the sort's stages are made here, every time: before the loop there are too many to keep)
-        sort_keys(k, ln);
-        uint32_t low[4];   // the lowest latency up to each of them
-        low[0] = (uint32_t)k[0];
+        constexpr uint32_t kDead = 0xFFFFFFu;   // accuracies are counted down from kDead - 1 where they fit 24 bits ...
+        const uint32_t below[4] = {(uint32_t)a.x - (uint32_t)acc_base, (uint32_t)a.y - (uint32_t)acc_base,
+                                   (uint32_t)a.z - (uint32_t)acc_base, (uint32_t)a.w - (uint32_t)acc_base};
+        const uint32_t tt[4] = {in ? t.x : 0xFFFFFFFFu, in ? t.y : 0xFFFFFFFFu, in ? t.z : 0xFFFFFFFFu, in ? t.w : 0xFFFFFFFFu};
+        bool wide = false;
 #pragma unroll
-        for (int j = 1; j < 4; ++j) low[j] = (uint32_t)k[j] < low[j - 1] ? (uint32_t)k[j] : low[j - 1];
-        n = low[3];
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t on = __shfl_up(n, d);
-            n = (lane >= d && on < n) ? on : n;
+        for (int j = 0; j < 4; ++j) wide = wide | ((tt[j] != 0xFFFFFFFFu) & (below[j] >= kDead));
+        int32_t s_acc[4];
+        uint32_t s_tot[4];
+        if (__ballot(wide) == 0ull) {
+            uint32_t k[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) k[j] = ((tt[j] != 0xFFFFFFFFu ? kDead - 1u - below[j] : kDead) << 8) | (uint32_t)(4 * lane + j);
+            sort_keys(k, ln);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool dead = (k[j] >> 8) == kDead;
+                s_acc[j] = dead ? INT32_MIN : (int32_t)((uint32_t)acc_base + (kDead - 1u - (k[j] >> 8)));
+                s_tot[j] = tot[dead ? c : c + (int32_t)(k[j] & 0xFFu)];
+                s_tot[j] = dead ? 0xFFFFFFFFu : s_tot[j];
+            }
+        } else {               // ... and are compared as they are where they do not
+            unsigned long long k[4];
+            const int32_t av[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) k[j] = tt[j] != 0xFFFFFFFFu ? ((unsigned long long)(~((uint32_t)av[j] ^ 0x80000000u)) << 32) | tt[j] : ~0ull;
+            sort_keys(k, ln);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { s_acc[j] = (int32_t)(~(uint32_t)(k[j] >> 32) ^ 0x80000000u); s_tot[j] = (uint32_t)k[j]; }
         }
-        uint32_t before = __shfl_up(n, 1);
+        // each with the lowest latency up to it
+#pragma unroll
+        for (int j = 1; j < 4; ++j) s_tot[j] = lower(s_tot[j], s_tot[j - 1]);
+        const uint32_t upto = scan_lanes(s_tot[3], 0xFFFFFFFFu, lower);
+        uint32_t before = (uint32_t)__shfl_up((int)upto, 1);
         before = lane ? before : 0xFFFFFFFFu;
         uint2 pair[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            pair[j] = make_uint2(~(uint32_t)(k[j] >> 32) ^ 0x80000000u, low[j] < before ? low[j] : before);
+        for (int j = 0; j < 4; ++j) pair[j] = make_uint2((uint32_t)s_acc[j], lower(s_tot[j], before));
         uint4 *blk = sorted + (int64_t)(c / kRankBlock) * kRankBlockNodes * 8;
         blk[8 + 2 * lane] = make_uint4(pair[0].x, pair[0].y, pair[1].x, pair[1].y);
         blk[8 + 2 * lane + 1] = make_uint4(pair[2].x, pair[2].y, pair[3].x, pair[3].y);
         if ((lane & 3) == 3) ((uint2 *)blk)[lane >> 2] = pair[3];
     }
-    if (lo < hi && hi == L && lane < 15) {   // the places past the end of every level
+    if (hi == L && lane < 15) {   // the places past the end of every level
         uint32_t at = 0;
         for (int level = 1;; ++level) {
             const int32_t n = level_nodes(L, level);
@@ -236,7 +313,7 @@ struct SliceColumns {
     const int32_t *acc;
     const uint32_t *tot;
     uint4 *nodes;
-    int32_t L;
+    int32_t L, acc_base;
 };
 template <bool kTwo>
 __device__ __forceinline__ SliceColumns slice_columns(int32_t s, int32_t t, int32_t b)
@@ -247,7 +324,7 @@ __device__ __forceinline__ SliceColumns slice_columns(int32_t s, int32_t t, int3
     if (kTwo && blockIdx.y) args += sizeof(TableView) + sizeof(IndexView);
     const __attribute__((address_space(4))) TableView *tv = (const __attribute__((address_space(4))) TableView *)args;
     const int64_t col = (int64_t)b * tv->Vp + tv->seg_off[t];
-    return SliceColumns{tv->acc_r + col, tv->tot_r + col, (uint4 *)((char *)tv->rank_hdr + (rank_nodes_at(tv->S) - rank_hdr_at(tv->S))) + (uint64_t)tv->rank_hdr[s].z * 8, tv->seg_len[t]};
+    return SliceColumns{tv->acc_r + col, tv->tot_r + col, (uint4 *)((char *)tv->rank_hdr + (rank_nodes_at(tv->S) - rank_hdr_at(tv->S))) + (uint64_t)tv->rank_hdr[s].z * 8, tv->seg_len[t], tv->acc_base};
 }
 
 // One wavefront per slice, kBuildWaves slices per workgroup.  An entry of the slice is a step exactly
@@ -524,7 +601,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
     }
     if (__builtin_expect(has && (trunc || !fits), 0)) {   // (the wavefront) queries of this slice may go through its entries in rank order
         const SliceColumns sc = slice_columns<kTwo>(s, t, b);
-        write_rank_nodes(sc.acc, sc.tot, sc.nodes, sc.L, 0, sc.L, lane, INT32_MIN, 0xFFFFFFFFu);
+        write_rank_nodes<(64 * kBuildPer > kRankUnsorted)>(sc.acc, sc.tot, sc.nodes, sc.L, 0, sc.L, lane, INT32_MIN, 0xFFFFFFFFu, sc.acc_base);
     }
     if (lane == 0 && inside) {
         // This build places by arrival and reads nobody's entry.  It takes its own out all the same: the build numbers
@@ -947,7 +1024,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableVi
             mx = (int32_t)parts[w][0][0] > mx ? (int32_t)parts[w][0][0] : mx;
             mn = parts[w][0][1] < mn ? parts[w][0][1] : mn;
         }
-        write_rank_nodes(sc.acc, sc.tot, sc.nodes, sc.L, from, to, lane, mx, mn);
+        write_rank_nodes<(kChunk > kRankUnsorted)>(sc.acc, sc.tot, sc.nodes, sc.L, from, to, lane, mx, mn, sc.acc_base);
     }
     if (wave != 0) return;   // (no barrier follows)
     if (fits && lane < K) {

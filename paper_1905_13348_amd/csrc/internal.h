@@ -40,7 +40,7 @@ struct TableView {
     //    end of every 16 entries (level 1), of every 256 (level 2), of every 4096, ..., as many levels as it
     //    takes to get to one node; level 1's nodes come first.  Places past the end of a level hold a pair
     //    that meets every requirement.
-    // 2. Behind the levels, for slices of more than 256 entries, 17 nodes per 256 entries: the entries by
+    // 2. Behind the levels, for slices of more than kRankUnsorted entries, 17 nodes per 256 entries: the entries by
     //    falling accuracy, each with the lowest latency so far (nodes 1..16), and the last pair of each of
     //    those nodes (node 0).
     // Null without an index.
@@ -168,6 +168,8 @@ __host__ __device__ inline size_t rank_nodes_at(int32_t S) { return (((size_t)S 
 __host__ __device__ inline uint4 *TableView::rank_nodes() const { return (uint4 *)((char *)rank_hdr + (rank_nodes_at(S) - rank_hdr_at(S))); }
 // TableView::rank_nodes of a slice of L entries: nodes of a level, of all levels, and of everything.
 constexpr int kRankBlock = 256, kRankBlockNodes = 17;
+// Slices the search never needs the sorted blocks of: behind the first 16 entries it tries as many as kRankAtOnce directly.
+constexpr int kRankAtOnce = 512, kRankUnsorted = kRankAtOnce + 16;
 __host__ __device__ inline int32_t level_nodes(int32_t L, int level) { return (int32_t)(((int64_t)L + ((int64_t)16 << (4 * level)) - 1) >> (4 * level + 4)); }
 __host__ __device__ inline int32_t all_level_nodes(int32_t L)
 {
@@ -175,7 +177,7 @@ __host__ __device__ inline int32_t all_level_nodes(int32_t L)
     for (int level = 1; n > 1; ++level) { n = level_nodes(L, level); sum += n; }
     return sum;
 }
-__host__ __device__ inline int32_t rank_blocks(int32_t L) { return L > kRankBlock ? (int32_t)(((int64_t)L + kRankBlock - 1) / kRankBlock) : 0; }
+__host__ __device__ inline int32_t rank_blocks(int32_t L) { return L > kRankUnsorted ? (int32_t)(((int64_t)L + kRankBlock - 1) / kRankBlock) : 0; }
 // Called by every thread of the first kernel of a selection.
 __device__ __forceinline__ void publish_index_stats(const TableView &tv)
 {

@@ -252,7 +252,7 @@ __device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const u
             if (lane == l) found = hit;
             continue;
         }
-        if (len - lo <= 512) {
+        if (len - lo <= kRankAtOnce) {
             const int64_t at0 = c + (lo + 4 * lane < len ? lo + 4 * lane : 0), at1 = c + (lo + 256 + 4 * lane < len ? lo + 256 + 4 * lane : 0);
             const uint4 a0 = *(const uint4 *)(tv.acc_r + at0), w0 = *(const uint4 *)(tv.tot_r + at0);
             const uint4 a1 = *(const uint4 *)(tv.acc_r + at1), w1 = *(const uint4 *)(tv.tot_r + at1);

@@ -6,7 +6,9 @@ import numpy as np
 import pytest
 
 from gpu_util import gpu_select, make_selector, table_args, to_dev
+from test_gpu_case1 import gpu_case1
 from test_gpu_parity import _assert_equal_everywhere, _table
+from test_gpu_tiered import gpu_select_tiered
 
 pytestmark = pytest.mark.gpu
 
@@ -97,4 +99,73 @@ def test_ranked_batches_and_short_rests(oracle_lib, kind):
     assert sel.info()["index_truncated"] > tb.num_tasks
     for n in (1, 2, 3, 2047, 2048, 2049, 4095, 4097, 8193, 16385, 32767, 65537, 131_072, 131_073):
         _assert_equal_everywhere(gpu_select(sel, *(x[:n] for x in qs)), want[:n], f"{kind} N={n}")
+    sel.destroy()
+
+
+@pytest.mark.parametrize("kind", ["stairs", "mixed", "noisy", "wide"])
+def test_ranked_many_slices(oracle_lib, kind):
+    """More than 512 slices in one pool (built one per wavefront), most of them truncated, a few of them long enough for
+    sorted blocks and for levels above the first."""
+    rng = np.random.default_rng(23)
+    T = 300
+    lengths = rng.integers(64, 150, T)
+    lengths[[0, 5, 100, 101, 299]] = (4097, 529, 600, 1025, 2000)
+    tb = _ranked_table(kind, tuple(int(n) for n in lengths), 2, rng)
+    qs = _ranked_queries(tb, 60_001, rng)
+    long = rng.random(60_001) < 0.4
+    qs[0][long] = rng.choice(np.asarray([0, 5, 100, 101, 299], np.int32), int(long.sum()))
+    sel = make_selector(tb, engine=0)
+    queue = tb.queue_us.copy()
+    for rnd in range(2):
+        if rnd:
+            rows, vals = rng.choice(tb.V, tb.V // 3, replace=False).astype(np.int32), rng.integers(0, 30_000, tb.V // 3).astype(np.int32)
+            sel.update_load(to_dev(rows), to_dev(vals))
+            oracle_lib.update_load(queue, rows, vals)
+        want = oracle_lib.select(*table_args(tb, queue), *qs)
+        for part in (slice(0, 2001), slice(None)):
+            _assert_equal_everywhere(gpu_select(sel, *(x[part] for x in qs)), want[part], f"{kind} round {rnd}")
+    sel.destroy()
+
+
+@pytest.mark.parametrize("T,B", [(20, 4), (130, 4)])
+def test_ranked_two_tiers(oracle_lib, T, B):
+    """Truncated slices in both tiers, up to 600 entries of either state: the nodes of two tables written by one
+    launch, one slice per workgroup and (more than 1024 slices) one per wavefront; masked entries in every sorted block."""
+    rng = np.random.default_rng(T)
+    lengths = [80] * T
+    lengths[0], lengths[3], lengths[T - 1] = 1300, 1100, 2100
+    tb = _ranked_table("noisy", tuple(lengths), B, rng)
+    state, load = rng.integers(0, 3, tb.V).astype(np.int32), rng.integers(100, 60_000, tb.V).astype(np.int32)
+    qs = _ranked_queries(tb, 20_003, rng)
+    long = rng.random(20_003) < 0.5
+    qs[0][long] = rng.choice(np.asarray([0, 3, T - 1], np.int32), int(long.sum()))
+    sel = make_selector(tb, engine=0)
+    sel.load_states(state, load)
+    state = state.copy()
+    for rnd in range(2):
+        if rnd:
+            rows, vals = rng.choice(tb.V, tb.V // 2, replace=False).astype(np.int32), rng.integers(0, 3, tb.V // 2).astype(np.int32)
+            sel.update_state(to_dev(rows), to_dev(vals))
+            oracle_lib.update_state(state, rows, vals)
+        for g, w in zip(gpu_select_tiered(sel, *qs), oracle_lib.select_tiered(*table_args(tb), state, load, *qs)):
+            _assert_equal_everywhere(g, w, f"tiers round {rnd}")
+        for g, w in zip(gpu_case1(sel, *qs), oracle_lib.select_case1(*table_args(tb), state, load, *qs)):
+            _assert_equal_everywhere(g, w, f"case I round {rnd}")
+    sel.destroy()
+
+
+@pytest.mark.parametrize("span", [0xFFFFFD, 0xFFFFFE, 0xFFFFFF, 0x1000000])
+@pytest.mark.parametrize("low", [-2**31, -2**31 + 1, -5, 2**31 - 1 - 0x1000000])
+def test_ranked_accuracies_around_24_bits(oracle_lib, low, span):
+    """Sorted blocks are made from accuracies counted in 24 bits where they fit, and as they are where not."""
+    rng = np.random.default_rng(span & 0xFF)
+    tb = _ranked_table("noisy", (600, 900), 2, rng)
+    acc = (low + np.floor((tb.acc_bp - 5000) / 9000 * span)).astype(np.int64)
+    acc[np.flatnonzero(tb.task_id == 0)[[7, 300]]] = (low, low + span)
+    acc[np.flatnonzero(tb.task_id == 1)[[800, 2]]] = (low, low + span)
+    tb = _table(2, tb.batch_sizes, tb.task_id, acc, tb.lat_us, tb.cost, tb.queue_us)
+    qs = _ranked_queries(tb, 20_001, rng)
+    sel = make_selector(tb, engine=0)
+    assert sel.info()["index_truncated"] == 4
+    _assert_equal_everywhere(gpu_select(sel, *qs), oracle_lib.select(*table_args(tb), *qs), f"{low} + {span}")
     sel.destroy()
