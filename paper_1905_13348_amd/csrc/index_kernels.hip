@@ -984,12 +984,12 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableVi
                 const int32_t x = __shfl_xor(most, o);
                 most = x > most ? x : most;
             }
-            most = got ? most : kIndexCap;   // (should the wait have run out: the most there can be)
+            most = got ? most : kIndexCap;   // (should the wait have run out: the most there can be, here and of the steps)
             sum += published;
             if (lane == 0) {
                 if (!grouped) {
                     ix.ctrl[kCtlPool] = ix.ctrl[kCtlPool0] + (uint32_t)sum;
-                    ix.ctrl[kCtlSteps] = ix.ctrl[kCtlSteps0] + ((uint32_t)(sum >> 32) & kRoomSteps);
+                    ix.ctrl[kCtlSteps] = got ? ix.ctrl[kCtlSteps0] + ((uint32_t)(sum >> 32) & kRoomSteps) : ix.step_cap;
                 }
                 ix.ctrl[kCtlTrunc] = (uint32_t)(sum >> kRoomTrunc);
                 ix.ctrl[kCtlMaxK] = (uint32_t)most;
