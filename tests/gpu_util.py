@@ -32,6 +32,24 @@ def make_selector(table, engine=0, lds_segment_limit=0):
     return sel
 
 
+def direct_limit(sel):
+    """The most queries that a plain selection of the handle answers straight from global memory; one more goes to
+    the lookup kernel (or, from 2^20 on and with groups, is binned by group).  As of the handle's latest selection."""
+    i = sel.info()
+    if not i["index_in_lds"]:
+        return 100_000
+    s = i["num_slices"]
+    pool = i["index_bytes"] - 16 * s - 4 * (i["index_steps"] + 1)
+    room = 160 * 1024 - 48 - ((s + 1) * 8 + 15) // 16 * 16
+    return 100_000 if pool <= room else 100_000 * pool // room
+
+
+def tiled_beyond(limit, *arrays):
+    """The arrays over and over, more than `limit` entries of each."""
+    times = limit // len(arrays[0]) + 1
+    return tuple(np.tile(a, times) for a in arrays)
+
+
 def table_args(tb, queue=None):
     return (tb.task_id, tb.acc_bp, tb.lat_us, tb.cost, tb.queue_us if queue is None else queue)
 

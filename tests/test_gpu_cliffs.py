@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_util import gpu_select, make_selector, query_args, table_args, to_dev
+from gpu_util import direct_limit, gpu_select, make_selector, query_args, table_args, tiled_beyond, to_dev
 from test_gpu_parity import ENGINE_IDS, ENGINES, _assert_equal_everywhere, _table
 
 pytestmark = pytest.mark.gpu
@@ -36,9 +36,9 @@ def test_index_degrades_after_a_load_report(oracle_lib, engine):
     queues rise with the cost faster than the latencies fall: the cheapest variant of a task dominates
     the others and every staircase has one step.  A report then empties all queues -- 200 steps per
     slice, of which the index keeps 62 -- and a second one restores them.  Parity throughout; the AUTO
-    handle turns to the exhaustive scan one call after the first report (the call that follows it
+    handle turns to the search in rank order one call after the first report (the call that follows it
     still runs the index lookup, whose first kernel tells the host what the rebuild found) and back
-    to the index one call after the second."""
+    to the index one call after the second.  (Its kernel is timed where the exhaustive scan's is.)"""
     T, n, B = 100, 200, 8
     i = np.tile(np.arange(n, dtype=np.int64), T)
     b = np.arange(B, dtype=np.int64)[None, :]
@@ -72,4 +72,24 @@ def test_index_degrades_after_a_load_report(oracle_lib, engine):
             info = sel.info()
             assert info["index_truncated"] == (T * B if bad else 0) and info["index_max_steps"] == (62 if bad else 1)
         assert used() == (("scan" if bad else "index") if engine == 0 else first)
+    sel.destroy()
+
+
+@pytest.mark.parametrize("kind", ["long_staircases", "wide_accuracy"])
+def test_cliff_tables_through_the_lookup_kernel(oracle_lib, kind):
+    """A handle that always uses the index, with more queries than are answered straight from memory: bodies of
+    truncated slices and slices without any, finished by the scan inside the lookup kernel."""
+    tb = workloads.make_cliff_table(kind, cfg=1)
+    q = query_args(workloads.make_queries(1, n=60_000))
+    want = oracle_lib.select(*table_args(tb), *q)
+    sel = make_selector(tb, engine=2)
+    gpu_select(sel, *q)                               # (what the limit depends on is known from the first call on)
+    parked = sel.info()["lookup_parked"]
+    many = tiled_beyond(direct_limit(sel), *q, want)
+    assert len(many[0]) < 1 << 20
+    _assert_equal_everywhere(gpu_select(sel, *many[:4]), many[4], kind)
+    info = sel.info()
+    assert info["lookup_scanned"] > 1000
+    if kind == "long_staircases":                     # (straight from memory every query counts as parked)
+        assert info["lookup_parked"] < parked * (len(many[0]) // len(q[0]))
     sel.destroy()

@@ -1,12 +1,12 @@
-"""Batches small enough to be answered straight from global memory, one lane per query, on both sides of
-the size where the LDS mirror takes over: an index that fits the mirror, one that does so in part, one
-laid out in groups and one whose headers leave no room for a mirror; arrays that start 4 bytes into
-their allocations.  Every answer against the CPU oracle."""
+"""Batches small enough to be answered straight from global memory, one lane per query, and batches on both
+sides of the size where the LDS mirror (or the group-by-group selection) takes over: an index that fits the
+mirror, one that does so in part, one laid out in groups and one whose headers leave no room for a mirror;
+arrays that start 4 bytes into their allocations.  Every answer against the CPU oracle."""
 import numpy as np
 import pytest
 
 import workloads
-from gpu_util import gpu_select_closest, make_selector, query_args, table_args
+from gpu_util import direct_limit, gpu_select, gpu_select_closest, make_selector, query_args, table_args, tiled_beyond
 from test_gpu_case1 import gpu_case1
 from test_gpu_getvariant import gpu_get_variant
 from test_gpu_parity import (_assert_equal_everywhere, _random_queries, _random_table, _staircase_queries,
@@ -51,6 +51,38 @@ def test_small_batches(oracle_lib, kind):
                 assert (got[n:] == -7).all()
     info = sel.info()
     assert info["lookup_parked"] >= info["lookup_second_body"] + info["lookup_unanswered"]
+    sel.destroy()
+
+
+def _few_groups():
+    rng = np.random.default_rng(15)
+    return _random_table(rng, 200, np.full(200, 500), 8)
+
+
+@pytest.mark.parametrize("kind", list(TABLES) + ["few_groups"])
+def test_both_sides_of_the_limit(oracle_lib, kind):
+    """As many queries as the limit, and one more; which kernel answered follows from the statistics: straight from
+    memory every valid query counts as parked, the lookup kernel parks what its first probe cannot decide."""
+    tb = _few_groups() if kind == "few_groups" else TABLES[kind]()
+    q = workloads.make_queries(1, n=60_001, seed=78)
+    rng = np.random.default_rng(7)
+    task, bidx = rng.integers(0, tb.num_tasks, q.N).astype(np.int32), rng.integers(0, tb.B, q.N).astype(np.int32)
+    qs = (task, *query_args(q)[1:3], bidx)
+    want = oracle_lib.select(*table_args(tb), *qs)
+    sel = make_selector(tb, engine=0)
+    gpu_select(sel, *qs)
+    limit = direct_limit(sel)
+    assert (limit > 100_000) == (kind in ("partly", "groups", "few_groups"))
+    assert (sel.info()["index_groups"] > 1) == (kind in ("groups", "few_groups", "no_mirror"))
+    if kind == "groups":        # binned by group from 2^20 on
+        assert limit >= 1 << 20
+        limit = (1 << 20) - 1
+    many = tiled_beyond(limit, *qs, want)
+    for n in (limit, limit + 1):
+        _assert_equal_everywhere(gpu_select(sel, *(x[:n] for x in many[:4])), many[4][:n], f"{kind} N={n}")
+        parked = sel.info()["lookup_parked"]
+        if kind != "no_mirror":     # (without a mirror the lookup kernel reads from memory too)
+            assert (parked == n) == (n == limit), (n, parked)
     sel.destroy()
 
 

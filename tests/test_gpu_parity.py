@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_util import gpu_select, make_selector, query_args, table_args, to_dev
+from gpu_util import direct_limit, gpu_select, make_selector, query_args, table_args, tiled_beyond, to_dev
 from pins import check_invariants
 
 pytestmark = pytest.mark.gpu
@@ -68,6 +68,15 @@ def _compare(oracle_lib, tb, queries, engine, lds_limit=0, label=""):
     want = oracle_lib.select(*table_args(tb), *queries)
     bad = np.flatnonzero(got != want)
     assert bad.size == 0, f"{label}: {bad.size} mismatches, first at {bad[:5]}: got {got[bad[:5]]} want {want[bad[:5]]}"
+    # once more, as many of them as it takes to leave the kernel for small batches
+    limit = direct_limit(sel) if engine != 1 else 0
+    if 0 < len(queries[0]) <= limit < 2_000_000:
+        many = tiled_beyond(limit, *queries, want)
+        bad = np.flatnonzero(gpu_select(sel, *many[:4]) != many[4])
+        assert bad.size == 0, f"{label}, N={len(many[0])}: {bad.size} mismatches, first at {bad[:5]}"
+        info = sel.info()
+        if info["index_in_lds"] and limit == 100_000 and info["index_truncated"] == 0:   # all of it in the mirror
+            assert info["lookup_global_body"] == 0
     sel.destroy()
     return got
 
@@ -202,7 +211,8 @@ def _staircase_queries(rng, tb, n_queries, n, lat0=100_000):
 @pytest.mark.parametrize("steps", [31, 32, 50, 62, 63, 300])
 def test_long_staircases(oracle_lib, engine, steps):
     """Slices whose staircase fills one index body exactly (31), needs the second one (32..62), or
-    exceeds the index capacity (63, 300: the in-kernel rank-ordered scan must finish the query)."""
+    exceeds the index capacity (63, 300: what the bodies leave open is finished in rank order).  Both straight
+    from memory and, in _compare, through the lookup kernel's mirror."""
     rng = np.random.default_rng(steps)
     tb = _staircase_table(5, steps)
     qs = _staircase_queries(rng, tb, 40_000, steps)
@@ -212,7 +222,7 @@ def test_long_staircases(oracle_lib, engine, steps):
         info = sel.info()
         assert info["index_max_steps"] == min(steps, 62)
         assert (info["index_truncated"] > 0) == (steps > 62)
-        if engine == 2 or steps <= 62:   # (auto hands a table of truncated slices to the scan engine)
+        if engine == 2 or steps <= 62:   # (auto searches a table of truncated slices in rank order)
             gpu_select(sel, *qs)
             info = sel.info()
             assert (info["lookup_second_body"] > 0) == (steps > 31)
@@ -302,6 +312,12 @@ def test_index_outgrows_lds_after_load_update(oracle_lib):
     want = oracle_lib.select(*table_args(tb, queue), *qs)
     assert np.array_equal(got, want)
     assert (want >= 0).mean() > 0.3 and len(np.unique(want)) > 1000
+    limit = direct_limit(sel)                      # (by now these 200,000 are few enough to be read from memory at once)
+    assert 200_000 < limit < 1_000_000
+    many = tiled_beyond(limit, *qs, want)
+    assert np.array_equal(gpu_select(sel, *many[:4]), many[4])
+    info = sel.info()
+    assert 0 < info["lookup_global_body"] < info["lookup_parked"] < len(many[0])
     sel.destroy()
 
 
@@ -548,6 +564,8 @@ def test_few_long_slices_with_reports(oracle_lib):
         want = oracle_lib.select(tb.task_id, tb.acc_bp, tb.lat_us, tb.cost, queue, *qs)
         bad = np.flatnonzero(got != want)
         assert bad.size == 0, f"round {rnd}: {bad.size} mismatches, first at {bad[:5]}"
+        many = tiled_beyond(direct_limit(sel), *qs, want)   # the lookup kernel as well
+        assert np.array_equal(gpu_select(sel, *many[:4]), many[4]), f"round {rnd}, N={len(many[0])}"
     info = sel.info()
     assert info["index_truncated"] == 0 and 20 <= info["index_max_steps"] <= 62
     sel.destroy()
