@@ -149,7 +149,8 @@ int infaas_sel_select(infaas_sel_t *h, int64_t N,
  * looked up in infaas_sel_create.  Limits: at most INFAAS_SEL_NOALLOC_MAX_QUERIES queries per
  * call (more: INVALID_ARG; split the batch), a device with at most 256 compute units, and a
  * handle that answers through the staircase index (not INFAAS_SEL_ENGINE_SCAN, whose bucketing
- * needs 20 bytes of scratch per query).  After infaas_sel_load_states it answers from the Active
+ * needs 20 bytes of scratch per query, and in automatic mode not while more than half of the slices
+ * exceed its capacity).  After infaas_sel_load_states it answers from the Active
  * variants only, like infaas_sel_select.  Kernel timing (infaas_sel_set_timing) does not cover it.
  * All calls on one GPU share the array, whichever handle or stream they use: calls that
  * overlap in time on one GPU race and give wrong answers; order them (one stream, or events).
@@ -507,11 +508,15 @@ typedef struct {
     int32_t index_hot_rows;     /* steps per slice whose caller row is kept beside the index in LDS */
     int64_t index_bytes;        /* size of the staircase index (as of the latest build a selection has run behind) */
     int64_t index_steps;        /* steps over all slices */
-    int64_t table_bytes;        /* device bytes of the variant store */
+    int64_t table_bytes;        /* device bytes of the variant store and of the levels and sorted blocks that slices
+                                   are searched through in rank order */
     int64_t scratch_bytes;      /* device bytes of scratch currently reserved */
     /* The most recent launch of the index lookup kernel on this handle (for a state-aware call: the
      * Inactive tier's): the queries whose answer the first group of their slice's staircase, as
-     * mirrored in LDS, could not decide, and what became of them.  Valid once the caller has
+     * mirrored in LDS, could not decide, and what became of them.  A small batch answered straight from global
+     * memory has no mirror: there every query with a valid slice and bound counts as parked, every answer of a first
+     * group as one from global memory, and the two tiers of a state-aware call are counted together.  All 0 after a
+     * selection that did not use the index.  Valid once the caller has
      * synchronised the stream of that call; infaas_sel_get_info copies them with a blocking hipMemcpy. */
     int64_t lookup_parked;      /* queries set aside for the slower paths */
     int64_t lookup_second_body; /* ... answered by the second group of steps */

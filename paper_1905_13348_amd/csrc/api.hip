@@ -387,7 +387,7 @@ int create_index(infaas_sel *h)
         }
     }
     // one allocation: the pool, then the headers, so that one 32-bit offset reaches both; behind them rank_hdr and,
-    // at a multiple of their size, the nodes of TableView::rank_nodes
+    // at a multiple of their size, the nodes of TableView::rank_nodes (counted with the table: they do not follow the index)
     ix.pool_bytes &= ~127u;
     const size_t nstats = (size_t)index_stat_blocks(h->num_cus) * kLookupStats;
     bool ok = dev_alloc(&ix.pool, (size_t)ix.pool_bytes + rank_nodes_at((int32_t)S) + (size_t)std::max<int64_t>(nodes, 1) * 128) == hipSuccess &&
@@ -421,6 +421,7 @@ int create_index(infaas_sel *h)
         return INFAAS_SEL_ERR_HIP;
     }
     h->have_index = true;
+    h->table_bytes += (S + 1) * 16 + nodes * 128;
     const int64_t fixed = kLdsCtrlBytes + lds_header_bytes((int32_t)S) + 16;
     const int64_t need = fixed + h->ix_stats[kCtlPool];
     // The lookup kernel mirrors the index in LDS when the slice headers leave at least half of it to
@@ -627,7 +628,10 @@ bool use_index(infaas_sel *h)
     // auto: the index (mirrored in LDS when it fits, read from global memory otherwise), unless
     // more than half of the slices could not be indexed completely when the table was loaded or, as
     // far as is known by now, when the index was last rebuilt -- their queries would mostly end in
-    // the in-kernel scan, which the bucketed scan engine does faster
+    // the in-kernel scan, and use_ranked()'s search or, without it, the bucketed scan engine does
+    // those faster.  (The share was chosen for that engine.  By the search's figures it pays from
+    // a few hundredths of the queries on: one that the lookup kernel scans for costs 2.3 ns there and 0.04 ns in rank order,
+    // one that the mirror answers 0.004 ns.)
     const int64_t S = (int64_t)h->T * h->B;
     return 2 * ((int64_t)trunc + nobody) <= S;
 }
@@ -872,7 +876,6 @@ int infaas_sel_load_variants(infaas_sel_t *h, int32_t V, const int32_t *task_id,
          up(h->d_seg_off, seg_off.data(), ((size_t)T + 1) * 4) && up(h->d_seg_len, seg_len.data(), (size_t)T * 4) &&
          up(h->d_slot_of, slot_of.data(), (size_t)std::max(V, 1) * 4) &&
          up(h->d_acc_r, acc_r.data(), (size_t)B * Vp * 4) && up(h->d_orig_r, orig_r.data(), (size_t)B * Vp * 4) &&
-        
          up(h->d_tot_r, tot_r.data(), (size_t)B * Vp * 4);
     if (!ok) {
         h->free_table();
@@ -1393,7 +1396,7 @@ int infaas_sel_select_noalloc(infaas_sel_t *h, int64_t N, const int32_t *d_task,
     }
     if (!h->have_index || !use_index(h)) {
         snprintf(g_last_error, sizeof(g_last_error),
-                 "infaas_sel_select_noalloc needs the staircase index (the exhaustive scan buckets the queries in memory it allocates)");
+                 "infaas_sel_select_noalloc needs the staircase index, in automatic mode complete for half of the slices or more");
         return INFAAS_SEL_ERR_INVALID_ARG;
     }
     if (index_park_bytes(h->num_cus) > kStaticScratchBytes) {

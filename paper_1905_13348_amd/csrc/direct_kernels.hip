@@ -115,9 +115,9 @@ __device__ __forceinline__ void leave_statistics(const IndexView &ix, uint32_t *
     if (blockIdx.x == 0 && threadIdx.x == 0) ix.stats[-1] = gridDim.x;
 }
 
-// Bound by the rate of scattered reads: 14 per query through a body (header, ten probes, two sets, row), each
-// lane another line.  Sixteen wavefronts per compute unit already saturate that: register caps for 24 to 32
-// (80 to 64 registers instead of 89) were measured 0-25% slower on batches of a million.
+// Bound by the rate of scattered reads: 15 per query through a body (its header, that of the slice in rank order, ten
+// probes, two sets, row), each lane another line.  The 80 registers allow 24 wavefronts per compute unit, which saturate
+// that: 16 to 32 of them differed by 0-25% on batches of a million, more of them being slower.
 template <bool kRanked>
 __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, IndexView ix, QueryView q, int32_t per_wave)
 {

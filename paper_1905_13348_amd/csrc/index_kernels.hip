@@ -912,7 +912,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableVi
     lds_barrier();
     before = parts[0][0][lane] + parts[1][0][lane] + parts[2][0][lane] + parts[3][0][lane];
     const int32_t pa = (int32_t)(before & 0xFFFFu), ps = (int32_t)(before >> 16);
-            if (wave == 0) { ranks[lane] = pa; ranks[64 + lane] = ps; }
+    if (wave == 0) { ranks[lane] = pa; ranks[64 + lane] = ps; }
     lds_barrier();
     // 2. the sets: lane p collects A[p] and S[p] of both bodies
     uint32_t ma0 = 0u, ms0 = 0u, ma1 = 0u, ms1 = 0u;
@@ -1625,8 +1625,8 @@ hipError_t launch_build(const TableView &ta, const IndexView &ia, const TableVie
     constexpr unsigned tables = kTwo ? 2 : 1;
     if (ta.S <= 0) return hipSuccess;
     const dim3 block(64 * kBuildWaves);
-    // One slice per workgroup as long as all of them are on the device at once (five workgroups of these registers
-    // to a compute unit; the sums over the slices before are short, too).  us for one slice per workgroup / per
+    // One slice per workgroup as long as all of them are on the device at once (four workgroups of these registers
+    // to each of 256 compute units; the sums over the slices before are short, too).  us for one slice per workgroup / per
     // wavefront: 160 slices of 45 entries 7.3 / 9.9, 400 of 2000 15.9 / 21, 600 of 60 on average 15.9 / 24.4; two tables
     // of 800 slices of 200 20.3 / 12.7; 1600 of 60 16.0 / 13.5.  Without groups only up to 512: an index of more
     // slices mostly outgrows the lookup's LDS mirror, and in the order of the slices' numbers, not of their arrival (short
