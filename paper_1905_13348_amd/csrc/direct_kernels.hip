@@ -30,7 +30,7 @@ __device__ __forceinline__ Query load_query(const TableView &tv, const QueryView
 // in their bodies go through their entries in rank order at once; otherwise only with what the bodies leave
 // open.  Counts in st what became of the queries, as the lookup kernel does; no query is decided by an
 // LDS copy here, so all count as parked.
-template <bool kRanked>
+template <bool kRanked, bool kAhead>
 __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want,
                                                       uint32_t (&st)[kLookupStats])
 {
@@ -63,7 +63,7 @@ __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const
     }
     const bool scan = want && ans < 0 && (h.y & kHdrTrunc);
     if (__ballot(scan)) {
-        const int32_t row = ranked_first_fit(tv, scan ? rh : make_uint4(0u, 0u, 0u, 0u), u.min_acc, (uint32_t)u.slo);
+        const int32_t row = ranked_first_fit<kAhead>(tv, scan ? rh : make_uint4(0u, 0u, 0u, 0u), u.min_acc, (uint32_t)u.slo);
         if (scan) ans = row;
         count(3, scan);
     }
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, Ind
         const int64_t i = i0 + wave * per + lane;
         const bool mine = !kRanked || lane < per;
         const Query u = load_query(tv, q, i, mine);
-        const int32_t ans = select_from_memory<kRanked>(tv, ix, u, u.valid, st);
+        const int32_t ans = select_from_memory<kRanked, true>(tv, ix, u, u.valid, st);
         if (mine && i < q.n) q.out[i] = ans;
     }
     leave_statistics(ix, l_st, st);
@@ -154,11 +154,11 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
     for (int64_t i0 = (int64_t)blockIdx.x * kDirThreads; i0 < q.n; i0 += (int64_t)gridDim.x * kDirThreads) {
         const int64_t i = i0 + threadIdx.x;
         const Query u = load_query(ta, q, i);
-        int32_t ans = select_from_memory<false>(ta, ia, u, u.valid, st), tier = ans >= 0 ? 1 : 0;
+        int32_t ans = select_from_memory<false, false>(ta, ia, u, u.valid, st), tier = ans >= 0 ? 1 : 0;
         if (kTiers) {
             const bool next = u.valid && ans < 0;
             if (__ballot(next)) {
-                const int32_t row = select_from_memory<false>(tb, ib, u, next, st);
+                const int32_t row = select_from_memory<false, false>(tb, ib, u, next, st);
                 if (next && row >= 0) { ans = row; tier = 2; }
             }
         }

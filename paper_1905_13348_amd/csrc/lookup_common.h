@@ -141,6 +141,8 @@ __device__ __forceinline__ int32_t closest_by_scan(const TableView &tv, int32_t 
 // use_ranked() (api.hip) took 3.1 ms per 4M queries instead of 1.2.  What bounds it is scattered reads of L2 lines,
 // two levels, two columns, a row and two headers per query.  (Comparisons are combined with & and |: with && the
 // 16-byte reads are split into dwords behind branches, 0.62 ms instead of 0.55.)
+// kAhead false: with fewer registers, for kernels that have the search beside much else.
+template <bool kAhead>
 __device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const uint4 &rh, int32_t min_acc, uint32_t bound)
 {
     const int lane = threadIdx.x & 63, sub = lane & 3, round = lane >> 4;
@@ -247,17 +249,18 @@ __device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const u
         };
         // All that is left at once: two rounds of reads instead of up to four.  (1M queries most of which have no answer,
         // 300 entries of random accuracy and latency to a slice: 337 us block by block, 111 so, 297 with the scan engine.)
-        if (len - lo <= 256) {
-            const int32_t hit = try_block(lo, len);
-            if (lane == l) found = hit;
-            continue;
-        }
-        if (len - lo <= kRankAtOnce) {
+        if (kAhead && len - lo > 256 && len - lo <= kRankAtOnce) {
             const int64_t at0 = c + (lo + 4 * lane < len ? lo + 4 * lane : 0), at1 = c + (lo + 256 + 4 * lane < len ? lo + 256 + 4 * lane : 0);
             const uint4 a0 = *(const uint4 *)(tv.acc_r + at0), w0 = *(const uint4 *)(tv.tot_r + at0);
             const uint4 a1 = *(const uint4 *)(tv.acc_r + at1), w1 = *(const uint4 *)(tv.tot_r + at1);
             int32_t hit = first_fit(a0, w0, lo, len);
             hit = hit < 0 ? first_fit(a1, w1, lo + 256, len) : hit;
+            if (lane == l) found = hit;
+            continue;
+        }
+        if (len - lo <= kRankAtOnce) {
+            int32_t hit = -1;
+            for (int32_t first = lo; hit < 0 && first < len; first += 256) hit = try_block(first, first + 256 < len ? first + 256 : len);
             if (lane == l) found = hit;
             continue;
         }
