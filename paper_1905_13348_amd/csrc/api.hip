@@ -496,9 +496,13 @@ int create_index(infaas_sel *h)
 
 // Lists for the queries that the first tier of a state-aware pass over up to n queries leaves open.
 // side: also the lists of the first tier's suggestions beside them (complete Case I), the same size again.
+bool open_there(const infaas_sel *h, int64_t n, bool side)
+{
+    return h->d_open && h->open_queries >= n && (h->open_side || !side);
+}
 int ensure_open(infaas_sel *h, int64_t n, bool side)
 {
-    if (h->d_open && h->open_queries >= n && (h->open_side || !side)) return INFAAS_SEL_OK;
+    if (open_there(h, n, side)) return INFAAS_SEL_OK;
     n = std::max(n, h->open_queries);
     side = side || h->open_side;
     // growing: nothing enqueued earlier may still use the old lists
@@ -1120,8 +1124,15 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     // 19.0 / 34.7 and 21.7 / 23.3 / 26.8 / 30.7)
     const bool direct = N <= direct_limit(h) + direct_limit(h->inactive);
     // The lists are allocated for direct calls too: the limits follow the index, and the same call after a report
-    // may need them where nothing can be allocated (under capture, after an eager call to warm up).
-    int rc = ensure_open(h, std::min(N, kMaxTierPass), closest);
+    // may need them where nothing can be allocated (under capture, after an eager call to warm up).  A direct call
+    // that is itself captured does without.
+    const int64_t most = std::min(N, kMaxTierPass);
+    int rc = INFAAS_SEL_OK;
+    if (!open_there(h, most, closest)) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (direct && hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+        if (capture == hipStreamCaptureStatusNone) rc = ensure_open(h, most, closest);
+    }
     if (rc != INFAAS_SEL_OK) return rc;
     if (workers) {
         // bring the worker of every variant, then of every step of both indexes, up to date

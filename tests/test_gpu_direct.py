@@ -167,3 +167,42 @@ def test_suggestions_around_their_own_limit(oracle_lib):
         parked.append(sel.info()["lookup_parked"])
     assert parked[0] >= valid - 1 and 0 < parked[1] < valid // 2   # (straight from memory every query counts as parked)
     sel.destroy()
+
+
+def test_a_small_call_captured_without_warm_up(oracle_lib):
+    """A call that needs no lists may be captured before any other; its replays answer, and the eager call behind
+    them allocates the lists."""
+    import torch
+    rng = np.random.default_rng(4)
+    tb = _random_table(rng, 9, np.full(9, 40), 3)
+    state, load = rng.integers(0, 4, tb.V).astype(np.int32), rng.integers(0, 50_000, tb.V).astype(np.int32)
+    n = 3001
+    sets = [_random_queries(rng, 9, 3, n) for _ in range(3)]
+    want = [oracle_lib.select_case1(*table_args(tb), state, load, *q) for q in sets]
+    loaded = make_selector(tb, engine=0)          # (so that the kernel's code is on the device)
+    loaded.load_states(state, load)
+    gpu_case1(loaded, *sets[0])
+    sel = make_selector(tb, engine=0)
+    sel.load_states(state, load)
+    before = sel.info()["scratch_bytes"]
+    dq = [torch.zeros(n, dtype=torch.int32, device="cuda") for _ in range(4)]
+    out = [torch.zeros(n, dtype=torch.int32, device="cuda") for _ in range(3)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sel.select_tiered_closest(*dq, *out)
+    assert sel.info()["scratch_bytes"] == before
+    for rnd in range(4):
+        for d, x in zip(dq, sets[rnd % 3]):
+            d.copy_(torch.from_numpy(x))
+        for o in out:
+            o.fill_(-9)
+        graph.replay()
+        torch.cuda.synchronize()
+        for g, w in zip(out, want[rnd % 3]):
+            _assert_equal_everywhere(g.cpu().numpy(), w, f"replay {rnd}")
+    sel.select_tiered_closest(*dq, *out)
+    torch.cuda.synchronize()
+    assert sel.info()["scratch_bytes"] >= before + 32 * n
+    loaded.destroy()
+    sel.destroy()
