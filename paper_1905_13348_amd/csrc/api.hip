@@ -524,10 +524,10 @@ int ensure_open(infaas_sel *h, int64_t n, bool side)
 
 // Up to this many queries a selection is answered straight from global memory, one lane per query, rather than
 // through an LDS mirror of the index.  The mirror costs its fill (2-4 us, more with many slices) and pays with 4
-// ps per query against 40 (measured, us for 10,000 / 80,000 / 150,000 / 300,000 queries; config 2's table, whole
-// index in LDS: 4.5 / 6.5 / 8.7 / 14.7 direct, 7.7 / 8.0 / 8.1 / 8.2 mirrored; config 1's, 92% of it: 4.2 / 5.8 / 8.1 /
-// 14.3 and 8.8 / 9.0 / 9.7 / 9.4; config 3's, 7%: 4.3 / 7.0 / 9.8 / 17.4 and 16.0 / 17.2 / 17.6 / 20.7).  The less of the
-// index the mirror holds, the later it pays.
+// ps per query against 20 (measured, us for 10,000 / 90,000 queries; config 2's table, whole index in LDS: 4.6 / 5.8
+// direct, 7.7 / 8.0 mirrored; config 1's, 92% of it: 4.1 / 4.7 and 8.8 / 9.0; config 3's, 7%, for 10,000 / 200,000 / 400,000: 4.5 /
+// 7.9 / 12.1 and 16.0 / 18 / 22).  The less of the index the mirror holds, the later it pays.  (The line was drawn when a direct
+// query cost 40 ps; by these figures it could lie somewhat higher.)
 constexpr int64_t kDirectQueries = 100000;
 // With suggestions the same holds (us for 65,000 / 100,000 / 300,000 queries: 100 tasks of 200 variants 7.9 / 9.5 / 17.9 direct,
 // 13.4 / 13.3 / 14.9 mirrored; config 3's table 9.4 / 11.2 / 22.5 and 27.6 / 28.6 / 33.4), except where the mirror holds nearly the
@@ -547,12 +547,20 @@ int64_t direct_limit(const infaas_sel *h, bool closest = false)
     return pool <= room ? kDirectQueries : kDirectQueries * pool / room;
 }
 
+// Whether the bodies of the index fit a compute unit's L1 (32 KB) with room to spare, so that a lane's own bisection stays there: 90,001
+// queries on 32 slices (5 KB) 6.2 us so, 6.6 with four lanes to a body; on 800 slices (237 KB) 6.3 and 5.3.
+bool in_l1(const infaas_sel *h)
+{
+    const volatile uint32_t *now = h->host_stats;
+    return h->ix.num_groups == 1 && (now ? now[4] : h->ix_stats[kCtlPool]) <= 24 * 1024;
+}
+
 // One pass of the index engine over n <= 2^28 queries.
 int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
     if (q.pass <= 1 && q.n <= direct_limit(h, q.pass == 1)) {
-        const hipError_t e = q.pass == 0 ? launch_direct_select(h->tv, h->ix, q, false, h->num_cus, st, t.ev())
+        const hipError_t e = q.pass == 0 ? launch_direct_select(h->tv, h->ix, q, false, in_l1(h), h->num_cus, st, t.ev())
                                          : launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, h->num_cus, st, t.ev());
         return HIP_OK(e) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
     }
@@ -656,7 +664,7 @@ bool use_ranked(const infaas_sel *h)
 int ranked_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_SCAN_LDS, st);
-    if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, true, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
+    if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, true, false, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
     return INFAAS_SEL_OK;
 }
 
@@ -1430,7 +1438,7 @@ int infaas_sel_select_noalloc(infaas_sel_t *h, int64_t N, const int32_t *d_task,
     q.pass = 0;
     // no event pair even when timing is on: taking one may create it
     if (q.n <= direct_limit(h)) {
-        if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
+        if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, in_l1(h), h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
     } else if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->static_park, h->index_lds_bytes, h->num_cus,
                                     (hipStream_t)hip_stream, nullptr)))
         return INFAAS_SEL_ERR_HIP;

@@ -30,39 +30,51 @@ __device__ __forceinline__ Query load_query(const TableView &tv, const QueryView
 // in their bodies go through their entries in rank order at once; otherwise only with what the bodies leave
 // open.  Counts in st what became of the queries, as the lookup kernel does; no query is decided by an
 // LDS copy here, so all count as parked.
-template <bool kRanked, bool kAhead>
+template <bool kRanked, bool kAhead, bool kByFour = true>
 __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want,
                                                       uint32_t (&st)[kLookupStats])
 {
     auto count = [&](int what, bool yes) { st[what] += (uint32_t)__builtin_popcountll(__ballot(yes)); };
-    const uint32_t max_k = ix.ctrl[kCtlMaxK0];
-    const int nit = 32 - __builtin_clz(max_k | 1u);    // <= 5
-    const GlobalMem gmem{ix.pool};
+    int nit = 0;
+    if (!kByFour) nit = 32 - __builtin_clz(ix.ctrl[kCtlMaxK0] | 1u);    // <= 5
     const uint32_t s = want ? u.s : (uint32_t)tv.S;
-    const uint4 h = ix.hdr[s], rh = tv.rank_hdr[s];
+    const uint4 h = ix.hdr[s];
+    uint4 rh{};
+    if (kRanked) rh = tv.rank_hdr[s];
     int32_t ans = -1;
     const bool body = want && !(h.y & kHdrPark) && !(kRanked && (h.y & kHdrTrunc));
     if (__ballot(body)) {
         const uint32_t keys0 = (h.y >> kHdrK0Shift) & 0x3Fu, keys1 = (h.y >> kHdrK1Shift) & 0x3Fu;
-        const uint32_t dd[1] = {acc_threshold(u.min_acc, tv.acc_base - 1)}, lim[1] = {(uint32_t)u.slo};
-        const uint32_t bd[1] = {body ? h.x : 0u}, ks[1] = {body ? keys0 : 2u};
-        uint32_t m[1];
-        search_bodies<1>(gmem, nit, bd, ks, dd, lim, m);
-        const bool hit0 = body && m[0] != 0u;
-        uint32_t at = hit0 ? h.z + (uint32_t)__builtin_ctz(m[0]) : 0u;   // (entry 0 of step_row is -1)
+        const uint32_t dd = acc_threshold(u.min_acc, tv.acc_base - 1), lim = (uint32_t)u.slo;
+        uint32_t m = 0u;
+        auto search = [&](bool on, uint32_t at, uint32_t re) __attribute__((always_inline)) {
+            if constexpr (kByFour) {
+                const uint32_t a = on ? at : 0u, r = on ? re : 0u;
+                if ((__ballot(on) >> 32) == 0ull) search_bodies_by_four<1>(ix.pool, a, r, dd, lim, m);
+                else search_bodies_by_four<4>(ix.pool, a, r, dd, lim, m);
+            } else {
+                const uint32_t a1[1] = {on ? at : 0u}, r1[1] = {on ? re : 2u}, d1[1] = {dd}, l1[1] = {lim};
+                uint32_t m1[1];
+                search_bodies<1>(GlobalMem{ix.pool}, nit, a1, r1, d1, l1, m1);
+                m = on ? m1[0] : 0u;
+            }
+        };
+        search(body, h.x, keys0);
+        const bool hit0 = m != 0u;
+        uint32_t at = hit0 ? h.z + (uint32_t)__builtin_ctz(m) : 0u;   // (entry 0 of step_row is -1)
         count(2, hit0);
         const bool more = body && !hit0 && keys1 != 0u;
         if (__ballot(more)) {
-            const uint32_t bd1[1] = {more ? h.x + body_bytes(keys0) : 0u}, ks1[1] = {more ? keys1 : 2u};
-            search_bodies<1>(gmem, nit, bd1, ks1, dd, lim, m);
-            const bool hit1 = more && m[0] != 0u;
-            if (hit1) at = h.z + kBodySteps + (uint32_t)__builtin_ctz(m[0]);
+            search(more, h.x + body_bytes(keys0), keys1);
+            const bool hit1 = m != 0u;
+            if (hit1) at = h.z + kBodySteps + (uint32_t)__builtin_ctz(m);
             count(1, hit1);
         }
         ans = ix.step_row[at];
     }
     const bool scan = want && ans < 0 && (h.y & kHdrTrunc);
     if (__ballot(scan)) {
+        if (!kRanked) rh = tv.rank_hdr[s];
         const int32_t row = ranked_first_fit<kAhead>(tv, scan ? rh : make_uint4(0u, 0u, 0u, 0u), u.min_acc, (uint32_t)u.slo);
         if (scan) ans = row;
         count(3, scan);
@@ -115,13 +127,12 @@ __device__ __forceinline__ void leave_statistics(const IndexView &ix, uint32_t *
     if (blockIdx.x == 0 && threadIdx.x == 0) ix.stats[-1] = gridDim.x;
 }
 
-// Bound by the rate of scattered reads: 15 per query through a body (its header, that of the slice in rank order, ten
-// probes, two sets, row), each lane another line.  The 80 registers allow 24 wavefronts per compute unit, which saturate
-// that: 16 to 32 of them differed by 0-25% on batches of a million, more of them being slower.
-template <bool kRanked>
-__global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, IndexView ix, QueryView q, int32_t per_wave)
+// Bound by the rate of scattered reads (header, three to five lines of the body, two sets, row: 20 ps per query, 40 with the lane's
+// own bisection, which kByFour false keeps for bodies that L1 holds).  The lanes of a wavefront take `per` queries.
+template <bool kRanked, bool kByFour>
+__global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, IndexView ix, QueryView q, int32_t per)
 {
-    const int32_t per = kRanked ? per_wave : 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, step = per * (kDirThreads / 64);
+    const int32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, step = per * (kDirThreads / 64);
     __shared__ uint32_t l_st[kLookupStats];
     publish_index_stats(tv);
     if (threadIdx.x < kLookupStats) l_st[threadIdx.x] = 0u;
@@ -129,9 +140,9 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, Ind
     uint32_t st[kLookupStats] = {0u, 0u, 0u, 0u, 0u};
     for (int64_t i0 = (int64_t)blockIdx.x * step; i0 < q.n; i0 += (int64_t)gridDim.x * step) {
         const int64_t i = i0 + wave * per + lane;
-        const bool mine = !kRanked || lane < per;
+        const bool mine = lane < per;
         const Query u = load_query(tv, q, i, mine);
-        const int32_t ans = select_from_memory<kRanked, true>(tv, ix, u, u.valid, st);
+        const int32_t ans = select_from_memory<kRanked, true, kByFour>(tv, ix, u, u.valid, st);
         if (mine && i < q.n) q.out[i] = ans;
     }
     leave_statistics(ix, l_st, st);
@@ -143,17 +154,19 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, Ind
 // At 1001 to 100,001 queries bound by its launch and the chain of dependent reads, like the two passes of the
 // lookup kernel that it replaces, but once and without the two LDS mirrors.
 template <bool kTiers, bool kSuggest, bool kWorker>
-__global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, IndexView ia, TableView tb, IndexView ib, QueryView q)
+__global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, IndexView ia, TableView tb, IndexView ib, QueryView q, int32_t per)
 {
+    const int32_t lane = threadIdx.x & 63, step = per * (kDirThreads / 64);
     __shared__ uint32_t l_st[kLookupStats];
     publish_index_stats(ta);
     if (kTiers) publish_index_stats(tb);
     if (threadIdx.x < kLookupStats) l_st[threadIdx.x] = 0u;
     __syncthreads();
     uint32_t st[kLookupStats] = {0u, 0u, 0u, 0u, 0u};
-    for (int64_t i0 = (int64_t)blockIdx.x * kDirThreads; i0 < q.n; i0 += (int64_t)gridDim.x * kDirThreads) {
-        const int64_t i = i0 + threadIdx.x;
-        const Query u = load_query(ta, q, i);
+    for (int64_t i0 = (int64_t)blockIdx.x * step; i0 < q.n; i0 += (int64_t)gridDim.x * step) {
+        const int64_t i = i0 + (int32_t)(threadIdx.x >> 6) * per + lane;
+        const bool mine = lane < per;
+        const Query u = load_query(ta, q, i, mine);
         int32_t ans = select_from_memory<false, false>(ta, ia, u, u.valid, st), tier = ans >= 0 ? 1 : 0;
         if (kTiers) {
             const bool next = u.valid && ans < 0;
@@ -176,7 +189,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
                 if (none) closest = sug;
             }
         }
-        if (i < q.n) {
+        if (mine && i < q.n) {
             q.out[i] = ans;
             if (kTiers) q.tier[i] = tier;
             if (kSuggest) q.closest[i] = closest;
@@ -188,27 +201,31 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
 
 }  // namespace
 
-hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int num_cus,
+hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, bool in_l1, int num_cus,
                                 hipStream_t st, const LaunchEvents *ev)
 {
-    // In rank order a wavefront finishes its hard queries one after the other, so a batch too small to give every
-    // SIMD two full wavefronts is spread over as many with fewer queries each.  (us for 1001 / 10,001 / 30,001 queries, 64 to a
+    // A batch too small to give every SIMD two full wavefronts is spread over as many with fewer queries each, down to the
+    // 16 that one round of search_bodies_by_four serves (two tiers, 1001 queries 8.5 -> 6.6 us, with workers 8.6 -> 6.7).
+    // In rank order, where a wavefront finishes its hard queries one after the other, down to one.  (us for 1001 / 10,001 / 30,001 queries, 64 to a
     // wavefront and so: 2000 entries of random accuracy and latency to a slice, most queries without an answer, 75 / 75 / 76 and
     // 6.1 / 14 / 23, with the scan engine 37 / 63 / 89; every entry a step, nothing hard about it, 6.0 / 6.1 / 6.1 and 6.2 / 6.2 /
     // 6.2, where four wavefronts per SIMD took 6.1 / 6.6 / 8.1.)
     int32_t per = 64;
-    while (ranked && per > 1 && ((int64_t)q.n + per / 2 - 1) / (per / 2) <= (int64_t)num_cus * 8) per /= 2;
+    while (per > (ranked ? 1 : 16) && ((int64_t)q.n + per / 2 - 1) / (per / 2) <= (int64_t)num_cus * 8) per /= 2;
     const int64_t step = per * (kDirThreads / 64), want = ((int64_t)q.n + step - 1) / step, most = index_stat_blocks(num_cus);
-    return launch_kernel(ev, ranked ? k_direct_select<true> : k_direct_select<false>, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, tv, ix, q, per);
+    auto kernel = ranked ? k_direct_select<true, true> : in_l1 ? k_direct_select<false, false> : k_direct_select<false, true>;
+    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, tv, ix, q, per);
 }
 
 hipError_t launch_direct_modes(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, const QueryView &q,
                                bool tiers, int num_cus, hipStream_t st, const LaunchEvents *ev)
 {
-    const int64_t want = ((int64_t)q.n + kDirThreads - 1) / kDirThreads, most = index_stat_blocks(num_cus);
+    int32_t per = 64;   // (as above)
+    while (per > 16 && ((int64_t)q.n + per / 2 - 1) / (per / 2) <= (int64_t)num_cus * 8) per /= 2;
+    const int64_t step = per * (kDirThreads / 64), want = ((int64_t)q.n + step - 1) / step, most = index_stat_blocks(num_cus);
     auto kernel = !tiers ? k_direct_modes<false, true, false> : q.worker ? (q.closest ? k_direct_modes<true, true, true> : k_direct_modes<true, false, true>)
                                                               : (q.closest ? k_direct_modes<true, true, false> : k_direct_modes<true, false, false>);
-    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, ta, ia, tb, ib, q);
+    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, ta, ia, tb, ib, q, per);
 }
 
 }  // namespace infaas

@@ -276,8 +276,9 @@ hipError_t launch_index_select(const TableView &tv, const IndexView &ix, const Q
                                int32_t *park_mem, uint32_t lds_bytes, int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
 int index_select_blocks(int num_cus);
 // One lane per query, everything read from global memory (L2): for calls too small to pay for the LDS
-// mirror, and (ranked) for tables most of whose slices the index cannot hold.  Selection only (q.pass 0).
-hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int num_cus,
+// mirror, and (ranked) for tables most of whose slices the index cannot hold.  in_l1: the bodies fit a compute unit's
+// L1.  Selection only (q.pass 0).
+hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, bool in_l1, int num_cus,
                                 hipStream_t st, const LaunchEvents *ev = nullptr);
 // The same for the other modes: selection with suggestion on one table (tiers false; tb, ib unused), or both tiers with
 // workers (q.worker, q.row_worker: of the Active tier, the Inactive tier's V entries behind them) and suggestions (q.closest).

@@ -206,3 +206,23 @@ def test_a_small_call_captured_without_warm_up(oracle_lib):
     assert sel.info()["scratch_bytes"] >= before + 32 * n
     loaded.destroy()
     sel.destroy()
+
+
+@pytest.mark.parametrize("steps", [1, 6, 7, 8, 9, 15, 16, 17, 23, 24, 25, 30, 31, 32, 38, 39, 61, 62, 63])
+def test_bodies_of_every_length(oracle_lib, steps):
+    """Four lanes read a body's keys, eight each: staircases that end in front of, at and behind every lane's share, in the
+    first body and in the second, and bounds that meet each key exactly, miss it by one, meet all or none."""
+    tb = _staircase_table(3, steps)
+    rows = np.arange(tb.V)
+    acc = np.concatenate([tb.acc_bp[rows] + d for d in (-1, 0, 1)] + [np.full(tb.V, x) for x in (-2**31, 2**31 - 1)])
+    tot = (tb.lat_us[:, 0] + tb.queue_us).astype(np.int64)
+    slo = np.concatenate([tot + d for d in (-1, 0, 1)] + [np.full(tb.V, x) for x in (0, 2**31 - 1)])
+    a, s = np.repeat(acc, 5), np.concatenate([np.roll(slo, k) for k in (0, 1, tb.V, 2 * tb.V, 3 * tb.V)])
+    n = a.size
+    q = tuple(np.clip(x, -2**31, 2**31 - 1).astype(np.int32) for x in
+              (np.arange(n) % 3, s, a, np.arange(n) // 3 % tb.B))
+    want = oracle_lib.select(*table_args(tb), *q)
+    sel = make_selector(tb, engine=2)
+    _assert_equal_everywhere(gpu_select(sel, *q), want, f"{steps} steps")
+    assert (want >= 0).any() and (want < 0).any()
+    sel.destroy()
