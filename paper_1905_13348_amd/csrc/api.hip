@@ -1493,7 +1493,10 @@ int infaas_sel_load_scaling(infaas_sel_t *h, const int32_t *arch_id, const int32
         std::vector<uint32_t> &blocks = blocks_of[down];
         std::vector<ScaleCand> &cand = cand_of[down];
         blocks.assign((size_t)std::max<int64_t>((int64_t)B * V, 1) * kScaleBlockWords, 0u);
-        if (V == 0) blocks[0] = 1u;   // the block an invalid request reads: throughput 1, no candidates (it is never used)
+        // the kernel divides by every throughput and drops what it has no use for: places without a candidate, and the block
+        // that an invalid request reads when there are no variants, hold a throughput of 1
+        for (size_t w = 0; w < blocks.size(); w += kScaleBlockWords)
+            for (int j = -1; j < kScaleInBlock; ++j) blocks[w + (j < 0 ? 0 : 8 + 4 * (size_t)j)] = 1u;
         cand_cost.clear();            // hardware cost of cand[k]
         for (int32_t b = 0; b < B; ++b)
             for (int32_t a = 0; a < A; ++a) {

@@ -27,30 +27,46 @@ namespace infaas {
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kChunk = 4;   // candidates of a list read together
-typedef unsigned __int128 u128;
+constexpr int kThreads = 64;   // one wavefront
+constexpr int kChunk = 2;   // candidates of a list read together
 
-// 1 / per for 1 <= per < 2^38, within 2^-40 relative: the hardware's estimate (v_rcp_f64, good to 2^-20 and better) and
-// one Newton step, a third of the instructions of the division.
-__device__ __forceinline__ double inverse(uint64_t per)
+// An exact cost of up to 94 bits, and below its last word who it belongs to: 0 for the running variant, the caller row + 1 for a
+// switch.  So the lower of two is the lower cost, and at a tie the running variant, else the lower row.
+struct Offer {
+    uint64_t high;
+    uint32_t low, who;
+};
+__device__ __forceinline__ bool operator<(const Offer &a, const Offer &b)
+{
+    const uint64_t x = ((uint64_t)a.low << 32) | a.who, y = ((uint64_t)b.low << 32) | b.who;
+    return (a.high < b.high) | ((a.high == b.high) & (x < y));
+}
+// n instances at `unit` each (below 2^62)
+__device__ __forceinline__ Offer offer_of(uint64_t unit, uint32_t n, uint32_t who)
+{
+    const uint64_t lo = (uint64_t)(uint32_t)unit * n;
+    return Offer{(unit >> 32) * n + (lo >> 32), (uint32_t)lo, who};
+}
+
+// ceil(need / per) for need < 2^31 and 1 <= per < 2^31: the hardware's estimate of 1 / per (v_rcp_f64, good to 2^-20 and
+// better) after one Newton step is within 2^-39 of it, relatively, so the quotient's integer part is the exact floor or one
+// beside it, and the remainder (which fits 32 bits in all three cases) tells which.
+__device__ __forceinline__ uint32_t ceil_div(uint32_t need, uint32_t per)
 {
     const double d = (double)per, r = __builtin_amdgcn_rcp(d);
-    return __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+    const double inv = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+    const uint32_t q = (uint32_t)((double)need * inv);
+    const int32_t rest = (int32_t)(need - q * per);
+    return q + (uint32_t)(rest > 0) + (uint32_t)(rest > (int32_t)per);
 }
 
-// ceil(need / per) for need < 2^38 and 1 <= per < 2^38 with a quotient below 2^32, given
-// per_inv = 1 / per within 2^-40: need * per_inv is within 2^-39 of the quotient relative to it, less than 2^-7
-// of a unit, so its integer part is the exact floor or one beside it; exact integer tests settle which.
-__device__ __forceinline__ uint32_t ceil_div(uint64_t need, uint64_t per, double per_inv)
-{
-    uint32_t q = (uint32_t)((double)need * per_inv);
-    uint64_t p = (uint64_t)q * per;
-    if (p > need) { q -= 1u; p -= per; }
-    else if (p + per <= need) { q += 1u; p += per; }
-    return q + (p < need ? 1u : 0u);
-}
+// The loads in front of this are issued together and arrive together: without it the compiler moves each of a block's words
+// behind the branch that first needs it, and a request waits for memory several times.
+__device__ __forceinline__ void arrived(uint4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
 
+// Bound by the requests' lines: 4M of them on 102 MB of blocks, read by a kernel that does nothing else, take 86 us together with
+// the fields and results; the continuations of long lists are 0.2 lines per request more.  Candidates are computed for every lane and masked, without branches; 32-bit quotients (the need is rounded up
+// to whole queries per second once: ceil(ceil(x / 100) / q) = ceil(x / (100 q))) and 96-bit costs.
 template <bool kDown>
 __global__ __launch_bounds__(kThreads) void k_scale(ScaleView sv, int64_t R, const int32_t *__restrict__ r_variant,
                                                     const int32_t *__restrict__ r_instances,
@@ -63,92 +79,102 @@ __global__ __launch_bounds__(kThreads) void k_scale(ScaleView sv, int64_t R, con
     for (int64_t r0 = (int64_t)blockIdx.x * kThreads; r0 < R; r0 += (int64_t)gridDim.x * kThreads) {
         const int64_t r = r0 + threadIdx.x;
         const bool in = r < R;
-        const int32_t cur = in ? __builtin_nontemporal_load(r_variant + r) : -1;
-        const int32_t n_cur = in ? __builtin_nontemporal_load(r_instances + r) : 0;
-        const int32_t load = in ? __builtin_nontemporal_load(r_load_qps + r) : 0;
-        const int32_t slo = in ? __builtin_nontemporal_load(r_slo_us + r) : 0;
-        const int32_t b = in ? __builtin_nontemporal_load(r_batch_idx + r) : 0;
+        const int64_t at = in ? r : r0;
+        const int32_t cur = __builtin_nontemporal_load(r_variant + at);
+        const int32_t b = __builtin_nontemporal_load(r_batch_idx + at);
+        const int32_t n_cur = __builtin_nontemporal_load(r_instances + at);
+        const int32_t load = __builtin_nontemporal_load(r_load_qps + at);
+        const int32_t slo = __builtin_nontemporal_load(r_slo_us + at);
         const bool valid = (uint32_t)cur < (uint32_t)sv.V && (uint32_t)b < (uint32_t)sv.B &&
                            (uint32_t)n_cur <= 1000000u && (uint32_t)load <= 1000000000u;
         // the request's block: one cache line, all of it requested at once
         const uint4 *blk = (const uint4 *)((kDown ? sv.blocks_down : sv.blocks) + ((int64_t)(valid ? b : 0) * sv.V + (valid ? cur : 0)) * kScaleBlockWords);
-        const uint4 head = blk[0];      // {throughput, hardware cost, cost of one instance}
-        const uint4 more = blk[1];      // {latency, candidates, their list, row of the fifth}
+        uint4 head = blk[0];      // {throughput, hardware cost, cost of one instance}
+        uint4 more = blk[1];      // {latency, candidates, their list, row of the fifth}
         uint4 slot[kScaleInBlock];
 #pragma unroll
         for (int j = 0; j < kScaleInBlock; ++j) slot[j] = blk[2 + j];   // {throughput, latency, cost of one instance}
-        const uint4 rows4 = blk[7];
-        const int32_t slot_row[kScaleInBlock] = {(int32_t)rows4.x, (int32_t)rows4.y, (int32_t)rows4.z, (int32_t)rows4.w,
-                                                 (int32_t)more.w};
+        uint4 rows4 = blk[7];
+        arrived(head);
+        arrived(more);
+#pragma unroll
+        for (int j = 0; j < kScaleInBlock; ++j) arrived(slot[j]);
+        arrived(rows4);
+        const uint32_t slot_row[kScaleInBlock] = {rows4.x, rows4.y, rows4.z, rows4.w, more.w};
         const uint32_t own_qps = head.x;
         const uint64_t own_unit = ((uint64_t)head.w << 32) | head.z;
-        const int32_t own_lat = (int32_t)more.x;
-        const int32_t m = (int32_t)more.y;
-        const uint64_t need = (uint64_t)(uint32_t)load * (uint32_t)sv.slack_pct;   // hundredths of a query per second
-        int32_t action = 0, variant = -1, instances = 0;
+        // whole queries per second the instances have to carry (for valid requests at most 2 * 10^9)
+        const uint32_t need = (uint32_t)(((uint64_t)(uint32_t)load * (uint32_t)sv.slack_pct + 99u) / 100u);
         // everything is compared with the credit for unloading the running instances added, so
         // that no difference can become negative
         const uint64_t saved = (uint64_t)head.y * (uint32_t)n_cur * 1000000u;   // < 2^61
-        bool have = false;
-        u128 best = 0;
-        int32_t best_row = -1;    // row of the best switch, -1: the running variant is best
+        const bool scaling = valid && (kDown || (uint64_t)own_qps * (uint32_t)n_cur < need);
+        const int32_t m = scaling ? (int32_t)more.y : 0;
+        Offer best{~0ull, 0u, 0u};   // (no cost comes near)
         uint32_t best_n = 0;
-        // a switch to a candidate (which has a higher throughput, resp. a lower hardware cost, than cur
-        // by construction); `floor_n`: the fewest instances a switch loads
-        auto offer = [&](uint32_t qps, int32_t lat, uint64_t unit, int32_t row, uint32_t floor_n) {
-            if (lat > slo) return;
-            const uint64_t per = 100u * (uint64_t)qps;
-            uint32_t inst = ceil_div(need, per, inverse(per));
-            inst = inst < floor_n ? floor_n : inst;
-            const u128 cost = (u128)unit * inst;
-            // the running variant keeps a tie; among switches of equal cost the lower row wins
-            const bool better = !have || cost < best || (cost == best && best_row >= 0 && row < best_row);
-            if (better) { best = cost; best_row = row; best_n = inst; have = true; }
-        };
-        auto offer_all = [&](uint32_t floor_n) {
-#pragma unroll
-            for (int j = 0; j < kScaleInBlock; ++j)
-                if (j < m) offer(slot[j].x, (int32_t)slot[j].y, ((uint64_t)slot[j].w << 32) | slot[j].z, slot_row[j], floor_n);
-            if (m > kScaleInBlock) {   // the rest of the prefix from the shared list, four at a time
-                const ScaleCand *list = (kDown ? sv.cand_down : sv.cand) + more.z;
-                for (int32_t i0 = kScaleInBlock; i0 < m; i0 += kChunk) {
-                    ScaleCand c[kChunk];
-#pragma unroll
-                    for (int j = 0; j < kChunk; ++j) c[j] = list[i0 + j < m ? i0 + j : m - 1];
-#pragma unroll
-                    for (int j = 0; j < kChunk; ++j)
-                        if (i0 + j < m) offer(c[j].qps, c[j].lat, c[j].unit, c[j].row, floor_n);
-                }
-            }
-        };
-        if constexpr (!kDown) {
-            const bool scaling = valid && (uint64_t)own_qps * (uint32_t)n_cur * 100u < need;
-            if (scaling) {
-                if (own_lat <= slo) {   // replicate
-                    const uint64_t per = 100u * (uint64_t)own_qps;
-                    best_n = ceil_div(need, per, inverse(per)) - (uint32_t)n_cur;
-                    best = (u128)own_unit * best_n + saved;
-                    have = true;
-                }
-                offer_all(0u);          // upgrade
-                action = !have ? 3 : (best_row < 0 ? 1 : 2);
-                if (have) {
-                    variant = best_row < 0 ? cur : best_row;
-                    instances = (int32_t)best_n;
-                }
-            }
-        } else if (valid) {
+        bool remove = false;
+        if constexpr (!kDown) {   // replicate
+            const uint32_t n = ceil_div(need, own_qps) - (uint32_t)n_cur;
+            Offer o = offer_of(own_unit, n, 0u);
+            const uint64_t low = (uint64_t)o.low + (uint32_t)saved;
+            o.high += (saved >> 32) + (low >> 32);
+            o.low = (uint32_t)low;
+            if ((int32_t)more.x <= slo) { best = o; best_n = n; }
+        } else {
             // keeping everything costs `saved` on this scale; removing one instance one hardware cost
             // less, allowed when at least one instance stays and the rest carries the load
-            best = saved;
-            have = true;
-            const bool removable = n_cur >= 2 && (uint64_t)own_qps * (uint32_t)(n_cur - 1) * 100u >= need;
-            const bool remove = removable && head.y > 0u;   // (at no hardware cost there is nothing to gain)
-            if (remove) best = saved - (uint64_t)head.y * 1000000u;
-            offer_all(1u);              // downgrade: at least one instance serves
-            if (best_row >= 0) { action = 2; variant = best_row; instances = (int32_t)best_n; }
-            else if (remove) { action = 1; variant = cur; instances = 1; }
+            remove = n_cur >= 2 && (uint64_t)own_qps * (uint32_t)(n_cur - 1) >= need && head.y > 0u;   // (at no hardware cost there is nothing to gain)
+            const uint64_t cost = remove ? saved - (uint64_t)head.y * 1000000u : saved;
+            best = Offer{cost >> 32, (uint32_t)cost, 0u};
         }
+        // a switch to a candidate (which has a higher throughput, resp. a lower hardware cost, than cur
+        // by construction); at least one instance serves after a downgrade
+        auto offer = [&](bool on, uint32_t qps, int32_t lat, uint64_t unit, uint32_t row) __attribute__((always_inline)) {
+            uint32_t n = ceil_div(need, qps);
+            if (kDown) n = n < 1u ? 1u : n;
+            const Offer o = offer_of(unit, n, row + 1u);
+            const bool better = on & (lat <= slo) & (o < best);
+            if (better) { best = o; best_n = n; }
+        };
+        // the rest of a longer prefix, from the shared list, four at a time; requested before the block's own are looked at
+        const ScaleCand *all = kDown ? sv.cand_down : sv.cand;
+        uint4 cand[kChunk];
+        uint32_t cand_row[kChunk];
+        auto request = [&](int32_t i0) __attribute__((always_inline)) {   // (lanes with nothing left read the first of all)
+#pragma unroll
+            for (int j = 0; j < kChunk; ++j) {
+                const ScaleCand *c = all + (i0 + j < m ? (int64_t)more.z + i0 + j : 0);
+                cand[j] = *(const uint4 *)c;
+                cand_row[j] = (uint32_t)c->row;
+            }
+        };
+        int32_t i0 = kScaleInBlock;
+        bool longer = __ballot(m > i0) != 0ull;
+        if (longer) request(i0);
+#pragma unroll
+        for (int j = 0; j < kScaleInBlock; ++j)
+            offer(j < m, slot[j].x, (int32_t)slot[j].y, ((uint64_t)slot[j].w << 32) | slot[j].z, slot_row[j]);
+        while (longer) {
+#pragma unroll
+            for (int j = 0; j < kChunk; ++j) {
+                arrived(cand[j]);
+                offer(i0 + j < m, cand[j].x, (int32_t)cand[j].y, ((uint64_t)cand[j].w << 32) | cand[j].z, cand_row[j]);
+            }
+            i0 += kChunk;
+            longer = __ballot(m > i0) != 0ull;
+            if (longer) request(i0);
+        }
+        int32_t action = 0, variant = -1, instances = 0;
+        if (kDown ? best.who != 0u : best.high != ~0ull) {
+            action = best.who ? 2 : 1;
+            variant = best.who ? (int32_t)best.who - 1 : cur;
+            instances = (int32_t)best_n;
+        } else if (kDown ? remove : true) {
+            action = kDown ? 1 : 3;
+            variant = kDown ? cur : -1;
+            instances = kDown ? 1 : 0;
+        }
+        if (!scaling) { action = 0; variant = -1; instances = 0; }
         if (in) {
             __builtin_nontemporal_store(action, out_action + r);
             __builtin_nontemporal_store(variant, out_variant + r);
@@ -167,9 +193,11 @@ hipError_t launch_scale(const ScaleView &sv, bool down, int64_t R, const int32_t
     if (R <= 0) return hipSuccess;
     const int64_t want = (R + kThreads - 1) / kThreads;
     // one request per lane (to 2^26 of them): the loop over a smaller grid makes every lane wait for its request's line
-    // before it asks for the next one's fields (4M requests: 129.5 us with 32 workgroups per compute unit, 125.5 so, the cheaper reciprocal
-    // included; 700,001 requests 24.5 and 23.9)
-    const int64_t blocks = want < (int64_t)num_cus * 1024 ? want : (int64_t)num_cus * 1024;
+    // before it asks for the next one's fields (4M requests 3% longer with 32 workgroups per compute unit).  One wavefront to a
+    // workgroup, so that none waits for its neighbours to leave, and lists two candidates at a time: us for 4M / 700,001 requests
+    // 99.8 / 21.1, with four at a time and four wavefronts 101.0 / 22.2; with a compiler that moved every word's load behind its
+    // first use, and branches, 128-bit quotients and costs 125.8 / 23.9.
+    const int64_t blocks = want < (int64_t)num_cus * 4096 ? want : (int64_t)num_cus * 4096;
     if (down)
         return launch_kernel(ev, k_scale<true>, dim3((unsigned)blocks), dim3(kThreads), 0, st, sv, R, r_variant,
                              r_instances, r_load_qps, r_slo_us, r_batch_idx, out_action, out_variant, out_instances);

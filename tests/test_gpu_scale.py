@@ -227,3 +227,32 @@ def test_scale_errors():
     with pytest.raises(lib.InfaasSelError):
         sel.scale(z, z, z, z, z, z.clone(), z.clone(), z.clone())
     sel.destroy()
+
+
+@pytest.mark.parametrize("per_arch", [1, 2, 5, 6, 7, 10, 11, 14, 15])
+def test_scale_lists_of_every_length_and_exact_quotients(oracle_lib, per_arch):
+    """Candidate lists that end at and beside the block's five places and the chunks of four behind them (nothing in an
+    architecture beats anything else: the dearer, the faster and the slower to answer), and loads that a whole number of instances carries
+    exactly, or but for one query per second, up to quotients of 10^9."""
+    rng = np.random.default_rng([47, per_arch])
+    archs, B = 40, 2
+    V = archs * per_arch
+    nth = np.arange(V) % per_arch
+    tb = workloads.VariantTable(num_tasks=1, batch_sizes=np.arange(1, B + 1, dtype=np.int32), task_id=np.zeros(V, np.int32),
+                                acc_bp=np.full(V, 8000, np.int32), lat_us=(100 + 10 * nth[:, None] + np.arange(B)).astype(np.int32),
+                                cost=np.ones((V, B), np.int32), queue_us=np.zeros(V, np.int32))
+    first = rng.integers(1, 50, archs)[np.arange(V) // per_arch]
+    prof = ((np.arange(V) // per_arch).astype(np.int32), (first + 3 * nth).astype(np.int32), (5 + nth).astype(np.int32),
+            rng.integers(0, 100_000, V).astype(np.int32))
+    R = 30_001
+    variant = rng.integers(0, V, R)
+    times = np.where(rng.random(R) < 0.1, rng.integers(1, 10**7, R), rng.integers(1, 40, R))
+    load = np.clip(prof[1][variant].astype(np.int64) * times + rng.integers(-1, 2, R), 0, 10**9)
+    req = tuple(np.asarray(x, dtype=np.int32) for x in
+                (variant, rng.integers(0, 30, R), load, 100 + rng.integers(0, 10 * per_arch + 10, R), rng.integers(0, B, R)))
+    sel = make_selector(tb, engine=0)
+    for lam, slack in ((0, 100), (3, 105), (50, 199)):
+        sel.load_scaling(*prof, lam, slack)
+        _check(oracle_lib, sel, tb, prof, lam, slack, req, f"{per_arch} to an architecture")
+        _check(oracle_lib, sel, tb, prof, lam, slack, req, f"{per_arch} to an architecture", down=True)
+    sel.destroy()
