@@ -122,7 +122,8 @@ struct infaas_sel {
     // worker selection (on the handle the caller holds; the step_worker arrays hang off both indexes)
     WorkerView wv{};
     std::vector<void *> worker_mem;              // the device arrays wv points into
-    bool workers_loaded = false, workers_dirty = false;
+    bool workers_loaded = false, workers_dirty = false;   // (dirty: older than the latest report)
+    bool rows_stale = false;                              // the Inactive half of wv.row_worker is older than the workers
     bool instance_states = false;                // the variants' states follow from their instances' (wv.inst_state)
     bool steps_stale = false;                    // this table's ix.step_worker is older than its index or the workers
 
@@ -220,7 +221,7 @@ void infaas_sel::drop_inactive()
     for (void *p : worker_mem) (void)hipFree(p);
     worker_mem.clear();
     wv = WorkerView{};
-    workers_loaded = workers_dirty = instance_states = false;
+    workers_loaded = workers_dirty = rows_stale = instance_states = false;
     (void)hipFree(ix.step_worker); (void)hipFree(ix.hot_worker);
     ix.step_worker = nullptr;
     ix.hot_worker = nullptr;
@@ -1145,18 +1146,18 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     if (workers) {
         // bring the worker of every variant, then of every step of both indexes, up to date
         infaas_sel *sub = h->inactive;
-        const bool rows = h->workers_dirty;
-        if (rows) {
+        if (h->workers_dirty) {
             LaunchTimer t(h, INFAAS_SEL_K_WORKER_TABLES, st);
             if (!HIP_OK(launch_worker_tables(h->wv, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
-            h->steps_stale = sub->steps_stale = true;
+            h->workers_dirty = false;
+            h->rows_stale = h->steps_stale = sub->steps_stale = true;
         }
-        if (h->steps_stale || sub->steps_stale) {
+        if (h->rows_stale || h->steps_stale || sub->steps_stale) {
             LaunchTimer t(h, INFAAS_SEL_K_STEP_WORKERS, st);
             if (!HIP_OK(launch_step_workers(h->wv, h->steps_stale ? &h->ix : nullptr, sub->steps_stale ? &sub->ix : nullptr,
-                                            h->T * h->B, rows, st, t.ev())))
+                                            h->T * h->B, h->rows_stale, st, t.ev())))
                 return INFAAS_SEL_ERR_HIP;
-            h->workers_dirty = h->steps_stale = sub->steps_stale = false;
+            h->rows_stale = h->steps_stale = sub->steps_stale = false;
         }
     }
     // The Active tier's lookup writes all result arrays and lists the valid queries it could not
@@ -1348,7 +1349,13 @@ namespace {
 int apply_instance_states(infaas_sel *h, hipStream_t st)
 {
     const int rc = apply_states(h, h->inactive, true, 0, nullptr, nullptr, st);
-    if (rc == INFAAS_SEL_OK) h->workers_dirty = true;
+    if (rc != INFAAS_SEL_OK) return rc;
+    // The derivation has gone through loads and utilisations, too.  (Not yet, if it has only been captured: a call in front of
+    // the graph's first replay must not take the tables for current.)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
+    h->workers_dirty = capture != hipStreamCaptureStatusNone;
+    h->rows_stale = true;
     return rc;
 }
 

@@ -333,6 +333,7 @@ hipError_t launch_instance_state_report(const WorkerView &wv, int32_t n, const i
                                         hipStream_t st, const LaunchEvents *ev = nullptr);
 // As launch_update_state for all rows, with the states that the instances' states give: Inactive without
 // instances, Active with an Active one, else Overloaded if some instance is, else Interfered.
+// Does what launch_worker_tables does besides.
 hipError_t launch_derive_states(const WorkerView &wv, const TableView &ta, const IndexView &ia, const TableView &tb,
                                 const IndexView &ib, hipStream_t st, const LaunchEvents *ev = nullptr);
 // best_cls and the Active half of row_worker from the current utilisations and loads.

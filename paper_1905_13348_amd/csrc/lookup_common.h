@@ -483,5 +483,37 @@ __device__ __forceinline__ ClosestStep closest_step(const Mem &mem, int nit, uin
     return c;
 }
 
+
+// ---------------------------------------------------------------- workers
+
+__device__ __forceinline__ uint64_t lower(uint64_t a, uint64_t b) { return b < a ? b : a; }
+// The instance with the smallest of these serves: by (load, worker).
+__device__ __forceinline__ uint64_t instance_key(const WorkerView &wv, int32_t i)
+{
+    return ((uint64_t)(uint32_t)wv.inst_load[i] << 32) | (uint32_t)wv.inst_worker[i];
+}
+
+// By a whole workgroup: the worker of class c with the smallest (utilisation, number).
+template <int kThreads>
+__device__ __forceinline__ void best_of_class(const WorkerView &wv, int32_t c)
+{
+    __shared__ uint64_t s_best[kThreads / 64];
+    const int32_t lo = wv.cls_off[c], hi = wv.cls_off[c + 1];
+    uint64_t best = ~0ull;
+    for (int32_t i = lo + (int32_t)threadIdx.x; i < hi; i += kThreads) {
+        const int32_t w = wv.cls_worker[i];
+        best = lower(best, ((uint64_t)(uint32_t)wv.util[w] << 32) | (uint32_t)w);   // utilisation is never negative
+    }
+#pragma unroll
+    for (int off = 32; off; off >>= 1) best = lower(best, __shfl_xor(best, off));
+    if ((threadIdx.x & 63) == 0) s_best[threadIdx.x >> 6] = best;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 1; k < kThreads / 64; ++k) best = lower(best, s_best[k]);
+        wv.best_cls[c] = hi > lo ? (int32_t)(uint32_t)best : -1;
+    }
+}
+
 }  // namespace
 }  // namespace infaas

@@ -148,6 +148,8 @@ __device__ __forceinline__ void set_state(const TableView &tv, int32_t v, int32_
 // (Section 4 keeps the state machine per variant instance): Inactive when it runs nowhere, Active when
 // some instance is, else Overloaded when some instance is, else Interfered.  idx null: entry i is row i.
 // Rewinds the allocators of both indexes, like a load update, because they are rebuilt afterwards.
+// It also leaves the workers of k_worker_tables behind, the last H workgroups those of the classes: it reads the instances anyway
+// (a launch less: reports on 768 workers and 20,000 instances, then 1M queries, 57.7 us -> 54.1).
 // Bound by latency: four to six dependent reads.  One launch for both tables, the derivation included, and no
 // store where nothing changes: 20,000 variants x 8 batch sizes, 5% of the instances reported, 18.4 us (three
 // launches) -> 4.6.
@@ -156,24 +158,42 @@ __global__ __launch_bounds__(256) void k_update_state(TableView ta, IndexView ia
                                                       const int32_t *__restrict__ idx, const int32_t *__restrict__ val,
                                                       WorkerView wv)
 {
+    if (kDerive && (int32_t)(gridDim.x - blockIdx.x) <= wv.H) {
+        best_of_class<256>(wv, (int32_t)(gridDim.x - blockIdx.x) - 1);
+        return;
+    }
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     rewind_index(ia, tid);
     rewind_index(ib, tid);
     const int32_t per_wave = 64 / ta.B, lane = threadIdx.x & 63;
     const int32_t e = lane / ta.B, b = lane - e * ta.B;
     const int64_t i = (tid >> 6) * per_wave + e;
-    if (e >= per_wave || i >= n) return;
+    const bool mine = e < per_wave && i < n;
     int32_t v = (int32_t)i, x;
     if (kDerive) {
-        const int32_t lo = wv.inst_off[v], hi = wv.inst_off[v + 1];
+        // (the lanes of an entry share its instances)
+        const int32_t lo = mine ? wv.inst_off[v] : 0, hi = mine ? wv.inst_off[v + 1] : 0;
         bool active = false, overloaded = false;
-        for (int32_t j = lo; j < hi; ++j) {
+        uint64_t best = ~0ull;
+        for (int32_t j = lo + b; j < hi; j += ta.B) {
             const int32_t c = wv.inst_state[j];
-            active = active || c == 1;
-            overloaded = overloaded || c == 2;
+            const uint64_t key = instance_key(wv, j);
+            active |= c == 1;
+            overloaded |= c == 2;
+            best = c == 1 ? lower(best, key) : best;
+        }
+        const uint64_t here = (ta.B < 64 ? (1ull << ta.B) - 1ull : ~0ull) << ((e * ta.B) & 63);
+        active = (__ballot(active) & here) != 0ull;
+        overloaded = (__ballot(overloaded) & here) != 0ull;
+        for (int32_t off = 1; off < ta.B; off <<= 1) {
+            const uint64_t o = __shfl_down(best, off);
+            best = b + off < ta.B ? lower(best, o) : best;
         }
         x = hi == lo ? 0 : (active ? 1 : (overloaded ? 2 : 3));
+        if (!mine) return;
+        if (b == 0) wv.row_worker[v] = best != ~0ull ? (int32_t)(uint32_t)best : -1;
     } else {
+        if (!mine) return;
         v = idx ? idx[i] : v;
         x = val[i];
         if ((uint32_t)v >= (uint32_t)ta.V || (uint32_t)x > 3u) return;
@@ -529,7 +549,7 @@ hipError_t launch_derive_states(const WorkerView &wv, const TableView &ta, const
                                 const IndexView &ib, hipStream_t st, const LaunchEvents *ev)
 {
     if (wv.V <= 0 || !wv.inst_state) return hipSuccess;
-    return launch_kernel(ev, k_update_state<true>, state_grid(ta, wv.V), dim3(256), 0, st, ta, ia, tb, ib, wv.V, nullptr, nullptr, wv);
+    return launch_kernel(ev, k_update_state<true>, dim3(state_grid(ta, wv.V).x + (unsigned)wv.H), dim3(256), 0, st, ta, ia, tb, ib, wv.V, nullptr, nullptr, wv);
 }
 
 hipError_t launch_histogram(const TableView &tv, const QueryView &q, const ScanScratch &sc,

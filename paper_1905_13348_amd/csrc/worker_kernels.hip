@@ -7,8 +7,10 @@
 // worker per variant up to date (k_worker_tables, from the reports applied by k_worker_report) and
 // copy it next to every step of the staircase indexes (k_step_workers); the lookup kernel then
 // fetches the worker of an answer with the same gather that fetches its row.  All of it is bound by
-// launches and latency (a few hundred KB), hence two launches, as many as there are dependencies.
+// launches and latency (a few hundred KB), hence two launches, as many as there are dependencies, and behind an instance state
+// report one: k_update_state, which goes through the instances anyway, does what k_worker_tables does.
 #include "internal.h"
+#include "lookup_common.h"
 
 #include <algorithm>
 
@@ -45,47 +47,21 @@ __global__ __launch_bounds__(kThreads) void k_instance_state_report(WorkerView w
     if ((uint32_t)j < (uint32_t)wv.I && c >= 1 && c <= 3) wv.inst_state[wv.inst_pos[j]] = c;
 }
 
-__device__ __forceinline__ uint64_t wave_min_u64(uint64_t v)
-{
-#pragma unroll
-    for (int off = 32; off; off >>= 1) {
-        const uint64_t o = __shfl_xor(v, off);
-        v = o < v ? o : v;
-    }
-    return v;
-}
-
 // The first H workgroups, one per hardware class: the worker with the smallest (utilisation, number).
 // The others, one lane per variant: the worker of its instance with the smallest (load, worker) -- of its
 // Active instances, when the instances carry states.
 __global__ __launch_bounds__(kThreads) void k_worker_tables(WorkerView wv)
 {
-    __shared__ uint64_t s_best[kThreads / 64];
-    uint64_t best = ~0ull;
     if ((int32_t)blockIdx.x < wv.H) {
-        const int32_t c = (int32_t)blockIdx.x;
-        const int32_t lo = wv.cls_off[c], hi = wv.cls_off[c + 1];
-        for (int32_t i = lo + (int32_t)threadIdx.x; i < hi; i += kThreads) {
-            const int32_t w = wv.cls_worker[i];
-            const uint64_t key = ((uint64_t)(uint32_t)wv.util[w] << 32) | (uint32_t)w;   // utilisation is never negative
-            best = key < best ? key : best;
-        }
-        best = wave_min_u64(best);
-        if ((threadIdx.x & 63) == 0) s_best[threadIdx.x >> 6] = best;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int k = 1; k < kThreads / 64; ++k) best = s_best[k] < best ? s_best[k] : best;
-            wv.best_cls[c] = hi > lo ? (int32_t)(uint32_t)best : -1;
-        }
+        best_of_class<kThreads>(wv, (int32_t)blockIdx.x);
         return;
     }
+    uint64_t best = ~0ull;
     const int32_t v = (int32_t)((blockIdx.x - (uint32_t)wv.H) * kThreads + threadIdx.x);
     if (v >= wv.V) return;
     for (int32_t i = wv.inst_off[v]; i < wv.inst_off[v + 1]; ++i) {
         if (wv.inst_state && wv.inst_state[i] != 1) continue;
-        const uint64_t key = ((uint64_t)(uint32_t)wv.inst_load[i] << 32) | (uint32_t)wv.inst_worker[i];
-        best = key < best ? key : best;
+        best = lower(best, instance_key(wv, i));
     }
     wv.row_worker[v] = best != ~0ull ? (int32_t)(uint32_t)best : -1;
 }

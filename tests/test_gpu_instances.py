@@ -150,3 +150,46 @@ def test_instance_state_errors():
     load_cluster(sel, cluster_args(wk))                       # a new cluster drops the instance states
     sel.update_state(z, z)
     sel.destroy()
+
+
+@pytest.mark.parametrize("B", [1, 2, 3, 5, 8, 13, 32])
+def test_workers_from_the_state_derivation(oracle_lib, B):
+    """The kernel that derives the variants' states shares a variant's instances among B lanes and leaves the workers behind, those of
+    the classes too: more and fewer instances than lanes, more workers of a class than a workgroup has lanes, ties, and the utilisation and load
+    report in front of the instance states' and behind it."""
+    rng = np.random.default_rng([61, B])
+    tb = _random_table(rng, 6, rng.integers(1, 60, 6), B, span=50)
+    state = rng.integers(0, 4, tb.V).astype(np.int32)
+    load = rng.integers(0, 50, tb.V).astype(np.int32)
+    variant_hw, worker_hw, util, inst_variant, inst_worker, iload = _random_cluster(rng, tb.V, state, 4, W=900)
+    many = np.repeat(rng.integers(0, tb.V, 3), (70, 31, B))                 # a few variants with many instances
+    inst_variant = np.concatenate([inst_variant, many]).astype(np.int32)
+    inst_worker = np.concatenate([inst_worker, rng.integers(0, 900, many.size)]).astype(np.int32)
+    iload = np.concatenate([iload, rng.integers(0, 4, many.size)]).astype(np.int32)
+    I = inst_variant.size
+    ist = rng.choice([1, 2, 3], I, p=[0.3, 0.4, 0.3]).astype(np.int32)
+    util = util.copy()
+    sel = make_selector(tb, engine=0)
+    sel.load_states(state, load)
+    load_cluster(sel, (variant_hw, worker_hw, util, inst_variant, inst_worker, iload))
+    sel.load_instance_states(ist)
+    q = _random_queries(rng, 6, B, 20_000, span=50)
+
+    def states():
+        idx = rng.permutation(I)[:max(1, I // 3)].astype(np.int32)
+        val = rng.integers(1, 4, idx.size).astype(np.int32)
+        sel.update_instance_states(to_dev(idx), to_dev(val))
+        ist[idx] = val
+
+    def workers():
+        w, i = rng.permutation(900)[:300].astype(np.int32), rng.permutation(I)[:max(1, I // 2)].astype(np.int32)
+        wu, il = rng.integers(0, 4, w.size).astype(np.int32), rng.integers(0, 4, i.size).astype(np.int32)
+        sel.update_workers(to_dev(w), to_dev(wu), to_dev(i), to_dev(il))
+        util[w] = wu
+        iload[i] = il
+
+    for turn, reports in enumerate(((), (states,), (workers, states), (states, workers), (workers,), (states, states))):
+        for report in reports:
+            report()
+        _check(oracle_lib, sel, tb, load, (variant_hw, worker_hw, util, inst_variant, inst_worker, iload), ist, q, f"turn {turn}")
+    sel.destroy()
