@@ -934,6 +934,21 @@ int infaas_sel_load_variants(infaas_sel_t *h, int32_t V, const int32_t *task_id,
     return INFAAS_SEL_OK;
 }
 
+namespace {
+
+bool is_captured(hipStream_t st)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+// Whether a build of the index may leave the steps' workers behind: when the worker of every variant is up to date.  (Not in
+// a graph: what is captured has not happened yet, and a call in front of the first replay must not rely on it.)
+bool may_fill_workers(const infaas_sel *h, hipStream_t st) { return h->workers_loaded && !h->workers_dirty && !is_captured(st); }
+
+}  // namespace
+
 int infaas_sel_update_load(infaas_sel_t *h, int32_t n, const int32_t *d_variant_idx,
                            const int32_t *d_queue_us, void *hip_stream)
 {
@@ -971,8 +986,20 @@ int apply_states(infaas_sel *h, infaas_sel *sub, bool derive, int32_t n, const i
         if (!HIP_OK(e)) return INFAAS_SEL_ERR_HIP;
     }
     h->steps_stale = sub->steps_stale = true;
+    if (derive) {   // it has gone through loads and utilisations, too
+        h->workers_dirty = is_captured(st);
+        h->rows_stale = true;
+    }
+    IndexView ia = h->ix, ib = sub->ix;
+    const bool fill = may_fill_workers(h, st);
+    if (fill) {
+        ia.fill.by_row = h->wv.row_worker;
+        ib.fill.cls = h->wv.var_cls; ib.fill.best = h->wv.best_cls;
+        if (h->rows_stale) ib.fill.rows = h->wv.row_worker + h->V;
+    }
     LaunchTimer t(h, INFAAS_SEL_K_INDEX_BUILD, st);
-    if (!HIP_OK(launch_index_build(h->tv, h->ix, sub->tv, sub->ix, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
+    if (!HIP_OK(launch_index_build(h->tv, ia, sub->tv, ib, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
+    if (fill) h->steps_stale = sub->steps_stale = h->rows_stale = false;
     return INFAAS_SEL_OK;
 }
 
@@ -1342,24 +1369,9 @@ int infaas_sel_update_workers(infaas_sel_t *h, int32_t n, const int32_t *d_worke
     return INFAAS_SEL_OK;
 }
 
-namespace {
-
 // The variants' states derived anew from the instances', applied to both tiers' tables, both indexes
 // rebuilt behind it (as after a state report).
-int apply_instance_states(infaas_sel *h, hipStream_t st)
-{
-    const int rc = apply_states(h, h->inactive, true, 0, nullptr, nullptr, st);
-    if (rc != INFAAS_SEL_OK) return rc;
-    // The derivation has gone through loads and utilisations, too.  (Not yet, if it has only been captured: a call in front of
-    // the graph's first replay must not take the tables for current.)
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
-    h->workers_dirty = capture != hipStreamCaptureStatusNone;
-    h->rows_stale = true;
-    return rc;
-}
-
-}  // namespace
+static int apply_instance_states(infaas_sel *h, hipStream_t st) { return apply_states(h, h->inactive, true, 0, nullptr, nullptr, st); }
 
 int infaas_sel_load_instance_states(infaas_sel_t *h, const int32_t *inst_state)
 {

@@ -327,6 +327,29 @@ __device__ __forceinline__ SliceColumns slice_columns(int32_t s, int32_t t, int3
     return SliceColumns{tv->acc_r + col, tv->tot_r + col, (uint4 *)((char *)tv->rank_hdr + (rank_nodes_at(tv->S) - rank_hdr_at(tv->S))) + (uint64_t)tv->rank_hdr[s].z * 8, tv->seg_len[t], tv->acc_base};
 }
 
+// Worker selection: the workers of the steps, like k_step_workers (worker_kernels.hip) makes them when the workers have changed and the
+// index has not.  Behind a state report it is a launch less (reports and 1M queries on 20,000 variants 54.1 us per turn with it, 50.2
+// so).  Builds of one table do without: 0.4 us of every load report's build, for handles that mostly have no workers.
+__device__ __forceinline__ int32_t worker_of_row(const StepFill &f, int32_t row)
+{
+    if (f.by_row) return f.by_row[row];
+    const int32_t c = f.cls[row];
+    return c >= 0 ? f.best[c] : -1;
+}
+__device__ __forceinline__ void store_step_worker(const IndexView &ix, int32_t s, int step, uint32_t at, int32_t worker)
+{
+    ix.step_worker[at] = worker;
+    if (ix.hot_worker && (uint32_t)step < ix.hot_rows)
+        ix.hot_worker[(uint32_t)s * ix.hot_rows + (uint32_t)step] = (uint32_t)worker < 0xFFFFu ? (uint16_t)worker : (uint16_t)0xFFFFu;
+}
+// Thread `at` of `threads`, with nothing else left to do.
+__device__ __forceinline__ void store_row_workers(const TableView &tv, const IndexView &ix, int32_t at, int32_t threads)
+{
+    if (at == 0) ix.step_worker[0] = -1;
+    if (ix.fill.rows)
+        for (int32_t v = at; v < tv.V; v += threads) ix.fill.rows[v] = worker_of_row(ix.fill, v);
+}
+
 // One wavefront per slice, kBuildWaves slices per workgroup.  An entry of the slice is a step exactly
 // when no entry ranked before it has at least its accuracy and at most its latency-plus-queue; that
 // relation is transitive, so it is enough to test an entry against the earlier STEPS.  The wavefront
@@ -584,6 +607,9 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
     uint32_t row_hi = 0;
     for (uint32_t j = 0; j < r0; ++j)
         row_hi |= ((uint32_t)__builtin_amdgcn_readlane(row, (int)j) >> 16) << (j * ix.row_hi_bits);
+    const bool fill = kTwo && (ix.fill.by_row || ix.fill.cls);
+    int32_t worker = -1;
+    if (fill && lane < K) worker = worker_of_row(ix.fill, row);
     __syncthreads();
     const bool has = inside && L > 0;
     const uint32_t off = s_off[wave], rec = s_rec[wave];
@@ -597,6 +623,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
             ix.step_row[rec + lane] = row;
             if ((uint32_t)lane < r0)   // in reverse in front of the body
                 *(uint16_t *)(body0 - 2 - 2 * lane) = (uint16_t)row;
+            if (fill) store_step_worker(ix, s, lane, rec + (uint32_t)lane, worker);
         }
     }
     if (__builtin_expect(has && (trunc || !fits), 0)) {   // (the wavefront) queries of this slice may go through its entries in rank order
@@ -636,6 +663,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
         if (threadIdx.x >= 2) atomicAdd(g, v);
         else if (v > __hip_atomic_load(g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(g, v);   // (mostly not)
     }
+    if (fill) store_row_workers(tv, ix, (int32_t)(blockIdx.x * blockDim.x + threadIdx.x), (int32_t)(gridDim.x * blockDim.x));
 }
 
 // Few slices, one per workgroup: the time is one slice's chain of dependent steps, so its four wavefronts take
@@ -1026,8 +1054,13 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableVi
         }
         write_rank_nodes<(kChunk > kRankUnsorted)>(sc.acc, sc.tot, sc.nodes, sc.L, from, to, lane, mx, mn, sc.acc_base);
     }
-    if (wave != 0) return;   // (no barrier follows)
+    const bool fill = kTwo && (ix.fill.by_row || ix.fill.cls);
+    if (wave != 0) {   // (no barrier follows)
+        if (fill) store_row_workers(tv, ix, s * 64 * (kBuildWaves - 1) + (int32_t)threadIdx.x - 64, tv.S * 64 * (kBuildWaves - 1));
+        return;
+    }
     if (fits && lane < K) {
+        if (fill) store_step_worker(ix, s, lane, rec + (uint32_t)lane, worker_of_row(ix.fill, row));
         ix.step_row[rec + lane] = row;
         if ((uint32_t)lane < r0)   // in reverse in front of the body
             *(uint16_t *)(body0 - 2 - 2 * lane) = (uint16_t)row;

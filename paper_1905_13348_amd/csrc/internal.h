@@ -114,6 +114,12 @@ __host__ __device__ inline uint32_t lds_header_bytes(int32_t S) { return (((uint
 __host__ __device__ inline uint32_t body_re(uint32_t steps) { return (steps + 2u) & ~1u; }   // Re of a body with `steps` steps
 __host__ __device__ inline uint32_t body_bytes(uint32_t re) { return 14u * re; }
 
+// Where a build finds the worker of a row, for the steps' workers (launch_step_workers) that it then leaves behind itself.
+struct StepFill {
+    const int32_t *by_row;        // [V] the worker by caller row (Active tier), or null: the best worker ...
+    const int32_t *cls, *best;    // ... of the row's hardware class (Inactive tier); null, too: the build writes no workers
+    int32_t *rows;                // [V] Inactive tier: where that goes for every row, or null
+};
 struct IndexView {
     uint4 *hdr;          // [S + 1] {body address (pool offset - 4), y (see kHdr*), first entry in step_row, end of bodies};
                          //         entry S is the header of an empty slice, used for queries outside the table
@@ -140,6 +146,7 @@ struct IndexView {
     const uint16_t *task_group;   // [T] group of every task; null when num_groups == 1
     const int32_t *group_task0;   // [num_groups + 1]
     uint32_t *gctrl;              // [2 num_groups] per group: bytes of its region and steps handed out
+    StepFill fill;       // for the build of both tiers' tables only
     uint32_t *stats;     // [kStatShare x compute units][kLookupStats] what the most recent lookup launch did;
                          // the word in front of it: how many entries that launch has written
 };

@@ -173,7 +173,7 @@ def test_workers_from_the_state_derivation(oracle_lib, B):
     sel.load_states(state, load)
     load_cluster(sel, (variant_hw, worker_hw, util, inst_variant, inst_worker, iload))
     sel.load_instance_states(ist)
-    q = _random_queries(rng, 6, B, 20_000, span=50)
+    q = _random_queries(rng, 6, B, 260_001, span=50)   # more than the two tables' limits: through the LDS mirrors too
 
     def states():
         idx = rng.permutation(I)[:max(1, I // 3)].astype(np.int32)
@@ -188,8 +188,19 @@ def test_workers_from_the_state_derivation(oracle_lib, B):
         util[w] = wu
         iload[i] = il
 
-    for turn, reports in enumerate(((), (states,), (workers, states), (states, workers), (workers,), (states, states))):
+    queue = tb.queue_us.copy()
+
+    def loads():
+        idx = rng.permutation(tb.V)[:max(1, tb.V // 4)].astype(np.int32)
+        val = rng.integers(0, 50, idx.size).astype(np.int32)
+        sel.update_load(to_dev(idx), to_dev(val))
+        queue[idx] = val
+
+    for turn, reports in enumerate(((), (states,), (workers, states), (states, workers), (workers,), (states, states), (loads,), (loads,),
+                                    (workers, loads), (states, loads), (loads, states), (loads, workers))):
         for report in reports:
             report()
-        _check(oracle_lib, sel, tb, load, (variant_hw, worker_hw, util, inst_variant, inst_worker, iload), ist, q, f"turn {turn}")
+        some = q if turn % 2 else tuple(x[:5001] for x in q)
+        _check(oracle_lib, sel, tb, load, (variant_hw, worker_hw, util, inst_variant, inst_worker, iload), ist, some, f"turn {turn}",
+               queue=queue)
     sel.destroy()
