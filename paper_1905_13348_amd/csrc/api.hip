@@ -1553,6 +1553,10 @@ int infaas_sel_load_scaling(infaas_sel_t *h, const int32_t *arch_id, const int32
                         w[j < 4 ? 28 + j : 7] = (uint32_t)c.row;
                     }
                 }
+                // of the list only what no block holds is left
+                const auto in_block = (std::ptrdiff_t)std::min<size_t>(n, kScaleInBlock);
+                cand.erase(cand.begin() + (std::ptrdiff_t)first, cand.begin() + (std::ptrdiff_t)first + in_block);
+                cand_cost.erase(cand_cost.begin() + (std::ptrdiff_t)first, cand_cost.begin() + (std::ptrdiff_t)first + in_block);
             }
         if (cand.empty()) cand.push_back(ScaleCand{1u, 0, 0ull, 0, {0, 0, 0}});
     }

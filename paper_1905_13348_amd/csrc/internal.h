@@ -355,9 +355,10 @@ hipError_t launch_step_workers(const WorkerView &wv, const IndexView *ia, const 
 //   0 saturation throughput Q of the row, 1 its hardware cost, 2-3 the cost of one loaded instance
 //   C * (1,000,000 + lambda * T_load), 4 its inference latency at the batch size, 5 the number m of
 //   candidates for an upgrade (those of its architecture's list with a higher throughput: a prefix
-//   of the list), 6 where that list starts in `cand`, 7 | 28-31 the caller rows of
+//   of the list), 6 where the list goes on in `cand`, 7 | 28-31 the caller rows of
 //   the first five candidates (the fifth in word 7), 8-27 those candidates, four words each.
-// Candidates beyond the fifth are read from the shared list.
+// Candidates beyond the fifth are read from `cand`, which holds every list from its sixth candidate on (100,000 variants
+// at 8 batch sizes: 2.3 MB, which L2 keeps; whole lists 11.8).
 constexpr int kScaleBlockWords = 32;
 constexpr int kScaleInBlock = 5;
 struct ScaleCand {    // one candidate for an upgrade, as the shared lists hold it
@@ -372,7 +373,7 @@ struct ScaleView {
     int32_t slack_pct;
     const uint32_t *blocks;   // [B][V][32]
     const ScaleCand *cand;    // per (batch size, architecture) the variants that can ever win an upgrade, by
-                              // descending throughput
+                              // descending throughput, from the sixth on
     // The same two for scaling down: the candidates of a row are those for a downgrade (the prefix with a
     // lower hardware cost of its architecture's list, which is sorted by ascending hardware cost).
     const uint32_t *blocks_down;

@@ -65,7 +65,8 @@ __device__ __forceinline__ uint32_t ceil_div(uint32_t need, uint32_t per)
 __device__ __forceinline__ void arrived(uint4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
 
 // Bound by the requests' lines: 4M of them on 102 MB of blocks, read by a kernel that does nothing else, take 86 us together with
-// the fields and results; the continuations of long lists are 0.2 lines per request more.  Candidates are computed for every lane and masked, without branches; 32-bit quotients (the need is rounded up
+// the fields and results, this kernel 99; the continuations of long lists, 0.2 lines per request more, come from L2 (whole lists
+// instead of their ends: 99.8).  Candidates are computed for every lane and masked, without branches; 32-bit quotients (the need is rounded up
 // to whole queries per second once: ceil(ceil(x / 100) / q) = ceil(x / (100 q))) and 96-bit costs.
 template <bool kDown>
 __global__ __launch_bounds__(kThreads) void k_scale(ScaleView sv, int64_t R, const int32_t *__restrict__ r_variant,
@@ -136,21 +137,22 @@ __global__ __launch_bounds__(kThreads) void k_scale(ScaleView sv, int64_t R, con
             const bool better = on & (lat <= slo) & (o < best);
             if (better) { best = o; best_n = n; }
         };
-        // the rest of a longer prefix, from the shared list, four at a time; requested before the block's own are looked at
+        // the rest of a longer prefix, from the shared list, two at a time; requested before the block's own are looked at
         const ScaleCand *all = kDown ? sv.cand_down : sv.cand;
+        const int32_t rest = m - kScaleInBlock;
         uint4 cand[kChunk];
         uint32_t cand_row[kChunk];
         auto request = [&](int32_t i0) __attribute__((always_inline)) {   // (lanes with nothing left read the first of all)
 #pragma unroll
             for (int j = 0; j < kChunk; ++j) {
-                const ScaleCand *c = all + (i0 + j < m ? (int64_t)more.z + i0 + j : 0);
+                const ScaleCand *c = all + (i0 + j < rest ? (int64_t)more.z + i0 + j : 0);
                 cand[j] = *(const uint4 *)c;
                 cand_row[j] = (uint32_t)c->row;
             }
         };
-        int32_t i0 = kScaleInBlock;
-        bool longer = __ballot(m > i0) != 0ull;
-        if (longer) request(i0);
+        int32_t i0 = 0;
+        bool longer = __ballot(rest > 0) != 0ull;
+        if (longer) request(0);
 #pragma unroll
         for (int j = 0; j < kScaleInBlock; ++j)
             offer(j < m, slot[j].x, (int32_t)slot[j].y, ((uint64_t)slot[j].w << 32) | slot[j].z, slot_row[j]);
@@ -158,10 +160,10 @@ __global__ __launch_bounds__(kThreads) void k_scale(ScaleView sv, int64_t R, con
 #pragma unroll
             for (int j = 0; j < kChunk; ++j) {
                 arrived(cand[j]);
-                offer(i0 + j < m, cand[j].x, (int32_t)cand[j].y, ((uint64_t)cand[j].w << 32) | cand[j].z, cand_row[j]);
+                offer(i0 + j < rest, cand[j].x, (int32_t)cand[j].y, ((uint64_t)cand[j].w << 32) | cand[j].z, cand_row[j]);
             }
             i0 += kChunk;
-            longer = __ballot(m > i0) != 0ull;
+            longer = __ballot(rest > i0) != 0ull;
             if (longer) request(i0);
         }
         int32_t action = 0, variant = -1, instances = 0;
@@ -195,7 +197,7 @@ hipError_t launch_scale(const ScaleView &sv, bool down, int64_t R, const int32_t
     // one request per lane (to 2^26 of them): the loop over a smaller grid makes every lane wait for its request's line
     // before it asks for the next one's fields (4M requests 3% longer with 32 workgroups per compute unit).  One wavefront to a
     // workgroup, so that none waits for its neighbours to leave, and lists two candidates at a time: us for 4M / 700,001 requests
-    // 99.8 / 21.1, with four at a time and four wavefronts 101.0 / 22.2; with a compiler that moved every word's load behind its
+    // 99 / 21.1, with four at a time and four wavefronts 101.0 / 22.2; with a compiler that moved every word's load behind its
     // first use, and branches, 128-bit quotients and costs 125.8 / 23.9.
     const int64_t blocks = want < (int64_t)num_cus * 4096 ? want : (int64_t)num_cus * 4096;
     if (down)
