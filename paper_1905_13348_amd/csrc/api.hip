@@ -525,10 +525,10 @@ int ensure_open(infaas_sel *h, int64_t n, bool side)
 
 // Up to this many queries a selection is answered straight from global memory, one lane per query, rather than
 // through an LDS mirror of the index.  The mirror costs its fill (2-4 us, more with many slices) and pays with 4
-// ps per query against 20 (measured, us for 10,000 / 90,000 queries; config 2's table, whole index in LDS: 4.6 / 5.8
-// direct, 7.7 / 8.0 mirrored; config 1's, 92% of it: 4.1 / 4.7 and 8.8 / 9.0; config 3's, 7%, for 10,000 / 200,000 / 400,000: 4.5 /
-// 7.9 / 12.1 and 16.0 / 18 / 22).  The less of the index the mirror holds, the later it pays.  (The line was drawn when a direct
-// query cost 40 ps; by these figures it could lie somewhat higher.)
+// ps per query against 15 to 20.  Measured, us for 100,000 / 200,000 / 300,000 queries, direct and mirrored: config 2's table, whole index in
+// LDS, 6.2 / 8.6 / 11.0 and 7.4 / 7.6 / 7.9; config 1's, 92% of it, 5.5 / 7.0 / 8.7 and 8.4 / 8.7 / 8.9; 200 tasks of 60 variants, about half of it, 5.5 / 6.9 /
+// 8.6 and 10.3 / 10.8 / 11.4 (700,000: 15.5 and 16.7); config 3's, 7%, 200,000 / 400,000: 7.9 / 12.1 and 18 / 22.  The less of the index
+// the mirror holds, the later it pays.  (Where no slice has a second body the line could lie at twice as many.)
 constexpr int64_t kDirectQueries = 100000;
 // With suggestions the same holds (us for 65,000 / 100,000 / 300,000 queries: 100 tasks of 200 variants 7.9 / 9.5 / 17.9 direct,
 // 13.4 / 13.3 / 14.9 mirrored; config 3's table 9.4 / 11.2 / 22.5 and 27.6 / 28.6 / 33.4), except where the mirror holds nearly the
@@ -1154,11 +1154,12 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     DeviceGuard g(h->device);
     if (!g.ok) return INFAAS_SEL_ERR_HIP;
     hipStream_t st = (hipStream_t)hip_stream;
-    // Two mirrors and two launches against one kernel: the sum of the tables' limits.  (us for 10,000 / 100,000 / 200,000 /
-    // 400,000 queries on 100 tasks of 200 variants: two tiers 7.8 / 8.2 / 12.8 / 21.4 direct, 13.9 / 14.9 / 14.9 / 15.9
-    // mirrored; with workers 8.8 / 8.7 / 13.8 / 22.8 and 16.9 / 17.9 / 18.4 / 20.2; complete Case I with workers 11.3 / 13.6 /
-    // 19.0 / 34.7 and 21.7 / 23.3 / 26.8 / 30.7)
-    const bool direct = N <= direct_limit(h) + direct_limit(h->inactive);
+    // Two mirrors and two launches against one kernel: three tenths more than the sum of the tables' limits, and so below the 2^18 queries
+    // that are in flight at once.  (us for 100,000 / 200,000 / 300,000 / 450,000 queries, direct and mirrored: two tiers behind a state report on
+    // 100 tasks of 200 variants 23.3 / 25.6 / 28.8 / 32.0 and 30.8 / 31.7 / 31.8 / 33.3, on 50 of 2000 29.4 / 32.3 / 36.0 / 40.0 and 36.5 / 37.1 /
+    // 37.7 / 38.5; complete Case I with workers 13.7 / 17.2 / 24.2 / 29.2 and 25.7 / 27.5 / 30.9 / 33.8, 14.8 / 18.1 / 25.5 / 30.5 and 22.2 / 24.4 /
+    // 23.1 / 24.9.)
+    const bool direct = N <= (direct_limit(h) + direct_limit(h->inactive)) / 10 * 13;
     // The lists are allocated for direct calls too: the limits follow the index, and the same call after a report
     // may need them where nothing can be allocated (under capture, after an eager call to warm up).  A direct call
     // that is itself captured does without.

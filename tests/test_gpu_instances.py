@@ -173,7 +173,7 @@ def test_workers_from_the_state_derivation(oracle_lib, B):
     sel.load_states(state, load)
     load_cluster(sel, (variant_hw, worker_hw, util, inst_variant, inst_worker, iload))
     sel.load_instance_states(ist)
-    q = _random_queries(rng, 6, B, 260_001, span=50)   # more than the two tables' limits: through the LDS mirrors too
+    q = _random_queries(rng, 6, B, 300_001, span=50)   # more than the two tables' limits: through the LDS mirrors too
 
     def states():
         idx = rng.permutation(I)[:max(1, I // 3)].astype(np.int32)
