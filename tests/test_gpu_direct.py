@@ -226,3 +226,31 @@ def test_bodies_of_every_length(oracle_lib, steps):
     _assert_equal_everywhere(gpu_select(sel, *q), want, f"{steps} steps")
     assert (want >= 0).any() and (want < 0).any()
     sel.destroy()
+
+
+@pytest.mark.parametrize("workers", [False, True])
+def test_both_sides_of_the_state_aware_limit(oracle_lib, workers):
+    """1.3 times the sum of the two tables' limits, and one query more: straight from memory every valid query counts as
+    parked, in both tiers that look at it; the lookup kernels park few.  Every element against the CPU oracle."""
+    import torch
+    from test_gpu_workers import cluster_args, load_cluster
+    tb = workloads.make_table(0)           # both mirrors hold everything: 100,000 queries each
+    st = workloads.make_states(0, tb.V)
+    q = tuple(x[:5000] for x in query_args(workloads.make_queries(0)))
+    sel = make_selector(tb, engine=0)
+    sel.load_states(st.state, st.load_us)
+    if workers:
+        cl = cluster_args(workloads.make_workers(0, st))
+        load_cluster(sel, cl)
+        want = oracle_lib.select_workers(*table_args(tb), st.state, st.load_us, *cl, *q)
+    else:
+        want = oracle_lib.select_tiered(*table_args(tb), st.state, st.load_us, *q)
+    for n in (260_000, 260_001):
+        dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda().repeat(n // 5000 + 1)[:n].contiguous() for x in q]
+        outs = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for _ in want]
+        (sel.select_workers if workers else sel.select_tiered)(*dev, *outs)
+        torch.cuda.synchronize()
+        for got, w in zip(outs, want):
+            _assert_equal_everywhere(got.cpu().numpy(), np.tile(w, n // 5000 + 1)[:n], f"N={n}")
+        assert (sel.info()["lookup_parked"] >= n) == (n == 260_000)
+    sel.destroy()
