@@ -126,6 +126,7 @@ struct infaas_sel {
     bool rows_stale = false;                              // the Inactive half of wv.row_worker is older than the workers
     bool instance_states = false;                // the variants' states follow from their instances' (wv.inst_state)
     bool steps_stale = false;                    // this table's ix.step_worker is older than its index or the workers
+    unsigned long long refreshed_in = 0;         // a capture that has recorded, behind the latest report, what brings these up to date; 0: none
 
     // staircase index
     IndexView ix{};
@@ -936,11 +937,15 @@ int infaas_sel_load_variants(infaas_sel_t *h, int32_t V, const int32_t *task_id,
 
 namespace {
 
-bool is_captured(hipStream_t st)
+// Whether what is enqueued on st is recorded into a graph instead of run (also where the runtime cannot tell).  id: number of
+// the capture, 0 where it is not known.
+bool is_captured(hipStream_t st, unsigned long long *id = nullptr)
 {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+    if ((id ? hipStreamGetCaptureInfo(st, &capture, id) : hipStreamIsCapturing(st, &capture)) == hipSuccess)
+        return capture != hipStreamCaptureStatusNone;
     (void)hipGetLastError();
+    if (id) *id = 0;
     return true;
 }
 // Whether a build of the index may leave the steps' workers behind: when the worker of every variant is up to date.  (Not in
@@ -967,6 +972,7 @@ int infaas_sel_update_load(infaas_sel_t *h, int32_t n, const int32_t *d_variant_
     }
     if (h->have_index) {  // the steps depend on the load: rebuild them behind the update
         h->steps_stale = true;
+        h->refreshed_in = 0;
         LaunchTimer t(h, INFAAS_SEL_K_INDEX_BUILD, st);
         if (!HIP_OK(launch_index_build(h->tv, h->ix, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
     }
@@ -986,6 +992,7 @@ int apply_states(infaas_sel *h, infaas_sel *sub, bool derive, int32_t n, const i
         if (!HIP_OK(e)) return INFAAS_SEL_ERR_HIP;
     }
     h->steps_stale = sub->steps_stale = true;
+    h->refreshed_in = 0;
     if (derive) {   // it has gone through loads and utilisations, too
         h->workers_dirty = is_captured(st);
         h->rows_stale = true;
@@ -1138,6 +1145,30 @@ int infaas_sel_select(infaas_sel_t *h, int64_t N, const int32_t *d_task, const i
 
 namespace {
 
+// Brings the worker of every variant, then of every step of both indexes, up to date.  What is only recorded into a graph
+// has not happened yet: it serves the calls recorded behind it, and an eager one does it again.
+int refresh_workers(infaas_sel *h, hipStream_t st)
+{
+    infaas_sel *sub = h->inactive;
+    const bool tables = h->workers_dirty, rows = tables || h->rows_stale, a = tables || h->steps_stale, b = tables || sub->steps_stale;
+    if (!rows && !a && !b) return INFAAS_SEL_OK;
+    unsigned long long id = 0;
+    const bool captured = is_captured(st, &id);
+    if (captured && id != 0 && id == h->refreshed_in) return INFAAS_SEL_OK;
+    if (tables) {
+        LaunchTimer t(h, INFAAS_SEL_K_WORKER_TABLES, st);
+        if (!HIP_OK(launch_worker_tables(h->wv, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
+    }
+    {
+        LaunchTimer t(h, INFAAS_SEL_K_STEP_WORKERS, st);
+        if (!HIP_OK(launch_step_workers(h->wv, a ? &h->ix : nullptr, b ? &sub->ix : nullptr, h->T * h->B, rows, st, t.ev())))
+            return INFAAS_SEL_ERR_HIP;
+    }
+    if (captured) h->refreshed_in = id;
+    else h->workers_dirty = h->rows_stale = h->steps_stale = sub->steps_stale = false;
+    return INFAAS_SEL_OK;
+}
+
 // The state-aware selection, with the worker of every answer when d_out_worker is given and with
 // the closest variant for the queries neither tier answers when d_out_closest is given.
 int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t *d_slo_us,
@@ -1165,29 +1196,9 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     // that is itself captured does without.
     const int64_t most = std::min(N, kMaxTierPass);
     int rc = INFAAS_SEL_OK;
-    if (!open_there(h, most, closest)) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (direct && hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
-        if (capture == hipStreamCaptureStatusNone) rc = ensure_open(h, most, closest);
-    }
+    if (!open_there(h, most, closest) && !(direct && is_captured(st))) rc = ensure_open(h, most, closest);
+    if (rc == INFAAS_SEL_OK && workers) rc = refresh_workers(h, st);
     if (rc != INFAAS_SEL_OK) return rc;
-    if (workers) {
-        // bring the worker of every variant, then of every step of both indexes, up to date
-        infaas_sel *sub = h->inactive;
-        if (h->workers_dirty) {
-            LaunchTimer t(h, INFAAS_SEL_K_WORKER_TABLES, st);
-            if (!HIP_OK(launch_worker_tables(h->wv, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
-            h->workers_dirty = false;
-            h->rows_stale = h->steps_stale = sub->steps_stale = true;
-        }
-        if (h->rows_stale || h->steps_stale || sub->steps_stale) {
-            LaunchTimer t(h, INFAAS_SEL_K_STEP_WORKERS, st);
-            if (!HIP_OK(launch_step_workers(h->wv, h->steps_stale ? &h->ix : nullptr, sub->steps_stale ? &sub->ix : nullptr,
-                                            h->T * h->B, h->rows_stale, st, t.ev())))
-                return INFAAS_SEL_ERR_HIP;
-            h->rows_stale = h->steps_stale = sub->steps_stale = false;
-        }
-    }
     // The Active tier's lookup writes all result arrays and lists the valid queries it could not
     // answer; the Inactive tier's lookup reads only those lists and fills in what it can answer.
     for (int64_t done = 0; done < N; done += kMaxTierPass) {
@@ -1349,6 +1360,7 @@ int infaas_sel_load_workers(infaas_sel_t *h, int32_t num_workers, const int32_t 
     h->wv = wv;
     h->workers_loaded = true;
     h->workers_dirty = true;
+    h->refreshed_in = 0;
     return INFAAS_SEL_OK;
 }
 
@@ -1367,6 +1379,7 @@ int infaas_sel_update_workers(infaas_sel_t *h, int32_t n, const int32_t *d_worke
     if (!HIP_OK(launch_worker_report(h->wv, n, d_worker_idx, d_worker_util, m, d_inst_idx, d_inst_load, st, t.ev())))
         return INFAAS_SEL_ERR_HIP;
     h->workers_dirty = true;
+    h->refreshed_in = 0;
     return INFAAS_SEL_OK;
 }
 

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_util import make_selector, table_args
+from gpu_util import make_selector, table_args, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -141,3 +141,124 @@ def test_graph_reports_workers_and_scaling(oracle_lib):
         for g, w in zip(res + dec + dec_down, want + want_dec + want_down):
             assert np.array_equal(g.cpu().numpy(), w), f"replay {rep}"
     sel.destroy()
+
+
+class _Cluster:
+    """A handle with workers (and instance states) beside a host copy of everything reports change, and one report of each
+    kind at a time on both."""
+
+    def __init__(self, oracle_lib, instances, n=5003, cfg=1):
+        self.lib, self.cfg, self.n, self.turn = oracle_lib, cfg, n, 0
+        times = 60                                # 300,180 queries go through the LDS mirrors, 5003 straight from memory
+        self.tb = workloads.make_table(cfg)
+        self.st = workloads.make_states(cfg, self.tb.V)
+        self.wk = workloads.make_workers(cfg, self.st)
+        self.state, self.queue = self.st.state.copy(), self.tb.queue_us.copy()
+        self.util, self.iload = self.wk.worker_util.copy(), self.wk.inst_load.copy()
+        self.ist = workloads.make_instance_states(cfg, self.wk.I) if instances else None
+        self.sel = make_selector(self.tb, engine=0)
+        self.sel.load_states(self.state, self.st.load_us)
+        self.load_workers()
+        q = workloads.make_queries(cfg, n=n)
+        self.q = (q.task, q.slo_us, q.min_acc_bp, q.batch_idx)
+        self.dq, self.out = [to_dev(np.tile(x, times)) for x in self.q], [to_dev(np.zeros(n * times)) for _ in range(3)]
+        self.staged = {}
+
+    def load_workers(self):
+        w = self.wk
+        self.sel.load_workers(w.worker_hw, self.util, w.variant_hw, w.inst_variant, w.inst_worker, self.iload)
+        if self.ist is not None:
+            self.sel.load_instance_states(self.ist)
+
+    def stage(self, kind):
+        """New contents for the device buffers of a report of this kind; what the device will hold once it has run."""
+        self.turn += 1
+        w, V, lib = self.wk, self.tb.V, self.lib
+        if kind == "load":
+            u = workloads.make_load_update(self.cfg, V, self.turn)
+            host = (u.variant_idx, u.queue_us)
+            lib.update_load(self.queue, *host)
+        elif kind == "state":
+            u = workloads.make_state_update(self.cfg, V, self.turn, fraction=0.3)
+            host = (u.variant_idx, u.state)
+            lib.update_state(self.state, *host)
+        elif kind == "workers":
+            u = workloads.make_worker_update(self.cfg, w.W, w.I, self.turn, fraction=0.5)
+            host = (u.worker_idx, u.worker_util, u.inst_idx, u.inst_load)
+            lib.update_worker_util(self.util, *host[:2])
+            lib.update_instance_load(self.iload, *host[2:])
+        else:
+            host = workloads.make_instance_state_update(self.cfg, w.I, self.turn, fraction=0.3)
+            lib.update_instance_state(self.ist, *host)
+        if kind not in self.staged:
+            self.staged[kind] = [to_dev(x) for x in host]
+        _fill(self.staged[kind], host)
+
+    def report(self, kind):
+        call = {"load": self.sel.update_load, "state": self.sel.update_state, "workers": self.sel.update_workers,
+                "instances": self.sel.update_instance_states}[kind]
+        call(*self.staged[kind])
+
+    def now(self, kind):
+        self.stage(kind)
+        self.report(kind)
+
+    def select(self):
+        self.sel.select_workers(*self.dq, *self.out)
+
+    def check(self, label, size=None):
+        import torch
+        size = size or self.out[0].numel()
+        torch.cuda.synchronize()
+        print(f"workers {label}", flush=True)
+        w = self.wk
+        tables = (*table_args(self.tb, self.queue), *(() if self.ist is not None else (self.state,)), self.st.load_us,
+                  w.variant_hw, w.worker_hw, self.util, w.inst_variant, w.inst_worker, self.iload)
+        want = self.lib.select_workers(*tables, *self.q) if self.ist is None else self.lib.select_instances(*tables, self.ist, *self.q)
+        for got, x, what in zip(self.out, want, ("variant", "tier", "worker")):
+            got = got.cpu().numpy()[:size]
+            assert np.array_equal(got, np.tile(x, size // self.n)), f"{label}: {what}"
+
+    def select_and_check(self, label):
+        for size in (self.n, self.out[0].numel()):
+            for o in self.out:
+                o.fill_(-9)
+            self.sel.select_workers(*self.dq, *self.out, n=size)
+            self.check(f"{label}, {size} queries", size)
+            assert (self.sel.info()["lookup_parked"] >= size * 0.9) == (size == self.n)
+
+
+def _record(fn):
+    import torch
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        fn()
+    return g
+
+
+@pytest.mark.parametrize("between", ["nothing", "state", "load", "reload"])
+def test_a_recorded_refresh_has_not_happened(oracle_lib, between):
+    """A selection with workers that is recorded behind a worker report, but not replayed yet, has brought nothing up to
+    date: neither for an eager call nor for the build behind a state report, nor for the graph of another selection."""
+    c = _Cluster(oracle_lib, instances=False)
+    c.select_and_check("eager")
+    for rnd in range(3):
+        if between == "reload":
+            c.load_workers()
+        else:
+            c.now("workers")
+        graph = _record(lambda: (c.select(), c.select()))
+        other = _record(c.select)
+        if between in ("state", "load"):
+            c.now(between)
+        if rnd < 2:
+            c.select_and_check(f"eager behind a recorded selection, round {rnd}")
+        if between in ("nothing", "reload"):    # (behind a report a selection is recorded again)
+            for g, what in ((other, "second"), (graph, "first"), (other, "second again")):
+                for o in c.out:
+                    o.fill_(-9)
+                g.replay()
+                c.check(f"the {what} graph, round {rnd}")
+        c.select_and_check(f"eager behind the replays, round {rnd}")
+    c.sel.destroy()
