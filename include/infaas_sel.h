@@ -338,7 +338,9 @@ int infaas_sel_update_instance_states(infaas_sel_t *h, int32_t n, const int32_t 
  *                      worker for it, see above)
  * The first call after a report (of load, state or workers) also enqueues the small kernels
  * that bring the per-variant workers up to date: a caller who captures this call into a HIP
- * graph has to capture the reports with it, or capture again after a report.
+ * graph has to capture the reports with it, or capture again after a report.  A report that is
+ * captured alone may be replayed in front of any call: from then on every eager call of this kind
+ * (and every capture of one) includes those kernels, until a new table is loaded.
  * Errors: INVALID_ARG, NOT_LOADED (no states or no workers loaded), HIP, OOM.
  */
 int infaas_sel_select_workers(infaas_sel_t *h, int64_t N,

@@ -127,6 +127,8 @@ struct infaas_sel {
     bool instance_states = false;                // the variants' states follow from their instances' (wv.inst_state)
     bool steps_stale = false;                    // this table's ix.step_worker is older than its index or the workers
     unsigned long long refreshed_in = 0;         // a capture that has recorded, behind the latest report, what brings these up to date; 0: none
+    unsigned long long reported_in = 0;          // the latest capture to record a report, if it has recorded no refresh behind it; 0: none
+    bool replays = false;                        // an earlier one did so too: its graph may be replayed in front of any call
 
     // staircase index
     IndexView ix{};
@@ -171,6 +173,8 @@ struct infaas_sel {
         (void)hipFree(d_state);
         d_state = nullptr;
         loaded = false;
+        reported_in = 0;   // (graphs of the old table's reports are of no use any more)
+        replays = false;
         table_bytes = 0;
         for (void *p : scale_mem) (void)hipFree(p);
         scale_mem.clear();
@@ -938,19 +942,27 @@ int infaas_sel_load_variants(infaas_sel_t *h, int32_t V, const int32_t *task_id,
 namespace {
 
 // Whether what is enqueued on st is recorded into a graph instead of run (also where the runtime cannot tell).  id: number of
-// the capture, 0 where it is not known.
+// the capture, 0 without one and where it is not known.
 bool is_captured(hipStream_t st, unsigned long long *id = nullptr)
 {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if ((id ? hipStreamGetCaptureInfo(st, &capture, id) : hipStreamIsCapturing(st, &capture)) == hipSuccess)
-        return capture != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    if (id) *id = 0;
+    const bool known = (id ? hipStreamGetCaptureInfo(st, &capture, id) : hipStreamIsCapturing(st, &capture)) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    if (id && (!known || capture == hipStreamCaptureStatusNone)) *id = 0;
+    return !known || capture != hipStreamCaptureStatusNone;
+}
+// To be called for every report; whether it is only recorded.  A recorded one arrives with every replay of its graph, behind the
+// back of the marks above: as long as the same capture records no refresh behind it, nothing counts as up to date.
+bool note_report(infaas_sel *h, hipStream_t st)
+{
+    h->refreshed_in = 0;
+    unsigned long long id = 0;
+    if (!is_captured(st, &id)) return false;
+    h->replays = h->replays || id == 0 || (h->reported_in != 0 && h->reported_in != id);
+    h->reported_in = id;
     return true;
 }
-// Whether a build of the index may leave the steps' workers behind: when the worker of every variant is up to date.  (Not in
-// a graph: what is captured has not happened yet, and a call in front of the first replay must not rely on it.)
-bool may_fill_workers(const infaas_sel *h, hipStream_t st) { return h->workers_loaded && !h->workers_dirty && !is_captured(st); }
+bool may_be_replayed(const infaas_sel *h) { return h->replays || h->reported_in != 0; }
 
 }  // namespace
 
@@ -972,7 +984,7 @@ int infaas_sel_update_load(infaas_sel_t *h, int32_t n, const int32_t *d_variant_
     }
     if (h->have_index) {  // the steps depend on the load: rebuild them behind the update
         h->steps_stale = true;
-        h->refreshed_in = 0;
+        note_report(h, st);
         LaunchTimer t(h, INFAAS_SEL_K_INDEX_BUILD, st);
         if (!HIP_OK(launch_index_build(h->tv, h->ix, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
     }
@@ -992,13 +1004,15 @@ int apply_states(infaas_sel *h, infaas_sel *sub, bool derive, int32_t n, const i
         if (!HIP_OK(e)) return INFAAS_SEL_ERR_HIP;
     }
     h->steps_stale = sub->steps_stale = true;
-    h->refreshed_in = 0;
+    const bool captured = note_report(h, st);
     if (derive) {   // it has gone through loads and utilisations, too
-        h->workers_dirty = is_captured(st);
+        h->workers_dirty = captured;
         h->rows_stale = true;
     }
     IndexView ia = h->ix, ib = sub->ix;
-    const bool fill = may_fill_workers(h, st);
+    // The build leaves the steps' workers behind when the worker of every variant is up to date.  (Not in a graph: what is
+    // captured has not happened yet, and a call in front of the first replay must not rely on it.)
+    const bool fill = h->workers_loaded && !h->workers_dirty && !captured && !may_be_replayed(h);
     if (fill) {
         ia.fill.by_row = h->wv.row_worker;
         ib.fill.cls = h->wv.var_cls; ib.fill.best = h->wv.best_cls;
@@ -1150,11 +1164,13 @@ namespace {
 int refresh_workers(infaas_sel *h, hipStream_t st)
 {
     infaas_sel *sub = h->inactive;
-    const bool tables = h->workers_dirty, rows = tables || h->rows_stale, a = tables || h->steps_stale, b = tables || sub->steps_stale;
-    if (!rows && !a && !b) return INFAAS_SEL_OK;
+    if (!h->workers_dirty && !h->rows_stale && !h->steps_stale && !sub->steps_stale && !may_be_replayed(h)) return INFAAS_SEL_OK;
     unsigned long long id = 0;
     const bool captured = is_captured(st, &id);
     if (captured && id != 0 && id == h->refreshed_in) return INFAAS_SEL_OK;
+    // (of the reports that this capture has recorded itself the marks tell)
+    const bool unknown = h->replays || (h->reported_in != 0 && h->reported_in != id);
+    const bool tables = unknown || h->workers_dirty, rows = tables || h->rows_stale, a = tables || h->steps_stale, b = tables || sub->steps_stale;
     if (tables) {
         LaunchTimer t(h, INFAAS_SEL_K_WORKER_TABLES, st);
         if (!HIP_OK(launch_worker_tables(h->wv, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
@@ -1164,8 +1180,12 @@ int refresh_workers(infaas_sel *h, hipStream_t st)
         if (!HIP_OK(launch_step_workers(h->wv, a ? &h->ix : nullptr, b ? &sub->ix : nullptr, h->T * h->B, rows, st, t.ev())))
             return INFAAS_SEL_ERR_HIP;
     }
-    if (captured) h->refreshed_in = id;
-    else h->workers_dirty = h->rows_stale = h->steps_stale = sub->steps_stale = false;
+    if (captured) {
+        h->refreshed_in = id;
+        if (h->reported_in == id) h->reported_in = 0;
+        return INFAAS_SEL_OK;
+    }
+    h->workers_dirty = h->rows_stale = h->steps_stale = sub->steps_stale = false;
     return INFAAS_SEL_OK;
 }
 
@@ -1379,7 +1399,7 @@ int infaas_sel_update_workers(infaas_sel_t *h, int32_t n, const int32_t *d_worke
     if (!HIP_OK(launch_worker_report(h->wv, n, d_worker_idx, d_worker_util, m, d_inst_idx, d_inst_load, st, t.ev())))
         return INFAAS_SEL_ERR_HIP;
     h->workers_dirty = true;
-    h->refreshed_in = 0;
+    note_report(h, st);
     return INFAAS_SEL_OK;
 }
 

@@ -262,3 +262,22 @@ def test_a_recorded_refresh_has_not_happened(oracle_lib, between):
                 c.check(f"the {what} graph, round {rnd}")
         c.select_and_check(f"eager behind the replays, round {rnd}")
     c.sel.destroy()
+
+
+@pytest.mark.parametrize("kind,instances", [("load", False), ("state", False), ("workers", False), ("workers", True), ("instances", True)])
+def test_graph_of_a_report_alone(oracle_lib, kind, instances):
+    """A report recorded without a selection: an eager selection with workers answers by it behind every replay, whatever
+    was reported and selected eagerly in between."""
+    c = _Cluster(oracle_lib, instances)
+    c.select_and_check("eager")
+    c.now(kind)
+    graph = _record(lambda: c.report(kind))
+    for rnd in range(4):
+        eager = kind if rnd % 2 == 0 else ("instances" if instances else "state")
+        c.now(eager)
+        if rnd >= 2:
+            c.select_and_check(f"{kind}, eager {eager}, round {rnd}")
+        c.stage(kind)
+        graph.replay()
+        c.select_and_check(f"{kind}, replay {rnd}")
+    c.sel.destroy()
