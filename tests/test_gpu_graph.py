@@ -281,3 +281,34 @@ def test_graph_of_a_report_alone(oracle_lib, kind, instances):
         graph.replay()
         c.select_and_check(f"{kind}, replay {rnd}")
     c.sel.destroy()
+
+
+def test_graph_of_instance_state_reports(oracle_lib):
+    """Worker and instance state report and the selection with workers in one graph, replayed between eager reports of both
+    kinds and eager selections."""
+    c = _Cluster(oracle_lib, instances=True)
+
+    def step():
+        c.report("workers")
+        c.report("instances")
+        c.select()
+
+    c.stage("workers")
+    c.stage("instances")
+    graph = _capture(step)                      # (the warm-up and the recorded step carry the same report)
+    for rnd in range(6):
+        if rnd % 3 == 1:
+            c.now("instances")
+            c.select_and_check(f"eager, round {rnd}")
+        elif rnd % 3 == 2:
+            c.now("instances")
+            c.now("workers")
+        c.stage("workers")
+        c.stage("instances")
+        for o in c.out:
+            o.fill_(-9)
+        graph.replay()
+        c.check(f"replay {rnd}")
+        if rnd % 2:
+            c.select_and_check(f"eager behind replay {rnd}")
+    c.sel.destroy()
