@@ -208,10 +208,19 @@ def test_a_small_call_captured_without_warm_up(oracle_lib):
     sel.destroy()
 
 
-@pytest.mark.parametrize("steps", [1, 6, 7, 8, 9, 15, 16, 17, 23, 24, 25, 30, 31, 32, 38, 39, 61, 62, 63])
+def _pool_bytes(sel):
+    """Bytes of the bodies of the handle's index (of the Active tier, if it has states), as of its latest selection."""
+    i = sel.info()
+    return i["index_bytes"] - 16 * i["num_slices"] - 4 * (i["index_steps"] + 1)
+
+
+LENGTHS = [1, 6, 7, 8, 9, 15, 16, 17, 23, 24, 25, 30, 31, 32, 38, 39, 61, 62, 63]
+
+
+@pytest.mark.parametrize("steps", LENGTHS)
 def test_bodies_of_every_length(oracle_lib, steps):
-    """Four lanes read a body's keys, eight each: staircases that end in front of, at and behind every lane's share, in the
-    first body and in the second, and bounds that meet each key exactly, miss it by one, meet all or none."""
+    """Six slices, whose bodies fit L1, so that every lane searches them by itself: bounds that meet each key exactly, miss it by
+    one, meet all or none."""
     tb = _staircase_table(3, steps)
     rows = np.arange(tb.V)
     acc = np.concatenate([tb.acc_bp[rows] + d for d in (-1, 0, 1)] + [np.full(tb.V, x) for x in (-2**31, 2**31 - 1)])
@@ -225,7 +234,52 @@ def test_bodies_of_every_length(oracle_lib, steps):
     sel = make_selector(tb, engine=2)
     _assert_equal_everywhere(gpu_select(sel, *q), want, f"{steps} steps")
     assert (want >= 0).any() and (want < 0).any()
+    assert _pool_bytes(sel) <= 24 * 1024
     sel.destroy()
+
+
+@pytest.mark.parametrize("steps", LENGTHS)
+def test_many_bodies_of_every_length(oracle_lib, steps):
+    """Four lanes read a body's keys, eight each, where the bodies are more than L1 holds: staircases that end in front of, at and
+    behind every lane's share, in the first body and in the second, and bounds that meet a key exactly, miss it by one, meet all
+    or none.  Batches that give a wavefront 16, 32 and 64 queries; every call, half of the tasks in either tier (whose
+    own staircases have as many steps); and the same on tables as small as in the test above."""
+    rng = np.random.default_rng([71, steps])
+    body = sum(14 * ((k + 2) // 2 * 2) for k in (min(steps, 31), min(steps, 62) - 31) if k > 0)
+    for half, large in ((2, False), (-(-110_000 // (2 * body)), True)):
+        tb = _staircase_table(2 * half, steps)
+        nth = np.arange(tb.V) % steps
+        load = (200 * nth).astype(np.int32)                      # in the Inactive tier the more accurate, the slower
+        state = (np.arange(tb.V) // steps % 2).astype(np.int32)  # odd tasks Active, even ones Inactive
+        n = 90_001
+        row = rng.integers(0, tb.V, n)
+        bidx = rng.integers(0, 2, n)
+        key = tb.lat_us[row, bidx].astype(np.int64) + np.where(rng.random(n) < 0.5, load[row], 0)
+        other = np.clip(row + rng.integers(-2, 3, n), 0, tb.V - 1)
+        acc = tb.acc_bp[other].astype(np.int64) + rng.integers(-1, 2, n)
+        slo = key + rng.integers(-1, 2, n)
+        acc[::17], slo[::19] = rng.choice([-2**31, 2**31 - 1], acc[::17].size), rng.choice([0, 2**31 - 1], slo[::19].size)
+        q = tuple(x.astype(np.int32) for x in (tb.task_id[row], slo, acc, bidx))
+        sel = make_selector(tb, engine=2)
+        want = oracle_lib.select(*table_args(tb), *q)
+        closest = oracle_lib.select_closest(*table_args(tb), *q)
+        assert (want >= 0).any() and (want < 0).any()
+        for size in (3001, 50_001, 74_001, 90_001):   # (suggestions turn to the lookup kernel above 75,000 where slices have second bodies)
+            cut = tuple(x[:size] for x in q)
+            _assert_equal_everywhere(gpu_select(sel, *cut), want[:size], f"{steps} steps N={size}")
+            for g, w in zip(gpu_select_closest(sel, *cut), closest):
+                _assert_equal_everywhere(g, w[:size], f"{steps} steps closest N={size}")
+        assert (_pool_bytes(sel) > 96 * 1024) == large
+        sel.load_states(state, load)
+        for call, want in ((gpu_select_tiered, oracle_lib.select_tiered(*table_args(tb), state, load, *q)),
+                           (gpu_case1, oracle_lib.select_case1(*table_args(tb), state, load, *q))):
+            assert all((want[1] == tier).any() for tier in (0, 1, 2))
+            for size in (3001, 50_001, 90_001, 180_002):
+                many = tuple(np.tile(x, 2)[:size] for x in q)
+                for g, w in zip(call(sel, *many), want):
+                    _assert_equal_everywhere(g, np.tile(w, 2)[:size], f"{steps} steps {call.__name__} N={size}")
+        assert (_pool_bytes(sel) > 96 * 1024) == large
+        sel.destroy()
 
 
 @pytest.mark.parametrize("workers", [False, True])
