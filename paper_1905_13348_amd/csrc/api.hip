@@ -528,6 +528,13 @@ int ensure_open(infaas_sel *h, int64_t n, bool side)
     return INFAAS_SEL_OK;
 }
 
+// Bytes of the bodies of the index as of its latest build that is known of (in groups: when it was loaded).
+int64_t body_pool(const infaas_sel *h)
+{
+    const volatile uint32_t *now = h->host_stats;
+    return h->ix.num_groups > 1 ? h->ix_bytes : now ? now[4] : h->ix_stats[kCtlPool];
+}
+
 // Up to this many queries a selection is answered straight from global memory, one lane per query, rather than
 // through an LDS mirror of the index.  The mirror costs its fill (2-4 us, more with many slices) and pays with 4
 // ps per query against 15 to 20.  Measured, us for 100,000 / 200,000 / 300,000 queries, direct and mirrored: config 2's table, whole index in
@@ -546,19 +553,11 @@ int64_t direct_limit(const infaas_sel *h, bool closest = false)
     if (h->index_lds_bytes == 0) return kDirectQueries;   // (no mirror, four interleaved queries per lane)
     const int64_t room = (int64_t)h->index_lds_bytes - kLdsCtrlBytes - lds_header_bytes(h->tv.S);
     const volatile uint32_t *now = h->host_stats;
-    const int64_t pool = h->ix.num_groups > 1 ? h->ix_bytes : now ? now[4] : h->ix_stats[kCtlPool];
+    const int64_t pool = body_pool(h);
     const uint32_t steps = now ? now[kCtlMaxK - kCtlMaxK0] : h->ix_stats[kCtlMaxK];
     const uint32_t open = now ? now[kCtlTrunc - kCtlMaxK0] + now[kCtlNoBody - kCtlMaxK0] : h->ix_stats[kCtlTrunc] + h->ix_stats[kCtlNoBody];
     if (closest && open == 0 && steps > (uint32_t)kBodySteps && 5 * pool <= 7 * room) return kDirectSuggestions;
     return pool <= room ? kDirectQueries : kDirectQueries * pool / room;
-}
-
-// Whether the bodies of the index fit a compute unit's L1 (32 KB) with room to spare, so that a lane's own bisection stays there: 90,001
-// queries on 32 slices (5 KB) 6.2 us so, 6.6 with four lanes to a body; on 800 slices (237 KB) 6.3 and 5.3.
-bool in_l1(const infaas_sel *h)
-{
-    const volatile uint32_t *now = h->host_stats;
-    return h->ix.num_groups == 1 && (now ? now[4] : h->ix_stats[kCtlPool]) <= 24 * 1024;
 }
 
 // One pass of the index engine over n <= 2^28 queries.
@@ -566,8 +565,8 @@ int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
     if (q.pass <= 1 && q.n <= direct_limit(h, q.pass == 1)) {
-        const hipError_t e = q.pass == 0 ? launch_direct_select(h->tv, h->ix, q, false, in_l1(h), h->num_cus, st, t.ev())
-                                         : launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, h->num_cus, st, t.ev());
+        const hipError_t e = q.pass == 0 ? launch_direct_select(h->tv, h->ix, q, false, body_pool(h), h->num_cus, st, t.ev())
+                                         : launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, body_pool(h), h->num_cus, st, t.ev());
         return HIP_OK(e) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
     }
     if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->d_park, h->index_lds_bytes, h->num_cus, st, t.ev())))
@@ -670,7 +669,7 @@ bool use_ranked(const infaas_sel *h)
 int ranked_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_SCAN_LDS, st);
-    if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, true, false, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
+    if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, true, body_pool(h), h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
     return INFAAS_SEL_OK;
 }
 
@@ -1233,7 +1232,8 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
         if (closest) q.closest = d_out_closest + done;
         if (direct) {
             LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
-            if (!HIP_OK(launch_direct_modes(h->tv, h->ix, h->inactive->tv, h->inactive->ix, q, true, h->num_cus, st, t.ev())))
+            if (!HIP_OK(launch_direct_modes(h->tv, h->ix, h->inactive->tv, h->inactive->ix, q, true, std::max(body_pool(h), body_pool(h->inactive)),
+                                           h->num_cus, st, t.ev())))
                 return INFAAS_SEL_ERR_HIP;
             continue;
         }
@@ -1491,7 +1491,7 @@ int infaas_sel_select_noalloc(infaas_sel_t *h, int64_t N, const int32_t *d_task,
     q.pass = 0;
     // no event pair even when timing is on: taking one may create it
     if (q.n <= direct_limit(h)) {
-        if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, in_l1(h), h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
+        if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, body_pool(h), h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
     } else if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->static_park, h->index_lds_bytes, h->num_cus,
                                     (hipStream_t)hip_stream, nullptr)))
         return INFAAS_SEL_ERR_HIP;

@@ -3,6 +3,8 @@
 #include "internal.h"
 #include "lookup_common.h"
 
+#include <type_traits>
+
 namespace infaas {
 
 namespace {
@@ -30,7 +32,7 @@ __device__ __forceinline__ Query load_query(const TableView &tv, const QueryView
 // in their bodies go through their entries in rank order at once; otherwise only with what the bodies leave
 // open.  Counts in st what became of the queries, as the lookup kernel does; no query is decided by an
 // LDS copy here, so all count as parked.
-template <bool kRanked, bool kAhead, bool kByFour = true>
+template <bool kRanked, bool kAhead, bool kByFour>
 __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want,
                                                       uint32_t (&st)[kLookupStats])
 {
@@ -151,9 +153,9 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, Ind
 // The other modes of the lookup in one launch: both tiers after one another for the lanes that need them, no lists
 // in between.  kTiers: ta / ia serve the Active variants, tb / ib the Inactive ones (otherwise there is only ta);
 // kSuggest: the closest variant (of both tiers) where there is no answer; kWorker: the worker of every answer.
-// At 1001 to 100,001 queries bound by its launch and the chain of dependent reads, like the two passes of the
-// lookup kernel that it replaces, but once and without the two LDS mirrors.
-template <bool kTiers, bool kSuggest, bool kWorker>
+// Bound by its launch and the chain of dependent reads, like the two passes of the lookup kernel that it replaces, but
+// once and without the two LDS mirrors.
+template <bool kTiers, bool kSuggest, bool kWorker, bool kByFour>
 __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, IndexView ia, TableView tb, IndexView ib, QueryView q, int32_t per)
 {
     const int32_t lane = threadIdx.x & 63, step = per * (kDirThreads / 64);
@@ -167,11 +169,11 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
         const int64_t i = i0 + (int32_t)(threadIdx.x >> 6) * per + lane;
         const bool mine = lane < per;
         const Query u = load_query(ta, q, i, mine);
-        int32_t ans = select_from_memory<false, false>(ta, ia, u, u.valid, st), tier = ans >= 0 ? 1 : 0;
+        int32_t ans = select_from_memory<false, false, kByFour>(ta, ia, u, u.valid, st), tier = ans >= 0 ? 1 : 0;
         if (kTiers) {
             const bool next = u.valid && ans < 0;
             if (__ballot(next)) {
-                const int32_t row = select_from_memory<false, false>(tb, ib, u, next, st);
+                const int32_t row = select_from_memory<false, false, kByFour>(tb, ib, u, next, st);
                 if (next && row >= 0) { ans = row; tier = 2; }
             }
         }
@@ -199,32 +201,59 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
     leave_statistics(kTiers ? ib : ia, l_st, st);
 }
 
+// Who searches a body: its lane by bisection, which is fast where L1 holds the lines that it probes, or four lanes that read all of its
+// keys (search_bodies_by_four), which takes a third more registers and more instructions.  Kernel us, bisection / four lanes, by the bytes of
+// the bodies:
+//   selection, 100,000 queries: 5 KB 4.2 / 4.6, 23 KB 5.2 / 5.4, 38 KB 5.1 / 5.0, 42 KB (two bodies to a slice) 5.8 / 6.4, 62 KB 5.6 / 5.5,
+//     92 KB 5.5 / 4.8, 134 KB 6.0 / 5.4, 173 KB 6.9 / 4.9
+//   two tiers, 1001 / 100,000 / 200,000: 5 KB 6.0 / 6.5 / 8.4 and 5.9 / 7.6 / 9.9, 38 KB 6.3 / 6.5 / 9.9 and 6.1 / 6.9 / 10.3, 60 KB 5.0 / 6.4 / 9.0
+//     and 4.8 / 7.0 / 9.5, 92 KB 5.4 / 7.0 / 10.5 and 4.9 / 7.0 / 9.4, 173 KB 6.7 / 8.6 / 13.1 and 6.4 / 8.0 / 10.9
+//   with a suggestion, one table, 60,000 / 80,000: 5 KB 7.2 / 7.7 and 7.7 / 8.5, 62 KB 7.4 / 8.4 and 7.7 / 8.4, 92 KB 7.4 / 8.2 and 7.6 / 8.0, 173 KB
+//     9.1 / 10.0 and 8.8 / 9.4
+//   and two tiers, 45,000 / 100,000 / 200,000: 5 KB 11.4 / 12.0 / 14.8 and 12.7 / 13.6 / 17.1, 62 KB 11.8 / 13.0 / 16.0 and 12.4 / 13.8 / 16.8,
+//     92 KB 11.8 / 13.3 / 16.6 and 12.5 / 14.2 / 16.9, 134 KB 12.0 / 13.7 / 17.9 and 12.8 / 14.4 / 17.2, 250 KB 12.6 / 14.6 / 20.4 and 13.6 / 15.0 / 18.3
+bool four_lanes(bool tiers, bool suggest, int64_t n, int32_t per, int64_t pool, int num_cus)
+{
+    if (!tiers && !suggest) return pool > 48 * 1024;
+    if (!suggest) return per == 16 || pool > 64 * 1024;
+    return tiers ? n > (int64_t)num_cus * 512 && pool > 96 * 1024 : per == 64 && pool > 64 * 1024;
+}
+
+// How many queries a wavefront takes.  A batch too small to give every SIMD two full wavefronts is spread over as many with fewer queries
+// each, down to the 16 that one round of search_bodies_by_four serves (two tiers, 1001 queries 8.5 -> 6.6 us, with workers 8.6 -> 6.7; to
+// bisection 16 to 64 of them are the same in a selection, and 16 up to 7% faster with two tiers).  In rank order, where a
+// wavefront finishes its hard queries one after the other, down to one.  (us for 1001 / 10,001 / 30,001 queries, 64 to a wavefront and so: 2000 entries of random
+// accuracy and latency to a slice, most queries without an answer, 75 / 75 / 76 and 6.1 / 14 / 23, with the scan engine 37 / 63 / 89; every entry a step, nothing
+// hard about it, 6.0 / 6.1 / 6.1 and 6.2 / 6.2 / 6.2, where four wavefronts per SIMD took 6.1 / 6.6 / 8.1.)
+int32_t queries_per_wave(int64_t n, int32_t least, int num_cus)
+{
+    int32_t per = 64;
+    while (per > least && (n + per / 2 - 1) / (per / 2) <= (int64_t)num_cus * 8) per /= 2;
+    return per;
+}
+
 }  // namespace
 
-hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, bool in_l1, int num_cus,
+hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int64_t pool, int num_cus,
                                 hipStream_t st, const LaunchEvents *ev)
 {
-    // A batch too small to give every SIMD two full wavefronts is spread over as many with fewer queries each, down to the
-    // 16 that one round of search_bodies_by_four serves (two tiers, 1001 queries 8.5 -> 6.6 us, with workers 8.6 -> 6.7).
-    // In rank order, where a wavefront finishes its hard queries one after the other, down to one.  (us for 1001 / 10,001 / 30,001 queries, 64 to a
-    // wavefront and so: 2000 entries of random accuracy and latency to a slice, most queries without an answer, 75 / 75 / 76 and
-    // 6.1 / 14 / 23, with the scan engine 37 / 63 / 89; every entry a step, nothing hard about it, 6.0 / 6.1 / 6.1 and 6.2 / 6.2 /
-    // 6.2, where four wavefronts per SIMD took 6.1 / 6.6 / 8.1.)
-    int32_t per = 64;
-    while (per > (ranked ? 1 : 16) && ((int64_t)q.n + per / 2 - 1) / (per / 2) <= (int64_t)num_cus * 8) per /= 2;
+    const int32_t per = queries_per_wave(q.n, ranked ? 1 : 16, num_cus);
     const int64_t step = per * (kDirThreads / 64), want = ((int64_t)q.n + step - 1) / step, most = index_stat_blocks(num_cus);
-    auto kernel = ranked ? k_direct_select<true, true> : in_l1 ? k_direct_select<false, false> : k_direct_select<false, true>;
+    auto kernel = ranked ? k_direct_select<true, true> : four_lanes(false, false, q.n, per, pool, num_cus) ? k_direct_select<false, true> : k_direct_select<false, false>;
     return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, tv, ix, q, per);
 }
 
 hipError_t launch_direct_modes(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, const QueryView &q,
-                               bool tiers, int num_cus, hipStream_t st, const LaunchEvents *ev)
+                               bool tiers, int64_t pool, int num_cus, hipStream_t st, const LaunchEvents *ev)
 {
-    int32_t per = 64;   // (as above)
-    while (per > 16 && ((int64_t)q.n + per / 2 - 1) / (per / 2) <= (int64_t)num_cus * 8) per /= 2;
+    const int32_t per = queries_per_wave(q.n, 16, num_cus);
     const int64_t step = per * (kDirThreads / 64), want = ((int64_t)q.n + step - 1) / step, most = index_stat_blocks(num_cus);
-    auto kernel = !tiers ? k_direct_modes<false, true, false> : q.worker ? (q.closest ? k_direct_modes<true, true, true> : k_direct_modes<true, false, true>)
-                                                              : (q.closest ? k_direct_modes<true, true, false> : k_direct_modes<true, false, false>);
+    auto pick = [&](auto by_four) {
+        constexpr bool f = decltype(by_four)::value;
+        return !tiers ? k_direct_modes<false, true, false, f> : q.worker ? (q.closest ? k_direct_modes<true, true, true, f> : k_direct_modes<true, false, true, f>)
+                                                              : (q.closest ? k_direct_modes<true, true, false, f> : k_direct_modes<true, false, false, f>);
+    };
+    auto kernel = four_lanes(tiers, q.closest != nullptr, q.n, per, pool, num_cus) ? pick(std::true_type{}) : pick(std::false_type{});
     return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, ta, ia, tb, ib, q, per);
 }
 
