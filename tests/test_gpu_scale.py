@@ -231,9 +231,9 @@ def test_scale_errors():
 
 @pytest.mark.parametrize("per_arch", [1, 2, 5, 6, 7, 10, 11, 14, 15])
 def test_scale_lists_of_every_length_and_exact_quotients(oracle_lib, per_arch):
-    """Candidate lists that end at and beside the block's five places and the chunks of four behind them (nothing in an
+    """Candidate lists that end at and beside the block's five places and the pairs behind them (nothing in an
     architecture beats anything else: the dearer, the faster and the slower to answer), and loads that a whole number of instances carries
-    exactly, or but for one query per second, up to quotients of 10^9."""
+    exactly, or but for one query per second."""
     rng = np.random.default_rng([47, per_arch])
     archs, B = 40, 2
     V = archs * per_arch
@@ -255,4 +255,30 @@ def test_scale_lists_of_every_length_and_exact_quotients(oracle_lib, per_arch):
         sel.load_scaling(*prof, lam, slack)
         _check(oracle_lib, sel, tb, prof, lam, slack, req, f"{per_arch} to an architecture")
         _check(oracle_lib, sel, tb, prof, lam, slack, req, f"{per_arch} to an architecture", down=True)
+    sel.destroy()
+
+
+def test_scale_largest_needs_throughputs_and_costs(oracle_lib):
+    """Both ends of what the kernel divides and multiplies: a need of up to 2 * 10^9 queries per second (10^9 at a slack of 200) by
+    throughputs from 1 to 2^31 - 1, and up to 2 * 10^9 instances at the largest cost of one."""
+    rng = np.random.default_rng(53)
+    archs, per_arch, B = 300, 9, 2
+    V = archs * per_arch
+    qps = rng.choice([1, 2, 3, 7, 999_999_999, 10**9, 10**9 + 1, 2 * 10**9 - 1, 2 * 10**9, 2 * 10**9 + 1, 2**31 - 2, 2**31 - 1], V)
+    tb = workloads.VariantTable(num_tasks=1, batch_sizes=np.arange(1, B + 1, dtype=np.int32), task_id=np.zeros(V, np.int32),
+                                acc_bp=np.full(V, 8000, np.int32), lat_us=(rng.integers(100, 110, V)[:, None] + np.arange(B)).astype(np.int32),
+                                cost=np.ones((V, B), np.int32), queue_us=np.zeros(V, np.int32))
+    prof = tuple(np.asarray(x, np.int32) for x in
+                 (np.arange(V) // per_arch, qps, rng.choice([0, 1, 2, 1_048_575, 1_048_576], V), rng.choice([0, 1, 2**31 - 2, 2**31 - 1], V)))
+    R = 40_001
+    variant = rng.integers(0, V, R)
+    load = rng.choice([0, 1, 2, 3, 6, 7, 499_999_999, 500_000_000, 999_999_999, 10**9], R)
+    req = tuple(np.asarray(x, np.int32) for x in
+                (variant, rng.choice([0, 1, 2, 999_999, 1_000_000], R), load, rng.choice([99, 104, 110, 2**31 - 1], R), rng.integers(0, B, R)))
+    sel = make_selector(tb, engine=0)
+    for lam, slack in ((0, 200), (1000, 200), (1000, 199), (1, 0)):
+        sel.load_scaling(*prof, lam, slack)
+        want = _check(oracle_lib, sel, tb, prof, lam, slack, req, "largest")
+        assert slack != 200 or want[2].max() == 2 * 10**9
+        _check(oracle_lib, sel, tb, prof, lam, slack, req, "largest", down=True)
     sel.destroy()
