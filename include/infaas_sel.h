@@ -378,7 +378,7 @@ int infaas_sel_select_workers_closest(infaas_sel_t *h, int64_t N,
  * program's objective wins:
  *     replicate:  C[cur] * (inst(cur) - n_cur) * (1 + lambda * T_load[cur])
  *     upgrade:    C[u] * inst(u) * (1 + lambda * T_load[u]) - C[cur] * n_cur
- * in exact integer arithmetic (lambda per second, T_load in microseconds, 128-bit products).
+ * in exact integer arithmetic (lambda per second, T_load in microseconds).
  * Readings where the text is silent: among upgrades of equal cost the lower row; replication
  * wins a tie against the cheapest upgrade; worker resources (constraint 3) are not part of the
  * decision.  Scaling down is infaas_sel_scale_down.

@@ -542,10 +542,11 @@ int64_t body_pool(const infaas_sel *h)
 // 8.6 and 10.3 / 10.8 / 11.4 (700,000: 15.5 and 16.7); config 3's, 7%, 200,000 / 400,000: 7.9 / 12.1 and 18 / 22.  The less of the index
 // the mirror holds, the later it pays.  (Where no slice has a second body the line could lie at twice as many.)
 constexpr int64_t kDirectQueries = 100000;
-// With suggestions the same holds (us for 65,000 / 100,000 / 300,000 queries: 100 tasks of 200 variants 7.9 / 9.5 / 17.9 direct,
-// 13.4 / 13.3 / 14.9 mirrored; config 3's table 9.4 / 11.2 / 22.5 and 27.6 / 28.6 / 33.4), except where the mirror holds nearly the
+// With suggestions the same holds (us for 65,000 / 100,000 / 300,000 queries: 100 tasks of 200 variants 7.6 / 8.0 / 15.5 direct,
+// 11.5 / 12.7 / 13.7 mirrored; config 3's table 10.5 / 11.5 / 21.9 and 35 / 38 / 42), except where the mirror holds nearly the
 // whole index (it does at 1.3 times its room, not at 1.5) and slices have second bodies, both of which a suggestion
-// searches (config 2's: 9.0 / 10.6 / 18.4 direct, 9.7 / 9.9 / 10.7 mirrored).  Slices that are not completely indexed
+// searches (config 2's: 8.6 / 9.5 / 17.3 direct, 9.6 / 10.1 / 10.7 mirrored; 60 tasks of 800 8.6 / 9.5 / 16.7 and 9.6 / 10.0 / 10.6: by
+// these the line could lie somewhat above 100,000).  Slices that are not completely indexed
 // (their queries cost the lookup kernel more than all others) leave the limit where it is for the selection.
 constexpr int64_t kDirectSuggestions = 75000;
 int64_t direct_limit(const infaas_sel *h, bool closest = false)
@@ -1204,11 +1205,15 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     DeviceGuard g(h->device);
     if (!g.ok) return INFAAS_SEL_ERR_HIP;
     hipStream_t st = (hipStream_t)hip_stream;
-    // Two mirrors and two launches against one kernel: three tenths more than the sum of the tables' limits, and so below the 2^18 queries
-    // that are in flight at once.  (us for 100,000 / 200,000 / 300,000 / 450,000 queries, direct and mirrored: two tiers behind a state report on
+    // Two mirrors and two launches against one kernel: three tenths more than the sum of the tables' limits.  Where both mirrors hold
+    // everything that is 260,000, just below the 2^18 queries that are in flight at once, where the time makes a step (us for 100,000 /
+    // 200,000 / 300,000 / 450,000 queries, direct and mirrored: two tiers behind a state report on
     // 100 tasks of 200 variants 23.3 / 25.6 / 28.8 / 32.0 and 30.8 / 31.7 / 31.8 / 33.3, on 50 of 2000 29.4 / 32.3 / 36.0 / 40.0 and 36.5 / 37.1 /
     // 37.7 / 38.5; complete Case I with workers 13.7 / 17.2 / 24.2 / 29.2 and 25.7 / 27.5 / 30.9 / 33.8, 14.8 / 18.1 / 25.5 / 30.5 and 22.2 / 24.4 /
-    // 23.1 / 24.9.)
+    // 23.1 / 24.9).  Where they hold a part of it the line grows with the limits, and direct is further ahead: at 1 / 1.3 / 2 times the sum, two
+    // tiers and complete Case I with workers, 200 tasks of 60 variants (60% of it in the mirror, sum 232,000) 10.6 / 13.0 / 18.2 and 19.8 / 20.6 / 22.8, 19.4 /
+    // 28.4 / 34.5 and 46.6 / 48.4 / 51.4; 400 of 100 (22%, 661,000) 24.9 / 29.7 / 42.0 and 51.1 / 57.8 / 74.7, 46.7 / 56.1 / 79.0 and 90.8 / 98.9 / 135.6; 1000
+    // of 100 on average (8%, 1.87M) 59.7 / 74.7 / 123 and 126 / 157 / 234, 134 / 172 / 282 and 215 / 295 / 407.
     const bool direct = N <= (direct_limit(h) + direct_limit(h->inactive)) / 10 * 13;
     // The lists are allocated for direct calls too: the limits follow the index, and the same call after a report
     // may need them where nothing can be allocated (under capture, after an eager call to warm up).  A direct call

@@ -13,7 +13,7 @@
 // else the decision reads about the variant, into a 128-byte block per (batch size, variant), so a
 // request costs one uncoalesced line (longer prefixes continue in the shared list).  All costs are
 // exact integers (times 1,000,000, because lambda is per second and the loading latency in
-// microseconds), compared in 128 bits.
+// microseconds) of at most 94 bits.
 //
 // Scaling down (Section 4.2.2, second algorithm) is the same kernel on a second set of blocks: keep,
 // or remove one instance when the others still carry the load, or downgrade to a variant of the same
