@@ -59,8 +59,7 @@ enum {
 enum {
     /* Default: the staircase index (per slice, the variants no cheaper variant dominates; a
      * query is two binary searches and a bit-set intersection), mirrored in one compute unit's
-     * LDS when it fits; when it does not, large batches are binned by groups of tasks whose part of
-     * the index fits and looked up group by group, small ones read it from global memory.  Queries the index cannot decide
+     * LDS when it fits; when it does not, or the batch is small, queries read it from global memory.  Queries the index cannot decide
      * (its per-slice capacity was exceeded) are finished by a rank-ordered scan inside the same
      * kernel, so results never depend on the engine.  While more than half of the slices exceed the
      * capacity, slices are searched in rank order through levels of running extremes instead. */
@@ -481,9 +480,9 @@ enum {
     INFAAS_SEL_K_WORKER_TABLES = 11,/* worker of every variant */
     INFAAS_SEL_K_STEP_WORKERS = 12,/* worker of every step of an index */
     INFAAS_SEL_K_SCALE = 13,     /* scaling decisions */
-    INFAAS_SEL_K_GROUP_BIN = 14, /* grouped index: queries binned by group of tasks */
-    INFAAS_SEL_K_GROUP_LOOKUP = 15,/* grouped index: lookup, one group's bodies in LDS per workgroup */
-    INFAAS_SEL_K_GROUP_FINISH = 16,/* grouped index: answers back into query order */
+    INFAAS_SEL_K_GROUP_BIN = 14, /* (14 to 16 are not launched any more) */
+    INFAAS_SEL_K_GROUP_LOOKUP = 15,
+    INFAAS_SEL_K_GROUP_FINISH = 16,
     INFAAS_SEL_K_INSTANCE_STATES = 17,/* instance state report */
     INFAAS_SEL_K_CLOSEST_SCAN = 18,/* closest-variant suggestions by exhaustive scan (no index) */
     INFAAS_SEL_K_SCALE_DOWN = 19,/* scaling-down decisions */
@@ -527,7 +526,7 @@ typedef struct {
     int64_t lookup_unanswered;  /* ... that ended without a feasible variant */
     int32_t index_groups;       /* 1: one LDS holds (part of) the whole index; more: the tasks are dealt to this many
                                    groups whose staircases fit one LDS each, and calls of a million queries or more
-                                   are binned by group and looked up group by group */
+                                   read one line of memory per query */
     int32_t reserved0;
 } infaas_sel_info;
 int infaas_sel_get_info(infaas_sel_t *h, infaas_sel_info *out);

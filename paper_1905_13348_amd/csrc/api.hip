@@ -135,10 +135,7 @@ struct infaas_sel {
     bool have_index = false;
     uint32_t index_lds_bytes = 0;     // dynamic LDS of the lookup kernel; 0 = read the index from global memory
     uint32_t ix_stats[kCtlWords] = {0};      // copy of ix.ctrl taken after the build at load time
-    std::vector<int32_t> group_task0;        // host copy of ix.group_task0 (empty: one group)
     int64_t ix_bytes = 0, ix_steps = 0;      // pool bytes and steps of the index when it was loaded
-    GroupScratch gs{};                       // scratch of the group-by-group selection (grows with the batch)
-    int64_t gs_queries = 0, gs_bytes = 0;    // batch size it is good for; its size
     int32_t *d_park = nullptr;        // queues of parked queries of the lookup kernel (fixed size)
     int64_t park_bytes = 0;
     uint32_t *host_stats = nullptr;   // pinned, device-visible: six counters of the latest index build (kCtlMaxK0 .., pool, steps)
@@ -196,18 +193,9 @@ struct infaas_sel {
         d_park = nullptr;
         park_bytes = 0;
         ix = IndexView{};
-        group_task0.clear();
-        free_group_scratch();
         last_stats = nullptr;
         have_index = false;
         index_lds_bytes = 0;
-    }
-    void free_group_scratch()
-    {
-        (void)hipFree(gs.rec); (void)hipFree(gs.perm); (void)hipFree(gs.res); (void)hipFree(gs.desc);
-        (void)hipFree(gs.gcount);
-        gs = GroupScratch{};
-        gs_queries = gs_bytes = 0;
     }
     void free_scratch()
     {
@@ -315,7 +303,7 @@ constexpr uint32_t kGroupRegionBytes = 144 * 1024;   // a group's bodies: what o
 constexpr uint32_t kGroupMaxSlices = 1900;           // ... 8 bytes of header each
 constexpr uint32_t kGroupStepCap = 16384;            // entries of step_row per group (a region holds at most 10,532 steps)
 constexpr int32_t kGroupMaxGroups = 120;
-constexpr int32_t kGroupMaxTasks = 16384;            // the binning kernel keeps the group of every task in LDS
+constexpr int32_t kGroupMaxTasks = 16384;            // (above, one region)
 constexpr uint32_t kGroupHotRows = 8;
 
 // Starting values of the allocator counters and the statistics, then one build, then the counters back.
@@ -392,17 +380,25 @@ int create_index(infaas_sel *h)
             seg += (L + 3) & ~3;
         }
     }
+    // keys run from 1 to the highest accuracy's (as far as there are keys for it), thresholds to one more
+    int64_t top = 1;
+    for (int32_t a : h->h_acc) top = std::max<int64_t>(top, std::min<int64_t>((int64_t)a - h->tv.acc_base, 65533) + 1);
+    ix.line_shift = std::min(kLineMaxShift, (uint32_t)__builtin_clz((uint32_t)(top + 1)));
+    ix.line_top = (uint32_t)top + 1u;
+    ix.line_rows = h->V <= (int64_t)1 << ix.line_shift ? 1u : 0u;
+    ix.line_plane = (uint32_t)(S + 1) * kLineBytes;
     // one allocation: the pool, then the headers, so that one 32-bit offset reaches both; behind them rank_hdr and,
-    // at a multiple of their size, the nodes of TableView::rank_nodes (counted with the table: they do not follow the index)
+    // at a multiple of their size, the nodes of TableView::rank_nodes and the lines (counted with the table: they do not follow the index)
     ix.pool_bytes &= ~127u;
     const size_t nstats = (size_t)index_stat_blocks(h->num_cus) * kLookupStats;
-    bool ok = dev_alloc(&ix.pool, (size_t)ix.pool_bytes + rank_nodes_at((int32_t)S) + (size_t)std::max<int64_t>(nodes, 1) * 128) == hipSuccess &&
+    bool ok = dev_alloc(&ix.pool, (size_t)ix.pool_bytes + rank_nodes_at((int32_t)S) + (size_t)std::max<int64_t>(nodes, 1) * 128 + (size_t)kLinePlanes * ix.line_plane) == hipSuccess &&
               dev_alloc(&ix.step_row, ix.step_cap) == hipSuccess && dev_alloc(&ix.ctrl, kCtlWords) == hipSuccess &&
               dev_alloc(&ix.stats, 4 + nstats) == hipSuccess && dev_alloc(&ix.gctrl, 2 * (size_t)kGroupMaxGroups) == hipSuccess &&
               dev_alloc(&ix.slice_room, (size_t)S) == hipSuccess;
     if (ix.stats) ix.stats += 4;   // (in front of it how many entries are in use)
     if (ok) {
         ix.hdr = (uint4 *)(ix.pool + ix.pool_bytes);
+        ix.lines = (uint8_t *)ix.hdr + rank_nodes_at((int32_t)S) + (size_t)std::max<int64_t>(nodes, 1) * 128;
         h->tv.rank_hdr = (const uint4 *)((char *)ix.hdr + rank_hdr_at((int32_t)S));
     }
     h->ix = ix;
@@ -418,7 +414,10 @@ int create_index(infaas_sel *h)
     uint8_t dummy[kDummyBodyBytes] = {0};
     for (uint32_t i = 8; i < 16; ++i) dummy[i] = 0xFF;  // latency sentinels of the empty body (Re = 2)
     const int32_t none = -1;
+    uint2 empty[kLineBytes / 8];   // the line of the empty slice
+    for (uint2 &e : empty) e = make_uint2(0u, kLineEnd);
     if (!HIP_OK(hipMemset(ix.stats - 1, 0, 4)) ||
+        !HIP_OK(hipMemcpy(ix.lines + (size_t)S * kLineBytes, empty, sizeof(empty), hipMemcpyHostToDevice)) ||
         !HIP_OK(hipMemcpy(ix.pool, dummy, sizeof(dummy), hipMemcpyHostToDevice)) ||
         !HIP_OK(hipMemcpy(ix.step_row, &none, 4, hipMemcpyHostToDevice)) ||
         !HIP_OK(hipMemcpy(&ix.hdr[S], hdrs.data(), hdrs.size() * 4, hipMemcpyHostToDevice)) ||
@@ -427,7 +426,7 @@ int create_index(infaas_sel *h)
         return INFAAS_SEL_ERR_HIP;
     }
     h->have_index = true;
-    h->table_bytes += (S + 1) * 16 + nodes * 128;
+    h->table_bytes += (S + 1) * 16 + nodes * 128 + (S + 1) * kLinePlanes * kLineBytes;
     const int64_t fixed = kLdsCtrlBytes + lds_header_bytes((int32_t)S) + 16;
     const int64_t need = fixed + h->ix_stats[kCtlPool];
     // The lookup kernel mirrors the index in LDS when the slice headers leave at least half of it to
@@ -442,8 +441,8 @@ int create_index(infaas_sel *h)
     if (need > 2 * (int64_t)kLdsMax && h->T <= kGroupMaxTasks) {
         // Not even half of the bodies fit one LDS: deal the tasks, in order, to groups whose bodies do (with a
         // fifth of the region left free, because staircases grow and shrink with the load), and build
-        // again with one region of the pool per group.  Large batches of queries are then binned by
-        // group and looked up group by group, every workgroup with its group's bodies in LDS.
+        // again with one region of the pool per group, each with its own allocation counters: thousands of
+        // slices do not wait for their turn at one pair.
         std::vector<uint32_t> hdr((size_t)S * 4);
         if (!HIP_OK(hipMemcpy(hdr.data(), h->ix.hdr, (size_t)S * 16, hipMemcpyDeviceToHost))) { h->free_index(); return INFAAS_SEL_ERR_HIP; }
         const uint32_t hot = std::min(kGroupHotRows, hot_max) & ~1u;
@@ -482,7 +481,6 @@ int create_index(infaas_sel *h)
             for (int32_t g = 1; up && g < G; ++g)   // every region begins with the dummy body
                 up = HIP_OK(hipMemcpy(h->ix.pool + (size_t)g * kGroupRegionBytes, dummy, sizeof(dummy), hipMemcpyHostToDevice));
             if (!up || build_index_now(h) != INFAAS_SEL_OK) { h->free_index(); return INFAAS_SEL_ERR_HIP; }
-            h->group_task0.assign(task0.begin(), task0.end());
             return INFAAS_SEL_OK;
         }
     }
@@ -561,10 +559,14 @@ int64_t direct_limit(const infaas_sel *h, bool closest = false)
     return pool <= room ? kDirectQueries : kDirectQueries * pool / room;
 }
 
+bool use_lines(const infaas_sel *h, int64_t n);
+
 // One pass of the index engine over n <= 2^28 queries.
 int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
+    if (q.pass == 0 && use_lines(h, q.n))
+        return HIP_OK(launch_line_select(h->tv, h->ix, q, h->num_cus, st, t.ev())) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
     if (q.pass <= 1 && q.n <= direct_limit(h, q.pass == 1)) {
         const hipError_t e = q.pass == 0 ? launch_direct_select(h->tv, h->ix, q, false, body_pool(h), h->num_cus, st, t.ev())
                                          : launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, body_pool(h), h->num_cus, st, t.ev());
@@ -575,60 +577,11 @@ int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
     return INFAAS_SEL_OK;
 }
 
-// Below this many queries a call is answered by the one-kernel lookup even when the index is laid
-// out in groups: the four launches of the group-by-group path cost more than they save.
-constexpr int64_t kGroupMinQueries = (int64_t)1 << 20;
-
-// Scratch of the group-by-group selection for batches of up to n queries.
-int ensure_group_scratch(infaas_sel *h, int64_t n)
-{
-    if (h->gs.rec && h->gs_queries >= n) return INFAAS_SEL_OK;
-    // growing: nothing enqueued earlier may still use the old buffers
-    if (!HIP_OK(hipDeviceSynchronize())) return INFAAS_SEL_ERR_HIP;
-    h->free_group_scratch();
-    const int64_t tiles = (n + kGroupTile - 1) / kGroupTile, padded = tiles * kGroupTile;
-    const size_t G1 = (size_t)h->ix.num_groups + 1;
-    GroupScratch gs{};
-    bool ok = dev_alloc(&gs.rec, (size_t)padded) == hipSuccess && dev_alloc(&gs.perm, (size_t)padded) == hipSuccess &&
-              dev_alloc(&gs.res, (size_t)padded) == hipSuccess && dev_alloc(&gs.desc, (size_t)tiles * G1) == hipSuccess &&
-              dev_alloc(&gs.gcount, G1) == hipSuccess;
-    h->gs = gs;
-    if (!ok) {
-        h->free_group_scratch();
-        (void)hipGetLastError();
-        return INFAAS_SEL_ERR_OOM;
-    }
-    if (!HIP_OK(hipMemset(gs.gcount, 0, G1 * 4))) { h->free_group_scratch(); return INFAAS_SEL_ERR_HIP; }
-    int32_t most = 0;
-    for (size_t g = 0; g + 1 < h->group_task0.size(); ++g) most = std::max(most, (h->group_task0[g + 1] - h->group_task0[g]) * h->B);
-    h->gs.max_group_slices = most;
-    h->gs.stat_blocks = index_select_blocks(h->num_cus);
-    h->gs_queries = padded;
-    h->gs_bytes = padded * 14 + (int64_t)tiles * (int64_t)G1 * 4;
-    return INFAAS_SEL_OK;
-}
-
-bool use_groups(const infaas_sel *h, int64_t n)
-{
-    return h->have_index && h->ix.num_groups > 1 && n >= kGroupMinQueries && (int)h->ix.num_groups <= h->num_cus &&
-           group_bin_lds_bytes(h->T, (int32_t)h->ix.num_groups) <= 64 * 1024;
-}
-
-// One pass of the group-by-group selection over n <= 2^28 queries (scratch must be there).
-int group_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
-{
-    {
-        LaunchTimer t(h, INFAAS_SEL_K_GROUP_BIN, st);
-        if (!HIP_OK(launch_group_bin(h->tv, h->ix, q, h->gs, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
-    }
-    {
-        LaunchTimer t(h, INFAAS_SEL_K_GROUP_LOOKUP, st);
-        if (!HIP_OK(launch_group_lookup(h->tv, h->ix, q, h->gs, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
-    }
-    LaunchTimer t(h, INFAAS_SEL_K_GROUP_FINISH, st);
-    if (!HIP_OK(launch_group_finish(h->tv, h->ix, q, h->gs, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
-    return INFAAS_SEL_OK;
-}
+// Whether one pass over n queries of the plain selection reads the lines of the index, a tile per workgroup at a time: where the
+// bodies need more than twice one LDS and a tile per workgroup is half full.  us by this / by binning the queries by group of tasks whose bodies
+// fit one LDS, 8000 slices: 1.05M queries 15.9 / 52.9, 2M 22.5 / 54.5, 4M 39.5 / 66.4, 16M (Zipf) 135 / 238, 64M 459 / 729.
+constexpr int64_t kLineQueries = (int64_t)1 << 20;
+bool use_lines(const infaas_sel *h, int64_t n) { return h->ix.num_groups > 1 && n >= kLineQueries; }
 
 bool use_index(infaas_sel *h)
 {
@@ -1126,9 +1079,8 @@ int select_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     // (the suggestion comes from the index whenever there is one; without one, from an exhaustive scan behind
     // the scan engine's selection)
     const bool idx = (closest && h->have_index) || h->inactive != nullptr || use_index(h);
-    const bool groups = idx && !closest && !h->inactive && use_groups(h, std::min(N, kMaxPass));
     const bool ranked = !idx && use_ranked(h);
-    int rc = groups ? ensure_group_scratch(h, std::min(N, kMaxPass)) : idx || ranked ? INFAAS_SEL_OK : ensure_scratch(h, std::min(N, kMaxPass));
+    int rc = idx || ranked ? INFAAS_SEL_OK : ensure_scratch(h, std::min(N, kMaxPass));
     if (rc != INFAAS_SEL_OK) return rc;
     for (int64_t done = 0; done < N; done += kMaxPass) {
         QueryView q{};
@@ -1137,7 +1089,7 @@ int select_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
         q.bidx = d_batch_idx + done; q.out = d_out_variant + done;
         q.closest = closest ? d_out_closest + done : nullptr;
         q.pass = closest ? 1 : 0;
-        rc = groups && q.n >= kGroupMinQueries ? group_pass(h, q, st) : idx ? index_pass(h, q, st) : ranked ? ranked_pass(h, q, st) : scan_pass(h, q, st);
+        rc = idx ? index_pass(h, q, st) : ranked ? ranked_pass(h, q, st) : scan_pass(h, q, st);
         if (rc != INFAAS_SEL_OK) return rc;
         if (closest && !idx) {
             LaunchTimer t(h, INFAAS_SEL_K_CLOSEST_SCAN, st);
@@ -1495,7 +1447,9 @@ int infaas_sel_select_noalloc(infaas_sel_t *h, int64_t N, const int32_t *d_task,
     q.task = d_task; q.slo = d_slo_us; q.min_acc = d_min_acc_bp; q.bidx = d_batch_idx; q.out = d_out_variant;
     q.pass = 0;
     // no event pair even when timing is on: taking one may create it
-    if (q.n <= direct_limit(h)) {
+    if (use_lines(h, q.n)) {
+        if (!HIP_OK(launch_line_select(h->tv, h->ix, q, h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
+    } else if (q.n <= direct_limit(h)) {
         if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, body_pool(h), h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
     } else if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->static_park, h->index_lds_bytes, h->num_cus,
                                     (hipStream_t)hip_stream, nullptr)))
@@ -1688,9 +1642,7 @@ int infaas_sel_reserve(infaas_sel_t *h, int64_t max_queries)
     if (!g.ok) return INFAAS_SEL_ERR_HIP;
     const int64_t cap = std::max<int64_t>(1, std::min(max_queries, kMaxPass));
     if (h->loaded && h->inactive) return ensure_open(h, std::min(cap, kMaxTierPass), h->open_side);
-    if (h->loaded && use_index(h))   // the index engine needs per-query scratch only where it works group by group
-        return use_groups(h, cap) ? ensure_group_scratch(h, cap) : INFAAS_SEL_OK;
-    if (h->loaded && use_ranked(h)) return INFAAS_SEL_OK;
+    if (h->loaded && (use_index(h) || use_ranked(h))) return INFAAS_SEL_OK;   // (no scratch per query)
     return ensure_scratch(h, cap);
 }
 
@@ -1764,7 +1716,7 @@ int infaas_sel_get_info(infaas_sel_t *h, infaas_sel_info *out)
     out->lds_segment_limit = h->lds_limit;
     out->wide_segments = h->wide_segments;
     out->table_bytes = h->table_bytes;
-    out->scratch_bytes = h->scratch_bytes + h->park_bytes + h->open_bytes + h->gs_bytes;
+    out->scratch_bytes = h->scratch_bytes + h->park_bytes + h->open_bytes;
     if (h->have_index) {
         out->index_in_lds = h->index_lds_bytes > 0 ? 1 : 0;
         out->index_groups = (int32_t)h->ix.num_groups;

@@ -100,6 +100,29 @@ __device__ __forceinline__ void body_store(uint8_t *body, int g0, int kb, int la
     if (lane < (int)re) { m_a[lane] = r.ma; m_s[lane] = r.ms; }   // lanes beyond kb hold the full set
 }
 
+// The lines of slice s (internal.h) by one wavefront, lane j < K holding step j and its caller row.  usable: the slice's accuracies fit
+// the keys (and, where entries name steps instead of rows, it has a header that leads to them); `trunc`: it has more steps.
+__device__ __forceinline__ void store_lines(const IndexView &ix, int32_t s, int32_t K, bool usable, bool trunc, int lane, int32_t st_acc, uint32_t st_tot,
+                                            int32_t row, int32_t acc_base)
+{
+    const uint32_t n = usable ? (uint32_t)K : 0u;
+    const uint32_t lo = ((uint32_t)(st_acc - acc_base + 1) << ix.line_shift) | (ix.line_rows ? (uint32_t)row : (uint32_t)lane);
+    const uint32_t hi = st_tot < kLineMaxTot ? st_tot : kLineMaxTot;
+    // lane j's place among the entries: steps 0-15, 16-30, 31-46, 47-61
+    const uint32_t j = (uint32_t)lane, plane = (uint32_t)(j >= 16u) + (uint32_t)(j >= 31u) + (uint32_t)(j >= 47u), i = j - line_step0(plane);
+    uint2 *line = (uint2 *)(ix.lines + plane * ix.line_plane + (uint32_t)s * kLineBytes);
+    // (a plane that the slice does not get to is not read and not written; lane 62 has no step, and writes the last entry of plane 3)
+    const bool reached = plane == 0u || (plane == 1u ? n >= 16u : plane == 2u ? n > 31u : n >= 47u);
+    const bool is_step = j < n;
+    const uint32_t end = usable ? (trunc ? kLineRank : kLineEnd) : kLineRank;
+    uint32_t what = kLineEnd;
+    if (j == 15u && !usable) what = kLineRank;   // nothing of the slice is in its lines
+    if (j == 62u) what = end;
+    if (reached && j < 63u) line[line_place(i)] = is_step ? make_uint2(lo, hi) : make_uint2(0u, what);
+    if (lane == 63 && n >= 16u)   // plane 1 has 15 steps: its last entry tells whether there are more
+        ((uint2 *)(ix.lines + ix.line_plane + (uint32_t)s * kLineBytes))[line_place(15u)] = make_uint2(0u, n > 31u ? kLineMore : kLineEnd);
+}
+
 constexpr int kBuildWaves = 4;                    // slices (wavefronts) per workgroup
 
 // Highest accuracy and lowest latency-plus-queue over entries [lo, hi) of a slice (hi - lo > 0; lo a multiple
@@ -626,6 +649,8 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
             if (fill) store_step_worker(ix, s, lane, rec + (uint32_t)lane, worker);
         }
     }
+    if (inside)
+        store_lines(ix, s, K, !has || ((int64_t)hi - (int64_t)tv.acc_base <= 65533 && lo >= tv.acc_base && (fits || ix.line_rows)), trunc, lane, st_acc, st_tot, row, tv.acc_base);
     if (__builtin_expect(has && (trunc || !fits), 0)) {   // (the wavefront) queries of this slice may go through its entries in rank order
         const SliceColumns sc = slice_columns<kTwo>(s, t, b);
         write_rank_nodes<(64 * kBuildPer > kRankUnsorted)>(sc.acc, sc.tot, sc.nodes, sc.L, 0, sc.L, lane, INT32_MIN, 0xFFFFFFFFu, sc.acc_base);
@@ -902,7 +927,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableVi
     const bool narrow = __ballot(lane < K && (st_acc < tv.acc_base || (int64_t)st_acc - (int64_t)tv.acc_base > 65533)) == 0ull;
     const uint32_t size = has && narrow ? rows + size0 + body_bytes(re1) : 0u;   // (a multiple of 4)
     // requested now, used at the end: the caller rows of the steps
-    const int32_t row = (wave == 0 && lane < K) ? tv.orig_r[(int64_t)b * tv.Vp + seg + st_pos] : 0;
+    const int32_t row = (!(wave & 1) && lane < K) ? tv.orig_r[(int64_t)b * tv.Vp + seg + st_pos] : 0;
     // Room in the pool and in step_row.  Without groups the slices are placed in the order of their
     // numbers, so that the layout does not depend on which workgroup was quicker: when the bodies
     // outgrow the LDS mirror of the lookup kernel, the slices it leaves out are always those of the
@@ -968,6 +993,8 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableVi
         }
         s_off[0] = off; s_rec[0] = rec;
     }
+    // wavefront 2 the lines, while wavefront 3 waits for the room (which they depend on only where their entries name steps)
+    if (wave == 2 && ix.line_rows) store_lines(ix, s, K, !has || narrow, trunc, lane, st_acc, st_tot, row, tv.acc_base);
     if (wave == 3 && (!grouped || s == tv.S - 1)) {
         // What the slices before this one need, lane by lane (with groups only for the statistics).  An entry counts once it carries this
         // build's number.  The wait is bounded: every slice publishes as soon as it knows its steps,
@@ -1029,6 +1056,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableVi
     const uint32_t off = s_off[0], rec = s_rec[0];
     const bool fits = has && (uint64_t)off + size <= ix.pool_bytes && (uint64_t)rec + K <= ix.step_cap && narrow;
     uint8_t *body0 = ix.pool + off + rows;
+    if (wave == 2 && !ix.line_rows) store_lines(ix, s, K, !has || fits, trunc, lane, st_acc, st_tot, row, tv.acc_base);
     if (wave <= 1 && fits && (wave == 0 || k1)) {   // wavefront 0 writes the first body, wavefront 1 the second
         const int h = 2 * wave;
         BodyRegs r{pa, ps, parts[0][h][lane] | parts[1][h][lane] | parts[2][h][lane] | parts[3][h][lane],

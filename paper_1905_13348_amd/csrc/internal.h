@@ -136,7 +136,7 @@ struct IndexView {
     unsigned long long *slice_room;   // [S] what slice s needs, published by the build that places the slices in the
                          // order of their numbers: bytes (20 bits) | build number (12) | steps (20) | truncated (12);
                          // the other build leaves kRoomNone in every entry
-    // Groups.  When the bodies of all slices do not fit one compute unit's LDS, the tasks are dealt, in
+    // Groups.  When the bodies of all slices need more than twice one compute unit's LDS, the tasks are dealt, in
     // order, to num_groups groups whose bodies do: group g owns the tasks [group_task0[g],
     // group_task0[g + 1]), the bytes [g * region_bytes, (g + 1) * region_bytes) of the pool (every region
     // starts with a copy of the empty dummy body) and the entries [g * group_step_cap, ...) of step_row;
@@ -146,10 +146,30 @@ struct IndexView {
     const uint16_t *task_group;   // [T] group of every task; null when num_groups == 1
     const int32_t *group_task0;   // [num_groups + 1]
     uint32_t *gctrl;              // [2 num_groups] per group: bytes of its region and steps handed out
+    // Lines: the steps once more, for searches straight from global memory (layout below).
+    uint8_t *lines;      // [kLinePlanes][S + 1] lines of 128 bytes; slice S is the empty one
+    uint32_t line_plane; // bytes of a plane
+    uint32_t line_shift; // bits of a first word below the accuracy key; they hold the caller row ...
+    uint32_t line_top;   // the highest accuracy threshold: above every key
+    uint32_t line_rows;  // ... where this is 1; where rows have more bits, the number of the step in its slice
     StepFill fill;       // for the build of both tiers' tables only
     uint32_t *stats;     // [kStatShare x compute units][kLookupStats] what the most recent lookup launch did;
                          // the word in front of it: how many entries that launch has written
 };
+// A line is 16 entries of two words in rank order: {accuracy key << line_shift | caller row, latency-plus-queue}.  Accuracies are
+// compared without taking the words apart (the threshold is shifted up and the row below it can only add), so a query tries an entry
+// with two comparisons, and the first entry that fits names the answer: no header, no sets, no row to look up elsewhere.  Four lanes read a line, 32
+// bytes each: entries 4 i .. 4 i + 3 lie where the i-th of them finds them with two 16-byte reads of which each
+// covers 64 consecutive bytes (line_place).  The steps of a slice are spread over kLinePlanes lines, one in each plane, so that the first
+// lines, where nearly all answers are, lie close together: steps 0-15, 16-30, 31-46 and 47-61 (the second body's begin a line).
+// The last entry of a line tells what follows: a step, or kLineMore below: the next line; kLineRank: the search in
+// rank order; kLineEnd: nothing.  Entries behind a slice's last step are {0, kLineEnd}, which nothing fits.
+constexpr int kLinePlanes = 4, kLineBytes = 128;
+constexpr uint32_t kLineEnd = 0xFFFFFFFFu, kLineRank = 0xFFFFFFE8u, kLineMore = 0u;   // second words; those of steps are at most ...
+constexpr uint32_t kLineMaxTot = 0x80000000u;   // ... this, which no latency bound reaches
+constexpr uint32_t kLineMaxShift = 28;
+__host__ __device__ inline uint32_t line_place(uint32_t i) { return ((i >> 1) & 1u) * 8u + (i >> 2) * 2u + (i & 1u); }   // of entry i, in units of 8 bytes
+__host__ __device__ inline uint32_t line_step0(uint32_t plane) { return plane * 16u - (plane >> 1); }   // number of a plane's first step: 0, 16, 31, 47
 // Counters of the index build.  Every slice takes its room with one 64-bit add on the pair
 // (kCtlPool, kCtlSteps) and waits for the answer; the statistics live on a cache line of their
 // own so that their updates, which nobody waits for, do not queue in front of those requests.
@@ -295,25 +315,9 @@ int index_stat_blocks(int num_cus);               // entries of IndexView::stats
 int32_t index_open_cap(int32_t n, int num_cus);   // records per workgroup of QueryView::open for a pass over n queries
 size_t index_park_bytes(int num_cus);
 
-// Selection group by group, for an index laid out in groups (IndexView::num_groups > 1).
-constexpr int kGroupTile = 16384;   // queries binned at a time
-struct GroupScratch {
-    uint2 *rec;          // [tiles * kGroupTile] records {latency bound, accuracy threshold (key space) | slice in its group << 16},
-                         //   the records of a tile grouped by group
-    uint16_t *perm;      // [tiles * kGroupTile] query -> where its record sits in its tile
-    int32_t *res;        // [tiles * kGroupTile] answers, in record order
-    uint32_t *desc;      // [tiles][groups + 1] the tile's run of every group: offset in the tile | length << 15
-    uint32_t *gcount;    // [groups + 1] records per group (cleared again by the last kernel of a call)
-    int32_t max_group_slices;   // slices of the largest group
-    int32_t stat_blocks;        // workgroups IndexView::stats has room for
-};
-size_t group_bin_lds_bytes(int32_t T, int32_t G);
-hipError_t launch_group_bin(const TableView &tv, const IndexView &ix, const QueryView &q, const GroupScratch &gs,
-                            int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
-hipError_t launch_group_lookup(const TableView &tv, const IndexView &ix, const QueryView &q, const GroupScratch &gs,
-                               int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
-hipError_t launch_group_finish(const TableView &tv, const IndexView &ix, const QueryView &q, const GroupScratch &gs,
-                               int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
+// The selection from the lines of the index, a tile of queries per workgroup at a time (q.pass 0).
+hipError_t launch_line_select(const TableView &tv, const IndexView &ix, const QueryView &q, int num_cus, hipStream_t st,
+                              const LaunchEvents *ev = nullptr);
 
 // Worker selection (Section 4.1: the worker that serves the selected variant).
 struct WorkerView {

@@ -354,6 +354,88 @@ __device__ __forceinline__ int32_t ranked_first_fit(const TableView &tv, const u
     return found >= 0 ? tv.orig_r[(int64_t)rh.x * 4 + found] : -1;
 }
 
+// ---- lines (internal.h)
+
+// What a query is compared with in a line: {accuracy threshold, shifted like the keys; latency bound}.
+__device__ __forceinline__ uint32_t line_threshold(const IndexView &ix, int32_t min_acc, int32_t acc_base_m1)
+{
+    const int32_t d = __builtin_elementwise_sub_sat(min_acc, acc_base_m1);   // keys are accuracy - acc_base_m1 >= 1
+    const int32_t top = (int32_t)ix.line_top;
+    return (uint32_t)(d < 1 ? 1 : d > top ? top : d) << ix.line_shift;
+}
+// What a line says to a query (lookup_lines): the entry that answers it, {number of the lane that had it << 30 | row}, or one of the
+// codes from kCodeOpen on, in this order: the next line may, kCodeRank, nothing does.
+constexpr uint32_t kCodeOpen = 0xE0000000u, kCodeRank = 0xFFFFFFFDu, kCodeNone = 0xFFFFFFFEu;
+__device__ __forceinline__ bool line_open(uint32_t code) { return code >= kCodeOpen && code < kCodeRank; }
+template <int kLane>
+__device__ __forceinline__ uint32_t of_quad(uint32_t v)   // the value of one of the four lanes of a quad
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kLane * 0x55, 0xF, 0xF, true);
+}
+// One query per lane: the line at byte `at` of `lines`, threshold d, latency bound l.  In round r the four lanes of every quad read the
+// line of the query of the r-th of them and compare it with all 16 entries, four to a lane.  `rounds`, where kSome is set: bit r
+// clear: none of the queries of round r is looked at (their code is 0).
+// Bound by the lines: a random one from L2 costs 4.5 ps on the whole card, 3.6 from L1 (quads that read two times 64 bytes and do nothing else);
+// 24 vector instructions to a round, 95 per 64 queries with what precedes and follows, are 2.4.
+template <bool kSome>
+__device__ __forceinline__ uint32_t lookup_lines(const uint8_t *lines, uint32_t at, uint32_t d, uint32_t l, uint32_t row_mask, uint32_t rounds = 15u)
+{
+    const uint32_t sub = threadIdx.x & 3u, tag = sub << 30, shift = sub == 3u ? 3u : 31u;
+    uint4 v[4][2];
+    uint32_t code = 0u;
+    auto request = [&](uint4 (&w)[2], uint32_t from) __attribute__((always_inline)) {
+        const uint32_t at32 = from + 16u * sub;   // (one 32-bit offset from a uniform base)
+        w[0] = *(const uint4 *)(lines + at32);
+        w[1] = *(const uint4 *)(lines + at32 + 64);
+    };
+    auto look = [&](const uint4 (&w)[2], uint32_t dr, uint32_t lr, uint32_t r) __attribute__((always_inline)) {
+        const bool f0 = (w[0].x >= dr) & (w[0].y <= lr), f1 = (w[0].z >= dr) & (w[0].w <= lr);
+        const bool f2 = (w[1].x >= dr) & (w[1].y <= lr), f3 = (w[1].z >= dr) & (w[1].w <= lr);
+        uint32_t word = f2 ? w[1].x : w[1].z;   // the first of the lane's four that fits
+        word = f1 ? w[0].z : word;
+        word = f0 ? w[0].x : word;
+        uint32_t mine = (word & row_mask) | tag;
+        // nothing fits: the last lane's last entry tells what follows (a step: a code between kCodeOpen and kCodeRank, kLineEnd: all
+        // ones); the other lanes say nothing (all ones, or one less)
+        mine = (f0 | f1 | f2 | f3) ? mine : __builtin_amdgcn_alignbit(~0u, w[1].w, shift);
+        uint32_t o = (uint32_t)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xF, 0xF, true);
+        mine = o < mine ? o : mine;
+        o = (uint32_t)__builtin_amdgcn_mov_dpp((int)mine, 0x4E, 0xF, 0xF, true);
+        mine = o < mine ? o : mine;
+        code = sub == r ? mine : code;
+    };
+    if (!kSome || (rounds & 1u)) request(v[0], of_quad<0>(at));
+    if (!kSome || (rounds & 2u)) request(v[1], of_quad<1>(at));
+    if (!kSome || (rounds & 4u)) request(v[2], of_quad<2>(at));
+    if (!kSome || (rounds & 8u)) request(v[3], of_quad<3>(at));
+    if (!kSome || (rounds & 1u)) look(v[0], of_quad<0>(d), of_quad<0>(l), 0u);
+    if (!kSome || (rounds & 2u)) look(v[1], of_quad<1>(d), of_quad<1>(l), 1u);
+    if (!kSome || (rounds & 4u)) look(v[2], of_quad<2>(d), of_quad<2>(l), 2u);
+    if (!kSome || (rounds & 8u)) look(v[3], of_quad<3>(d), of_quad<3>(l), 3u);
+    return code;
+}
+// The rounds of lookup_lines that the lanes in a set belong to.
+__device__ __forceinline__ uint32_t rounds_of(uint64_t lanes)
+{
+    uint32_t w = (uint32_t)lanes | (uint32_t)(lanes >> 32);
+    w |= w >> 16; w |= w >> 8; w |= w >> 4;
+    return w & 15u;
+}
+// From the first line's code on: the lines that follow, for the lanes that need them; `plane` gets the plane of the last one looked at.
+__device__ __forceinline__ uint32_t follow_lines(const IndexView &ix, uint32_t code, uint32_t s, uint32_t d, uint32_t l, uint32_t empty, uint32_t &plane)
+{
+    plane = 0u;
+    const uint32_t row_mask = (1u << ix.line_shift) - 1u;
+    for (uint32_t p = 1; p < (uint32_t)kLinePlanes; ++p) {
+        const bool more = line_open(code);
+        const uint64_t some = __ballot(more);
+        if (some == 0ull) break;
+        const uint32_t next = lookup_lines<true>(ix.lines, more ? p * ix.line_plane + s * kLineBytes : empty * kLineBytes, d, l, row_mask, rounds_of(some));
+        code = more ? next : code;
+        plane = more ? p : plane;
+    }
+    return code;
+}
 // Accuracy bound in key space: keys are acc - acc_base + 1 >= 1, so the bound is
 // min_acc - acc_base + 1 limited to [1, 65536] (65536 is above every key).
 __device__ __forceinline__ uint32_t acc_threshold(int32_t min_acc, int32_t acc_base_m1)

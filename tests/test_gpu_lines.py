@@ -1,0 +1,39 @@
+"""The lines of the index (16 steps each, in four planes): staircases that end at and around the ends of the
+planes, and tables whose caller rows do not fit beside the accuracy keys.  Every answer against the CPU oracle."""
+import numpy as np
+import pytest
+
+from gpu_util import gpu_select, make_selector, table_args
+from test_gpu_parity import _assert_equal_everywhere, _staircase_queries, _staircase_table, _table
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows_beyond_the_entries(tb):
+    """The same table behind one more task whose two variants spread the accuracies over 16 bits: 16 bits are left
+    for rows, and there are more rows than that."""
+    task = np.concatenate([tb.task_id, np.full(2, tb.num_tasks, np.int32)])
+    return _table(tb.num_tasks + 1, tb.batch_sizes, task, np.concatenate([tb.acc_bp, [tb.acc_bp.min(), tb.acc_bp.min() + 60_000]]),
+                  np.concatenate([tb.lat_us, np.full((2, tb.B), 1000)]), np.concatenate([tb.cost, np.full((2, tb.B), 5)]),
+                  np.concatenate([tb.queue_us, [0, 0]]))
+
+
+@pytest.mark.parametrize("rows", ["in_the_entries", "beyond"])
+@pytest.mark.parametrize("steps", [15, 16, 17, 30, 31, 32, 46, 47, 48, 61, 62, 63])
+def test_staircases_around_the_ends_of_the_planes(oracle_lib, steps, rows):
+    """As many steps in every slice as fill a plane, one less and one more: a large batch (a tile per workgroup at a time),
+    one of the least size that goes there, and a small one (one query per lane)."""
+    rng = np.random.default_rng(steps)
+    tb = _staircase_table(-(-70_000 // steps), steps, B=1)
+    if rows == "beyond":
+        tb = _rows_beyond_the_entries(tb)
+    sel = make_selector(tb, engine=2)
+    assert sel.info()["index_groups"] > 1 and sel.info()["index_max_steps"] == min(steps, 62)
+    qs = _staircase_queries(rng, tb, 300_007, steps)
+    want = oracle_lib.select(*table_args(tb), *qs)
+    for n in (2_100_049, 1 << 20, 60_001):
+        times = n // len(want) + 1
+        got = gpu_select(sel, *(np.tile(x, times)[:n] for x in qs))
+        _assert_equal_everywhere(got, np.tile(want, times)[:n], f"{steps} steps, rows {rows}, N={n}")
+    assert (want >= 0).any() and (want < 0).any()
+    sel.destroy()
