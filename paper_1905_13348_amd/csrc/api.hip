@@ -383,15 +383,14 @@ int create_index(infaas_sel *h)
     // keys run from 1 to the highest accuracy's (as far as there are keys for it), thresholds to one more
     int64_t top = 1;
     for (int32_t a : h->h_acc) top = std::max<int64_t>(top, std::min<int64_t>((int64_t)a - h->tv.acc_base, 65533) + 1);
-    ix.line_shift = std::min(kLineMaxShift, (uint32_t)__builtin_clz((uint32_t)(top + 1)));
+    ix.line_form = std::min(kLineMaxShift, (uint32_t)__builtin_clz((uint32_t)(top + 1)));
     ix.line_top = (uint32_t)top + 1u;
-    ix.line_rows = h->V <= (int64_t)1 << ix.line_shift ? 1u : 0u;
-    ix.line_plane = (uint32_t)(S + 1) * kLineBytes;
+    if (h->V > (int64_t)1 << ix.line_shift()) ix.line_form |= 1u << 31;
     // one allocation: the pool, then the headers, so that one 32-bit offset reaches both; behind them rank_hdr and,
     // at a multiple of their size, the nodes of TableView::rank_nodes and the lines (counted with the table: they do not follow the index)
     ix.pool_bytes &= ~127u;
     const size_t nstats = (size_t)index_stat_blocks(h->num_cus) * kLookupStats;
-    bool ok = dev_alloc(&ix.pool, (size_t)ix.pool_bytes + rank_nodes_at((int32_t)S) + (size_t)std::max<int64_t>(nodes, 1) * 128 + (size_t)kLinePlanes * ix.line_plane) == hipSuccess &&
+    bool ok = dev_alloc(&ix.pool, (size_t)ix.pool_bytes + rank_nodes_at((int32_t)S) + (size_t)std::max<int64_t>(nodes, 1) * 128 + (size_t)kLinePlanes * line_plane((int32_t)S)) == hipSuccess &&
               dev_alloc(&ix.step_row, ix.step_cap) == hipSuccess && dev_alloc(&ix.ctrl, kCtlWords) == hipSuccess &&
               dev_alloc(&ix.stats, 4 + nstats) == hipSuccess && dev_alloc(&ix.gctrl, 2 * (size_t)kGroupMaxGroups) == hipSuccess &&
               dev_alloc(&ix.slice_room, (size_t)S) == hipSuccess;
@@ -568,8 +567,8 @@ int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
     if (q.pass == 0 && use_lines(h, q.n))
         return HIP_OK(launch_line_select(h->tv, h->ix, q, h->num_cus, st, t.ev())) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
     if (q.pass <= 1 && q.n <= direct_limit(h, q.pass == 1)) {
-        const hipError_t e = q.pass == 0 ? launch_direct_select(h->tv, h->ix, q, false, body_pool(h), h->num_cus, st, t.ev())
-                                         : launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, body_pool(h), h->num_cus, st, t.ev());
+        const hipError_t e = q.pass == 0 ? launch_direct_select(h->tv, h->ix, q, false, h->num_cus, st, t.ev())
+                                         : launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, h->num_cus, st, t.ev());
         return HIP_OK(e) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
     }
     if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->d_park, h->index_lds_bytes, h->num_cus, st, t.ev())))
@@ -623,7 +622,7 @@ bool use_ranked(const infaas_sel *h)
 int ranked_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_SCAN_LDS, st);
-    if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, true, body_pool(h), h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
+    if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, true, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
     return INFAAS_SEL_OK;
 }
 
@@ -1189,8 +1188,7 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
         if (closest) q.closest = d_out_closest + done;
         if (direct) {
             LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
-            if (!HIP_OK(launch_direct_modes(h->tv, h->ix, h->inactive->tv, h->inactive->ix, q, true, std::max(body_pool(h), body_pool(h->inactive)),
-                                           h->num_cus, st, t.ev())))
+            if (!HIP_OK(launch_direct_modes(h->tv, h->ix, h->inactive->tv, h->inactive->ix, q, true, h->num_cus, st, t.ev())))
                 return INFAAS_SEL_ERR_HIP;
             continue;
         }
@@ -1450,7 +1448,7 @@ int infaas_sel_select_noalloc(infaas_sel_t *h, int64_t N, const int32_t *d_task,
     if (use_lines(h, q.n)) {
         if (!HIP_OK(launch_line_select(h->tv, h->ix, q, h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
     } else if (q.n <= direct_limit(h)) {
-        if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, body_pool(h), h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
+        if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
     } else if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->static_park, h->index_lds_bytes, h->num_cus,
                                     (hipStream_t)hip_stream, nullptr)))
         return INFAAS_SEL_ERR_HIP;

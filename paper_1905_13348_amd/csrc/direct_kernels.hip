@@ -3,8 +3,6 @@
 #include "internal.h"
 #include "lookup_common.h"
 
-#include <type_traits>
-
 namespace infaas {
 
 namespace {
@@ -28,53 +26,37 @@ __device__ __forceinline__ Query load_query(const TableView &tv, const QueryView
     return u;
 }
 
-// The selection for the lanes in `want` (of valid queries), -1 elsewhere.  kRanked: slices whose steps are not all
-// in their bodies go through their entries in rank order at once; otherwise only with what the bodies leave
-// open.  Counts in st what became of the queries, as the lookup kernel does; no query is decided by an
-// LDS copy here, so all count as parked.
-template <bool kRanked, bool kAhead, bool kByFour>
-__device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want,
+// The selection for the lanes in `want` (of valid queries), -1 elsewhere.  `rounds`: of lookup_lines, those of the lanes that have
+// queries at all.  kRanked: slices that the index does not hold completely go through their entries in rank order at once;
+// otherwise only with what their lines leave open.  Counts in st what became of the queries, as the lookup kernel does; no query
+// is decided by an LDS copy here, so all count as parked.
+template <bool kRanked, bool kAhead>
+__device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want, uint32_t rounds,
                                                       uint32_t (&st)[kLookupStats])
 {
     auto count = [&](int what, bool yes) { st[what] += (uint32_t)__builtin_popcountll(__ballot(yes)); };
-    int nit = 0;
-    if (!kByFour) nit = 32 - __builtin_clz(ix.ctrl[kCtlMaxK0] | 1u);    // <= 5
-    const uint32_t s = want ? u.s : (uint32_t)tv.S;
-    const uint4 h = ix.hdr[s];
+    uint32_t s = want ? u.s : (uint32_t)tv.S;
     uint4 rh{};
-    if (kRanked) rh = tv.rank_hdr[s];
-    int32_t ans = -1;
-    const bool body = want && !(h.y & kHdrPark) && !(kRanked && (h.y & kHdrTrunc));
-    if (__ballot(body)) {
-        const uint32_t keys0 = (h.y >> kHdrK0Shift) & 0x3Fu, keys1 = (h.y >> kHdrK1Shift) & 0x3Fu;
-        const uint32_t dd = acc_threshold(u.min_acc, tv.acc_base - 1), lim = (uint32_t)u.slo;
-        uint32_t m = 0u;
-        auto search = [&](bool on, uint32_t at, uint32_t re) __attribute__((always_inline)) {
-            if constexpr (kByFour) {
-                const uint32_t a = on ? at : 0u, r = on ? re : 0u;
-                if ((__ballot(on) >> 32) == 0ull) search_bodies_by_four<1>(ix.pool, a, r, dd, lim, m);
-                else search_bodies_by_four<4>(ix.pool, a, r, dd, lim, m);
-            } else {
-                const uint32_t a1[1] = {on ? at : 0u}, r1[1] = {on ? re : 2u}, d1[1] = {dd}, l1[1] = {lim};
-                uint32_t m1[1];
-                search_bodies<1>(GlobalMem{ix.pool}, nit, a1, r1, d1, l1, m1);
-                m = on ? m1[0] : 0u;
-            }
-        };
-        search(body, h.x, keys0);
-        const bool hit0 = m != 0u;
-        uint32_t at = hit0 ? h.z + (uint32_t)__builtin_ctz(m) : 0u;   // (entry 0 of step_row is -1)
-        count(2, hit0);
-        const bool more = body && !hit0 && keys1 != 0u;
-        if (__ballot(more)) {
-            search(more, h.x + body_bytes(keys0), keys1);
-            const bool hit1 = m != 0u;
-            if (hit1) at = h.z + kBodySteps + (uint32_t)__builtin_ctz(m);
-            count(1, hit1);
-        }
-        ans = ix.step_row[at];
+    bool scan = false;
+    if (kRanked) {
+        rh = tv.rank_hdr[s];
+        scan = want && rh.w != 0u;
+        s = scan ? (uint32_t)tv.S : s;
     }
-    const bool scan = want && ans < 0 && (h.y & kHdrTrunc);
+    int32_t ans = -1;
+    if (!kRanked || __ballot(want && !scan)) {
+        const uint32_t d = line_threshold(ix, u.min_acc, tv.acc_base - 1), l = (uint32_t)u.slo, row_mask = (1u << ix.line_shift()) - 1u;
+        uint32_t code, plane;
+        if (rounds == 15u) code = lookup_lines<false>(ix.lines, s * kLineBytes, d, l, row_mask);
+        else code = lookup_lines<true>(ix.lines, s * kLineBytes, d, l, row_mask, rounds);
+        code = want ? code : kCodeNone;   // (of a round that was left out: nothing)
+        code = follow_lines(ix, code, s, d, l, tv.S, plane);
+        const bool hit = code < kCodeOpen;
+        if (hit) ans = ix.line_rows() ? (int32_t)(code & row_mask) : ix.step_row[ix.hdr[s].z + (code & row_mask)];
+        if (!kRanked) scan = code == kCodeRank;
+        count(1, hit && plane > 1u);
+        count(2, hit && plane <= 1u);
+    }
     if (__ballot(scan)) {
         if (!kRanked) rh = tv.rank_hdr[s];
         const int32_t row = ranked_first_fit<kAhead>(tv, scan ? rh : make_uint4(0u, 0u, 0u, 0u), u.min_acc, (uint32_t)u.slo);
@@ -87,23 +69,15 @@ __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const
 }
 
 // The closest variant of the table for the lanes in `want` (queries inside the table that nothing satisfies),
-// and how far it is from the requirements: from the bodies, or where they are not all of the slice's steps
+// and how far it is from the requirements: from the lines, or where they do not hold all of the slice's steps
 // by the wavefront over the whole slice.
 __device__ __forceinline__ int32_t closest_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want, HowFar &how)
 {
-    how = HowFar{3, 0, 0};
-    int32_t sug = -1;
     const uint32_t s = want ? u.s : (uint32_t)tv.S;
-    const uint4 h = ix.hdr[s];
-    const bool by_index = want && !(h.y & (kHdrPark | kHdrTrunc));
-    if (__ballot(by_index)) {
-        const uint32_t max_k = ix.ctrl[kCtlMaxK0];
-        const ClosestStep c = closest_step(GlobalMem{ix.pool}, 32 - __builtin_clz(max_k | 1u), by_index ? h.x : 0u,
-                                           by_index ? (h.y >> kHdrK0Shift) & 0x3Fu : 2u, by_index ? (h.y >> kHdrK1Shift) & 0x3Fu : 0u,
-                                           acc_threshold(u.min_acc, tv.acc_base - 1), u.slo, u.min_acc, tv.acc_base - 1);
-        if (by_index && c.step >= 0) { sug = ix.step_row[h.z + (uint32_t)c.step]; how = c.how; }
-    }
-    uint64_t rest = __ballot(want && !by_index);
+    const uint32_t code = closest_in_lines(ix, want, s, tv.S, line_threshold(ix, u.min_acc, tv.acc_base - 1), u.slo, u.min_acc, tv.acc_base - 1, how);
+    int32_t sug = -1;
+    if (want && code < kCodeOpen) sug = ix.line_rows() ? (int32_t)code : ix.step_row[ix.hdr[s].z + code];
+    uint64_t rest = __ballot(want && code == kCodeRank);
     while (rest) {
         const int l = __builtin_ctzll(rest);
         rest &= rest - 1;
@@ -129,23 +103,36 @@ __device__ __forceinline__ void leave_statistics(const IndexView &ix, uint32_t *
     if (blockIdx.x == 0 && threadIdx.x == 0) ix.stats[-1] = gridDim.x;
 }
 
-// Bound by the rate of scattered reads (header, three to five lines of the body, two sets, row: 20 ps per query, 40 with the lane's
-// own bisection, which kByFour false keeps for bodies that L1 holds).  The lanes of a wavefront take `per` queries.
-template <bool kRanked, bool kByFour>
-__global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, IndexView ix, QueryView q, int32_t per)
+// Where the lanes' queries are: `per` of them to a wavefront, so that few of them are spread over its quads, each of which
+// reads one line at a time.
+struct Spread {
+    int32_t number;   // of this lane's query
+    bool mine;        // it has one
+    uint32_t rounds;  // of lookup_lines, those of the lanes that have
+};
+__device__ __forceinline__ Spread spread_of(int32_t spread)   // 2^spread lanes to a query
 {
-    const int32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, step = per * (kDirThreads / 64);
+    const int32_t lane = threadIdx.x & 63;
+    return Spread{lane >> spread, (lane & ((1 << spread) - 1)) == 0, spread == 0 ? 15u : spread == 1 ? 5u : 1u};
+}
+
+// Bound by the rate of scattered reads, a line (4.5 ps) and its share of further ones per query, and below 100,000 queries by the launch
+// and three dependent trips to memory (arguments, fields, line).
+template <bool kRanked>
+__global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, IndexView ix, QueryView q, int32_t spread)
+{
+    const int32_t wave = threadIdx.x >> 6, per = 64 >> spread, step = per * (kDirThreads / 64);
+    const Spread sp = spread_of(spread);
     __shared__ uint32_t l_st[kLookupStats];
     publish_index_stats(tv);
     if (threadIdx.x < kLookupStats) l_st[threadIdx.x] = 0u;
     __syncthreads();
     uint32_t st[kLookupStats] = {0u, 0u, 0u, 0u, 0u};
     for (int64_t i0 = (int64_t)blockIdx.x * step; i0 < q.n; i0 += (int64_t)gridDim.x * step) {
-        const int64_t i = i0 + wave * per + lane;
-        const bool mine = lane < per;
-        const Query u = load_query(tv, q, i, mine);
-        const int32_t ans = select_from_memory<kRanked, true, kByFour>(tv, ix, u, u.valid, st);
-        if (mine && i < q.n) q.out[i] = ans;
+        const int64_t i = i0 + wave * per + sp.number;
+        const Query u = load_query(tv, q, i, sp.mine);
+        const int32_t ans = select_from_memory<kRanked, true>(tv, ix, u, u.valid, sp.rounds, st);
+        if (sp.mine && i < q.n) q.out[i] = ans;
     }
     leave_statistics(ix, l_st, st);
 }
@@ -155,10 +142,11 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, Ind
 // kSuggest: the closest variant (of both tiers) where there is no answer; kWorker: the worker of every answer.
 // Bound by its launch and the chain of dependent reads, like the two passes of the lookup kernel that it replaces, but
 // once and without the two LDS mirrors.
-template <bool kTiers, bool kSuggest, bool kWorker, bool kByFour>
-__global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, IndexView ia, TableView tb, IndexView ib, QueryView q, int32_t per)
+template <bool kTiers, bool kSuggest, bool kWorker>
+__global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, IndexView ia, TableView tb, IndexView ib, QueryView q, int32_t spread)
 {
-    const int32_t lane = threadIdx.x & 63, step = per * (kDirThreads / 64);
+    const int32_t per = 64 >> spread, step = per * (kDirThreads / 64);
+    const Spread sp = spread_of(spread);
     __shared__ uint32_t l_st[kLookupStats];
     publish_index_stats(ta);
     if (kTiers) publish_index_stats(tb);
@@ -166,14 +154,14 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
     __syncthreads();
     uint32_t st[kLookupStats] = {0u, 0u, 0u, 0u, 0u};
     for (int64_t i0 = (int64_t)blockIdx.x * step; i0 < q.n; i0 += (int64_t)gridDim.x * step) {
-        const int64_t i = i0 + (int32_t)(threadIdx.x >> 6) * per + lane;
-        const bool mine = lane < per;
+        const int64_t i = i0 + (int32_t)(threadIdx.x >> 6) * per + sp.number;
+        const bool mine = sp.mine;
         const Query u = load_query(ta, q, i, mine);
-        int32_t ans = select_from_memory<false, false, kByFour>(ta, ia, u, u.valid, st), tier = ans >= 0 ? 1 : 0;
+        int32_t ans = select_from_memory<false, false>(ta, ia, u, u.valid, sp.rounds, st), tier = ans >= 0 ? 1 : 0;
         if (kTiers) {
             const bool next = u.valid && ans < 0;
             if (__ballot(next)) {
-                const int32_t row = select_from_memory<false, false, kByFour>(tb, ib, u, next, st);
+                const int32_t row = select_from_memory<false, false>(tb, ib, u, next, rounds_of(__ballot(next)), st);
                 if (next && row >= 0) { ans = row; tier = 2; }
             }
         }
@@ -201,24 +189,6 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
     leave_statistics(kTiers ? ib : ia, l_st, st);
 }
 
-// Who searches a body: its lane by bisection, which is fast where L1 holds the lines that it probes, or four lanes that read all of its
-// keys (search_bodies_by_four), which takes a third more registers and more instructions.  Kernel us, bisection / four lanes, by the bytes of
-// the bodies:
-//   selection, 100,000 queries: 5 KB 4.2 / 4.6, 23 KB 5.2 / 5.4, 38 KB 5.1 / 5.0, 42 KB (two bodies to a slice) 5.8 / 6.4, 62 KB 5.6 / 5.5,
-//     92 KB 5.5 / 4.8, 134 KB 6.0 / 5.4, 173 KB 6.9 / 4.9
-//   two tiers, 1001 / 100,000 / 200,000: 5 KB 6.0 / 6.5 / 8.4 and 5.9 / 7.6 / 9.9, 38 KB 6.3 / 6.5 / 9.9 and 6.1 / 6.9 / 10.3, 60 KB 5.0 / 6.4 / 9.0
-//     and 4.8 / 7.0 / 9.5, 92 KB 5.4 / 7.0 / 10.5 and 4.9 / 7.0 / 9.4, 173 KB 6.7 / 8.6 / 13.1 and 6.4 / 8.0 / 10.9
-//   with a suggestion, one table, 60,000 / 80,000: 5 KB 7.2 / 7.7 and 7.7 / 8.5, 62 KB 7.4 / 8.4 and 7.7 / 8.4, 92 KB 7.4 / 8.2 and 7.6 / 8.0, 173 KB
-//     9.1 / 10.0 and 8.8 / 9.4
-//   and two tiers, 45,000 / 100,000 / 200,000: 5 KB 11.4 / 12.0 / 14.8 and 12.7 / 13.6 / 17.1, 62 KB 11.8 / 13.0 / 16.0 and 12.4 / 13.8 / 16.8,
-//     92 KB 11.8 / 13.3 / 16.6 and 12.5 / 14.2 / 16.9, 134 KB 12.0 / 13.7 / 17.9 and 12.8 / 14.4 / 17.2, 250 KB 12.6 / 14.6 / 20.4 and 13.6 / 15.0 / 18.3
-bool four_lanes(bool tiers, bool suggest, int64_t n, int32_t per, int64_t pool, int num_cus)
-{
-    if (!tiers && !suggest) return pool > 48 * 1024;
-    if (!suggest) return per == 16 || pool > 64 * 1024;
-    return tiers ? n > (int64_t)num_cus * 512 && pool > 96 * 1024 : per == 64 && pool > 64 * 1024;
-}
-
 // How many queries a wavefront takes.  A batch too small to give every SIMD two full wavefronts is spread over as many with fewer queries
 // each, down to the 16 that one round of search_bodies_by_four serves (two tiers, 1001 queries 8.5 -> 6.6 us, with workers 8.6 -> 6.7; to
 // bisection 16 to 64 of them are the same in a selection, and 16 up to 7% faster with two tiers).  In rank order, where a
@@ -234,27 +204,23 @@ int32_t queries_per_wave(int64_t n, int32_t least, int num_cus)
 
 }  // namespace
 
-hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int64_t pool, int num_cus,
+hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int num_cus,
                                 hipStream_t st, const LaunchEvents *ev)
 {
     const int32_t per = queries_per_wave(q.n, ranked ? 1 : 16, num_cus);
     const int64_t step = per * (kDirThreads / 64), want = ((int64_t)q.n + step - 1) / step, most = index_stat_blocks(num_cus);
-    auto kernel = ranked ? k_direct_select<true, true> : four_lanes(false, false, q.n, per, pool, num_cus) ? k_direct_select<false, true> : k_direct_select<false, false>;
-    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, tv, ix, q, per);
+    auto kernel = ranked ? k_direct_select<true> : k_direct_select<false>;
+    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, tv, ix, q, __builtin_ctz(64u / (unsigned)per));
 }
 
 hipError_t launch_direct_modes(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, const QueryView &q,
-                               bool tiers, int64_t pool, int num_cus, hipStream_t st, const LaunchEvents *ev)
+                               bool tiers, int num_cus, hipStream_t st, const LaunchEvents *ev)
 {
     const int32_t per = queries_per_wave(q.n, 16, num_cus);
     const int64_t step = per * (kDirThreads / 64), want = ((int64_t)q.n + step - 1) / step, most = index_stat_blocks(num_cus);
-    auto pick = [&](auto by_four) {
-        constexpr bool f = decltype(by_four)::value;
-        return !tiers ? k_direct_modes<false, true, false, f> : q.worker ? (q.closest ? k_direct_modes<true, true, true, f> : k_direct_modes<true, false, true, f>)
-                                                              : (q.closest ? k_direct_modes<true, true, false, f> : k_direct_modes<true, false, false, f>);
-    };
-    auto kernel = four_lanes(tiers, q.closest != nullptr, q.n, per, pool, num_cus) ? pick(std::true_type{}) : pick(std::false_type{});
-    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, ta, ia, tb, ib, q, per);
+    auto kernel = !tiers ? k_direct_modes<false, true, false> : q.worker ? (q.closest ? k_direct_modes<true, true, true> : k_direct_modes<true, false, true>)
+                                                              : (q.closest ? k_direct_modes<true, true, false> : k_direct_modes<true, false, false>);
+    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, ta, ia, tb, ib, q, __builtin_ctz(64u / (unsigned)per));
 }
 
 }  // namespace infaas

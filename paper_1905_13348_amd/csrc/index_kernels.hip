@@ -100,17 +100,21 @@ __device__ __forceinline__ void body_store(uint8_t *body, int g0, int kb, int la
     if (lane < (int)re) { m_a[lane] = r.ma; m_s[lane] = r.ms; }   // lanes beyond kb hold the full set
 }
 
+// Whether a step's latency would read as what follows its line (lane j < K holding step j).
+__device__ __forceinline__ bool line_ends_odd(int lane, int32_t K, uint32_t st_tot)
+{
+    return __ballot((lane == 15 || lane == 46) && lane < K && st_tot >= kLineMaxTot) != 0ull;
+}
 // The lines of slice s (internal.h) by one wavefront, lane j < K holding step j and its caller row.  usable: the slice's accuracies fit
 // the keys (and, where entries name steps instead of rows, it has a header that leads to them); `trunc`: it has more steps.
-__device__ __forceinline__ void store_lines(const IndexView &ix, int32_t s, int32_t K, bool usable, bool trunc, int lane, int32_t st_acc, uint32_t st_tot,
+__device__ __forceinline__ void store_lines(const IndexView &ix, int32_t S, int32_t s, int32_t K, bool usable, bool trunc, int lane, int32_t st_acc, uint32_t st_tot,
                                             int32_t row, int32_t acc_base)
 {
     const uint32_t n = usable ? (uint32_t)K : 0u;
-    const uint32_t lo = ((uint32_t)(st_acc - acc_base + 1) << ix.line_shift) | (ix.line_rows ? (uint32_t)row : (uint32_t)lane);
-    const uint32_t hi = st_tot < kLineMaxTot ? st_tot : kLineMaxTot;
+    const uint32_t lo = ((uint32_t)(st_acc - acc_base + 1) << ix.line_shift()) | (ix.line_rows() ? (uint32_t)row : (uint32_t)lane);
     // lane j's place among the entries: steps 0-15, 16-30, 31-46, 47-61
     const uint32_t j = (uint32_t)lane, plane = (uint32_t)(j >= 16u) + (uint32_t)(j >= 31u) + (uint32_t)(j >= 47u), i = j - line_step0(plane);
-    uint2 *line = (uint2 *)(ix.lines + plane * ix.line_plane + (uint32_t)s * kLineBytes);
+    uint2 *line = (uint2 *)(ix.lines + plane * line_plane(S) + (uint32_t)s * kLineBytes);
     // (a plane that the slice does not get to is not read and not written; lane 62 has no step, and writes the last entry of plane 3)
     const bool reached = plane == 0u || (plane == 1u ? n >= 16u : plane == 2u ? n > 31u : n >= 47u);
     const bool is_step = j < n;
@@ -118,9 +122,9 @@ __device__ __forceinline__ void store_lines(const IndexView &ix, int32_t s, int3
     uint32_t what = kLineEnd;
     if (j == 15u && !usable) what = kLineRank;   // nothing of the slice is in its lines
     if (j == 62u) what = end;
-    if (reached && j < 63u) line[line_place(i)] = is_step ? make_uint2(lo, hi) : make_uint2(0u, what);
+    if (reached && j < 63u) line[line_place(i)] = is_step ? make_uint2(lo, st_tot) : make_uint2(0u, what);
     if (lane == 63 && n >= 16u)   // plane 1 has 15 steps: its last entry tells whether there are more
-        ((uint2 *)(ix.lines + ix.line_plane + (uint32_t)s * kLineBytes))[line_place(15u)] = make_uint2(0u, n > 31u ? kLineMore : kLineEnd);
+        ((uint2 *)(ix.lines + line_plane(S) + (uint32_t)s * kLineBytes))[line_place(15u)] = make_uint2(0u, n > 31u ? kLineMore : kLineEnd);
 }
 
 constexpr int kBuildWaves = 4;                    // slices (wavefronts) per workgroup
@@ -633,11 +637,14 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
     const bool fill = kTwo && (ix.fill.by_row || ix.fill.cls);
     int32_t worker = -1;
     if (fill && lane < K) worker = worker_of_row(ix.fill, row);
-    __syncthreads();
     const bool has = inside && L > 0;
+    const bool narrow = (int64_t)hi - (int64_t)tv.acc_base <= 65533 && lo >= tv.acc_base && !line_ends_odd(lane, K, st_tot);   // 16-bit accuracy keys
+    // the lines, while the room is waited for (which they depend on only where their entries name steps)
+    if (inside && ix.line_rows()) store_lines(ix, tv.S, s, K, !has || narrow, trunc, lane, st_acc, st_tot, row, tv.acc_base);
+    __syncthreads();
     const uint32_t off = s_off[wave], rec = s_rec[wave];
     const bool fits = has && (uint64_t)off + size <= ix.pool_bytes && (uint64_t)rec + K <= ix.step_cap &&
-                      (int64_t)hi - (int64_t)tv.acc_base <= 65533 && lo >= tv.acc_base;   // 16-bit accuracy keys
+                      narrow;
     if (fits) {
         uint8_t *body0 = ix.pool + off + rows;
         body_store(body0, 0, k0, lane, st_acc, st_tot, tv.acc_base, b0);
@@ -649,8 +656,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
             if (fill) store_step_worker(ix, s, lane, rec + (uint32_t)lane, worker);
         }
     }
-    if (inside)
-        store_lines(ix, s, K, !has || ((int64_t)hi - (int64_t)tv.acc_base <= 65533 && lo >= tv.acc_base && (fits || ix.line_rows)), trunc, lane, st_acc, st_tot, row, tv.acc_base);
+    if (inside && !ix.line_rows()) store_lines(ix, tv.S, s, K, !has || fits, trunc, lane, st_acc, st_tot, row, tv.acc_base);
     if (__builtin_expect(has && (trunc || !fits), 0)) {   // (the wavefront) queries of this slice may go through its entries in rank order
         const SliceColumns sc = slice_columns<kTwo>(s, t, b);
         write_rank_nodes<(64 * kBuildPer > kRankUnsorted)>(sc.acc, sc.tot, sc.nodes, sc.L, 0, sc.L, lane, INT32_MIN, 0xFFFFFFFFu, sc.acc_base);
@@ -661,6 +667,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build(TableView ta, 
         // number instead costs a read of a line that the allocation's atomics keep busy: 42 us instead of 34 for two
         // tables of 1600 slices.)
         ix.slice_room[s] = kRoomNone;
+        ((uint32_t *)(tv.rank_hdr + s))[3] = (uint32_t)(has && (trunc || !fits));
         if (fits) {
             const uint32_t y = (re0 << kHdrK0Shift) | (re1 << kHdrK1Shift) | (trunc ? kHdrTrunc : 0u) |
                                ((k1 || trunc) ? kHdrDeep : 0u) | row_hi;
@@ -924,7 +931,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableVi
     const uint32_t rows = (2u * r0 + 3u) & ~3u, size0 = body_bytes(re0);
     const bool has = L > 0;
     // accuracies that do not fit 16-bit keys: no bodies, and no room asked for
-    const bool narrow = __ballot(lane < K && (st_acc < tv.acc_base || (int64_t)st_acc - (int64_t)tv.acc_base > 65533)) == 0ull;
+    const bool narrow = __ballot(lane < K && (st_acc < tv.acc_base || (int64_t)st_acc - (int64_t)tv.acc_base > 65533)) == 0ull && !line_ends_odd(lane, K, st_tot);
     const uint32_t size = has && narrow ? rows + size0 + body_bytes(re1) : 0u;   // (a multiple of 4)
     // requested now, used at the end: the caller rows of the steps
     const int32_t row = (!(wave & 1) && lane < K) ? tv.orig_r[(int64_t)b * tv.Vp + seg + st_pos] : 0;
@@ -994,7 +1001,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableVi
         s_off[0] = off; s_rec[0] = rec;
     }
     // wavefront 2 the lines, while wavefront 3 waits for the room (which they depend on only where their entries name steps)
-    if (wave == 2 && ix.line_rows) store_lines(ix, s, K, !has || narrow, trunc, lane, st_acc, st_tot, row, tv.acc_base);
+    if (wave == 2 && ix.line_rows()) store_lines(ix, tv.S, s, K, !has || narrow, trunc, lane, st_acc, st_tot, row, tv.acc_base);
     if (wave == 3 && (!grouped || s == tv.S - 1)) {
         // What the slices before this one need, lane by lane (with groups only for the statistics).  An entry counts once it carries this
         // build's number.  The wait is bounded: every slice publishes as soon as it knows its steps,
@@ -1056,7 +1063,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableVi
     const uint32_t off = s_off[0], rec = s_rec[0];
     const bool fits = has && (uint64_t)off + size <= ix.pool_bytes && (uint64_t)rec + K <= ix.step_cap && narrow;
     uint8_t *body0 = ix.pool + off + rows;
-    if (wave == 2 && !ix.line_rows) store_lines(ix, s, K, !has || fits, trunc, lane, st_acc, st_tot, row, tv.acc_base);
+    if (wave == 2 && !ix.line_rows()) store_lines(ix, tv.S, s, K, !has || fits, trunc, lane, st_acc, st_tot, row, tv.acc_base);
     if (wave <= 1 && fits && (wave == 0 || k1)) {   // wavefront 0 writes the first body, wavefront 1 the second
         const int h = 2 * wave;
         BodyRegs r{pa, ps, parts[0][h][lane] | parts[1][h][lane] | parts[2][h][lane] | parts[3][h][lane],
@@ -1097,6 +1104,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_index_build_shared(TableVi
     for (uint32_t j = 0; j < r0; ++j)
         row_hi |= ((uint32_t)__builtin_amdgcn_readlane(row, (int)j) >> 16) << (j * ix.row_hi_bits);
     if (lane == 0) {
+        ((uint32_t *)(tv.rank_hdr + s))[3] = (uint32_t)(has && (trunc || !fits));
         if (fits) {
             const uint32_t y = (re0 << kHdrK0Shift) | (re1 << kHdrK1Shift) | (trunc ? kHdrTrunc : 0u) |
                                ((k1 || trunc) ? kHdrDeep : 0u) | row_hi;

@@ -45,7 +45,8 @@ struct TableView {
     //    those nodes (node 0).
     // Null without an index.
     const uint4 *rank_hdr;      // [S + 1] {first entry of the slice in the rank-ordered columns, divided by 4; its entries; its first
-                                //         node in rank_nodes; unused}; entry S stands for no slice (0 entries)
+                                //         node in rank_nodes; written by the build: 1 where the index does not hold the slice
+                                //         completely, else 0}; entry S stands for no slice (0 entries)
     __host__ __device__ uint4 *rank_nodes() const;   // [nodes][8]
     int32_t acc_base;           // smallest accuracy in the table; index keys are acc - acc_base + 1
     // State-aware selection: a table serves one state (Active or Inactive).  Variants in another
@@ -148,15 +149,15 @@ struct IndexView {
     uint32_t *gctrl;              // [2 num_groups] per group: bytes of its region and steps handed out
     // Lines: the steps once more, for searches straight from global memory (layout below).
     uint8_t *lines;      // [kLinePlanes][S + 1] lines of 128 bytes; slice S is the empty one
-    uint32_t line_plane; // bytes of a plane
-    uint32_t line_shift; // bits of a first word below the accuracy key; they hold the caller row ...
+    uint32_t line_form;  // bits of a first word below the accuracy key; sign bit: they hold the number of the step in its slice instead of its caller row
     uint32_t line_top;   // the highest accuracy threshold: above every key
-    uint32_t line_rows;  // ... where this is 1; where rows have more bits, the number of the step in its slice
+    __host__ __device__ __forceinline__ bool line_rows() const { return (int32_t)line_form >= 0; }
+    __host__ __device__ __forceinline__ uint32_t line_shift() const { return line_form & 31u; }
     StepFill fill;       // for the build of both tiers' tables only
     uint32_t *stats;     // [kStatShare x compute units][kLookupStats] what the most recent lookup launch did;
                          // the word in front of it: how many entries that launch has written
 };
-// A line is 16 entries of two words in rank order: {accuracy key << line_shift | caller row, latency-plus-queue}.  Accuracies are
+// A line is 16 entries of two words in rank order: {accuracy key << line_shift() | caller row, latency-plus-queue}.  Accuracies are
 // compared without taking the words apart (the threshold is shifted up and the row below it can only add), so a query tries an entry
 // with two comparisons, and the first entry that fits names the answer: no header, no sets, no row to look up elsewhere.  Four lanes read a line, 32
 // bytes each: entries 4 i .. 4 i + 3 lie where the i-th of them finds them with two 16-byte reads of which each
@@ -165,10 +166,11 @@ struct IndexView {
 // The last entry of a line tells what follows: a step, or kLineMore below: the next line; kLineRank: the search in
 // rank order; kLineEnd: nothing.  Entries behind a slice's last step are {0, kLineEnd}, which nothing fits.
 constexpr int kLinePlanes = 4, kLineBytes = 128;
-constexpr uint32_t kLineEnd = 0xFFFFFFFFu, kLineRank = 0xFFFFFFE8u, kLineMore = 0u;   // second words; those of steps are at most ...
-constexpr uint32_t kLineMaxTot = 0x80000000u;   // ... this, which no latency bound reaches
+constexpr uint32_t kLineEnd = 0xFFFFFFFFu, kLineRank = 0xFFFFFFE8u, kLineMore = 0u;   // second words, where the first word is 0
+constexpr uint32_t kLineMaxTot = 0xFFFFFFE0u;   // a slice with a step of this latency or a longer one at the end of a line gets no lines and no body
 constexpr uint32_t kLineMaxShift = 28;
 __host__ __device__ inline uint32_t line_place(uint32_t i) { return ((i >> 1) & 1u) * 8u + (i >> 2) * 2u + (i & 1u); }   // of entry i, in units of 8 bytes
+__host__ __device__ inline uint32_t line_plane(int32_t S) { return ((uint32_t)S + 1u) * (uint32_t)kLineBytes; }   // bytes of a plane
 __host__ __device__ inline uint32_t line_step0(uint32_t plane) { return plane * 16u - (plane >> 1); }   // number of a plane's first step: 0, 16, 31, 47
 // Counters of the index build.  Every slice takes its room with one 64-bit add on the pair
 // (kCtlPool, kCtlSteps) and waits for the answer; the statistics live on a cache line of their
@@ -303,14 +305,13 @@ hipError_t launch_index_select(const TableView &tv, const IndexView &ix, const Q
                                int32_t *park_mem, uint32_t lds_bytes, int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
 int index_select_blocks(int num_cus);
 // One lane per query, everything read from global memory (L2): for calls too small to pay for the LDS
-// mirror, and (ranked) for tables most of whose slices the index cannot hold.  pool: bytes of the bodies, of the larger
-// index where there are two (it decides who searches a body, not what is found).  Selection only (q.pass 0).
-hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int64_t pool, int num_cus,
+// mirror, and (ranked) for tables most of whose slices the index cannot hold.  Selection only (q.pass 0).
+hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int num_cus,
                                 hipStream_t st, const LaunchEvents *ev = nullptr);
 // The same for the other modes: selection with suggestion on one table (tiers false; tb, ib unused), or both tiers with
 // workers (q.worker, q.row_worker: of the Active tier, the Inactive tier's V entries behind them) and suggestions (q.closest).
 hipError_t launch_direct_modes(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, const QueryView &q,
-                               bool tiers, int64_t pool, int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
+                               bool tiers, int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
 int index_stat_blocks(int num_cus);               // entries of IndexView::stats
 int32_t index_open_cap(int32_t n, int num_cus);   // records per workgroup of QueryView::open for a pass over n queries
 size_t index_park_bytes(int num_cus);

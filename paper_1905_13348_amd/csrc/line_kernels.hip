@@ -30,7 +30,7 @@ __global__ __launch_bounds__(kLineThreads) void k_line_select(TableView tv, Inde
     if (tid < kLookupStats) l_st[tid] = 0u;
     if (tid == 0) l_count = 0u;
     uint32_t st[kLookupStats] = {0u, 0u, 0u, 0u, 0u};
-    const uint32_t row_mask = (1u << ix.line_shift) - 1u;
+    const uint32_t row_mask = (1u << ix.line_shift()) - 1u;
     const int32_t acc_base_m1 = tv.acc_base - 1;
     const bool aligned = ((((uintptr_t)q.task) | ((uintptr_t)q.slo) | ((uintptr_t)q.min_acc) | ((uintptr_t)q.bidx) | ((uintptr_t)q.out)) & 15u) == 0;
     constexpr int kGroups = kLineQueries / 4;   // a lane's queries: four consecutive ones in each
@@ -42,18 +42,18 @@ __global__ __launch_bounds__(kLineThreads) void k_line_select(TableView tv, Inde
         const bool have = first + (uint32_t)lane < count;
         const v4i e = l_open[have ? first + (uint32_t)lane : first];
         const uint32_t s = have ? (uint32_t)e.w : (uint32_t)tv.S;
-        const uint4 h = ix.hdr[s];
-        const bool scan = have && (h.y & kHdrTrunc);
+        const uint4 rh = tv.rank_hdr[s];
+        const bool scan = have && rh.w != 0u;
         uint32_t plane;
-        const uint32_t code = follow_lines(ix, have && !scan ? kCodeOpen : kCodeNone, s, (uint32_t)e.z, (uint32_t)e.y, (uint32_t)tv.S, plane);
+        const uint32_t code = follow_lines(ix, have && !scan ? kCodeOpen : kCodeNone, s, (uint32_t)e.z, (uint32_t)e.y, tv.S, plane);
         const bool hit = code < kCodeOpen;
-        int32_t ans = hit ? (ix.line_rows ? (int32_t)(code & row_mask) : ix.step_row[h.z + (code & row_mask)]) : -1;
+        int32_t ans = hit ? (ix.line_rows() ? (int32_t)(code & row_mask) : ix.step_row[ix.hdr[s].z + (code & row_mask)]) : -1;
         st[1] += (uint32_t)__builtin_popcountll(__ballot(hit && plane > 1u));
         st[2] += (uint32_t)__builtin_popcountll(__ballot(hit && plane == 1u));
         const uint64_t scanned = __ballot(scan);
         if (scanned) {
             st[3] += (uint32_t)__builtin_popcountll(scanned);
-            const uint4 none = make_uint4(0u, 0u, 0u, 0u), rh = tv.rank_hdr[s];
+            const uint4 none = make_uint4(0u, 0u, 0u, 0u);
             const int32_t am = q.min_acc[have ? e.x : 0];
             const int32_t row = ranked_first_fit<false>(tv, scan ? rh : none, am, (uint32_t)e.y);
             ans = scan ? row : ans;
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(kLineThreads) void k_line_select(TableView tv, Inde
                 }
                 st[0] += total;
             }
-            if (!ix.line_rows) {   // entries name steps
+            if (!ix.line_rows()) {   // entries name steps
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (r[e] >= 0) r[e] = ix.step_row[ix.hdr[slice[4 * g + e]].z + (uint32_t)r[e]];

@@ -8,7 +8,6 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
-typedef uint32_t v4u __attribute__((ext_vector_type(4), aligned(4)));   // (keys are aligned to 4 bytes)
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
 {
@@ -82,68 +81,6 @@ __device__ __forceinline__ void search_bodies(const Mem &mem, int nit, const uin
         const uint32_t s_at = pt[k] + 8u * re[k];
         m[k] = mem.ld32(a_at, 4u) & mem.ld32(s_at, 4u);
     }
-}
-
-// First fitting step of a body in global memory, one body per lane (body, re: its address and its keys per array; re 0: none,
-// m is 0), as a bit set.  By bisection (search_bodies) a lane makes ten scattered reads of one key, five after one another; here
-// four lanes read all keys of a body together, eight to a lane, so that a search is two trips to memory (keys, then sets) and
-// touches the three to five lines that the body consists of.  The keys are sorted and end with a sentinel that no query
-// meets, so the count is the place of the first key that fails, whatever lies behind it.  Round r serves the
-// lanes 16 r .. 16 r + 15; all four together, or kRounds at a time, passing over those without a body.
-// Bound by the reads it has left (8 per query with header and row instead of 15).  Selections of 400,001 / 200,003 queries on 8000
-// slices 21.5 / 12.6 us by bisection, 12.1 / 7.9 so; 90,001 queries on 800 slices 6.3 and 5.3.
-template <int kRounds>
-__device__ __forceinline__ void search_bodies_by_four(const uint8_t *pool, uint32_t body, uint32_t re, uint32_t dd, uint32_t lim, uint32_t &m)
-{
-    const int lane = threadIdx.x & 63, sub = lane & 3;
-    const uint64_t some = __ballot(re != 0u);
-    uint32_t counts = 0;   // accuracy keys met | latency keys met << 8
-    const uint32_t what = re | (dd << 8);   // (dd <= 65536)
-#pragma unroll
-    for (int r0 = 0; r0 < 4; r0 += kRounds) {
-        if (kRounds < 4 && ((some >> (16 * r0)) & (kRounds == 1 ? 0xFFFFull : 0xFFFFFFFFull)) == 0ull) continue;
-        v4u ka[kRounds], kt[kRounds][2];
-        uint32_t d[kRounds], l[kRounds];
-        bool in[kRounds];
-#pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
-            const int from = 16 * (r0 + r) + (lane >> 2);
-            const uint32_t w = (uint32_t)__shfl((int)what, from), at = (uint32_t)__shfl((int)body, from);
-            l[r] = (uint32_t)__shfl((int)lim, from);
-            d[r] = w >> 8;
-            in[r] = 8u * (uint32_t)sub < (w & 0x3Fu);   // (lanes past the end read what the first of the four reads)
-            const uint8_t *p = pool + at + 4u;
-            ka[r] = *(const v4u *)(p + (in[r] ? 16 * sub : 0));
-            const v4u *q = (const v4u *)(p + 2u * (w & 0x3Fu) + (in[r] ? 32 * sub : 0));
-            kt[r][0] = q[0];
-            kt[r][1] = q[1];
-        }
-#pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
-            uint32_t a = 0, t = 0;   // a bit per key that is met, the first key's uppermost
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                a = (a << 1) + (uint32_t)((ka[r][k] & 0xFFFFu) >= d[r]);
-                a = (a << 1) + (uint32_t)((ka[r][k] >> 16) >= d[r]);
-            }
-#pragma unroll
-            for (int k = 0; k < 8; ++k) t = (t << 1) + (uint32_t)(kt[r][k >> 2][k & 3] <= l[r]);
-            const int up = 24 - 8 * sub;
-            a = in[r] ? a << up : 0u;
-            t = in[r] ? t << up : 0u;
-            a |= (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0xB1, 0xF, 0xF, true);
-            t |= (uint32_t)__builtin_amdgcn_mov_dpp((int)t, 0xB1, 0xF, 0xF, true);
-            a |= (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0x4E, 0xF, 0xF, true);
-            t |= (uint32_t)__builtin_amdgcn_mov_dpp((int)t, 0x4E, 0xF, 0xF, true);
-            // (at most 31 steps, so the last bit is never set and there is a first key that fails)
-            const uint32_t c = (uint32_t)__builtin_clz(~a | 1u) | ((uint32_t)__builtin_clz(~t | 1u) << 8);
-            const uint32_t mine = (uint32_t)__shfl((int)c, 4 * (lane & 15));
-            counts = (lane >> 4) == r0 + r ? mine : counts;
-        }
-    }
-    const uint8_t *sets = pool + body + 4u + 6u * re;   // (without a body: some words of the pool)
-    const uint32_t sa = *(const uint32_t *)(sets + 4u * (counts & 0xFFu)), ss = *(const uint32_t *)(sets + 4u * re + 4u * (counts >> 8));
-    m = re ? sa & ss : 0u;
 }
 
 // The closest variant of slice (t, b) for a query that nothing satisfies, by the whole wavefront over
@@ -361,7 +298,7 @@ __device__ __forceinline__ uint32_t line_threshold(const IndexView &ix, int32_t 
 {
     const int32_t d = __builtin_elementwise_sub_sat(min_acc, acc_base_m1);   // keys are accuracy - acc_base_m1 >= 1
     const int32_t top = (int32_t)ix.line_top;
-    return (uint32_t)(d < 1 ? 1 : d > top ? top : d) << ix.line_shift;
+    return (uint32_t)(d < 1 ? 1 : d > top ? top : d) << ix.line_shift();
 }
 // What a line says to a query (lookup_lines): the entry that answers it, {number of the lane that had it << 30 | row}, or one of the
 // codes from kCodeOpen on, in this order: the next line may, kCodeRank, nothing does.
@@ -422,20 +359,95 @@ __device__ __forceinline__ uint32_t rounds_of(uint64_t lanes)
     return w & 15u;
 }
 // From the first line's code on: the lines that follow, for the lanes that need them; `plane` gets the plane of the last one looked at.
-__device__ __forceinline__ uint32_t follow_lines(const IndexView &ix, uint32_t code, uint32_t s, uint32_t d, uint32_t l, uint32_t empty, uint32_t &plane)
+__device__ __forceinline__ uint32_t follow_lines(const IndexView &ix, uint32_t code, uint32_t s, uint32_t d, uint32_t l, int32_t S, uint32_t &plane)
 {
     plane = 0u;
-    const uint32_t row_mask = (1u << ix.line_shift) - 1u;
+    const uint32_t row_mask = (1u << ix.line_shift()) - 1u;
     for (uint32_t p = 1; p < (uint32_t)kLinePlanes; ++p) {
         const bool more = line_open(code);
         const uint64_t some = __ballot(more);
         if (some == 0ull) break;
-        const uint32_t next = lookup_lines<true>(ix.lines, more ? p * ix.line_plane + s * kLineBytes : empty * kLineBytes, d, l, row_mask, rounds_of(some));
+        const uint32_t next = lookup_lines<true>(ix.lines, (more ? p * ((uint32_t)S + 1u) + s : (uint32_t)S) * kLineBytes, d, l, row_mask, rounds_of(some));
         code = more ? next : code;
         plane = more ? p : plane;
     }
     return code;
 }
+// The closest variant of slice s for a query that nothing satisfies (closest_by_scan's order), from the slice's lines, one query per
+// lane of those in `want`: its code as lookup_lines gives it, kCodeNone where the slice has nothing to offer, kCodeRank where
+// the lines do not hold all of its steps (the closest variant is always a step); how far it is goes to *how.  Where some step is
+// within the latency bound it is the most accurate of those; else where some step is accurate enough the fastest of those; else the
+// fastest of all, the most accurate among equally fast ones; the earliest at a tie: the smallest of {which of the three, 2 bits; latency, none
+// for the first | accuracy from above, 16 bits; place}, by the four lanes of a quad over their entries, then over the lines.
+// The first line is in L1 from the selection; bound by the instructions, 90 to a round.
+__device__ __forceinline__ uint32_t closest_in_lines(const IndexView &ix, bool want, uint32_t s, int32_t S, uint32_t d, int32_t slo, int32_t min_acc, int32_t acc_base_m1,
+                                                     HowFar &how)
+{
+    const uint32_t sub = threadIdx.x & 3u, shift = sub == 3u ? 3u : 31u, keys = ix.line_shift(), row_mask = (1u << keys) - 1u;
+    const uint32_t under = slo < 0 ? 0u : (uint32_t)slo + 1u;   // latencies below this are within the bound
+    uint32_t b_hi = ~0u, b_lo = ~0u, b_word = 0u, next = want ? kCodeOpen : kCodeNone;   // the best so far: {order, first word}; what follows
+    for (uint32_t p = 0; p < (uint32_t)kLinePlanes; ++p) {
+        const uint64_t some = __ballot(line_open(next));
+        if (some == 0ull) break;
+        const uint32_t at = (line_open(next) ? p * ((uint32_t)S + 1u) + s : (uint32_t)S) * kLineBytes, rounds = rounds_of(some);
+        uint32_t r_hi = ~0u, r_lo = ~0u, r_word = 0u, r_next = kCodeNone;
+        auto look = [&](uint32_t from, uint32_t dr, uint32_t ur, uint32_t r) __attribute__((always_inline)) {
+            const uint32_t at32 = from + 16u * sub;
+            const uint4 w0 = *(const uint4 *)(ix.lines + at32), w1 = *(const uint4 *)(ix.lines + at32 + 64);
+            const uint32_t first[4] = {w0.x, w0.z, w1.x, w1.z}, tot[4] = {w0.y, w0.w, w1.y, w1.w};
+            uint32_t m_hi = ~0u, m_lo = ~0u, m_word = 0u;
+            auto take = [&](uint32_t hi, uint32_t lo, uint32_t word) __attribute__((always_inline)) {
+                const bool lower = (hi < m_hi) | ((hi == m_hi) & (lo < m_lo));
+                m_hi = lower ? hi : m_hi;
+                m_lo = lower ? lo : m_lo;
+                m_word = lower ? word : m_word;
+            };
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const bool near = tot[k] < ur, good = first[k] >= dr, step = (first[k] != 0u) & (tot[k] != 0xFFFFFFFFu);
+                // {case, 2 bits; upper 30 bits of the latency}, {its lower 2 bits; accuracy from above, 16 bits; place in the line}
+                const uint32_t t = near ? 0u : tot[k];
+                const uint32_t hi = (near ? 0u : good ? 1u << 30 : 2u << 30) | (t >> 2);
+                const uint32_t lo = (t << 30) | ((0xFFFFu - (good & !near ? 0u : first[k] >> keys)) << 8) | (4u * sub + k);
+                if (step) take(hi, lo, first[k]);
+            }
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {   // the lowest of the four lanes
+                auto other = [&](uint32_t v) __attribute__((always_inline)) {
+                    return o == 0 ? (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true) : (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);
+                };
+                const uint32_t o_hi = other(m_hi), o_lo = other(m_lo), o_word = other(m_word);
+                take(o_hi, o_lo, o_word);
+            }
+            const uint32_t follows = of_quad<3>(__builtin_amdgcn_alignbit(~0u, w1.w, shift));   // (of the last lane)
+            r_hi = sub == r ? m_hi : r_hi;
+            r_lo = sub == r ? m_lo : r_lo;
+            r_word = sub == r ? m_word : r_word;
+            r_next = sub == r ? follows : r_next;
+        };
+        if (rounds & 1u) look(of_quad<0>(at), of_quad<0>(d), of_quad<0>(under), 0u);
+        if (rounds & 2u) look(of_quad<1>(at), of_quad<1>(d), of_quad<1>(under), 1u);
+        if (rounds & 4u) look(of_quad<2>(at), of_quad<2>(d), of_quad<2>(under), 2u);
+        if (rounds & 8u) look(of_quad<3>(at), of_quad<3>(d), of_quad<3>(under), 3u);
+        // (the lines before come first: places count from 0 in each)
+        const uint32_t r_cmp = r_lo >> 8, b_cmp = b_lo >> 8;
+        const bool lower = line_open(next) & ((r_hi < b_hi) | ((r_hi == b_hi) & (r_cmp < b_cmp)));
+        b_hi = lower ? r_hi : b_hi;
+        b_lo = lower ? r_lo : b_lo;
+        b_word = lower ? r_word : b_word;
+        next = line_open(next) ? r_next : next;
+    }
+    how = HowFar{3, 0, 0};
+    if (next == kCodeRank) return kCodeRank;
+    if (b_word == 0u) return kCodeNone;
+    const uint32_t which = b_hi >> 30;
+    const int64_t tot = ((int64_t)(b_hi & 0x3FFFFFFFu) << 2) | (int64_t)(b_lo >> 30);
+    how.missed = which == 2u ? 2 : 1;
+    how.over = which == 0u ? 0 : tot - (int64_t)slo;
+    how.shortf = which == 1u ? 0 : (int64_t)min_acc - ((int64_t)(b_word >> keys) + (int64_t)acc_base_m1);
+    return b_word & row_mask;
+}
+
 // Accuracy bound in key space: keys are acc - acc_base + 1 >= 1, so the bound is
 // min_acc - acc_base + 1 limited to [1, 65536] (65536 is above every key).
 __device__ __forceinline__ uint32_t acc_threshold(int32_t min_acc, int32_t acc_base_m1)

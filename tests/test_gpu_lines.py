@@ -3,7 +3,7 @@ planes, and tables whose caller rows do not fit beside the accuracy keys.  Every
 import numpy as np
 import pytest
 
-from gpu_util import gpu_select, make_selector, table_args
+from gpu_util import gpu_select, gpu_select_closest, make_selector, table_args
 from test_gpu_parity import _assert_equal_everywhere, _staircase_queries, _staircase_table, _table
 
 pytestmark = pytest.mark.gpu
@@ -36,4 +36,38 @@ def test_staircases_around_the_ends_of_the_planes(oracle_lib, steps, rows):
         got = gpu_select(sel, *(np.tile(x, times)[:n] for x in qs))
         _assert_equal_everywhere(got, np.tile(want, times)[:n], f"{steps} steps, rows {rows}, N={n}")
     assert (want >= 0).any() and (want < 0).any()
+    sel.destroy()
+
+
+@pytest.mark.parametrize("steps", [15, 16, 17, 31, 32, 47, 48, 62, 63])
+def test_suggestions_around_the_ends_of_the_planes(oracle_lib, steps):
+    """The closest variant from the lines: staircases of these lengths, bounds that leave every requirement, one or both
+    missed, negative and largest bounds among them, and ties in accuracy and latency (an odd task has pairs of both)."""
+    rng = np.random.default_rng(100 + steps)
+    tb = _staircase_table(6, steps, B=2)
+    odd = tb.task_id % 2 == 1
+    tb.acc_bp[odd] = tb.acc_bp[odd] // 20 * 20
+    tb.lat_us[odd] = tb.lat_us[odd] // 2000 * 2000
+    sel = make_selector(tb, engine=2)
+    n = 20_011
+    task, bidx = rng.integers(0, 6, n), rng.integers(0, 2, n)
+    acc = rng.choice([-2**31, 0, 900, 1000, 1300, 2000, 70_000, 2**31 - 1], n) + rng.integers(0, 2 * steps, n) * (rng.random(n) < 0.5)
+    slo = rng.choice([-2**31, -1, 0, 1, 20_000, 60_000, 90_000, 2**31 - 1], n)
+    slo = np.where((slo > 1) & (slo < 2**31 - 1), slo + rng.integers(-20_000, 20_000, n), slo)
+    qs = tuple(np.asarray(np.clip(x, -2**31, 2**31 - 1), np.int32) for x in (task, slo, acc, bidx))
+    for got, want, what in zip(gpu_select_closest(sel, *qs), oracle_lib.select_closest(*table_args(tb), *qs), ("variant", "closest")):
+        _assert_equal_everywhere(got, want, f"{steps} steps, {what}")
+    sel.destroy()
+
+
+def test_latencies_that_read_like_the_end_of_a_line(oracle_lib):
+    """Latency plus queue just below 2^32 at every step, the last of the first line among them."""
+    n = 20
+    i = np.arange(n)
+    tb = _table(1, [1], np.zeros(n, np.int32), 1000 + 10 * i, np.full((n, 1), 2**31 - 1), (10 + i)[:, None], 2**31 - 1 - i)
+    sel = make_selector(tb, engine=2)
+    acc = np.asarray([0, 1000, 1095, 1150, 1155, 1190, 1200], np.int32)
+    qs = (np.zeros(7, np.int32), np.full(7, 2**31 - 1, np.int32), acc, np.zeros(7, np.int32))
+    for got, want in zip(gpu_select_closest(sel, *qs), oracle_lib.select_closest(*table_args(tb), *qs)):
+        _assert_equal_everywhere(got, want, "latencies below 2^32")
     sel.destroy()
