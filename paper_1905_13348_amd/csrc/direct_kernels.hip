@@ -19,7 +19,9 @@ __device__ __forceinline__ Query load_query(const TableView &tv, const QueryView
 {
     const bool in = mine && i < q.n;
     Query u;
-    u.task = in ? q.task[i] : -1; u.slo = in ? q.slo[i] : -1; u.min_acc = in ? q.min_acc[i] : 0; u.bidx = in ? q.bidx[i] : -1;
+    const int64_t at = in ? i : 0;   // (every lane reads: four loads in a row, without branches; there is a query 0)
+    u.task = q.task[at]; u.slo = q.slo[at]; u.min_acc = q.min_acc[at]; u.bidx = q.bidx[at];
+    u.task = in ? u.task : -1;
     u.inside = (uint32_t)u.task < (uint32_t)tv.T && (uint32_t)u.bidx < (uint32_t)tv.B;
     u.valid = u.inside && u.slo >= 0;
     u.s = u.inside ? (uint32_t)u.task * (uint32_t)tv.B + (uint32_t)u.bidx : (uint32_t)tv.S;
@@ -90,16 +92,21 @@ __device__ __forceinline__ int32_t closest_from_memory(const TableView &tv, cons
     return sug;
 }
 
-// The workgroup's counts into its entry of the statistics (l_st: kLookupStats words of LDS, cleared before).
-__device__ __forceinline__ void leave_statistics(const IndexView &ix, uint32_t *l_st, const uint32_t (&st)[kLookupStats])
+// The workgroup's counts into its entry of the statistics.
+__device__ __forceinline__ void leave_statistics(const IndexView &ix, const uint32_t (&st)[kLookupStats])
 {
+    __shared__ uint32_t l_st[kDirThreads / 64][kLookupStats];
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-        for (int k = 0; k < kLookupStats; ++k)
-            if (st[k]) atomicAdd(&l_st[k], st[k]);
+        for (int k = 0; k < kLookupStats; ++k) l_st[threadIdx.x >> 6][k] = st[k];
     }
     __syncthreads();
-    if (threadIdx.x < kLookupStats) ix.stats[blockIdx.x * kLookupStats + threadIdx.x] = l_st[threadIdx.x];
+    if (threadIdx.x < kLookupStats) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (int w = 0; w < kDirThreads / 64; ++w) sum += l_st[w][threadIdx.x];
+        ix.stats[blockIdx.x * kLookupStats + threadIdx.x] = sum;
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) ix.stats[-1] = gridDim.x;
 }
 
@@ -123,18 +130,18 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, Ind
 {
     const int32_t wave = threadIdx.x >> 6, per = 64 >> spread, step = per * (kDirThreads / 64);
     const Spread sp = spread_of(spread);
-    __shared__ uint32_t l_st[kLookupStats];
-    publish_index_stats(tv);
-    if (threadIdx.x < kLookupStats) l_st[threadIdx.x] = 0u;
-    __syncthreads();
+    const uint32_t news = request_index_stats(tv);
+    bool first = true;
     uint32_t st[kLookupStats] = {0u, 0u, 0u, 0u, 0u};
     for (int64_t i0 = (int64_t)blockIdx.x * step; i0 < q.n; i0 += (int64_t)gridDim.x * step) {
         const int64_t i = i0 + wave * per + sp.number;
         const Query u = load_query(tv, q, i, sp.mine);
+        if (first) hand_on_index_stats(tv, news);
+        first = false;
         const int32_t ans = select_from_memory<kRanked, true>(tv, ix, u, u.valid, sp.rounds, st);
         if (sp.mine && i < q.n) q.out[i] = ans;
     }
-    leave_statistics(ix, l_st, st);
+    leave_statistics(ix, st);
 }
 
 // The other modes of the lookup in one launch: both tiers after one another for the lanes that need them, no lists
@@ -147,16 +154,16 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
 {
     const int32_t per = 64 >> spread, step = per * (kDirThreads / 64);
     const Spread sp = spread_of(spread);
-    __shared__ uint32_t l_st[kLookupStats];
-    publish_index_stats(ta);
-    if (kTiers) publish_index_stats(tb);
-    if (threadIdx.x < kLookupStats) l_st[threadIdx.x] = 0u;
-    __syncthreads();
+    const uint32_t news = request_index_stats(ta), news2 = kTiers ? request_index_stats(tb) : 0u;
+    bool first = true;
     uint32_t st[kLookupStats] = {0u, 0u, 0u, 0u, 0u};
     for (int64_t i0 = (int64_t)blockIdx.x * step; i0 < q.n; i0 += (int64_t)gridDim.x * step) {
         const int64_t i = i0 + (int32_t)(threadIdx.x >> 6) * per + sp.number;
         const bool mine = sp.mine;
         const Query u = load_query(ta, q, i, mine);
+        if (first) hand_on_index_stats(ta, news);
+        if (kTiers && first) hand_on_index_stats(tb, news2);
+        first = false;
         int32_t ans = select_from_memory<false, false>(ta, ia, u, u.valid, sp.rounds, st), tier = ans >= 0 ? 1 : 0;
         if (kTiers) {
             const bool next = u.valid && ans < 0;
@@ -186,7 +193,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
             if (kWorker) q.worker[i] = ans >= 0 ? q.row_worker[(tier == 2 ? ta.V : 0) + ans] : -1;
         }
     }
-    leave_statistics(kTiers ? ib : ia, l_st, st);
+    leave_statistics(kTiers ? ib : ia, st);
 }
 
 // How many queries a wavefront takes.  A batch too small to give every SIMD two full wavefronts is spread over as many with fewer queries

@@ -207,12 +207,19 @@ __host__ __device__ inline int32_t all_level_nodes(int32_t L)
     return sum;
 }
 __host__ __device__ inline int32_t rank_blocks(int32_t L) { return L > kRankUnsorted ? (int32_t)(((int64_t)L + kRankBlock - 1) / kRankBlock) : 0; }
-// Called by every thread of the first kernel of a selection.
-__device__ __forceinline__ void publish_index_stats(const TableView &tv)
+// Called by every thread of the first kernel of a selection.  In two parts, with what the kernel has to read in between: the first requests the
+// counters, the second hands them on.  (Waited for in front of everything else they cost a small call 0.5 us; written at its
+// end, the call waits for the host's memory.)
+__device__ __forceinline__ uint32_t request_index_stats(const TableView &tv)
 {
-    if (tv.stat_dst && blockIdx.x == 0 && threadIdx.x < 6)   // words 4, 5: pool bytes and step_row entries handed out
-        tv.stat_dst[threadIdx.x] = tv.stat_src[threadIdx.x < 4 ? kCtlMaxK0 + threadIdx.x : kCtlPool + (threadIdx.x - 4)];
+    if (!tv.stat_dst || blockIdx.x != 0 || threadIdx.x >= 6) return 0u;
+    return tv.stat_src[threadIdx.x < 4 ? kCtlMaxK0 + threadIdx.x : kCtlPool + (threadIdx.x - 4)];   // words 4, 5: pool bytes and step_row entries handed out
 }
+__device__ __forceinline__ void hand_on_index_stats(const TableView &tv, uint32_t word)
+{
+    if (tv.stat_dst && blockIdx.x == 0 && threadIdx.x < 6) tv.stat_dst[threadIdx.x] = word;
+}
+__device__ __forceinline__ void publish_index_stats(const TableView &tv) { hand_on_index_stats(tv, request_index_stats(tv)); }
 
 constexpr uint32_t kDummyBodyBytes = 64;     // 4 unused bytes, the empty body (28 bytes), padding
 constexpr uint32_t kEmptyHdrY = 2u << kHdrK0Shift;  // Re = 2 (sentinels only), no second body
