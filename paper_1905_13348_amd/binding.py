@@ -143,16 +143,20 @@ def _host_i32(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.int32)
 
 
-_torch = None       # the module and its int32, looked up once (a small call's time is this file's)
+_torch = None       # the module, its tensor class and its int32, looked up once (a small call's time is this file's)
+_tensor = None
 _int32 = None
 _raw_stream = None   # raw handle of a device's current stream
+_current_device = None
 
 
 def _use_torch():
-    global _torch, _int32, _raw_stream
+    global _torch, _tensor, _int32, _raw_stream, _current_device
     if _torch is None:
         import torch
         _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+        _tensor = torch.Tensor
         _int32 = torch.int32
         _torch = torch
     return _torch
@@ -160,6 +164,9 @@ def _use_torch():
 
 def _dev_ptr(t, n: int, name: str) -> int:
     """Raw device pointer of an int32 CUDA/HIP tensor with at least n elements."""
+    # (a plain tensor, by identities: 0.22 us instead of 0.32 for each of a call's arrays)
+    if t.__class__ is _tensor and t.dtype is _int32 and t.is_cuda and t.is_contiguous() and t.numel() >= n:
+        return t.data_ptr()
     torch = _torch or _use_torch()
     if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != _int32 \
             or not t.is_contiguous() or t.numel() < n:
@@ -171,7 +178,9 @@ def _stream_ptr(stream) -> int:
     torch = _torch or _use_torch()
     if stream is None:
         if _raw_stream is not None:   # (what current_stream() wraps in an object: 0.2 us instead of 1)
-            return _raw_stream(torch.cuda.current_device())
+            if not torch.cuda.is_initialized():   # (never behind a device tensor)
+                torch.cuda.init()
+            return _raw_stream(_current_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
