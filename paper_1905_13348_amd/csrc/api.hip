@@ -532,55 +532,98 @@ int64_t body_pool(const infaas_sel *h)
     return h->ix.num_groups > 1 ? h->ix_bytes : now ? now[4] : h->ix_stats[kCtlPool];
 }
 
-// Up to this many queries a selection is answered straight from global memory, one lane per query, rather than
-// through an LDS mirror of the index.  The mirror costs its fill (2-4 us, more with many slices) and pays with 4
-// ps per query against 15 to 20.  Measured, us for 100,000 / 200,000 / 300,000 queries, direct and mirrored: config 2's table, whole index in
-// LDS, 6.2 / 8.6 / 11.0 and 7.4 / 7.6 / 7.9; config 1's, 92% of it, 5.5 / 7.0 / 8.7 and 8.4 / 8.7 / 8.9; 200 tasks of 60 variants, about half of it, 5.5 / 6.9 /
-// 8.6 and 10.3 / 10.8 / 11.4 (700,000: 15.5 and 16.7); config 3's, 7%, 200,000 / 400,000: 7.9 / 12.1 and 18 / 22.  The less of the index
-// the mirror holds, the later it pays.  (Where no slice has a second body the line could lie at twice as many.)
+// Which way a lookup goes.  The mirror costs its fill (2-4 us, more with many slices) and pays with 4 ps per query, if it holds the
+// query's slice and the slice's first body has the answer; a line read from memory costs 7 to 9, one query per lane or, with a tile of them
+// at a time, 6 to 8 and a start of 2 us.  Up to direct_limit() every query counts as parked, as ever; beyond it the same kernel may
+// still be the faster one (below).
 constexpr int64_t kDirectQueries = 100000;
-// With suggestions the same holds (us for 65,000 / 100,000 / 300,000 queries: 100 tasks of 200 variants 7.6 / 8.0 / 15.5 direct,
-// 11.5 / 12.7 / 13.7 mirrored; config 3's table 10.5 / 11.5 / 21.9 and 35 / 38 / 42), except where the mirror holds nearly the
-// whole index (it does at 1.3 times its room, not at 1.5) and slices have second bodies, both of which a suggestion
-// searches (config 2's: 8.6 / 9.5 / 17.3 direct, 9.6 / 10.1 / 10.7 mirrored; 60 tasks of 800 8.6 / 9.5 / 16.7 and 9.6 / 10.0 / 10.6: by
-// these the line could lie somewhat above 100,000).  Slices that are not completely indexed
-// (their queries cost the lookup kernel more than all others) leave the limit where it is for the selection.
 constexpr int64_t kDirectSuggestions = 75000;
-int64_t direct_limit(const infaas_sel *h, bool closest = false)
+struct IndexShape {
+    int64_t pool, room;   // bytes of the bodies, and what the mirror has for them (0: no mirror)
+    double outside;       // share of the bodies outside the mirror
+    double open;          // share of the slices that the index does not hold completely
+    double steps;         // per slice
+    uint32_t most;        // steps of the slice that has most
+};
+IndexShape shape_of(const infaas_sel *h)
 {
-    if (h->index_lds_bytes == 0) return kDirectQueries;   // (no mirror, four interleaved queries per lane)
-    const int64_t room = (int64_t)h->index_lds_bytes - kLdsCtrlBytes - lds_header_bytes(h->tv.S);
     const volatile uint32_t *now = h->host_stats;
-    const int64_t pool = body_pool(h);
-    const uint32_t steps = now ? now[kCtlMaxK - kCtlMaxK0] : h->ix_stats[kCtlMaxK];
-    const uint32_t open = now ? now[kCtlTrunc - kCtlMaxK0] + now[kCtlNoBody - kCtlMaxK0] : h->ix_stats[kCtlTrunc] + h->ix_stats[kCtlNoBody];
-    if (closest && open == 0 && steps > (uint32_t)kBodySteps && 5 * pool <= 7 * room) return kDirectSuggestions;
-    return pool <= room ? kDirectQueries : kDirectQueries * pool / room;
+    const bool fresh = now && h->ix.num_groups <= 1;
+    const double S = std::max(1, h->T * h->B);
+    IndexShape x{};
+    x.pool = body_pool(h);
+    x.room = h->index_lds_bytes == 0 ? 0 : (int64_t)h->index_lds_bytes - kLdsCtrlBytes - lds_header_bytes(h->tv.S);
+    x.outside = x.pool > x.room ? 1.0 - (double)x.room / (double)x.pool : 0.0;
+    x.open = (now ? now[kCtlTrunc - kCtlMaxK0] + now[kCtlNoBody - kCtlMaxK0] : h->ix_stats[kCtlTrunc] + h->ix_stats[kCtlNoBody]) / S;
+    x.steps = (fresh ? (double)now[5] : (double)h->ix_steps) / S;
+    x.most = now ? now[kCtlMaxK - kCtlMaxK0] : h->ix_stats[kCtlMaxK];
+    return x;
+}
+int64_t direct_limit(const infaas_sel *h, const IndexShape &x, bool closest = false)
+{
+    if (x.room == 0) return kDirectQueries;
+    if (closest && x.open == 0 && x.most > (uint32_t)kBodySteps && 5 * x.pool <= 7 * x.room) return kDirectSuggestions;
+    return x.pool <= x.room ? kDirectQueries : kDirectQueries * x.pool / x.room;
+}
+// The plain selection: whether the mirror is ahead of the lines from `n` queries on.  us for 300,000 / 600,000 / 1M / 4M / 16M queries, a lane
+// per query (a tile at a time) and mirrored: 50 tasks of 2000 variants, all in the mirror, 7.0 / 11.2 / 16.0 / 50 / 209 (-, -, 14.9 / 42 / 151)
+// and 8.2 / 10.1 / 11.3 / 25 / 72; 100 of 200, 8% outside, 6.5 / 10.4 / 14.4 / 45 / 196 (-, -, 13.5 / 40 / 146) and 9.7 / 12.0 / 14.3 / 39 / 142; 200 of 60,
+// half outside, 6.2 / 9.5 / 13.1 / 39 / 180 (-, -, 13.0 / 38 / 135) and 13.2 / 17.7 / 24.0 / 73 / 279.  So a query pays 50 ps for every share
+// of the bodies outside, 4.7 less than from a line otherwise, and the start 1.5 us more; slices that are not completely indexed, which the
+// lookup kernel scans, cost 2.3 ns.
+bool mirror_pays(const IndexShape &x, int64_t n)
+{
+    return x.room > 0 && n > 350000 && 50.0 * x.outside + 2300.0 * x.open + 1.5e6 / (double)n < 4.7;
+}
+// ... and where it is not, from how many queries on a tile at a time is ahead of a lane per query (8000 slices, 900,000 queries 13.6 and 14.8, 1.05M
+// 15.5 and 15.9; 64M queries, binned by group of tasks whose bodies fit one LDS, 729, so 459).
+constexpr int64_t kLineQueries = 900000;
+// Beyond which size every selection counts as one that the lookup kernel or a kernel in its place has made.
+constexpr int64_t kLargeQueries = (int64_t)1 << 20;
+// With suggestions, and in two tiers, up to how many queries a lane per query is ahead (us at 300,000 / 600,000 / 1M / 1.5M, a lane per
+// query and mirrored): suggestions on 50 tasks of 2000 15.2 / 22.8 / - and 11.3 / 13.3, on 100 of 200 14.8 / 23.3 / 35 and 16.0 / 18.5 / 21.7, on 200 of 60 13.3 / 20.7 /
+// 30.9 / 43 and 26 / 30 / 37 / 50; two tiers behind reports, with workers, 42 / 48 / 57 / 70 and 51 / 53 / 55 / 60, 34 / 39 / 46 / 58 and 45 / 48 / 51 / 57, 33 / 37 / 43 / 53
+// and 48 / 52 / 59 / 70, on 8 of 32 25 / 30 / 36 / 43.5 and 35 / 37 / 40 / 46; complete Case I 21 / 31 / 45 and 26 / 31 / 35, 22 / 34 / 50 and 34 / 38 / 43, 20 / 32 / 48 / 68 and 51 / 57 / 68 /
+// 93, 19 / 31 / 46 and 33 / 37 / 42.  What is outside the mirror and longer staircases (more lines to a query) move the line.
+int64_t direct_pays(const IndexShape &x, bool tiers, bool closest)
+{
+    if (x.room == 0) return INT64_MAX;
+    const bool brief = x.steps <= 16.0;
+    const double base = !tiers ? (brief ? 280e3 : 150e3) : closest ? (brief ? 700e3 : 550e3) : (brief ? 1.2e6 : 800e3);
+    return (int64_t)(base * (1.0 + (tiers ? 15.0 : 4.0) * x.outside) * (1.0 + 200.0 * x.open));
 }
 
-bool use_lines(const infaas_sel *h, int64_t n);
+// How many slices the mirror would hold, as bodies are placed in the order of the slices (or of their arrival).
+int32_t resident_slices(const infaas_sel *h, const IndexShape &x) { return (int32_t)((1.0 - x.outside) * (h->T * h->B)); }
+
+// The plain selection, n <= 2^28 queries.  park: the lookup kernel's queues.
+hipError_t launch_select(const infaas_sel *h, const QueryView &q, int32_t *park, hipStream_t st, const LaunchEvents *ev = nullptr)
+{
+    const IndexShape x = shape_of(h);
+    if (q.n < kLargeQueries && q.n <= direct_limit(h, x)) return launch_direct_select(h->tv, h->ix, q, false, 0, h->num_cus, st, ev);
+    if (mirror_pays(x, q.n)) return launch_index_select(h->tv, h->ix, q, park, h->index_lds_bytes, h->num_cus, st, ev);
+    if (q.n >= kLineQueries) return launch_line_select(h->tv, h->ix, q, h->num_cus, st, ev);
+    return launch_direct_select(h->tv, h->ix, q, false, resident_slices(h, x), h->num_cus, st, ev);
+}
 
 // One pass of the index engine over n <= 2^28 queries.
 int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
-    if (q.pass == 0 && use_lines(h, q.n))
-        return HIP_OK(launch_line_select(h->tv, h->ix, q, h->num_cus, st, t.ev())) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
-    if (q.pass <= 1 && q.n <= direct_limit(h, q.pass == 1)) {
-        const hipError_t e = q.pass == 0 ? launch_direct_select(h->tv, h->ix, q, false, h->num_cus, st, t.ev())
-                                         : launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, h->num_cus, st, t.ev());
-        return HIP_OK(e) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
+    if (q.pass == 0) return HIP_OK(launch_select(h, q, h->d_park, st, t.ev())) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
+    if (q.pass == 1) {
+        const IndexShape x = shape_of(h);
+        const bool all = q.n <= direct_limit(h, x, true);
+        if (all || q.n <= direct_pays(x, false, true)) {
+            const hipError_t e = launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, all ? 0 : resident_slices(h, x),
+                                                     h->num_cus, st, t.ev());
+            return HIP_OK(e) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
+        }
     }
     if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->d_park, h->index_lds_bytes, h->num_cus, st, t.ev())))
         return INFAAS_SEL_ERR_HIP;
     return INFAAS_SEL_OK;
 }
-
-// Whether one pass over n queries of the plain selection reads the lines of the index, a tile per workgroup at a time: where the
-// bodies need more than twice one LDS and a tile per workgroup is half full.  us by this / by binning the queries by group of tasks whose bodies
-// fit one LDS, 8000 slices: 1.05M queries 15.9 / 52.9, 2M 22.5 / 54.5, 4M 39.5 / 66.4, 16M (Zipf) 135 / 238, 64M 459 / 729.
-constexpr int64_t kLineQueries = (int64_t)1 << 20;
-bool use_lines(const infaas_sel *h, int64_t n) { return h->ix.num_groups > 1 && n >= kLineQueries; }
 
 bool use_index(infaas_sel *h)
 {
@@ -622,7 +665,7 @@ bool use_ranked(const infaas_sel *h)
 int ranked_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_SCAN_LDS, st);
-    if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, true, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
+    if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, true, 0, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
     return INFAAS_SEL_OK;
 }
 
@@ -1156,16 +1199,11 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     DeviceGuard g(h->device);
     if (!g.ok) return INFAAS_SEL_ERR_HIP;
     hipStream_t st = (hipStream_t)hip_stream;
-    // Two mirrors and two launches against one kernel: three tenths more than the sum of the tables' limits.  Where both mirrors hold
-    // everything that is 260,000, just below the 2^18 queries that are in flight at once, where the time makes a step (us for 100,000 /
-    // 200,000 / 300,000 / 450,000 queries, direct and mirrored: two tiers behind a state report on
-    // 100 tasks of 200 variants 23.3 / 25.6 / 28.8 / 32.0 and 30.8 / 31.7 / 31.8 / 33.3, on 50 of 2000 29.4 / 32.3 / 36.0 / 40.0 and 36.5 / 37.1 /
-    // 37.7 / 38.5; complete Case I with workers 13.7 / 17.2 / 24.2 / 29.2 and 25.7 / 27.5 / 30.9 / 33.8, 14.8 / 18.1 / 25.5 / 30.5 and 22.2 / 24.4 /
-    // 23.1 / 24.9).  Where they hold a part of it the line grows with the limits, and direct is further ahead: at 1 / 1.3 / 2 times the sum, two
-    // tiers and complete Case I with workers, 200 tasks of 60 variants (60% of it in the mirror, sum 232,000) 10.6 / 13.0 / 18.2 and 19.8 / 20.6 / 22.8, 19.4 /
-    // 28.4 / 34.5 and 46.6 / 48.4 / 51.4; 400 of 100 (22%, 661,000) 24.9 / 29.7 / 42.0 and 51.1 / 57.8 / 74.7, 46.7 / 56.1 / 79.0 and 90.8 / 98.9 / 135.6; 1000
-    // of 100 on average (8%, 1.87M) 59.7 / 74.7 / 123 and 126 / 157 / 234, 134 / 172 / 282 and 215 / 295 / 407.
-    const bool direct = N <= (direct_limit(h) + direct_limit(h->inactive)) / 10 * 13;
+    // One kernel against two mirrors and two launches.  Up to 1.3 times the sum of the tables' limits every query counts as parked.
+    const IndexShape xa = shape_of(h), xb = shape_of(h->inactive);
+    const bool all = N <= (direct_limit(h, xa) + direct_limit(h->inactive, xb)) / 10 * 13;
+    const bool direct = all || N <= std::max(direct_pays(xa, true, closest), direct_pays(xb, true, closest));
+    const int32_t resident = all ? 0 : std::min(resident_slices(h, xa), resident_slices(h, xb));
     // The lists are allocated for direct calls too: the limits follow the index, and the same call after a report
     // may need them where nothing can be allocated (under capture, after an eager call to warm up).  A direct call
     // that is itself captured does without.
@@ -1188,7 +1226,7 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
         if (closest) q.closest = d_out_closest + done;
         if (direct) {
             LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
-            if (!HIP_OK(launch_direct_modes(h->tv, h->ix, h->inactive->tv, h->inactive->ix, q, true, h->num_cus, st, t.ev())))
+            if (!HIP_OK(launch_direct_modes(h->tv, h->ix, h->inactive->tv, h->inactive->ix, q, true, resident, h->num_cus, st, t.ev())))
                 return INFAAS_SEL_ERR_HIP;
             continue;
         }
@@ -1445,13 +1483,7 @@ int infaas_sel_select_noalloc(infaas_sel_t *h, int64_t N, const int32_t *d_task,
     q.task = d_task; q.slo = d_slo_us; q.min_acc = d_min_acc_bp; q.bidx = d_batch_idx; q.out = d_out_variant;
     q.pass = 0;
     // no event pair even when timing is on: taking one may create it
-    if (use_lines(h, q.n)) {
-        if (!HIP_OK(launch_line_select(h->tv, h->ix, q, h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
-    } else if (q.n <= direct_limit(h)) {
-        if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, false, h->num_cus, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
-    } else if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->static_park, h->index_lds_bytes, h->num_cus,
-                                    (hipStream_t)hip_stream, nullptr)))
-        return INFAAS_SEL_ERR_HIP;
+    if (!HIP_OK(launch_select(h, q, h->static_park, (hipStream_t)hip_stream))) return INFAAS_SEL_ERR_HIP;
     h->last_stats = h->ix.stats;
     return INFAAS_SEL_OK;
 }
