@@ -33,7 +33,7 @@ __device__ __forceinline__ Query load_query(const TableView &tv, const QueryView
 // otherwise only with what their lines leave open.  Counts in st what became of the queries, as a lookup kernel does whose
 // mirror holds the first `resident` slices (0: none).
 template <bool kRanked, bool kAhead>
-__device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want, uint32_t rounds,
+__device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want, uint32_t rounds, bool packed,
                                                       int32_t resident, uint32_t (&st)[kLookupStats])
 {
     const bool away = want && u.s >= (uint32_t)resident;
@@ -51,7 +51,8 @@ __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const
     if (!kRanked || __ballot(want && !scan)) {
         const uint32_t d = line_threshold(ix, u.min_acc, tv.acc_base - 1), l = (uint32_t)u.slo, row_mask = (1u << ix.line_shift()) - 1u;
         uint32_t code, plane;
-        if (rounds == 15u) code = lookup_lines<false>(ix.lines, s * kLineBytes, d, l, row_mask);
+        if (packed) code = lookup_lines_packed(ix.lines, __ballot(want), s * kLineBytes, d, l, row_mask);
+        else if (rounds == 15u) code = lookup_lines<false>(ix.lines, s * kLineBytes, d, l, row_mask);
         else code = lookup_lines<true>(ix.lines, s * kLineBytes, d, l, row_mask, rounds);
         code = want ? code : kCodeNone;   // (of a round that was left out: nothing)
         code = follow_lines(ix, code, s, d, l, tv.S, plane);
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, Ind
         const Query u = load_query(tv, q, i, sp.mine);
         if (first) hand_on_index_stats(tv, news);
         first = false;
-        const int32_t ans = select_from_memory<kRanked, true>(tv, ix, u, u.valid, sp.rounds, resident, st);
+        const int32_t ans = select_from_memory<kRanked, true>(tv, ix, u, u.valid, sp.rounds, false, resident, st);
         if (sp.mine && i < q.n) q.out[i] = ans;
     }
     leave_statistics(ix, st);
@@ -168,11 +169,11 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
         if (first) hand_on_index_stats(ta, news);
         if (kTiers && first) hand_on_index_stats(tb, news2);
         first = false;
-        int32_t ans = select_from_memory<false, false>(ta, ia, u, u.valid, sp.rounds, resident, st), tier = ans >= 0 ? 1 : 0;
+        int32_t ans = select_from_memory<false, false>(ta, ia, u, u.valid, sp.rounds, false, resident, st), tier = ans >= 0 ? 1 : 0;
         if (kTiers) {
             const bool next = u.valid && ans < 0;
             if (__ballot(next)) {
-                const int32_t row = select_from_memory<false, false>(tb, ib, u, next, rounds_of(__ballot(next)), resident, st);
+                const int32_t row = select_from_memory<false, false>(tb, ib, u, next, 15u, __builtin_popcountll(__ballot(next)) <= 48, resident, st);
                 if (next && row >= 0) { ans = row; tier = 2; }
             }
         }

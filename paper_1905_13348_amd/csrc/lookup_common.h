@@ -309,6 +309,24 @@ __device__ __forceinline__ uint32_t of_quad(uint32_t v)   // the value of one of
 {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kLane * 0x55, 0xF, 0xF, true);
 }
+// What a line says, of which this lane has four entries, for the four lanes of its quad.  tag: the lane's number in the quad << 30;
+// shift: 3 in the last of the four, else 31.
+__device__ __forceinline__ uint32_t line_says(const uint4 &w0, const uint4 &w1, uint32_t d, uint32_t l, uint32_t row_mask, uint32_t tag, uint32_t shift)
+{
+    const bool f0 = (w0.x >= d) & (w0.y <= l), f1 = (w0.z >= d) & (w0.w <= l);
+    const bool f2 = (w1.x >= d) & (w1.y <= l), f3 = (w1.z >= d) & (w1.w <= l);
+    uint32_t word = f2 ? w1.x : w1.z;   // the first of the lane's four that fits
+    word = f1 ? w0.z : word;
+    word = f0 ? w0.x : word;
+    uint32_t mine = (word & row_mask) | tag;
+    // nothing fits: the last lane's last entry tells what follows (a step: a code between kCodeOpen and kCodeRank, kLineEnd: all
+    // ones); the other lanes say nothing (all ones, or one less)
+    mine = (f0 | f1 | f2 | f3) ? mine : __builtin_amdgcn_alignbit(~0u, w1.w, shift);
+    uint32_t o = (uint32_t)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xF, 0xF, true);
+    mine = o < mine ? o : mine;
+    o = (uint32_t)__builtin_amdgcn_mov_dpp((int)mine, 0x4E, 0xF, 0xF, true);
+    return o < mine ? o : mine;
+}
 // One query per lane: the line at byte `at` of `lines`, threshold d, latency bound l.  In round r the four lanes of every quad read the
 // line of the query of the r-th of them and compare it with all 16 entries, four to a lane.  `rounds`, where kSome is set: bit r
 // clear: none of the queries of round r is looked at (their code is 0).
@@ -326,19 +344,7 @@ __device__ __forceinline__ uint32_t lookup_lines(const uint8_t *lines, uint32_t 
         w[1] = *(const uint4 *)(lines + at32 + 64);
     };
     auto look = [&](const uint4 (&w)[2], uint32_t dr, uint32_t lr, uint32_t r) __attribute__((always_inline)) {
-        const bool f0 = (w[0].x >= dr) & (w[0].y <= lr), f1 = (w[0].z >= dr) & (w[0].w <= lr);
-        const bool f2 = (w[1].x >= dr) & (w[1].y <= lr), f3 = (w[1].z >= dr) & (w[1].w <= lr);
-        uint32_t word = f2 ? w[1].x : w[1].z;   // the first of the lane's four that fits
-        word = f1 ? w[0].z : word;
-        word = f0 ? w[0].x : word;
-        uint32_t mine = (word & row_mask) | tag;
-        // nothing fits: the last lane's last entry tells what follows (a step: a code between kCodeOpen and kCodeRank, kLineEnd: all
-        // ones); the other lanes say nothing (all ones, or one less)
-        mine = (f0 | f1 | f2 | f3) ? mine : __builtin_amdgcn_alignbit(~0u, w[1].w, shift);
-        uint32_t o = (uint32_t)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xF, 0xF, true);
-        mine = o < mine ? o : mine;
-        o = (uint32_t)__builtin_amdgcn_mov_dpp((int)mine, 0x4E, 0xF, 0xF, true);
-        mine = o < mine ? o : mine;
+        const uint32_t mine = line_says(w[0], w[1], dr, lr, row_mask, tag, shift);
         code = sub == r ? mine : code;
     };
     if (!kSome || (rounds & 1u)) request(v[0], of_quad<0>(at));
@@ -351,12 +357,39 @@ __device__ __forceinline__ uint32_t lookup_lines(const uint8_t *lines, uint32_t 
     if (!kSome || (rounds & 8u)) look(v[3], of_quad<3>(d), of_quad<3>(l), 3u);
     return code;
 }
-// The rounds of lookup_lines that the lanes in a set belong to.
-__device__ __forceinline__ uint32_t rounds_of(uint64_t lanes)
+// The lanes of a set, 16 to a round and each of them to a quad, so that a few queries of a wavefront take one round instead of the four
+// that they are spread over.  Every lane of the wavefront has to be there.  (us, with the rounds of the lanes and so: complete Case I, 250,001 queries on 50
+// tasks of 2000 variants 17.3 / 13.4, 1M on 200 of 60 48.4 / 36.1; suggestions, 300,000 on 100 of 200 14.8 / 11.5.)
+struct Packed {
+    uint32_t count;   // lanes in the set
+    uint32_t place;   // of this lane: among them, or behind them
+    uint32_t lane;    // of the one whose place this lane's number is
+    __device__ __forceinline__ explicit Packed(uint64_t set)
+    {
+        const uint32_t me = threadIdx.x & 63u;
+        count = (uint32_t)__builtin_popcountll(set);
+        place = ((set >> me) & 1u) ? lanes_below(set) : count + lanes_below(~set);
+        lane = (uint32_t)__builtin_amdgcn_ds_permute((int)(place * 4u), (int)me);
+    }
+    // The lane this lane's quad works for in the round that begins with place r0, and of what that quad has found what is this lane's.
+    __device__ __forceinline__ int source(uint32_t r0) const { return __shfl((int)lane, (int)(r0 + ((threadIdx.x & 63u) >> 2))); }
+    __device__ __forceinline__ uint32_t back(uint32_t v) const { return (uint32_t)__shfl((int)v, (int)(4u * (place & 15u))); }
+    __device__ __forceinline__ bool mine(uint32_t r0) const { return place < count && (place >> 4) == (r0 >> 4); }
+};
+// lookup_lines for the lanes in `set` (the others get kCodeNone, and name the empty line).
+__device__ __forceinline__ uint32_t lookup_lines_packed(const uint8_t *lines, uint64_t set, uint32_t at, uint32_t d, uint32_t l, uint32_t row_mask)
 {
-    uint32_t w = (uint32_t)lanes | (uint32_t)(lanes >> 32);
-    w |= w >> 16; w |= w >> 8; w |= w >> 4;
-    return w & 15u;
+    const uint32_t sub = threadIdx.x & 3u, tag = sub << 30, shift = sub == 3u ? 3u : 31u;
+    const Packed p(set);
+    uint32_t code = kCodeNone;
+    for (uint32_t r0 = 0; r0 < p.count; r0 += 16u) {
+        const int from = p.source(r0);
+        const uint32_t at32 = (uint32_t)__shfl((int)at, from) + 16u * sub, dr = (uint32_t)__shfl((int)d, from), lr = (uint32_t)__shfl((int)l, from);
+        const uint4 w0 = *(const uint4 *)(lines + at32), w1 = *(const uint4 *)(lines + at32 + 64);
+        const uint32_t says = p.back(line_says(w0, w1, dr, lr, row_mask, tag, shift));
+        code = p.mine(r0) ? says : code;
+    }
+    return code;
 }
 // From the first line's code on: the lines that follow, for the lanes that need them; `plane` gets the plane of the last one looked at.
 __device__ __forceinline__ uint32_t follow_lines(const IndexView &ix, uint32_t code, uint32_t s, uint32_t d, uint32_t l, int32_t S, uint32_t &plane)
@@ -367,7 +400,7 @@ __device__ __forceinline__ uint32_t follow_lines(const IndexView &ix, uint32_t c
         const bool more = line_open(code);
         const uint64_t some = __ballot(more);
         if (some == 0ull) break;
-        const uint32_t next = lookup_lines<true>(ix.lines, (more ? p * ((uint32_t)S + 1u) + s : (uint32_t)S) * kLineBytes, d, l, row_mask, rounds_of(some));
+        const uint32_t next = lookup_lines_packed(ix.lines, some, (more ? p * ((uint32_t)S + 1u) + s : (uint32_t)S) * kLineBytes, d, l, row_mask);
         code = more ? next : code;
         plane = more ? p : plane;
     }
@@ -379,7 +412,7 @@ __device__ __forceinline__ uint32_t follow_lines(const IndexView &ix, uint32_t c
 // within the latency bound it is the most accurate of those; else where some step is accurate enough the fastest of those; else the
 // fastest of all, the most accurate among equally fast ones; the earliest at a tie: the smallest of {which of the three, 2 bits; latency, none
 // for the first | accuracy from above, 16 bits; place}, by the four lanes of a quad over their entries, then over the lines.
-// The first line is in L1 from the selection; bound by the instructions, 90 to a round.
+// The first line is in L1 from the selection; bound by the instructions, 100 to a round.
 __device__ __forceinline__ uint32_t closest_in_lines(const IndexView &ix, bool want, uint32_t s, int32_t S, uint32_t d, int32_t slo, int32_t min_acc, int32_t acc_base_m1,
                                                      HowFar &how)
 {
@@ -389,10 +422,12 @@ __device__ __forceinline__ uint32_t closest_in_lines(const IndexView &ix, bool w
     for (uint32_t p = 0; p < (uint32_t)kLinePlanes; ++p) {
         const uint64_t some = __ballot(line_open(next));
         if (some == 0ull) break;
-        const uint32_t at = (line_open(next) ? p * ((uint32_t)S + 1u) + s : (uint32_t)S) * kLineBytes, rounds = rounds_of(some);
+        const uint32_t at = (line_open(next) ? p * ((uint32_t)S + 1u) + s : (uint32_t)S) * kLineBytes;
+        const Packed packed(some);
         uint32_t r_hi = ~0u, r_lo = ~0u, r_word = 0u, r_next = kCodeNone;
-        auto look = [&](uint32_t from, uint32_t dr, uint32_t ur, uint32_t r) __attribute__((always_inline)) {
-            const uint32_t at32 = from + 16u * sub;
+        for (uint32_t r0 = 0; r0 < packed.count; r0 += 16u) {
+            const int from = packed.source(r0);
+            const uint32_t at32 = (uint32_t)__shfl((int)at, from) + 16u * sub, dr = (uint32_t)__shfl((int)d, from), ur = (uint32_t)__shfl((int)under, from);
             const uint4 w0 = *(const uint4 *)(ix.lines + at32), w1 = *(const uint4 *)(ix.lines + at32 + 64);
             const uint32_t first[4] = {w0.x, w0.z, w1.x, w1.z}, tot[4] = {w0.y, w0.w, w1.y, w1.w};
             uint32_t m_hi = ~0u, m_lo = ~0u, m_word = 0u;
@@ -420,15 +455,13 @@ __device__ __forceinline__ uint32_t closest_in_lines(const IndexView &ix, bool w
                 take(o_hi, o_lo, o_word);
             }
             const uint32_t follows = of_quad<3>(__builtin_amdgcn_alignbit(~0u, w1.w, shift));   // (of the last lane)
-            r_hi = sub == r ? m_hi : r_hi;
-            r_lo = sub == r ? m_lo : r_lo;
-            r_word = sub == r ? m_word : r_word;
-            r_next = sub == r ? follows : r_next;
-        };
-        if (rounds & 1u) look(of_quad<0>(at), of_quad<0>(d), of_quad<0>(under), 0u);
-        if (rounds & 2u) look(of_quad<1>(at), of_quad<1>(d), of_quad<1>(under), 1u);
-        if (rounds & 4u) look(of_quad<2>(at), of_quad<2>(d), of_quad<2>(under), 2u);
-        if (rounds & 8u) look(of_quad<3>(at), of_quad<3>(d), of_quad<3>(under), 3u);
+            const uint32_t f_hi = packed.back(m_hi), f_lo = packed.back(m_lo), f_word = packed.back(m_word), f_next = packed.back(follows);
+            const bool my = packed.mine(r0);
+            r_hi = my ? f_hi : r_hi;
+            r_lo = my ? f_lo : r_lo;
+            r_word = my ? f_word : r_word;
+            r_next = my ? f_next : r_next;
+        }
         // (the lines before come first: places count from 0 in each)
         const uint32_t r_cmp = r_lo >> 8, b_cmp = b_lo >> 8;
         const bool lower = line_open(next) & ((r_hi < b_hi) | ((r_hi == b_hi) & (r_cmp < b_cmp)));
