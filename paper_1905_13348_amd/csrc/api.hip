@@ -580,17 +580,19 @@ bool mirror_pays(const IndexShape &x, int64_t n)
 constexpr int64_t kLineQueries = 900000;
 // Beyond which size every selection counts as one that the lookup kernel or a kernel in its place has made.
 constexpr int64_t kLargeQueries = (int64_t)1 << 20;
-// With suggestions, and in two tiers, up to how many queries a lane per query is ahead (us at 300,000 / 600,000 / 1M / 1.5M, a lane per
-// query and mirrored): suggestions on 50 tasks of 2000 15.2 / 22.8 / - and 11.3 / 13.3, on 100 of 200 14.8 / 23.3 / 35 and 16.0 / 18.5 / 21.7, on 200 of 60 13.3 / 20.7 /
-// 30.9 / 43 and 26 / 30 / 37 / 50; two tiers behind reports, with workers, 42 / 48 / 57 / 70 and 51 / 53 / 55 / 60, 34 / 39 / 46 / 58 and 45 / 48 / 51 / 57, 33 / 37 / 43 / 53
-// and 48 / 52 / 59 / 70, on 8 of 32 25 / 30 / 36 / 43.5 and 35 / 37 / 40 / 46; complete Case I 21 / 31 / 45 and 26 / 31 / 35, 22 / 34 / 50 and 34 / 38 / 43, 20 / 32 / 48 / 68 and 51 / 57 / 68 /
-// 93, 19 / 31 / 46 and 33 / 37 / 42.  What is outside the mirror and longer staircases (more lines to a query) move the line.
+// With suggestions, and in two tiers, up to how many queries a lane per query is ahead (us at 300,000 / 600,000 / 1M / 1.5M / 2.5M, a lane per
+// query and mirrored).  Suggestions on 50 tasks of 2000 variants 13.2 / 19.4 and 11.2 / 13.3, on 100 of 200 11.3 / 17.2 / 25.2 and 16.0 / 19.2 / 21.8, on 200
+// of 60 11.8 / 17.4 / 24.5 / 33 / 56 and 26 / 30 / 37 / 50 / 72, on 8 of 32 8.8 / 13.4 / 18.9 and 10.5 / 12.7 / 14.7.  Two tiers behind reports, with workers:
+// 42 / 47 / 55 / 66 and 51 / 53 / 55 / 60, 36 / 40 / 44 / 55 / 75 and 45 / 48 / 51 / 58 / 72, 35 / 38 / 43 / 53 / 74 and 48 / 52 / 59 / 71 / 95, 25 / 30 / 35 / 42 / 65 and
+// 35 / 37 / 40 / 46 / 57.  Complete Case I: 18 / 26 / 38 / 52 and 26 / 31 / 34 / 41, 17 / 25 / 36 / 50 / 81 and 34 / 38 / 43 / 55 / 81, 17 / 25 / 36 / 51 / 82 and 45 / 56 /
+// 68 / 93 / 132, 15 / 23 / 34 / 47 / 77 and 33 / 37 / 43 / 55 / 80.  What is outside the mirror and longer staircases (more lines to a query) move
+// the line.
 int64_t direct_pays(const IndexShape &x, bool tiers, bool closest)
 {
     if (x.room == 0) return INT64_MAX;
     const bool brief = x.steps <= 16.0;
-    const double base = !tiers ? (brief ? 280e3 : 150e3) : closest ? (brief ? 700e3 : 550e3) : (brief ? 1.2e6 : 800e3);
-    return (int64_t)(base * (1.0 + (tiers ? 15.0 : 4.0) * x.outside) * (1.0 + 200.0 * x.open));
+    const double base = !tiers ? (brief ? 450e3 : 200e3) : closest ? (brief ? 2.2e6 : 800e3) : (brief ? 1.55e6 : 950e3);
+    return (int64_t)(base * (1.0 + (tiers ? 15.0 : 8.0) * x.outside) * (1.0 + 200.0 * x.open));
 }
 
 // How many slices the mirror would hold, as bodies are placed in the order of the slices (or of their arrival).
@@ -616,7 +618,7 @@ int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
         const bool all = q.n <= direct_limit(h, x, true);
         if (all || q.n <= direct_pays(x, false, true)) {
             const hipError_t e = launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, all ? 0 : resident_slices(h, x),
-                                                     h->num_cus, st, t.ev());
+                                                     x.open > 0, h->num_cus, st, t.ev());
             return HIP_OK(e) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
         }
     }
@@ -1226,7 +1228,7 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
         if (closest) q.closest = d_out_closest + done;
         if (direct) {
             LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
-            if (!HIP_OK(launch_direct_modes(h->tv, h->ix, h->inactive->tv, h->inactive->ix, q, true, resident, h->num_cus, st, t.ev())))
+            if (!HIP_OK(launch_direct_modes(h->tv, h->ix, h->inactive->tv, h->inactive->ix, q, true, resident, xa.open > 0 || xb.open > 0, h->num_cus, st, t.ev())))
                 return INFAAS_SEL_ERR_HIP;
             continue;
         }

@@ -32,8 +32,9 @@ __device__ __forceinline__ Query load_query(const TableView &tv, const QueryView
 // queries at all.  kRanked: slices that the index does not hold completely go through their entries in rank order at once;
 // otherwise only with what their lines leave open.  Counts in st what became of the queries, as a lookup kernel does whose
 // mirror holds the first `resident` slices (0: none).
+// incomplete: there are such slices, and their queries do so here too.
 template <bool kRanked, bool kAhead>
-__device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want, uint32_t rounds, bool packed,
+__device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want, uint32_t rounds, bool packed, bool incomplete,
                                                       int32_t resident, uint32_t (&st)[kLookupStats])
 {
     const bool away = want && u.s >= (uint32_t)resident;
@@ -42,7 +43,7 @@ __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const
     uint32_t s = want ? u.s : (uint32_t)tv.S;
     uint4 rh{};
     bool scan = false;
-    if (kRanked) {
+    if (kRanked || incomplete) {
         rh = tv.rank_hdr[s];
         scan = want && rh.w != 0u;
         s = scan ? (uint32_t)tv.S : s;
@@ -58,13 +59,13 @@ __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const
         code = follow_lines(ix, code, s, d, l, tv.S, plane);
         const bool hit = code < kCodeOpen;
         if (hit) ans = ix.line_rows() ? (int32_t)(code & row_mask) : ix.step_row[ix.hdr[s].z + (code & row_mask)];
-        if (!kRanked) scan = code == kCodeRank;
+        if (!kRanked) scan = scan || code == kCodeRank;
         count(1, hit && plane > 1u);
         count(2, hit && plane <= 1u && away);
         deep = plane > 1u;
     }
     if (__ballot(scan)) {
-        if (!kRanked) rh = tv.rank_hdr[s];
+        if (!kRanked && !incomplete) rh = tv.rank_hdr[s];
         const int32_t row = ranked_first_fit<kAhead>(tv, scan ? rh : make_uint4(0u, 0u, 0u, 0u), u.min_acc, (uint32_t)u.slo);
         if (scan) ans = row;
         count(3, scan);
@@ -78,10 +79,12 @@ __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const
 // The closest variant of the table for the lanes in `want` (queries inside the table that nothing satisfies),
 // and how far it is from the requirements: from the lines, or where they do not hold all of the slice's steps
 // by the wavefront over the whole slice.
-__device__ __forceinline__ int32_t closest_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want, HowFar &how)
+__device__ __forceinline__ int32_t closest_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want, bool incomplete, HowFar &how)
 {
     const uint32_t s = want ? u.s : (uint32_t)tv.S;
-    const uint32_t code = closest_in_lines(ix, want, s, tv.S, line_threshold(ix, u.min_acc, tv.acc_base - 1), u.slo, u.min_acc, tv.acc_base - 1, how);
+    const bool scan = incomplete && tv.rank_hdr[s].w != 0u;
+    uint32_t code = closest_in_lines(ix, want && !scan, s, tv.S, line_threshold(ix, u.min_acc, tv.acc_base - 1), u.slo, u.min_acc, tv.acc_base - 1, how);
+    code = scan ? kCodeRank : code;
     int32_t sug = -1;
     if (want && code < kCodeOpen) sug = ix.line_rows() ? (int32_t)code : ix.step_row[ix.hdr[s].z + code];
     uint64_t rest = __ballot(want && code == kCodeRank);
@@ -143,7 +146,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, Ind
         const Query u = load_query(tv, q, i, sp.mine);
         if (first) hand_on_index_stats(tv, news);
         first = false;
-        const int32_t ans = select_from_memory<kRanked, true>(tv, ix, u, u.valid, sp.rounds, false, resident, st);
+        const int32_t ans = select_from_memory<kRanked, true>(tv, ix, u, u.valid, sp.rounds, false, false, resident, st);
         if (sp.mine && i < q.n) q.out[i] = ans;
     }
     leave_statistics(ix, st);
@@ -155,7 +158,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, Ind
 // Bound by its launch and the chain of dependent reads, like the two passes of the lookup kernel that it replaces, but
 // once and without the two LDS mirrors.
 template <bool kTiers, bool kSuggest, bool kWorker>
-__global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, IndexView ia, TableView tb, IndexView ib, QueryView q, int32_t spread, int32_t resident)
+__global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, IndexView ia, TableView tb, IndexView ib, QueryView q, int32_t spread, int32_t resident, bool incomplete)
 {
     const int32_t per = 64 >> spread, step = per * (kDirThreads / 64);
     const Spread sp = spread_of(spread);
@@ -169,11 +172,11 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
         if (first) hand_on_index_stats(ta, news);
         if (kTiers && first) hand_on_index_stats(tb, news2);
         first = false;
-        int32_t ans = select_from_memory<false, false>(ta, ia, u, u.valid, sp.rounds, false, resident, st), tier = ans >= 0 ? 1 : 0;
+        int32_t ans = select_from_memory<false, false>(ta, ia, u, u.valid, sp.rounds, false, incomplete, resident, st), tier = ans >= 0 ? 1 : 0;
         if (kTiers) {
             const bool next = u.valid && ans < 0;
             if (__ballot(next)) {
-                const int32_t row = select_from_memory<false, false>(tb, ib, u, next, 15u, __builtin_popcountll(__ballot(next)) <= 48, resident, st);
+                const int32_t row = select_from_memory<false, false>(tb, ib, u, next, 15u, __builtin_popcountll(__ballot(next)) <= 48, incomplete, resident, st);
                 if (next && row >= 0) { ans = row; tier = 2; }
             }
         }
@@ -182,10 +185,10 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
             const bool none = u.inside && ans < 0;
             if (__ballot(none)) {
                 HowFar how;
-                int32_t sug = closest_from_memory(ta, ia, u, none, how);
+                int32_t sug = closest_from_memory(ta, ia, u, none, incomplete, how);
                 if (kTiers) {   // the closer of the two tiers' suggestions, the first tier's at a tie
                     HowFar how2;
-                    const int32_t sug2 = closest_from_memory(tb, ib, u, none, how2);
+                    const int32_t sug2 = closest_from_memory(tb, ib, u, none, incomplete, how2);
                     if (sug2 >= 0 && !(sug >= 0 && closer_or_equal(how, how2))) sug = sug2;
                 }
                 if (none) closest = sug;
@@ -226,13 +229,13 @@ hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const 
 }
 
 hipError_t launch_direct_modes(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, const QueryView &q,
-                               bool tiers, int32_t resident, int num_cus, hipStream_t st, const LaunchEvents *ev)
+                               bool tiers, int32_t resident, bool incomplete, int num_cus, hipStream_t st, const LaunchEvents *ev)
 {
     const int32_t per = queries_per_wave(q.n, 16, num_cus);
     const int64_t step = per * (kDirThreads / 64), want = ((int64_t)q.n + step - 1) / step, most = index_stat_blocks(num_cus);
     auto kernel = !tiers ? k_direct_modes<false, true, false> : q.worker ? (q.closest ? k_direct_modes<true, true, true> : k_direct_modes<true, false, true>)
                                                               : (q.closest ? k_direct_modes<true, true, false> : k_direct_modes<true, false, false>);
-    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, ta, ia, tb, ib, q, __builtin_ctz(64u / (unsigned)per), resident);
+    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, ta, ia, tb, ib, q, __builtin_ctz(64u / (unsigned)per), resident, incomplete);
 }
 
 }  // namespace infaas
