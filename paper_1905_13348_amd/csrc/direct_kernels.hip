@@ -205,8 +205,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
 }
 
 // How many queries a wavefront takes.  A batch too small to give every SIMD two full wavefronts is spread over as many with fewer queries
-// each, down to the 16 that one round of search_bodies_by_four serves (two tiers, 1001 queries 8.5 -> 6.6 us, with workers 8.6 -> 6.7; to
-// bisection 16 to 64 of them are the same in a selection, and 16 up to 7% faster with two tiers).  In rank order, where a
+// each, down to the 16 that are one round of lookup_lines.  In rank order, where a
 // wavefront finishes its hard queries one after the other, down to one.  (us for 1001 / 10,001 / 30,001 queries, 64 to a wavefront and so: 2000 entries of random
 // accuracy and latency to a slice, most queries without an answer, 75 / 75 / 76 and 6.1 / 14 / 23, with the scan engine 37 / 63 / 89; every entry a step, nothing
 // hard about it, 6.0 / 6.1 / 6.1 and 6.2 / 6.2 / 6.2, where four wavefronts per SIMD took 6.1 / 6.6 / 8.1.)
