@@ -1,6 +1,9 @@
 """Two handles with different tables working at the same time on two streams: every answer against the
 CPU oracle.  A handle owns its table, index and scratch memory, so handles do not have to be ordered
 with each other (only infaas_sel_select_noalloc shares memory between handles)."""
+import ctypes
+import threading
+
 import numpy as np
 import pytest
 
@@ -42,3 +45,43 @@ def test_two_handles_on_two_streams(oracle_lib):
             assert bad.size == 0, f"config {c} round {r}: {bad.size} differ, first at {bad[:5]}"
     for sel in sels:
         sel.destroy()
+
+
+def _thread_local_data(library):
+    """Address of the calling thread's thread-local data of a loaded library; 0 while the thread has read none of it."""
+    class Info(ctypes.Structure):
+        _fields_ = [("addr", ctypes.c_size_t), ("name", ctypes.c_char_p), ("phdr", ctypes.c_void_p), ("phnum", ctypes.c_uint16),
+                    ("adds", ctypes.c_ulonglong), ("subs", ctypes.c_ulonglong), ("tls_module", ctypes.c_size_t), ("tls_data", ctypes.c_size_t)]
+    found = []
+
+    @ctypes.CFUNCTYPE(ctypes.c_int, ctypes.POINTER(Info), ctypes.c_size_t, ctypes.c_void_p)
+    def look(info, size, data):
+        if info.contents.name.endswith(library.encode()):
+            found.append((info.contents.tls_module, info.contents.tls_data))
+        return 0
+    ctypes.CDLL(None).dl_iterate_phdr(look, None)
+    assert len(found) == 1 and found[0][0] > 0
+    return found[0][1]
+
+
+@pytest.mark.parametrize("call", ["select", "update_load"])
+def test_a_call_brings_its_threads_storage_up_to_date(call):
+    """A thread that has called the library has read a thread-local variable of it (without which every other library's cost it more)."""
+    import torch
+    tb = workloads.make_table(0)
+    sel = make_selector(tb, engine=0)
+    dev = [to_dev(x[:1000]) for x in query_args(workloads.make_queries(0))]
+    out = torch.empty_like(dev[0])
+    rows = to_dev(np.arange(10))
+    seen = []
+
+    def work():
+        seen.append(_thread_local_data("libinfaas_sel.so"))
+        sel.select(*dev, out) if call == "select" else sel.update_load(rows, rows)
+        seen.append(_thread_local_data("libinfaas_sel.so"))
+    thread = threading.Thread(target=work)
+    thread.start()
+    thread.join()
+    torch.cuda.synchronize()
+    assert len(seen) == 2 and seen[0] == 0 and seen[1] != 0
+    sel.destroy()
