@@ -1445,7 +1445,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
             // parked: a miss that the second body / the scan may still turn into a hit; in the
             // closest-variant mode also every final miss of a query inside the table
             df[k] = !hit && ((int32_t)y[k] < 0 || (kSuggest && sl_of[k] != (uint32_t)tv.S));
-            if (kSuggest && (int32_t)y[k] >= 0) sl_of[k] |= kParkFinal;   // nothing feasible: only the suggestion is open
+            if (kSuggest && df[k] && (int32_t)y[k] >= 0) sl_of[k] |= kParkFinal;   // nothing feasible: only the suggestion is open
         }
         p_i0 = i0;
 #pragma unroll

@@ -140,3 +140,30 @@ def test_case1_config3_and_config2(oracle_lib):
         var, tier, sug = _check(oracle_lib, sel, tb, st.state, st.load_us, query_args(q), f"config{cfg}")
         assert ((var < 0) & (sug >= 0)).sum() > 10_000
         sel.destroy()
+
+
+@pytest.mark.parametrize("workers", [False, True])
+def test_queries_outside_the_table_are_not_listed(workers):
+    """A large call (two passes of the lookup kernel) of queries outside the table, and lanes beyond its end: the first pass
+    lists none of them for the second, which counts as parked what it finds in the lists."""
+    import torch
+    from test_gpu_workers import cluster_args, load_cluster
+    tb = workloads.make_table(0)
+    st = workloads.make_states(0, tb.V)
+    sel = make_selector(tb, engine=0)
+    sel.load_states(st.state, st.load_us)
+    if workers:
+        load_cluster(sel, cluster_args(workloads.make_workers(0, st)))
+    n = 8_000_001
+    task, bidx = (torch.zeros(n, dtype=torch.int32, device="cuda") for _ in range(2))
+    task[::2], bidx[1::2] = tb.num_tasks, -1
+    slo, acc = torch.full_like(task, I32MAX), torch.full_like(task, -I32MAX)
+    outs = [torch.full_like(task, -9) for _ in range(4 if workers else 3)]
+    sel.set_timing(True)
+    (sel.select_workers_closest if workers else sel.select_tiered_closest)(task, slo, acc, bidx, *outs)
+    torch.cuda.synchronize()
+    assert sel.get_timings()["index_select"]["launches"] == 2
+    for k, o in enumerate(outs):
+        assert (o == (0 if k == 1 else -1)).all()
+    assert sel.info()["lookup_parked"] == 0
+    sel.destroy()
