@@ -495,6 +495,14 @@ typedef struct {
 int infaas_sel_set_timing(infaas_sel_t *h, int32_t enabled); /* also resets the counters */
 int infaas_sel_get_timings(infaas_sel_t *h, infaas_sel_timings *out);
 
+/* Ways of a lookup in the index; which one a call takes depends on its size and on the shape of the index. */
+enum {
+    INFAAS_SEL_ROUTE_NONE = 0,   /* no selection yet, or one that did not use the index */
+    INFAAS_SEL_ROUTE_MEMORY = 1, /* a lane per query, straight from global memory */
+    INFAAS_SEL_ROUTE_MIRROR = 2, /* through a mirror of the index in every compute unit's LDS */
+    INFAAS_SEL_ROUTE_TILES = 3   /* a tile of queries per workgroup at a time, one line of global memory per query */
+};
+
 /* Sizes the library derived from the loaded table. */
 typedef struct {
     int32_t num_variants;       /* V */
@@ -512,12 +520,13 @@ typedef struct {
     int64_t table_bytes;        /* device bytes of the variant store and of the levels and sorted blocks that slices
                                    are searched through in rank order */
     int64_t scratch_bytes;      /* device bytes of scratch currently reserved */
-    /* The most recent launch of the index lookup kernel on this handle (for a state-aware call: the
-     * Inactive tier's): the queries whose answer the first group of their slice's staircase, as
-     * mirrored in LDS, could not decide, and what became of them.  A small batch answered straight from global
-     * memory has no mirror: there every query with a valid slice and bound counts as parked, every answer of a first
-     * group as one from global memory, and the two tiers of a state-aware call are counted together.  All 0 after a
-     * selection that did not use the index.  Valid once the caller has
+    /* The most recent index lookup on this handle (of a state-aware call in two launches: the
+     * Inactive tier's): the queries that were set aside, and what became of them.  By lookup_route:
+     * MIRROR: those whose answer the first group of their slice's staircase, as mirrored in LDS, could not decide;
+     * TILES:  those whose answer the first line of their slice could not decide;
+     * MEMORY: every query with a valid slice and bound (every answer of a first group then counts as one from global
+     *         memory), and the two tiers of a state-aware call are counted together.
+     * All 0 after a selection that did not use the index.  Valid once the caller has
      * synchronised the stream of that call; infaas_sel_get_info copies them with a blocking hipMemcpy. */
     int64_t lookup_parked;      /* queries set aside for the slower paths */
     int64_t lookup_second_body; /* ... answered by the second group of steps */
@@ -527,7 +536,7 @@ typedef struct {
     int32_t index_groups;       /* 1: one LDS holds (part of) the whole index; more: the tasks are dealt to this many
                                    groups whose staircases fit one LDS each, and calls of a million queries or more
                                    read one line of memory per query */
-    int32_t reserved0;
+    int32_t lookup_route;       /* INFAAS_SEL_ROUTE_*: how the most recent selection was looked up */
 } infaas_sel_info;
 int infaas_sel_get_info(infaas_sel_t *h, infaas_sel_info *out);
 

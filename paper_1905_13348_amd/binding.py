@@ -55,7 +55,7 @@ class _Info(ctypes.Structure):
                 ("scratch_bytes", ctypes.c_int64),
                 ("lookup_parked", ctypes.c_int64), ("lookup_second_body", ctypes.c_int64),
                 ("lookup_global_body", ctypes.c_int64), ("lookup_scanned", ctypes.c_int64),
-                ("lookup_unanswered", ctypes.c_int64), ("index_groups", ctypes.c_int32), ("reserved0", ctypes.c_int32)]
+                ("lookup_unanswered", ctypes.c_int64), ("index_groups", ctypes.c_int32), ("lookup_route", ctypes.c_int32)]
 
 
 _lib: Optional[ctypes.CDLL] = None

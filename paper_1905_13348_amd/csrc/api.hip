@@ -145,6 +145,7 @@ struct infaas_sel {
     uint32_t *host_stats = nullptr;   // pinned, device-visible: six counters of the latest index build (kCtlMaxK0 .., pool, steps)
     int32_t *static_park = nullptr;   // the same queues inside the library's static device array (may be null)
     const uint32_t *last_stats = nullptr;   // statistics of the most recent lookup launch (this table's or the Inactive tier's)
+    int32_t last_route = 0;                 // INFAAS_SEL_ROUTE_* of that launch
 
     // scan scratch
     ScanScratch sc{};
@@ -538,8 +539,7 @@ int64_t body_pool(const infaas_sel *h)
 
 // Which way a lookup goes.  The mirror costs its fill (2-4 us, more with many slices) and pays with 4 ps per query, if it holds the
 // query's slice and the slice's first body has the answer; a line read from memory costs 7 to 9, one query per lane or, with a tile of them
-// at a time, 6 to 8 and a start of 2 us.  Up to direct_limit() every query counts as parked, as ever; beyond it the same kernel may
-// still be the faster one (below).
+// at a time, 6 to 8 and a start of 2 us.
 constexpr int64_t kDirectQueries = 100000;
 constexpr int64_t kDirectSuggestions = 75000;
 struct IndexShape {
@@ -582,7 +582,6 @@ bool mirror_pays(const IndexShape &x, int64_t n)
 // ... and where it is not, from how many queries on a tile at a time is ahead of a lane per query (8000 slices, 900,000 queries 13.6 and 14.8, 1.05M
 // 15.5 and 15.9; 64M queries, binned by group of tasks whose bodies fit one LDS, 729, so 459).
 constexpr int64_t kLineQueries = 900000;
-// Beyond which size every selection counts as one that the lookup kernel or a kernel in its place has made.
 constexpr int64_t kLargeQueries = (int64_t)1 << 20;
 // With suggestions, and in two tiers, up to how many queries a lane per query is ahead (us at 300,000 / 600,000 / 1M / 1.5M / 2.5M, a lane per
 // query and mirrored).  Suggestions on 50 tasks of 2000 variants 13.2 / 19.4 and 11.2 / 13.3, on 100 of 200 11.3 / 17.2 / 25.2 and 16.0 / 19.2 / 21.8, on 200
@@ -599,17 +598,15 @@ int64_t direct_pays(const IndexShape &x, bool tiers, bool closest)
     return (int64_t)(base * (1.0 + (tiers ? 15.0 : 8.0) * x.outside) * (1.0 + 200.0 * x.open));
 }
 
-// How many slices the mirror would hold, as bodies are placed in the order of the slices (or of their arrival).
-int32_t resident_slices(const infaas_sel *h, const IndexShape &x) { return (int32_t)((1.0 - x.outside) * (h->T * h->B)); }
-
 // The plain selection, n <= 2^28 queries.  park: the lookup kernel's queues.
-hipError_t launch_select(const infaas_sel *h, const QueryView &q, int32_t *park, hipStream_t st, const LaunchEvents *ev = nullptr)
+hipError_t launch_select(infaas_sel *h, const QueryView &q, int32_t *park, hipStream_t st, const LaunchEvents *ev = nullptr)
 {
     const IndexShape x = shape_of(h);
-    if (q.n < kLargeQueries && q.n <= direct_limit(h, x)) return launch_direct_select(h->tv, h->ix, q, false, 0, h->num_cus, st, ev);
-    if (mirror_pays(x, q.n)) return launch_index_select(h->tv, h->ix, q, park, h->index_lds_bytes, h->num_cus, st, ev);
-    if (q.n >= kLineQueries) return launch_line_select(h->tv, h->ix, q, h->num_cus, st, ev);
-    return launch_direct_select(h->tv, h->ix, q, false, resident_slices(h, x), h->num_cus, st, ev);
+    const bool few = q.n < kLargeQueries && q.n <= direct_limit(h, x);
+    h->last_route = !few && mirror_pays(x, q.n) ? INFAAS_SEL_ROUTE_MIRROR : !few && q.n >= kLineQueries ? INFAAS_SEL_ROUTE_TILES : INFAAS_SEL_ROUTE_MEMORY;
+    if (h->last_route == INFAAS_SEL_ROUTE_MIRROR) return launch_index_select(h->tv, h->ix, q, park, h->index_lds_bytes, h->num_cus, st, ev);
+    if (h->last_route == INFAAS_SEL_ROUTE_TILES) return launch_line_select(h->tv, h->ix, q, h->num_cus, st, ev);
+    return launch_direct_select(h->tv, h->ix, q, false, h->num_cus, st, ev);
 }
 
 // One pass of the index engine over n <= 2^28 queries.
@@ -619,13 +616,13 @@ int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
     if (q.pass == 0) return HIP_OK(launch_select(h, q, h->d_park, st, t.ev())) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
     if (q.pass == 1) {
         const IndexShape x = shape_of(h);
-        const bool all = q.n <= direct_limit(h, x, true);
-        if (all || q.n <= direct_pays(x, false, true)) {
-            const hipError_t e = launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, all ? 0 : resident_slices(h, x),
-                                                     x.open > 0, h->num_cus, st, t.ev());
+        if (q.n <= direct_limit(h, x, true) || q.n <= direct_pays(x, false, true)) {
+            h->last_route = INFAAS_SEL_ROUTE_MEMORY;
+            const hipError_t e = launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, x.open > 0, h->num_cus, st, t.ev());
             return HIP_OK(e) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
         }
     }
+    h->last_route = INFAAS_SEL_ROUTE_MIRROR;
     if (!HIP_OK(launch_index_select(h->tv, h->ix, q, h->d_park, h->index_lds_bytes, h->num_cus, st, t.ev())))
         return INFAAS_SEL_ERR_HIP;
     return INFAAS_SEL_OK;
@@ -671,7 +668,7 @@ bool use_ranked(const infaas_sel *h)
 int ranked_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
 {
     LaunchTimer t(h, INFAAS_SEL_K_SCAN_LDS, st);
-    if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, true, 0, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
+    if (!HIP_OK(launch_direct_select(h->tv, h->ix, q, true, h->num_cus, st, t.ev()))) return INFAAS_SEL_ERR_HIP;
     return INFAAS_SEL_OK;
 }
 
@@ -1205,11 +1202,9 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     DeviceGuard g(h->device);
     if (!g.ok) return INFAAS_SEL_ERR_HIP;
     hipStream_t st = (hipStream_t)hip_stream;
-    // One kernel against two mirrors and two launches.  Up to 1.3 times the sum of the tables' limits every query counts as parked.
+    // One kernel against two mirrors and two launches.
     const IndexShape xa = shape_of(h), xb = shape_of(h->inactive);
-    const bool all = N <= (direct_limit(h, xa) + direct_limit(h->inactive, xb)) / 10 * 13;
-    const bool direct = all || N <= std::max(direct_pays(xa, true, closest), direct_pays(xb, true, closest));
-    const int32_t resident = all ? 0 : std::min(resident_slices(h, xa), resident_slices(h, xb));
+    const bool direct = N <= (direct_limit(h, xa) + direct_limit(h->inactive, xb)) / 10 * 13 || N <= std::max(direct_pays(xa, true, closest), direct_pays(xb, true, closest));
     // The lists are allocated for direct calls too: the limits follow the index, and the same call after a report
     // may need them where nothing can be allocated (under capture, after an eager call to warm up).  A direct call
     // that is itself captured does without.
@@ -1230,9 +1225,10 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
         q.open_cap = index_open_cap(q.n, h->num_cus);
         if (workers) { q.worker = d_out_worker + done; q.row_worker = h->wv.row_worker; }
         if (closest) q.closest = d_out_closest + done;
+        h->last_route = INFAAS_SEL_ROUTE_MEMORY;
         if (direct) {
             LaunchTimer t(h, INFAAS_SEL_K_INDEX_SELECT, st);
-            if (!HIP_OK(launch_direct_modes(h->tv, h->ix, h->inactive->tv, h->inactive->ix, q, true, resident, xa.open > 0 || xb.open > 0, h->num_cus, st, t.ev())))
+            if (!HIP_OK(launch_direct_modes(h->tv, h->ix, h->inactive->tv, h->inactive->ix, q, true, xa.open > 0 || xb.open > 0, h->num_cus, st, t.ev())))
                 return INFAAS_SEL_ERR_HIP;
             continue;
         }
@@ -1756,6 +1752,7 @@ int infaas_sel_get_info(infaas_sel_t *h, infaas_sel_info *out)
     if (h->have_index) {
         out->index_in_lds = h->index_lds_bytes > 0 ? 1 : 0;
         out->index_groups = (int32_t)h->ix.num_groups;
+        out->lookup_route = h->last_stats ? h->last_route : 0;
         // (as of the latest build that a selection has run behind, else as loaded)
         const volatile uint32_t *now = h->host_stats;
         out->index_truncated = (int32_t)(now ? now[kCtlTrunc - kCtlMaxK0] + now[kCtlNoBody - kCtlMaxK0]

@@ -30,15 +30,13 @@ __device__ __forceinline__ Query load_query(const TableView &tv, const QueryView
 
 // The selection for the lanes in `want` (of valid queries), -1 elsewhere.  `rounds`: of lookup_lines, those of the lanes that have
 // queries at all.  kRanked: slices that the index does not hold completely go through their entries in rank order at once;
-// otherwise only with what their lines leave open.  Counts in st what became of the queries, as a lookup kernel does whose
-// mirror holds the first `resident` slices (0: none).
+// otherwise only with what their lines leave open.  Counts in st what became of the queries; there is no mirror, so all of
+// them count as set aside.
 // incomplete: there are such slices, and their queries do so here too.
 template <bool kRanked, bool kAhead>
 __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const IndexView &ix, const Query &u, bool want, uint32_t rounds, bool packed, bool incomplete,
-                                                      int32_t resident, uint32_t (&st)[kLookupStats])
+                                                      uint32_t (&st)[kLookupStats])
 {
-    const bool away = want && u.s >= (uint32_t)resident;
-    bool deep = false;   // beyond the first group of steps
     auto count = [&](int what, bool yes) { st[what] += (uint32_t)__builtin_popcountll(__ballot(yes)); };
     uint32_t s = want ? u.s : (uint32_t)tv.S;
     uint4 rh{};
@@ -61,8 +59,7 @@ __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const
         if (hit) ans = ix.line_rows() ? (int32_t)(code & row_mask) : ix.step_row[ix.hdr[s].z + (code & row_mask)];
         if (!kRanked) scan = scan || code == kCodeRank;
         count(1, hit && plane > 1u);
-        count(2, hit && plane <= 1u && away);
-        deep = plane > 1u;
+        count(2, hit && plane <= 1u);
     }
     if (__ballot(scan)) {
         if (!kRanked && !incomplete) rh = tv.rank_hdr[s];
@@ -70,9 +67,8 @@ __device__ __forceinline__ int32_t select_from_memory(const TableView &tv, const
         if (scan) ans = row;
         count(3, scan);
     }
-    const bool parked = away || (want && (deep || scan));
-    count(0, parked);
-    count(4, parked && ans < 0);
+    count(0, want);
+    count(4, want && ans < 0);
     return ans;
 }
 
@@ -134,7 +130,7 @@ __device__ __forceinline__ Spread spread_of(int32_t spread)   // 2^spread lanes 
 // Bound by the rate of scattered reads, a line (4.5 ps) and its share of further ones per query, and below 100,000 queries by the launch
 // and three dependent trips to memory (arguments, fields, line).
 template <bool kRanked>
-__global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, IndexView ix, QueryView q, int32_t spread, int32_t resident)
+__global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, IndexView ix, QueryView q, int32_t spread)
 {
     const int32_t wave = threadIdx.x >> 6, per = 64 >> spread, step = per * (kDirThreads / 64);
     const Spread sp = spread_of(spread);
@@ -146,7 +142,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, Ind
         const Query u = load_query(tv, q, i, sp.mine);
         if (first) hand_on_index_stats(tv, news);
         first = false;
-        const int32_t ans = select_from_memory<kRanked, true>(tv, ix, u, u.valid, sp.rounds, false, false, resident, st);
+        const int32_t ans = select_from_memory<kRanked, true>(tv, ix, u, u.valid, sp.rounds, false, false, st);
         if (sp.mine && i < q.n) q.out[i] = ans;
     }
     leave_statistics(ix, st);
@@ -158,7 +154,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_select(TableView tv, Ind
 // Bound by its launch and the chain of dependent reads, like the two passes of the lookup kernel that it replaces, but
 // once and without the two LDS mirrors.
 template <bool kTiers, bool kSuggest, bool kWorker>
-__global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, IndexView ia, TableView tb, IndexView ib, QueryView q, int32_t spread, int32_t resident, bool incomplete)
+__global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, IndexView ia, TableView tb, IndexView ib, QueryView q, int32_t spread, bool incomplete)
 {
     const int32_t per = 64 >> spread, step = per * (kDirThreads / 64);
     const Spread sp = spread_of(spread);
@@ -172,11 +168,11 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_modes(TableView ta, Inde
         if (first) hand_on_index_stats(ta, news);
         if (kTiers && first) hand_on_index_stats(tb, news2);
         first = false;
-        int32_t ans = select_from_memory<false, false>(ta, ia, u, u.valid, sp.rounds, false, incomplete, resident, st), tier = ans >= 0 ? 1 : 0;
+        int32_t ans = select_from_memory<false, false>(ta, ia, u, u.valid, sp.rounds, false, incomplete, st), tier = ans >= 0 ? 1 : 0;
         if (kTiers) {
             const bool next = u.valid && ans < 0;
             if (__ballot(next)) {
-                const int32_t row = select_from_memory<false, false>(tb, ib, u, next, 15u, __builtin_popcountll(__ballot(next)) <= 48, incomplete, resident, st);
+                const int32_t row = select_from_memory<false, false>(tb, ib, u, next, 15u, __builtin_popcountll(__ballot(next)) <= 48, incomplete, st);
                 if (next && row >= 0) { ans = row; tier = 2; }
             }
         }
@@ -218,23 +214,23 @@ int32_t queries_per_wave(int64_t n, int32_t least, int num_cus)
 
 }  // namespace
 
-hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int32_t resident, int num_cus,
+hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int num_cus,
                                 hipStream_t st, const LaunchEvents *ev)
 {
     const int32_t per = queries_per_wave(q.n, ranked ? 1 : 16, num_cus);
     const int64_t step = per * (kDirThreads / 64), want = ((int64_t)q.n + step - 1) / step, most = index_stat_blocks(num_cus);
     auto kernel = ranked ? k_direct_select<true> : k_direct_select<false>;
-    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, tv, ix, q, __builtin_ctz(64u / (unsigned)per), resident);
+    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, tv, ix, q, __builtin_ctz(64u / (unsigned)per));
 }
 
 hipError_t launch_direct_modes(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, const QueryView &q,
-                               bool tiers, int32_t resident, bool incomplete, int num_cus, hipStream_t st, const LaunchEvents *ev)
+                               bool tiers, bool incomplete, int num_cus, hipStream_t st, const LaunchEvents *ev)
 {
     const int32_t per = queries_per_wave(q.n, 16, num_cus);
     const int64_t step = per * (kDirThreads / 64), want = ((int64_t)q.n + step - 1) / step, most = index_stat_blocks(num_cus);
     auto kernel = !tiers ? k_direct_modes<false, true, false> : q.worker ? (q.closest ? k_direct_modes<true, true, true> : k_direct_modes<true, false, true>)
                                                               : (q.closest ? k_direct_modes<true, true, false> : k_direct_modes<true, false, false>);
-    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, ta, ia, tb, ib, q, __builtin_ctz(64u / (unsigned)per), resident, incomplete);
+    return launch_kernel(ev, kernel, dim3((unsigned)(want < most ? want : most)), dim3(kDirThreads), 0, st, ta, ia, tb, ib, q, __builtin_ctz(64u / (unsigned)per), incomplete);
 }
 
 }  // namespace infaas

@@ -312,16 +312,15 @@ hipError_t launch_index_select(const TableView &tv, const IndexView &ix, const Q
                                int32_t *park_mem, uint32_t lds_bytes, int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
 int index_select_blocks(int num_cus);
 // One lane per query, everything read from global memory (L2): for calls too small to pay for the LDS
-// mirror, and (ranked) for tables most of whose slices the index cannot hold.  resident: in the statistics, queries of the first so many slices count
-// as parked only where a lookup through the mirror would park them, the others all do.  Selection only (q.pass 0).
-hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int32_t resident, int num_cus,
+// mirror, and (ranked) for tables most of whose slices the index cannot hold.  Selection only (q.pass 0).
+hipError_t launch_direct_select(const TableView &tv, const IndexView &ix, const QueryView &q, bool ranked, int num_cus,
                                 hipStream_t st, const LaunchEvents *ev = nullptr);
 // incomplete: some slices are not held completely by the index; their queries go through rank order at once (20 tasks of 1415 variants, all of
 // them steps, 1973 queries with suggestions 18.5 us through their lines, 16.0 so).
 // The same for the other modes: selection with suggestion on one table (tiers false; tb, ib unused), or both tiers with
 // workers (q.worker, q.row_worker: of the Active tier, the Inactive tier's V entries behind them) and suggestions (q.closest).
 hipError_t launch_direct_modes(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, const QueryView &q,
-                               bool tiers, int32_t resident, bool incomplete, int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
+                               bool tiers, bool incomplete, int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
 int index_stat_blocks(int num_cus);               // entries of IndexView::stats
 int32_t index_open_cap(int32_t n, int num_cus);   // records per workgroup of QueryView::open for a pass over n queries
 size_t index_park_bytes(int num_cus);

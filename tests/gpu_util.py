@@ -32,22 +32,59 @@ def make_selector(table, engine=0, lds_segment_limit=0):
     return sel
 
 
-def direct_limit(sel):
-    """The most queries that a plain selection of the handle answers straight from global memory; one more goes to
-    the lookup kernel (or, from 2^20 on and with groups, is binned by group).  As of the handle's latest selection."""
-    i = sel.info()
-    if not i["index_in_lds"]:
-        return 100_000
-    s = i["num_slices"]
-    pool = i["index_bytes"] - 16 * s - 4 * (i["index_steps"] + 1)
-    room = 160 * 1024 - 48 - ((s + 1) * 8 + 15) // 16 * 16
-    return 100_000 if pool <= room else 100_000 * pool // room
+# ways of a lookup (INFAAS_SEL_ROUTE_*)
+MEMORY, MIRROR, TILES = 1, 2, 3
 
 
-def tiled_beyond(limit, *arrays):
-    """The arrays over and over, more than `limit` entries of each."""
-    times = limit // len(arrays[0]) + 1
-    return tuple(np.tile(a, times) for a in arrays)
+class Repeated:
+    """Queries over and over on the device, and a call of a handle on as many of them as asked for.  `want`: the oracle's
+    results for the queries, one array per result array of the call."""
+
+    def __init__(self, sel, call, queries, want):
+        self.sel, self.call = sel, call
+        self.queries, self.want = [to_dev(x) for x in queries], [to_dev(x) for x in want]
+
+    def _many(self, x, n):
+        return x.repeat(n // x.numel() + 1)[:n]
+
+    def route(self, n, shift=0):
+        """The call on n queries, from arrays that start `shift` elements into their allocations; which way it went."""
+        import torch
+        args = [torch.cat([x.new_zeros(shift), self._many(x, n)])[shift:] for x in self.queries]
+        self.got = [torch.full((n + shift,), -7, dtype=torch.int32, device="cuda")[shift:] for _ in self.want]
+        self.call(*args, *self.got, n=n)
+        torch.cuda.synchronize()
+        return self.sel.info()["lookup_route"]
+
+    def check(self, n, route, label, shift=0):
+        """... which has to be `route` (None: not a lane per query), with the oracle's answers everywhere."""
+        import torch
+        label = f"{label} N={n} shift={shift}"
+        print(label, flush=True)
+        taken = self.route(n, shift)
+        assert taken != MEMORY if route is None else taken == route, f"{label}: route {taken}"
+        for k, (got, want) in enumerate(zip(self.got, self.want)):
+            bad = torch.nonzero(got != self._many(want, n)).flatten()
+            assert bad.numel() == 0, f"{label}: result {k}: {bad.numel()} differ, first at {bad[:5].tolist()}"
+
+    def last_from_memory(self, most):
+        """The most queries that go a lane per query; the next goes another way.  `most` queries go another way, one does not."""
+        lo, hi = 1, most
+        assert self.route(lo) == MEMORY and self.route(hi) != MEMORY
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (mid, hi) if self.route(mid) == MEMORY else (lo, mid)
+        return lo
+
+    def least_beyond(self, least, most, route=None):
+        """A size from `least` on that goes `route` (None: not a lane per query)."""
+        n = least
+        while True:
+            taken = self.route(n)
+            if (taken != MEMORY) if route is None else taken == route:
+                return n
+            n = n * 3 // 2 + 1
+            assert n <= most, f"{n} queries: still route {taken}"
 
 
 def table_args(tb, queue=None):

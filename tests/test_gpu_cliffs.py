@@ -7,8 +7,10 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_util import direct_limit, gpu_select, make_selector, query_args, table_args, tiled_beyond, to_dev
+from gpu_util import MEMORY, TILES, Repeated, gpu_select, gpu_select_closest, make_selector, query_args, table_args, to_dev
+from test_gpu_case1 import gpu_case1
 from test_gpu_parity import ENGINE_IDS, ENGINES, _assert_equal_everywhere, _table
+from test_gpu_tiered import gpu_select_tiered
 
 pytestmark = pytest.mark.gpu
 
@@ -76,20 +78,58 @@ def test_index_degrades_after_a_load_report(oracle_lib, engine):
 
 
 @pytest.mark.parametrize("kind", ["long_staircases", "wide_accuracy"])
-def test_cliff_tables_through_the_lookup_kernel(oracle_lib, kind):
-    """A handle that always uses the index, with more queries than are answered straight from memory: bodies of
-    truncated slices and slices without any, finished by the scan inside the lookup kernel."""
+def test_cliff_tables_a_tile_at_a_time(oracle_lib, kind):
+    """A handle that always uses the index, with more queries than go a lane per query: lines of truncated slices and of slices
+    without any, finished in rank order inside the same kernel."""
     tb = workloads.make_cliff_table(kind, cfg=1)
     q = query_args(workloads.make_queries(1, n=60_000))
-    want = oracle_lib.select(*table_args(tb), *q)
     sel = make_selector(tb, engine=2)
-    gpu_select(sel, *q)                               # (what the limit depends on is known from the first call on)
-    parked = sel.info()["lookup_parked"]
-    many = tiled_beyond(direct_limit(sel), *q, want)
-    assert len(many[0]) < 1 << 20
-    _assert_equal_everywhere(gpu_select(sel, *many[:4]), many[4], kind)
-    info = sel.info()
-    assert info["lookup_scanned"] > 1000
-    if kind == "long_staircases":                     # (straight from memory every query counts as parked)
-        assert info["lookup_parked"] < parked * (len(many[0]) // len(q[0]))
+    many = Repeated(sel, sel.select, q, [oracle_lib.select(*table_args(tb), *q)])
+    for n, route in ((899_999, MEMORY), (900_000, TILES), (1_234_567, TILES)):
+        many.check(n, route, kind)
+        info = sel.info()
+        assert info["lookup_scanned"] > 1000
+        if kind == "long_staircases":                 # (straight from memory every query counts as set aside)
+            assert (info["lookup_parked"] == n) == (route == MEMORY)
+    sel.destroy()
+
+
+@pytest.mark.parametrize("call", ["closest", "tiered", "case1"])
+def test_first_call_behind_the_report_that_overfills_the_slices(oracle_lib, call):
+    """The table of test_index_degrades_after_a_load_report: the host learns from a call that the slices are incomplete, so the first call behind
+    the report looks them up as if they were not.  Suggestions, two tiers, and both; then the call that knows, and back."""
+    T, n, B = 100, 200, 8
+    i = np.tile(np.arange(n, dtype=np.int64), T)
+    b = np.arange(B, dtype=np.int64)[None, :]
+    good = (600 * i).astype(np.int32)
+    tb = _table(T, [1, 2, 4, 8, 16, 32, 64, 128], np.repeat(np.arange(T, dtype=np.int32), n), np.full(T * n, 8000),
+                (60_000 - 295 * i)[:, None] + 10 * b, (100 + i)[:, None] + b, good)
+    q = query_args(workloads.make_queries(1, n=20_001))
+    sel = make_selector(tb, engine=0)
+    state, load = np.where(np.arange(tb.V) % 4 == 0, 0, 1).astype(np.int32), np.full(tb.V, 3000, np.int32)
+    queue = tb.queue_us.copy()
+    rows = np.arange(tb.V, dtype=np.int32)
+    if call != "closest":
+        sel.load_states(state, load)
+
+    def check(label):
+        tables = table_args(tb, queue)
+        if call == "closest":
+            got, want = gpu_select_closest(sel, *q), oracle_lib.select_closest(*tables, *q)
+        elif call == "tiered":
+            got, want = gpu_select_tiered(sel, *q), oracle_lib.select_tiered(*tables, state, load, *q)
+        else:
+            got, want = gpu_case1(sel, *q), oracle_lib.select_case1(*tables, state, load, *q)
+        for g, w in zip(got, want):
+            _assert_equal_everywhere(g, w, f"{call} {label}")
+
+    check("as loaded")
+    for values, bad in ((np.zeros(tb.V, np.int32), True), (good, False)):
+        before = sel.info()["index_truncated"]
+        sel.update_load(to_dev(rows), to_dev(values))
+        oracle_lib.update_load(queue, rows, values)
+        assert sel.info()["index_truncated"] == before
+        check("behind the report")
+        assert sel.info()["index_truncated"] == (T * B if bad else 0)
+        check("once more")
     sel.destroy()

@@ -1,16 +1,17 @@
 """Batches small enough to be answered straight from global memory, one lane per query, and batches on both
-sides of the size where the LDS mirror (or the group-by-group selection) takes over: an index that fits the
+sides of the size where the LDS mirror (or a tile of queries at a time) takes over: an index that fits the
 mirror, one that does so in part, one laid out in groups and one whose headers leave no room for a mirror;
 arrays that start 4 bytes into their allocations.  Every answer against the CPU oracle."""
 import numpy as np
 import pytest
 
 import workloads
-from gpu_util import direct_limit, gpu_select, gpu_select_closest, make_selector, query_args, table_args, tiled_beyond
+from gpu_util import (MEMORY, MIRROR, TILES, Repeated, gpu_select, gpu_select_closest, make_selector, query_args,
+                      table_args)
 from test_gpu_case1 import gpu_case1
 from test_gpu_getvariant import gpu_get_variant
 from test_gpu_parity import (_assert_equal_everywhere, _random_queries, _random_table, _staircase_queries,
-                             _staircase_table)
+                             _staircase_table, _table)
 from test_gpu_tiered import gpu_select_tiered
 from test_gpu_workers import _random_cluster, gpu_select_workers, load_cluster
 
@@ -61,39 +62,46 @@ def _few_groups():
 
 @pytest.mark.parametrize("kind", list(TABLES) + ["few_groups"])
 def test_both_sides_of_the_limit(oracle_lib, kind):
-    """As many queries as the limit, and one more; which kernel answered follows from the statistics: straight from
-    memory every valid query counts as parked, the lookup kernel parks what its first probe cannot decide."""
+    """As many queries as go a lane per query, and one more, which go through the mirror where it holds the whole index and a tile
+    at a time elsewhere.  The statistics are those of what was done: straight from memory every query counts as set aside."""
     tb = _few_groups() if kind == "few_groups" else TABLES[kind]()
     q = workloads.make_queries(1, n=60_001, seed=78)
     rng = np.random.default_rng(7)
     task, bidx = rng.integers(0, tb.num_tasks, q.N).astype(np.int32), rng.integers(0, tb.B, q.N).astype(np.int32)
     qs = (task, *query_args(q)[1:3], bidx)
-    want = oracle_lib.select(*table_args(tb), *qs)
     sel = make_selector(tb, engine=0)
-    gpu_select(sel, *qs)
-    limit = direct_limit(sel)
-    assert (limit > 100_000) == (kind in ("partly", "groups", "few_groups"))
     assert (sel.info()["index_groups"] > 1) == (kind in ("groups", "few_groups", "no_mirror"))
-    if kind == "groups":        # binned by group from 2^20 on
-        assert limit >= 1 << 20
-        limit = (1 << 20) - 1
-    many = tiled_beyond(limit, *qs, want)
-    for n in (limit, limit + 1):
-        _assert_equal_everywhere(gpu_select(sel, *(x[:n] for x in many[:4])), many[4][:n], f"{kind} N={n}")
-        parked = sel.info()["lookup_parked"]
-        if kind != "no_mirror":     # (without a mirror the lookup kernel reads from memory too)
-            assert (parked == n) == (n == limit), (n, parked)
+    assert sel.info()["lookup_route"] == 0
+    many = Repeated(sel, sel.select, qs, [oracle_lib.select(*table_args(tb), *qs)])
+    limit = many.last_from_memory(1_500_001)
+    many.check(limit, MEMORY, kind)
+    info = sel.info()
+    assert info["lookup_parked"] == limit and info["lookup_global_body"] > limit // 4
+    many.check(limit + 1, MIRROR if kind == "mirrored" else TILES, kind)
+    assert sel.info()["lookup_parked"] < limit // 2
     sel.destroy()
 
 
-@pytest.mark.parametrize("kind", ["ties", "staircase63", "staircase300", "one_tier", "masked"])
+@pytest.mark.parametrize("kind", ["ties", "staircase62", "staircase63", "staircase300", "one_tier", "masked", "partly", "few_incomplete"])
 def test_every_mode_below_and_above_the_limit(oracle_lib, kind):
-    """The calls besides the plain selection on tables that make their paths differ: ties, slices with more
-    steps than the index keeps, slices without a variant of one tier or of both.  3001 queries in one call
-    (straight from memory) and the same queries over and over in a call of 300,000 (through the LDS
-    mirrors and, with states, the lists between the tiers); every element against the CPU oracle."""
+    """The calls on tables that make their paths differ: ties, two bodies to a slice, slices with more steps than the index keeps
+    (all, or so few that the mirror still pays), slices without a variant of one tier or of both, bodies that the mirror does not
+    hold.  3001 queries in one call (straight from memory) and the same queries over and over, in a call of 300,100 and, unless
+    all slices are incomplete (which goes straight from memory at every size), in one that goes through the LDS mirrors and, with
+    states, the lists between the tiers; aligned arrays and others; every element against the CPU oracle."""
     rng = np.random.default_rng(len(kind) * 31)
-    if kind.startswith("staircase"):
+    if kind == "partly":
+        tb, span = _random_table(rng, 100, np.full(100, 190), 8), None
+        q = _random_queries(rng, 100, 8, 3001)
+    elif kind == "few_incomplete":     # one slice of 1500, most of whose steps the index does not keep
+        small, long_ = _random_table(rng, 1499, np.full(1499, 4), 1), _staircase_table(1, 300, B=1)
+        tb, span = _table(1500, [1], np.concatenate([small.task_id, long_.task_id + 1499]), np.concatenate([small.acc_bp, long_.acc_bp]),
+                          np.concatenate([small.lat_us, long_.lat_us]), np.concatenate([small.cost, long_.cost]),
+                          np.concatenate([small.queue_us, long_.queue_us])), None
+        q = tuple(np.concatenate(x) for x in zip(_random_queries(rng, 1499, 1, 2000),
+                                                 [a + (1499 if k == 0 else 0) for k, a in enumerate(_staircase_queries(rng, long_, 1001, 300))]))
+        q = tuple(x.astype(np.int32) for x in q)
+    elif kind.startswith("staircase"):
         steps = int(kind[9:])
         tb, span = _staircase_table(5, steps), None
         q = _staircase_queries(rng, tb, 3001, steps)
@@ -116,18 +124,34 @@ def test_every_mode_below_and_above_the_limit(oracle_lib, kind):
         for g, w, what in zip(got, want, ("variant", "second", "third", "fourth")):
             _assert_equal_everywhere(g, np.tile(w, times) if g.size > w.size else w, f"{kind} {label} {what}")
 
+    def through_the_mirror(call, want, label):
+        if kind in ("staircase63", "staircase300"):
+            return
+        many = Repeated(sel, call, q, want)
+        n = many.least_beyond(351_007, 40_000_000, MIRROR)
+        for m, shift in ((n, 0), (n + 2, 1)):
+            many.check(m, MIRROR, f"{kind} {label}", shift)
+
     sel = make_selector(tb, engine=2)
     want = oracle_lib.select_closest(*table_args(tb), *q)
+    through_the_mirror(sel.select, want[:1], "select")
     for qs in (q, many):
         check(gpu_select_closest(sel, *qs), want, f"closest N={len(qs[0])}")
+    through_the_mirror(sel.select_closest, want, "closest")
+    if kind == "partly":
+        assert sel.info()["lookup_global_body"] > 0
+    if kind == "few_incomplete":
+        assert sel.info()["lookup_scanned"] > 0
     sel.load_states(state, load)
     load_cluster(sel, cl)
-    for name, call, want in (("tiered", gpu_select_tiered, oracle_lib.select_tiered(*table_args(tb), state, load, *q)),
-                             ("case1", gpu_case1, oracle_lib.select_case1(*table_args(tb), state, load, *q)),
-                             ("workers", gpu_select_workers, oracle_lib.select_workers(*table_args(tb), state, load, *cl, *q)),
-                             ("getvariant", gpu_get_variant, oracle_lib.get_variant(*table_args(tb), state, load, *cl, *q))):
+    for name, call, method, want in (
+            ("tiered", gpu_select_tiered, sel.select_tiered, oracle_lib.select_tiered(*table_args(tb), state, load, *q)),
+            ("case1", gpu_case1, sel.select_tiered_closest, oracle_lib.select_case1(*table_args(tb), state, load, *q)),
+            ("workers", gpu_select_workers, sel.select_workers, oracle_lib.select_workers(*table_args(tb), state, load, *cl, *q)),
+            ("getvariant", gpu_get_variant, sel.select_workers_closest, oracle_lib.get_variant(*table_args(tb), state, load, *cl, *q))):
         for qs in (q, many):
             check(call(sel, *qs), want, f"{name} N={len(qs[0])}")
+        through_the_mirror(method, want, name)
     sel.destroy()
 
 
@@ -153,19 +177,20 @@ def test_a_small_call_leaves_the_scratch_of_its_size(oracle_lib):
 
 def test_suggestions_around_their_own_limit(oracle_lib):
     """An index that the mirror holds nearly completely and that has second bodies: suggestions turn to the lookup
-    kernel above 75,000 queries, the plain selection above more than 100,000."""
+    kernel earlier than the plain selection."""
     tb = workloads.make_table(2)
     sel = make_selector(tb, engine=0)
     assert sel.info()["index_max_steps"] > 31
     q = query_args(workloads.make_queries(2, n=75_001, seed=9))
     want = oracle_lib.select_closest(*table_args(tb), *q)
-    valid = int((q[1] >= 0).sum())
-    parked = []
-    for n in (75_000, 75_001):
-        for g, w in zip(gpu_select_closest(sel, *(x[:n] for x in q)), want):
-            _assert_equal_everywhere(g, w[:n], f"closest N={n}")
-        parked.append(sel.info()["lookup_parked"])
-    assert parked[0] >= valid - 1 and 0 < parked[1] < valid // 2   # (straight from memory every query counts as parked)
+    assert (q[1] >= 0).all()
+    many = Repeated(sel, sel.select_closest, q, want)
+    limit = many.last_from_memory(1_000_001)
+    many.check(limit, MEMORY, "closest")
+    assert sel.info()["lookup_parked"] == limit
+    many.check(limit + 1, MIRROR, "closest")
+    assert 0 < sel.info()["lookup_parked"] < limit // 2
+    assert Repeated(sel, sel.select, q, want[:1]).last_from_memory(1_000_001) > limit
     sel.destroy()
 
 
@@ -284,11 +309,10 @@ def test_many_bodies_of_every_length(oracle_lib, steps):
 
 @pytest.mark.parametrize("workers", [False, True])
 def test_both_sides_of_the_state_aware_limit(oracle_lib, workers):
-    """1.3 times the sum of the two tables' limits, and one query more: straight from memory every valid query counts as
-    parked, in both tiers that look at it; the lookup kernels park few.  Every element against the CPU oracle."""
-    import torch
+    """As many queries as one kernel answers for both tiers, and one query more: straight from memory every valid query counts as
+    set aside, in both tiers that look at it; the lookup kernels set few aside.  Every element against the CPU oracle."""
     from test_gpu_workers import cluster_args, load_cluster
-    tb = workloads.make_table(0)           # both mirrors hold everything: 100,000 queries each
+    tb = workloads.make_table(0)           # both mirrors hold everything
     st = workloads.make_states(0, tb.V)
     q = tuple(x[:5000] for x in query_args(workloads.make_queries(0)))
     sel = make_selector(tb, engine=0)
@@ -299,12 +323,10 @@ def test_both_sides_of_the_state_aware_limit(oracle_lib, workers):
         want = oracle_lib.select_workers(*table_args(tb), st.state, st.load_us, *cl, *q)
     else:
         want = oracle_lib.select_tiered(*table_args(tb), st.state, st.load_us, *q)
-    for n in (260_000, 260_001):
-        dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda().repeat(n // 5000 + 1)[:n].contiguous() for x in q]
-        outs = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for _ in want]
-        (sel.select_workers if workers else sel.select_tiered)(*dev, *outs)
-        torch.cuda.synchronize()
-        for got, w in zip(outs, want):
-            _assert_equal_everywhere(got.cpu().numpy(), np.tile(w, n // 5000 + 1)[:n], f"N={n}")
-        assert (sel.info()["lookup_parked"] >= n) == (n == 260_000)
+    many = Repeated(sel, sel.select_workers if workers else sel.select_tiered, q, want)
+    limit = many.last_from_memory(8_000_001)
+    many.check(limit, MEMORY, "two tiers")
+    assert sel.info()["lookup_parked"] >= limit
+    many.check(limit + 1, MIRROR, "two tiers")
+    assert sel.info()["lookup_parked"] < limit // 2
     sel.destroy()

@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_util import direct_limit, gpu_select, make_selector, query_args, table_args, tiled_beyond, to_dev
+from gpu_util import MEMORY, MIRROR, TILES, Repeated, gpu_select, make_selector, query_args, table_args, to_dev
 from pins import check_invariants
 
 pytestmark = pytest.mark.gpu
@@ -69,14 +69,9 @@ def _compare(oracle_lib, tb, queries, engine, lds_limit=0, label=""):
     bad = np.flatnonzero(got != want)
     assert bad.size == 0, f"{label}: {bad.size} mismatches, first at {bad[:5]}: got {got[bad[:5]]} want {want[bad[:5]]}"
     # once more, as many of them as it takes to leave the kernel for small batches
-    limit = direct_limit(sel) if engine != 1 else 0
-    if 0 < len(queries[0]) <= limit < 2_000_000:
-        many = tiled_beyond(limit, *queries, want)
-        bad = np.flatnonzero(gpu_select(sel, *many[:4]) != many[4])
-        assert bad.size == 0, f"{label}, N={len(many[0])}: {bad.size} mismatches, first at {bad[:5]}"
-        info = sel.info()
-        if info["index_in_lds"] and limit == 100_000 and info["index_truncated"] == 0:   # all of it in the mirror
-            assert info["lookup_global_body"] == 0
+    if 0 < len(queries[0]) < 900_000 and sel.info()["lookup_route"] == MEMORY:
+        many = Repeated(sel, sel.select, queries, [want])
+        many.check(many.least_beyond(350_001 + len(queries[0]) % 1000, 2_000_000), None, label)
     sel.destroy()
     return got
 
@@ -290,9 +285,8 @@ def test_rows_scattered_over_a_large_table(oracle_lib, engine):
 
 def test_index_outgrows_lds_after_load_update(oracle_lib):
     """At load every slice has a one-step staircase (row 0 of each task dominates the rest), so the
-    index fits in LDS.  A load report then pushes those rows out of reach: all staircases grow to
-    62 steps, the index no longer fits, and the queries of the slices left outside LDS are
-    finished from the index copy in global memory."""
+    index fits in LDS, and a large call goes through the mirror.  A load report then pushes those rows out of
+    reach: all staircases grow to 62 steps, the index no longer fits, and such a call goes a tile at a time."""
     T, n = 700, 62
     tb = _staircase_table(T, n, B=1)
     first = np.arange(T) * n
@@ -303,7 +297,9 @@ def test_index_outgrows_lds_after_load_update(oracle_lib):
     assert sel.info()["index_in_lds"] == 1 and sel.info()["index_max_steps"] == 1
     qs = _staircase_queries(rng, tb, 200_000, n)
     got = gpu_select(sel, *qs)
-    assert np.array_equal(got, oracle_lib.select(*table_args(tb), *qs))
+    want = oracle_lib.select(*table_args(tb), *qs)
+    assert np.array_equal(got, want)
+    Repeated(sel, sel.select, qs, [want]).check(1_000_001, MIRROR, "as loaded")
     queue = tb.queue_us.copy()
     idx = first.astype(np.int32); val = np.full(T, 2_000_000_000, np.int32)
     sel.update_load(to_dev(idx), to_dev(val))
@@ -312,12 +308,10 @@ def test_index_outgrows_lds_after_load_update(oracle_lib):
     want = oracle_lib.select(*table_args(tb, queue), *qs)
     assert np.array_equal(got, want)
     assert (want >= 0).mean() > 0.3 and len(np.unique(want)) > 1000
-    limit = direct_limit(sel)                      # (by now these 200,000 are few enough to be read from memory at once)
-    assert 200_000 < limit < 1_000_000
-    many = tiled_beyond(limit, *qs, want)
-    assert np.array_equal(gpu_select(sel, *many[:4]), many[4])
+    many = Repeated(sel, sel.select, qs, [want])
+    many.check(1_000_001, TILES, "grown")
     info = sel.info()
-    assert 0 < info["lookup_global_body"] < info["lookup_parked"] < len(many[0])
+    assert 0 < info["lookup_unanswered"] <= info["lookup_parked"] < 1_000_001
     sel.destroy()
 
 
@@ -416,13 +410,14 @@ def test_config2_full_size_every_query(oracle_lib, engine):
         assert info["index_max_steps"] > 31 and info["lookup_second_body"] > 1000
         assert info["lookup_parked"] >= info["lookup_second_body"] + info["lookup_unanswered"] > 0
         assert info["lookup_global_body"] == 0 and info["lookup_scanned"] == 0   # the whole index is in LDS
+        assert info["lookup_route"] == MIRROR
     sel.destroy()
 
 
 @pytest.mark.parametrize("engine", ENGINES, ids=ENGINE_IDS)
 def test_config3_full_size_every_query(oracle_lib, engine):
     """64M queries over 1,000 tasks with lognormal segment sizes and a bimodal objective; the
-    index does not fit in LDS, so most queries are answered from its copy in global memory."""
+    index does not fit in LDS, so every query reads the first line of its slice."""
     tb, q, want = _full_reference(oracle_lib, 3)
     _say(f"config3 engine={engine}: N={q.N} V={tb.V}")
     sel = make_selector(tb, engine=engine)
@@ -431,17 +426,15 @@ def test_config3_full_size_every_query(oracle_lib, engine):
     assert 0 < int((want < 0).sum()) < q.N
     if engine != 1:
         info = sel.info()
-        # the tasks were dealt to groups; the few queries a group's LDS copy cannot decide (second
-        # group of steps) were finished from global memory
-        assert info["index_groups"] > 4 and info["lookup_parked"] > 0
+        # the few queries that the first line cannot decide were set aside and finished from the lines that follow
+        assert info["index_groups"] > 4 and info["lookup_parked"] > 0 and info["lookup_route"] == TILES
         assert info["lookup_parked"] >= info["lookup_second_body"] + info["lookup_unanswered"] > 0
-        # a batch too small for the group-by-group path takes the one-kernel lookup, where most
-        # slices are answered from the copy of the index in global memory
-        n = 900_000
+        # a batch too small for a tile at a time goes a lane per query
+        n = 800_000
         got = gpu_select(sel, *(x[:n] for x in query_args(q)))
-        _assert_equal_everywhere(got, want[:n], "config3, one-kernel lookup")
+        _assert_equal_everywhere(got, want[:n], "config3, a lane per query")
         info = sel.info()
-        assert info["lookup_parked"] > n // 2 and info["lookup_global_body"] > n // 10
+        assert info["lookup_parked"] == n and info["lookup_global_body"] > n // 10 and info["lookup_route"] == MEMORY
     sel.destroy()
     if engine == ENGINES[-1]:
         _FULL.clear()
@@ -490,6 +483,7 @@ def test_config4_streaming_sampled(oracle_lib):
             _assert_equal_everywhere(got, want, f"config4 chunk {chunk}")
             info = sel.info()
             assert info["lookup_second_body"] > 0 and info["lookup_parked"] > info["lookup_second_body"]
+            assert info["lookup_route"] in (MIRROR, TILES)   # (reports let the bodies grow by up to a tenth over the mirror)
         else:
             _sampled_parity(oracle_lib, tb, queue, q, got, 20_000, rng, f"config4 chunk {chunk}")
     assert np.array_equal(sel.read_load(tb.V), queue)
@@ -564,8 +558,8 @@ def test_few_long_slices_with_reports(oracle_lib):
         want = oracle_lib.select(tb.task_id, tb.acc_bp, tb.lat_us, tb.cost, queue, *qs)
         bad = np.flatnonzero(got != want)
         assert bad.size == 0, f"round {rnd}: {bad.size} mismatches, first at {bad[:5]}"
-        many = tiled_beyond(direct_limit(sel), *qs, want)   # the lookup kernel as well
-        assert np.array_equal(gpu_select(sel, *many[:4]), many[4]), f"round {rnd}, N={len(many[0])}"
+        many = Repeated(sel, sel.select, qs, [want])   # the lookup kernel as well
+        many.check(400_001, MIRROR, f"round {rnd}")
     info = sel.info()
     assert info["index_truncated"] == 0 and 20 <= info["index_max_steps"] <= 62
     sel.destroy()
@@ -587,8 +581,7 @@ def test_few_slices_of_nothing_but_steps(oracle_lib, engine):
 
 def test_512_slices_in_groups(oracle_lib):
     """512 slices of 600 steps each: one workgroup per slice in the build, and bodies (62 steps kept
-    per slice, 470 KB) that need groups; a call below and one above the size from which queries are
-    binned by group."""
+    per slice, 470 KB) that need groups; a call that goes a lane per query and one that goes a tile at a time."""
     rng = np.random.default_rng(79)
     tb = _staircase_table(64, 600, B=8)
     sel = make_selector(tb, engine=2)
@@ -600,6 +593,7 @@ def test_512_slices_in_groups(oracle_lib):
         want = oracle_lib.select(*table_args(tb), *qs)
         bad = np.flatnonzero(got != want)
         assert bad.size == 0, f"N={n}: {bad.size} mismatches, first at {bad[:5]}"
+        assert sel.info()["lookup_route"] == (MEMORY if n < 900_000 else TILES)
     sel.destroy()
 
 

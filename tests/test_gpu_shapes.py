@@ -4,7 +4,7 @@ element against the CPU oracle."""
 import numpy as np
 import pytest
 
-from gpu_util import DeviceQueries, direct_limit, gpu_select, gpu_select_closest, make_selector, table_args, tiled_beyond
+from gpu_util import MIRROR, Repeated, gpu_select, gpu_select_closest, make_selector, table_args
 from test_gpu_parity import _random_queries, _random_table
 from test_gpu_scale import gpu_scale
 from test_gpu_tiered import gpu_select_tiered
@@ -67,7 +67,6 @@ def test_lookup_kernel_on_a_small_odd_table(oracle_lib, seed):
     """The same tables with more queries than are answered straight from memory: the lookup kernel with its LDS
     mirror, parked queries and drain, for the plain selection (both entry points) and with suggestions; arrays
     that start 4 bytes into their allocations."""
-    import torch
     rng = np.random.default_rng(9000 + seed)
     T = int(rng.choice([1, 1, 2, 3, 7]))
     B = int(rng.choice([1, 1, 2, 3, 5, 8]))
@@ -79,18 +78,11 @@ def test_lookup_kernel_on_a_small_odd_table(oracle_lib, seed):
     queries = _random_queries(rng, T, B, 4999, span=span)
     want = oracle_lib.select_closest(*table_args(tb), *queries)
     sel = make_selector(tb, engine=2)
-    many = tiled_beyond(direct_limit(sel), *queries, *want)
-    many = tuple(x[:many[0].size - 64 * (seed % 5) - seed] for x in many)
-    dq = DeviceQueries(*many[:4])
-    shifted = [torch.cat([torch.zeros(1, dtype=torch.int32, device="cuda"), x])[1:] for x in (dq.task, dq.slo, dq.min_acc, dq.bidx)]
-    print(f"lookup shape case {seed}: T={T} B={B} sizes={sizes.tolist()} N={dq.n}", flush=True)
-    for args in ([dq.task, dq.slo, dq.min_acc, dq.bidx], shifted):
-        for call in (sel.select, sel.select_noalloc):
-            dq.out.fill_(-7)
-            call(*args, dq.out, n=dq.n)
-            torch.cuda.synchronize()
-            assert np.array_equal(dq.out.cpu().numpy(), many[4]), call.__name__
-            assert sel.info()["lookup_global_body"] == 0      # (straight from memory every first body counts there)
-    got = gpu_select_closest(sel, *many[:4])
-    assert np.array_equal(got[0], many[4]) and np.array_equal(got[1], many[5]), "select_closest"
+    label = f"lookup shape case {seed}: T={T} B={B} sizes={sizes.tolist()}"
+    for call, results in ((sel.select, want[:1]), (sel.select_noalloc, want[:1]), (sel.select_closest, want)):
+        many = Repeated(sel, call, queries, results)
+        n = many.least_beyond(350_001 + 64 * (seed % 5) + seed, 4_000_000, MIRROR)
+        for shift in (0, 1):
+            many.check(n, MIRROR, f"{label} {call.__name__}", shift)
+            assert sel.info()["lookup_global_body"] == 0
     sel.destroy()
