@@ -540,8 +540,6 @@ int64_t body_pool(const infaas_sel *h)
 // Which way a lookup goes.  The mirror costs its fill (2-4 us, more with many slices) and pays with 4 ps per query, if it holds the
 // query's slice and the slice's first body has the answer; a line read from memory costs 7 to 9, one query per lane or, with a tile of them
 // at a time, 6 to 8 and a start of 2 us.
-constexpr int64_t kDirectQueries = 100000;
-constexpr int64_t kDirectSuggestions = 75000;
 struct IndexShape {
     int64_t pool, room;   // bytes of the bodies, and what the mirror has for them (0: no mirror)
     double outside;       // share of the bodies outside the mirror
@@ -563,12 +561,6 @@ IndexShape shape_of(const infaas_sel *h)
     x.most = now ? now[kCtlMaxK - kCtlMaxK0] : h->ix_stats[kCtlMaxK];
     return x;
 }
-int64_t direct_limit(const infaas_sel *h, const IndexShape &x, bool closest = false)
-{
-    if (x.room == 0) return kDirectQueries;
-    if (closest && x.open == 0 && x.most > (uint32_t)kBodySteps && 5 * x.pool <= 7 * x.room) return kDirectSuggestions;
-    return x.pool <= x.room ? kDirectQueries : kDirectQueries * x.pool / x.room;
-}
 // The plain selection: whether the mirror is ahead of the lines from `n` queries on.  us for 300,000 / 600,000 / 1M / 4M / 16M queries, a lane
 // per query (a tile at a time) and mirrored: 50 tasks of 2000 variants, all in the mirror, 7.0 / 11.2 / 16.0 / 50 / 209 (-, -, 14.9 / 42 / 151)
 // and 8.2 / 10.1 / 11.3 / 25 / 72; 100 of 200, 8% outside, 6.5 / 10.4 / 14.4 / 45 / 196 (-, -, 13.5 / 40 / 146) and 9.7 / 12.0 / 14.3 / 39 / 142; 200 of 60,
@@ -582,28 +574,62 @@ bool mirror_pays(const IndexShape &x, int64_t n)
 // ... and where it is not, from how many queries on a tile at a time is ahead of a lane per query (8000 slices, 900,000 queries 13.6 and 14.8, 1.05M
 // 15.5 and 15.9; 64M queries, binned by group of tasks whose bodies fit one LDS, 729, so 459).
 constexpr int64_t kLineQueries = 900000;
-constexpr int64_t kLargeQueries = (int64_t)1 << 20;
-// With suggestions, and in two tiers, up to how many queries a lane per query is ahead (us at 300,000 / 600,000 / 1M / 1.5M / 2.5M, a lane per
-// query and mirrored).  Suggestions on 50 tasks of 2000 variants 13.2 / 19.4 and 11.2 / 13.3, on 100 of 200 11.3 / 17.2 / 25.2 and 16.0 / 19.2 / 21.8, on 200
-// of 60 11.8 / 17.4 / 24.5 / 33 / 56 and 26 / 30 / 37 / 50 / 72, on 8 of 32 8.8 / 13.4 / 18.9 and 10.5 / 12.7 / 14.7.  Two tiers behind reports, with workers:
-// 42 / 47 / 55 / 66 and 51 / 53 / 55 / 60, 36 / 40 / 44 / 55 / 75 and 45 / 48 / 51 / 58 / 72, 35 / 38 / 43 / 53 / 74 and 48 / 52 / 59 / 71 / 95, 25 / 30 / 35 / 42 / 65 and
-// 35 / 37 / 40 / 46 / 57.  Complete Case I: 18 / 26 / 38 / 52 and 26 / 31 / 34 / 41, 17 / 25 / 36 / 50 / 81 and 34 / 38 / 43 / 55 / 81, 17 / 25 / 36 / 51 / 82 and 45 / 56 /
-// 68 / 93 / 132, 15 / 23 / 34 / 47 / 77 and 33 / 37 / 43 / 55 / 80.  What is outside the mirror and longer staircases (more lines to a query) move
-// the line.
-int64_t direct_pays(const IndexShape &x, bool tiers, bool closest)
+// With suggestions (b null), and in two tiers (a the Active one, which all queries visit), whether a lane per query straight from memory is
+// ahead of the mirror.  Both are a start and a time per query, here in us and us per million; the crossing moves with the steps per slice (fewer
+// steps: more queries without an answer, each of them a drain and a second tier for the mirror), with the share of the bodies outside and
+// with the slices that are not completely indexed (2.3 ns per query in the lookup kernel's scan).  us, memory / mirror:
+//   tasks x variants x batches  steps  outside                 300,000        600,000        1M             1.5M           2.2M           4M
+//   suggestions
+//     8 x 32 x 4                   9   0                         8.3 / 10.4                   18.1 / 13.7    23.3 / 19.3                   (450,000: 9.9 / 11.1)
+//     40 x 100 x 8                11   0                        10.2 / 10.6                   23.2 / 14.0    30.7 / 19.4                   (450,000: 12.3 / 11.1)
+//     50 x 2000 x 8               24   0                        12.0 / 11.0                   26.6 / 14.0    35.5 / 16.9                   (200,000: 8.8 / 10.6)
+//     200 x 400 x 3               18   0.05                     11.0 / 13.5                   24.2 / 19.1    32.4 / 26.4                   (450,000: 13.2 / 14.5)
+//     100 x 200 x 8               14   0.11                     10.2 / 15.2                   23.6 / 21.4    30.7 / 29.3                   (700,000: 17.7 / 18.6)
+//     100 x 600 x 8               20   0.34                     11.3 / 20.1                   25.3 / 30.7    33.6 / 40.0                   (5M: 110 / 101)
+//     200 x 60 x 8                10   0.40                     10.5 / 24.6                   23.3 / 36.2    31.4 / 50.0                   (16M: 305 / 383)
+//   two tiers, behind a state report
+//     40 x 100 x 8                 9   0                        23.3 / 30.8    27.9 / 33.3    33.1 / 36.0    38.9 / 40.5    47.9 / 47.0    80 / 61
+//     50 x 2000 x 8               20   0                        30.4 / 37.8    34.5 / 39.1    39.5 / 40.6    45.4 / 44.2    55.3 / 49.0    90 / 60
+//     100 x 600 x 8               16   0.19                     30.4 / 40.5    34.3 / 42.8    39.2 / 46.9    44.8 / 53.8    54.5 / 62.0    89 / 82
+//     200 x 60 x 8                 7   0.23                     26.0 / 34.4    30.3 / 41.3    34.9 / 45.7    40.8 / 52.9    49.8 / 62.4    83 / 90
+//   with workers, behind reports on them and on instance states
+//     40 x 100 x 8                 9   0                        30.1 / 40.7                   40.8 / 47.1    46.5 / 52.2                   96 / 78
+//     50 x 2000 x 8               21   0                        40.9 / 50.0                   50.5 / 53.6    56.8 / 58.2                   110 / 78
+//   complete Case I, with workers
+//     8 x 32 x 4                   6   0                        15.5 / 33.3    23.9 / 37.7    34.6 / 41.3    45.1 / 51.4    65.8 / 67.5    125 / 109
+//     100 x 200 x 8               11   0                        16.3 / 33.2    25.1 / 37.7    36.0 / 42.5    47.2 / 49.7    68.4 / 62.6    129 / 105
+//     50 x 2000 x 8               20   0                        16.9 / 24.2    26.2 / 29.9    37.8 / 34.1    50.5 / 39.9    71.1 / 45.0    133 / 64
+//     100 x 600 x 8               16   0.20                     17.1 / 37.6    26.1 / 46.1    37.7 / 52.1    49.3 / 62.9    71.4 / 75.8    135 / 119
+//     200 x 60 x 8                 7   0.23                     17.1 / 49.3    25.8 / 54.3    36.6 / 61.3    48.7 / 81.9    69.2 / 114     130 / 183
+// Without a mirror (16,000 slices) there is only the way from memory; a lookup kernel that read the bodies from there took two to four times as long
+// (suggestions for 349,999 / 4M queries 29 and 269 against 12 and 75, two tiers 2M 224 against 129).
+bool memory_pays(const IndexShape &a, const IndexShape *b, bool workers, bool closest, int64_t n)
 {
-    if (x.room == 0) return INT64_MAX;
-    const bool brief = x.steps <= 16.0;
-    const double base = !tiers ? (brief ? 450e3 : 200e3) : closest ? (brief ? 2.2e6 : 800e3) : (brief ? 1.55e6 : 950e3);
-    return (int64_t)(base * (1.0 + (tiers ? 15.0 : 8.0) * x.outside) * (1.0 + 200.0 * x.open));
+    if (a.room == 0 || (b && b->room == 0)) return true;
+    const double m = 1e-6 * (double)n, steps = a.steps, outside = a.outside + (b ? b->outside : 0.0);
+    double memory, start, each;   // the mirror's: start + each * m
+    if (!b) {
+        memory = 5.0 + (a.most < 16u ? 14.0 : 17.5 + 0.14 * steps) * m;   // (below 16 steps no slice has a second line)
+        start = outside > 0 ? 10.8 + 15.0 * outside : 9.3;
+        each = outside > 0 ? 7.5 + 27.0 * outside : 4.7;
+    } else if (closest) {
+        memory = 7.5 + 28.2 * m + 3.5 * std::max(0.0, m - 2.2);   // (beyond, the last-level cache does not hold the arrays of several calls)
+        start = std::max(20.0, 32.0 - 0.6 * steps) + 40.0 * outside;
+        each = std::max(9.0, 21.0 - 0.5 * steps) + 700.0 / std::max(1.0, steps) * outside;
+    } else {
+        memory = (workers ? 13.4 : 13.2) * m + 5.5 * std::max(0.0, m - 2.5);
+        start = workers ? 10.6 : 9.0;
+        each = std::max(5.5, (workers ? 10.8 : 9.8) - 0.19 * steps) + 25.0 * outside;
+    }
+    each += 2300.0 * (a.open + (b ? b->open : 0.0));
+    return memory <= start + each * m;
 }
 
 // The plain selection, n <= 2^28 queries.  park: the lookup kernel's queues.
 hipError_t launch_select(infaas_sel *h, const QueryView &q, int32_t *park, hipStream_t st, const LaunchEvents *ev = nullptr)
 {
     const IndexShape x = shape_of(h);
-    const bool few = q.n < kLargeQueries && q.n <= direct_limit(h, x);
-    h->last_route = !few && mirror_pays(x, q.n) ? INFAAS_SEL_ROUTE_MIRROR : !few && q.n >= kLineQueries ? INFAAS_SEL_ROUTE_TILES : INFAAS_SEL_ROUTE_MEMORY;
+    h->last_route = mirror_pays(x, q.n) ? INFAAS_SEL_ROUTE_MIRROR : q.n >= kLineQueries ? INFAAS_SEL_ROUTE_TILES : INFAAS_SEL_ROUTE_MEMORY;
     if (h->last_route == INFAAS_SEL_ROUTE_MIRROR) return launch_index_select(h->tv, h->ix, q, park, h->index_lds_bytes, h->num_cus, st, ev);
     if (h->last_route == INFAAS_SEL_ROUTE_TILES) return launch_line_select(h->tv, h->ix, q, h->num_cus, st, ev);
     return launch_direct_select(h->tv, h->ix, q, false, h->num_cus, st, ev);
@@ -616,7 +642,7 @@ int index_pass(infaas_sel *h, const QueryView &q, hipStream_t st)
     if (q.pass == 0) return HIP_OK(launch_select(h, q, h->d_park, st, t.ev())) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
     if (q.pass == 1) {
         const IndexShape x = shape_of(h);
-        if (q.n <= direct_limit(h, x, true) || q.n <= direct_pays(x, false, true)) {
+        if (memory_pays(x, nullptr, false, true, q.n)) {
             h->last_route = INFAAS_SEL_ROUTE_MEMORY;
             const hipError_t e = launch_direct_modes(h->tv, h->ix, h->tv, h->ix, q, false, x.open > 0, h->num_cus, st, t.ev());
             return HIP_OK(e) ? INFAAS_SEL_OK : INFAAS_SEL_ERR_HIP;
@@ -1204,7 +1230,7 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     hipStream_t st = (hipStream_t)hip_stream;
     // One kernel against two mirrors and two launches.
     const IndexShape xa = shape_of(h), xb = shape_of(h->inactive);
-    const bool direct = N <= (direct_limit(h, xa) + direct_limit(h->inactive, xb)) / 10 * 13 || N <= std::max(direct_pays(xa, true, closest), direct_pays(xb, true, closest));
+    const bool direct = memory_pays(xa, &xb, workers, closest, N);
     // The lists are allocated for direct calls too: the limits follow the index, and the same call after a report
     // may need them where nothing can be allocated (under capture, after an eager call to warm up).  A direct call
     // that is itself captured does without.
