@@ -1445,7 +1445,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
             // parked: a miss that the second body / the scan may still turn into a hit; in the
             // closest-variant mode also every final miss of a query inside the table
             df[k] = !hit && ((int32_t)y[k] < 0 || (kSuggest && sl_of[k] != (uint32_t)tv.S));
-            if (kSuggest && df[k] && (int32_t)y[k] >= 0) sl_of[k] |= kParkFinal;   // nothing feasible: only the suggestion is open
+            if (kSuggest && (int32_t)y[k] >= 0) sl_of[k] |= kParkFinal;   // nothing feasible: only the suggestion is open
         }
         p_i0 = i0;
 #pragma unroll
@@ -1465,7 +1465,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
             uint32_t total = 0;
 #pragma unroll
             for (int k = 0; k < kPerThread; ++k) {
-                om[k] = __ballot(m[k] == 0u && !df[k] && sl_of[k] != (uint32_t)tv.S);
+                om[k] = __ballot(m[k] == 0u && !df[k] && (sl_of[k] & ~kParkFinal) != (uint32_t)tv.S);
                 total += (uint32_t)__builtin_popcountll(om[k]);
             }
             if (total) {
