@@ -137,7 +137,7 @@ struct infaas_sel {
     // staircase index
     IndexView ix{};
     bool have_index = false;
-    uint32_t index_lds_bytes = 0;     // dynamic LDS of the lookup kernel; 0 = read the index from global memory
+    uint32_t index_lds_bytes = 0;     // dynamic LDS of the lookup kernel; 0 = no mirror: every lookup reads lines from global memory
     uint32_t ix_stats[kCtlWords] = {0};      // copy of ix.ctrl taken after the build at load time
     int64_t ix_bytes = 0, ix_steps = 0;      // pool bytes and steps of the index when it was loaded
     int32_t *d_park = nullptr;        // queues of parked queries of the lookup kernel (fixed size)
@@ -192,7 +192,7 @@ struct infaas_sel {
         if (ix.stats) (void)hipFree(ix.stats - 4);
         (void)hipFree(ix.slice_room);   // (rank_hdr and the nodes behind it are in pool's allocation)
         tv.rank_hdr = nullptr;
-        (void)hipFree((void *)ix.task_group); (void)hipFree((void *)ix.group_task0); (void)hipFree(ix.gctrl);
+        (void)hipFree((void *)ix.task_group); (void)hipFree(ix.gctrl);
         (void)hipFree(ix.step_worker); (void)hipFree(ix.hot_worker);
         (void)hipFree(d_park);
         d_park = nullptr;
@@ -304,11 +304,13 @@ int ensure_scratch(infaas_sel *h, int64_t capacity)
 
 constexpr uint32_t kLdsMax = 160 * 1024;  // dynamic LDS the lookup kernel may ask for
 
-constexpr uint32_t kGroupRegionBytes = 144 * 1024;   // a group's bodies: what one LDS holds next to its slices' headers
-constexpr uint32_t kGroupMaxSlices = 1900;           // ... 8 bytes of header each
+// Groups of tasks (IndexView::num_groups).  What they are for is the spread of the build's requests for room over as many pairs of
+// counters; any sizes that make tens of groups of a table with thousands of slices do.
+constexpr uint32_t kGroupRegionBytes = 144 * 1024;   // bytes of a group's bodies
+constexpr uint32_t kGroupMaxSlices = 1900;
 constexpr uint32_t kGroupStepCap = 16384;            // entries of step_row per group (a region holds at most 10,532 steps)
 constexpr int32_t kGroupMaxGroups = 120;
-constexpr int32_t kGroupMaxTasks = 16384;            // (above, one region)
+constexpr int32_t kGroupMaxTasks = 16384;            // of a table in groups; one of more tasks keeps one region
 constexpr uint32_t kGroupHotRows = 8;
 
 // Starting values of the allocator counters and the statistics, then one build, then the counters back.
@@ -435,24 +437,23 @@ int create_index(infaas_sel *h)
     const int64_t need = fixed + h->ix_stats[kCtlPool];
     // The lookup kernel mirrors the index in LDS when the slice headers leave at least half of it to
     // the bodies; bodies that do not fit stay in global memory and their queries take the slower
-    // path inside the same kernel.  With more headers than that the kernel reads everything from
-    // global memory.
+    // path inside the same kernel.  With more headers than that there is no mirror (memory_pays()).
     h->index_lds_bytes = fixed <= (int64_t)kLdsMax / 2 ? kLdsMax : 0u;
     // 2 bytes of a step's caller row sit in front of its body, the bits above in a 14-bit header field
     const uint32_t row_bits = h->V > 1 ? 64u - (uint32_t)__builtin_clzll((unsigned long long)(h->V - 1)) : 1u;
     h->ix.row_hi_bits = row_bits > 16 ? row_bits - 16 : 0u;
     const uint32_t hot_max = std::min<uint32_t>(h->ix.row_hi_bits ? kRowHiField / h->ix.row_hi_bits : (uint32_t)kBodySteps, kBodySteps);
     if (need > 2 * (int64_t)kLdsMax && h->T <= kGroupMaxTasks) {
-        // Not even half of the bodies fit one LDS: deal the tasks, in order, to groups whose bodies do (with a
-        // fifth of the region left free, because staircases grow and shrink with the load), and build
-        // again with one region of the pool per group, each with its own allocation counters: thousands of
-        // slices do not wait for their turn at one pair.
+        // Not even half of the bodies fit one LDS, so mostly thousands of slices: deal the tasks, in order, to groups whose
+        // bodies fit a region (with a fifth of it left free, because staircases grow and shrink with the load), and build
+        // again with one region of the pool per group, each with its own allocation counters: the slices
+        // do not wait for their turn at one pair.
         std::vector<uint32_t> hdr((size_t)S * 4);
         if (!HIP_OK(hipMemcpy(hdr.data(), h->ix.hdr, (size_t)S * 16, hipMemcpyDeviceToHost))) { h->free_index(); return INFAAS_SEL_ERR_HIP; }
         const uint32_t hot = std::min(kGroupHotRows, hot_max) & ~1u;
         const uint32_t target = (kGroupRegionBytes - kDummyBodyBytes) / 5 * 4;
         std::vector<uint16_t> task_group((size_t)h->T);
-        std::vector<int32_t> task0{0};
+        int32_t G = 1;
         uint32_t bytes = 0, slices = 0;
         for (int32_t t = 0; t < h->T; ++t) {
             uint32_t tb = 0;
@@ -461,27 +462,23 @@ int create_index(infaas_sel *h)
                 if (e[0] != 0u) tb += e[3] - (e[0] + 4u) + 2u * hot + 4u;   // bodies, and room for the first steps' rows
             }
             if (slices > 0 && (bytes + tb > target || slices + (uint32_t)h->B > kGroupMaxSlices)) {
-                task0.push_back(t);
+                ++G;
                 bytes = slices = 0;
             }
             bytes += tb; slices += (uint32_t)h->B;
-            task_group[(size_t)t] = (uint16_t)(task0.size() - 1);
+            task_group[(size_t)t] = (uint16_t)(G - 1);
         }
-        task0.push_back(h->T);
-        const int32_t G = (int32_t)task0.size() - 1;
         if (G > 1 && G <= kGroupMaxGroups && (uint32_t)h->B <= kGroupMaxSlices) {
             uint16_t *d_tg = nullptr;
-            int32_t *d_t0 = nullptr;
-            if (dev_alloc(&d_tg, (size_t)h->T) != hipSuccess || dev_alloc(&d_t0, (size_t)G + 1) != hipSuccess) {
-                (void)hipFree(d_tg); (void)hipFree(d_t0); (void)hipGetLastError();
+            if (dev_alloc(&d_tg, (size_t)h->T) != hipSuccess) {
+                (void)hipGetLastError();
                 h->free_index();
                 return INFAAS_SEL_ERR_OOM;
             }
-            h->ix.task_group = d_tg; h->ix.group_task0 = d_t0;
+            h->ix.task_group = d_tg;
             h->ix.num_groups = (uint32_t)G; h->ix.region_bytes = kGroupRegionBytes; h->ix.group_step_cap = kGroupStepCap;
             h->ix.hot_rows = hot;
-            bool up = HIP_OK(hipMemcpy(d_tg, task_group.data(), (size_t)h->T * 2, hipMemcpyHostToDevice)) &&
-                      HIP_OK(hipMemcpy(d_t0, task0.data(), ((size_t)G + 1) * 4, hipMemcpyHostToDevice));
+            bool up = HIP_OK(hipMemcpy(d_tg, task_group.data(), (size_t)h->T * 2, hipMemcpyHostToDevice));
             for (int32_t g = 1; up && g < G; ++g)   // every region begins with the dummy body
                 up = HIP_OK(hipMemcpy(h->ix.pool + (size_t)g * kGroupRegionBytes, dummy, sizeof(dummy), hipMemcpyHostToDevice));
             if (!up || build_index_now(h) != INFAAS_SEL_OK) { h->free_index(); return INFAAS_SEL_ERR_HIP; }
@@ -667,7 +664,7 @@ bool use_index(infaas_sel *h)
         trunc = ((volatile uint32_t *)h->host_stats)[kCtlTrunc - kCtlMaxK0];
         nobody = ((volatile uint32_t *)h->host_stats)[kCtlNoBody - kCtlMaxK0];
     }
-    // auto: the index (mirrored in LDS when it fits, read from global memory otherwise), unless
+    // auto: the index, unless
     // more than half of the slices could not be indexed completely when the table was loaded or, as
     // far as is known by now, when the index was last rebuilt -- their queries would mostly end in
     // the in-kernel scan, and use_ranked()'s search or, without it, the bucketed scan engine does

@@ -1147,7 +1147,7 @@ __device__ __forceinline__ HowFar unpack_side(const v4i &r)
 // that neither tier can answer the closest variant of the two tiers (6 writes the first tier's
 // suggestion, and how far it is from the requirements, beside every record of its lists (q.open_side);
 // 7 compares it with its own).  8 and 9: 6 and 7 with the workers of 4 and 5.
-template <bool kLds, int kMode>
+template <int kMode>
 __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, IndexView ix, QueryView q,
                                                               int32_t *__restrict__ park_mem, uint32_t lds_cap)
 {
@@ -1161,7 +1161,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t nhdr = (uint32_t)tv.S + 1u;
-    const uint32_t hdr_bytes = kLds ? lds_header_bytes(tv.S) : 0u;
+    const uint32_t hdr_bytes = lds_header_bytes(tv.S);
     const uint32_t lds_base = (uint32_t)(uintptr_t)(INFAAS_LDS uint32_t *)lds_w;
     const uint32_t lds_hdr0 = lds_base + kLdsCtrlBytes;
     const uint32_t rebase = lds_hdr0 + hdr_bytes;      // LDS address of pool offset 0
@@ -1243,7 +1243,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
     };
 
     Fields fa, fb;   // two buffers in rotation: searched now, next
-    if (kLds) {
+    {
         // Mirror the index: all global loads of a lane (its headers and up to kFillDepth x 16 bytes
         // of bodies) are issued before the first LDS write, so the fill costs about one memory
         // round trip.  The whole LDS capacity is copied, used or not, which keeps the copy
@@ -1289,7 +1289,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
         }
     }
     // worker selection: 16-bit workers of the hot steps behind the bodies (lds_cap excludes them)
-    const bool hot_w = kLds && kWorker && ix.hot_worker != nullptr;
+    const bool hot_w = kWorker && ix.hot_worker != nullptr;
     const uint32_t hotw_base = rebase + lds_cap;
     if (hot_w) {
         const uint32_t nw = (nhdr - 1u) * ix.hot_rows;   // 16-bit entries; the array has 8 more behind them
@@ -1398,21 +1398,14 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
                                        : (ok ? own : (uint32_t)tv.S);
             // the slice a parked record names
             sl_of[k] = kSecond ? (uint32_t)cur.tk[k] : (kSuggest ? (inside ? own : (uint32_t)tv.S) : s);
-            if (kLds) {
-                const v2u h = lmem.ld64(lds_hdr0 + s * kLdsHdrBytes);
-                body[k] = h.x & ((1u << kLdsAddrBits) - 1u); y[k] = h.y; rec[k] = h.y & 0xFFFFu;
-                rbase[k] = h.x >> kLdsAddrBits;
-            } else {
-                const uint4 h = ix.hdr[s];
-                body[k] = h.x; y[k] = h.y; rec[k] = h.z;
-                rbase[k] = h.y & ((1u << kRowHiField) - 1u);
-            }
+            const v2u h = lmem.ld64(lds_hdr0 + s * kLdsHdrBytes);
+            body[k] = h.x & ((1u << kLdsAddrBits) - 1u); y[k] = h.y; rec[k] = h.y & 0xFFFFu;
+            rbase[k] = h.x >> kLdsAddrBits;
             keys[k] = (y[k] >> kHdrK0Shift) & 0x3Fu;   // Re of the first body
             dd[k] = acc_threshold(cur.am[k], acc_base_m1);
             lim[k] = (uint32_t)cur.sl[k];
         }
-        if (kLds) search_bodies<kPerThread>(lmem, nit, body, keys, dd, lim, m);
-        else search_bodies<kPerThread>(gmem, nit, body, keys, dd, lim, m);
+        search_bodies<kPerThread>(lmem, nit, body, keys, dd, lim, m);
         bool df[kPerThread];
 #pragma unroll
         for (int k = 0; k < kPerThread; ++k) {
@@ -1425,7 +1418,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
             // step reads and reports.
             const bool inl = step < ix.hot_rows;
             const uint32_t at = inl ? body[k] - 2u * step : body[k];
-            p_lrow[k] = kLds ? (int32_t)lmem.ld16(at, 2u) : (int32_t)gmem.ld16(at, 2u);
+            p_lrow[k] = (int32_t)lmem.ld16(at, 2u);
             p_base[k] = (rbase[k] >> ((step * ix.row_hi_bits) & 31u)) & row_hi_mask;
             p_grow[k] = *(const int32_t *)((const char *)ix.step_row + ((hit && !inl) ? (rec[k] + step) * 4u : 0u));
             p_inl[k] = inl;
@@ -1500,13 +1493,10 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
         const int32_t s_ld = __hip_atomic_load(e + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         const bool final_miss = kSuggest && have && ((uint32_t)s_ld & kParkFinal);
         const uint32_t s = have ? ((uint32_t)s_ld & ~kParkFinal) : (uint32_t)tv.S;   // idle lanes: the empty slice
-        uint32_t y = 0, rec = 0, lbody = rebase, gbody = 0;
-        bool resident = false;
-        if (kLds) {
-            const v2u h = lmem.ld64(lds_hdr0 + s * kLdsHdrBytes);
-            resident = !(h.y & kHdrPark);
-            lbody = h.x & ((1u << kLdsAddrBits) - 1u); y = h.y; rec = h.y & 0xFFFFu;
-        }
+        const v2u h = lmem.ld64(lds_hdr0 + s * kLdsHdrBytes);
+        const bool resident = !(h.y & kHdrPark);
+        const uint32_t lbody = h.x & ((1u << kLdsAddrBits) - 1u);
+        uint32_t y = h.y, rec = h.y & 0xFFFFu, gbody = 0;
         if (__ballot(!resident)) {   // slices without a body in LDS: header from global memory
             const uint4 g = ix.hdr[resident ? (uint32_t)tv.S : s];
             if (!resident) { y = g.y; rec = g.z; gbody = g.x; }
@@ -1523,7 +1513,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
         bool done = final_miss;
         // bodies in global memory (the first one only if the main loop could not use an LDS copy):
         // both are searched together, level by level, so that one body's trips to memory hide the other's
-        const bool need_g0 = have && indexed && kLds && !resident && !done;
+        const bool need_g0 = have && indexed && !resident && !done;
         const bool need_g1 = have && indexed && keys1 != 0u && !resident && !done;
         if (__ballot(need_g0 | need_g1)) {
             const uint32_t bd[2] = {need_g0 ? gbody : 0u, need_g1 ? gbody + size0 : 0u};
@@ -1540,7 +1530,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
         }
         // second body of a slice whose bodies are in LDS
         const bool need_l1 = have && indexed && keys1 != 0u && resident && !done;
-        if (kLds && __ballot(need_l1)) {
+        if (__ballot(need_l1)) {
             const uint32_t bd[1] = {need_l1 ? lbody + size0 : rebase}, ks[1] = {need_l1 ? keys1 : 2u};
             uint32_t m[1];
             search_bodies<1>(lmem, nit, bd, ks, dd, lim, m);
@@ -1602,7 +1592,7 @@ __global__ __launch_bounds__(kSelThreads) void k_index_select(TableView tv, Inde
             int32_t sug = ans;
             HowFar mine{3, 0, 0};   // how far the suggestion is from the requirements
             const bool in_lds = by_index && resident, in_mem = by_index && !resident;
-            if (kLds && __ballot(in_lds)) {
+            if (__ballot(in_lds)) {
                 const ClosestStep c = closest_step(lmem, nit, in_lds ? lbody : rebase, in_lds ? keys0 : 2u,
                                                    in_lds ? keys1 : 0u, dd[0], slo, min_acc, acc_base_m1);
                 if (in_lds && c.step >= 0) { sug = ix.step_row[rec + (uint32_t)c.step]; mine = c.how; }
@@ -1756,34 +1746,24 @@ hipError_t launch_index_select(const TableView &tv, const IndexView &ix, const Q
                                int32_t *park_mem, uint32_t lds_bytes, int num_cus, hipStream_t st, const LaunchEvents *ev)
 {
     const int blocks = index_select_blocks(num_cus);
-    if (lds_bytes > 0) {
-        const uint32_t fixed = kLdsCtrlBytes + lds_header_bytes(tv.S);
-        lds_bytes = fixed + ((lds_bytes - fixed) & ~15u);
-        auto kernel = q.pass == 1 ? k_index_select<true, 1> : q.pass == 2 ? k_index_select<true, 2> :
-                      q.pass == 3 ? k_index_select<true, 3> : q.pass == 4 ? k_index_select<true, 4> :
-                      q.pass == 5 ? k_index_select<true, 5> : q.pass == 6 ? k_index_select<true, 6> :
-                      q.pass == 7 ? k_index_select<true, 7> : q.pass == 8 ? k_index_select<true, 8> :
-                      q.pass == 9 ? k_index_select<true, 9> : k_index_select<true, 0>;
-        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds_bytes);
-        if (e != hipSuccess) return e;
-        // the worker modes keep the 16-bit workers of the hot steps behind the bodies
-        uint32_t hot = 0;
-        const bool worker_pass = q.pass == 4 || q.pass == 5 || q.pass == 8 || q.pass == 9;
-        if (worker_pass && ix.hot_worker) hot = ((uint32_t)tv.S * ix.hot_rows * 2u + 15u) & ~15u;
-        if (hot + 1024u > lds_bytes - fixed) hot = 0;   // (never with a sensible table; the kernel then must not look for them)
-        IndexView ixk = ix;
-        if (!hot) ixk.hot_worker = nullptr;
-        return launch_kernel(ev, kernel, dim3((unsigned)blocks), dim3((unsigned)kSelThreads), lds_bytes, st, tv, ixk, q,
-                             park_mem, lds_bytes - fixed - hot);
-    }
-    auto kernel = q.pass == 1 ? k_index_select<false, 1> : q.pass == 2 ? k_index_select<false, 2> :
-                  q.pass == 3 ? k_index_select<false, 3> : q.pass == 4 ? k_index_select<false, 4> :
-                  q.pass == 5 ? k_index_select<false, 5> : q.pass == 6 ? k_index_select<false, 6> :
-                  q.pass == 7 ? k_index_select<false, 7> : q.pass == 8 ? k_index_select<false, 8> :
-                  q.pass == 9 ? k_index_select<false, 9> : k_index_select<false, 0>;
-    return launch_kernel(ev, kernel, dim3((unsigned)blocks), dim3((unsigned)kSelThreads), kLdsCtrlBytes, st, tv, ix, q,
-                         park_mem, 0u);
+    const uint32_t fixed = kLdsCtrlBytes + lds_header_bytes(tv.S);
+    if (lds_bytes <= fixed) return hipErrorInvalidValue;   // (no mirror: nothing sends a call here)
+    lds_bytes = fixed + ((lds_bytes - fixed) & ~15u);
+    auto kernel = q.pass == 1 ? k_index_select<1> : q.pass == 2 ? k_index_select<2> : q.pass == 3 ? k_index_select<3> :
+                  q.pass == 4 ? k_index_select<4> : q.pass == 5 ? k_index_select<5> : q.pass == 6 ? k_index_select<6> :
+                  q.pass == 7 ? k_index_select<7> : q.pass == 8 ? k_index_select<8> : q.pass == 9 ? k_index_select<9> : k_index_select<0>;
+    hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds_bytes);
+    if (e != hipSuccess) return e;
+    // the worker modes keep the 16-bit workers of the hot steps behind the bodies
+    uint32_t hot = 0;
+    const bool worker_pass = q.pass == 4 || q.pass == 5 || q.pass == 8 || q.pass == 9;
+    if (worker_pass && ix.hot_worker) hot = ((uint32_t)tv.S * ix.hot_rows * 2u + 15u) & ~15u;
+    if (hot + 1024u > lds_bytes - fixed) hot = 0;   // (never with a sensible table; the kernel then must not look for them)
+    IndexView ixk = ix;
+    if (!hot) ixk.hot_worker = nullptr;
+    return launch_kernel(ev, kernel, dim3((unsigned)blocks), dim3((unsigned)kSelThreads), lds_bytes, st, tv, ixk, q,
+                         park_mem, lds_bytes - fixed - hot);
 }
 
 }  // namespace infaas

@@ -138,14 +138,13 @@ struct IndexView {
                          // order of their numbers: bytes (20 bits) | build number (12) | steps (20) | truncated (12);
                          // the other build leaves kRoomNone in every entry
     // Groups.  When the bodies of all slices need more than twice one compute unit's LDS, the tasks are dealt, in
-    // order, to num_groups groups whose bodies do: group g owns the tasks [group_task0[g],
-    // group_task0[g + 1]), the bytes [g * region_bytes, (g + 1) * region_bytes) of the pool (every region
+    // order, to num_groups groups, each with allocation counters of its own: group g owns
+    // the bytes [g * region_bytes, (g + 1) * region_bytes) of the pool (every region
     // starts with a copy of the empty dummy body) and the entries [g * group_step_cap, ...) of step_row;
     // a slice that finds its group's region full is stored behind the regions.  num_groups == 1: one
     // region, the whole pool.
     uint32_t num_groups, region_bytes, group_step_cap;
     const uint16_t *task_group;   // [T] group of every task; null when num_groups == 1
-    const int32_t *group_task0;   // [num_groups + 1]
     uint32_t *gctrl;              // [2 num_groups] per group: bytes of its region and steps handed out
     // Lines: the steps once more, for searches straight from global memory (layout below).
     uint8_t *lines;      // [kLinePlanes][S + 1] lines of 128 bytes; slice S is the empty one
@@ -305,8 +304,7 @@ hipError_t launch_index_build(const TableView &tv, const IndexView &ix, hipStrea
 // Both tables of a state-aware handle in one launch.
 hipError_t launch_index_build(const TableView &ta, const IndexView &ia, const TableView &tb, const IndexView &ib, hipStream_t st,
                               const LaunchEvents *ev = nullptr);
-// lds_bytes: dynamic LDS of the lookup kernel when the index is mirrored in LDS, 0 to read it
-// from global memory.  park_mem: index_park_bytes() of device memory (16-byte aligned) for the
+// lds_bytes: dynamic LDS of the lookup kernel, for its mirror of the index.  park_mem: index_park_bytes() of device memory (16-byte aligned) for the
 // queues of parked queries; its size does not depend on the number of queries.
 hipError_t launch_index_select(const TableView &tv, const IndexView &ix, const QueryView &q,
                                int32_t *park_mem, uint32_t lds_bytes, int num_cus, hipStream_t st, const LaunchEvents *ev = nullptr);
