@@ -23,7 +23,7 @@ constexpr uint32_t kLineOpenLds = (kLineDrain + kLineThreads * kLineQueries) * 1
 // instead of 20): 64M queries on 1000 tasks of 100 variants on average 684 us.
 __global__ __launch_bounds__(kLineThreads) void k_line_select(TableView tv, IndexView ix, QueryView q, int32_t tile)
 {
-    extern __shared__ __align__(16) v4i l_open[];   // queries set aside: {query, latency bound, threshold, slice}
+    extern __shared__ __align__(16) v4i l_open[];   // queries set aside: {query, latency bound, accuracy bound, slice}
     __shared__ uint32_t l_st[kLookupStats], l_count;
     publish_index_stats(tv);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -41,11 +41,11 @@ __global__ __launch_bounds__(kLineThreads) void k_line_select(TableView tv, Inde
     auto finish = [&](uint32_t first, uint32_t count) {
         const bool have = first + (uint32_t)lane < count;
         const v4i e = l_open[have ? first + (uint32_t)lane : first];
-        const uint32_t s = have ? (uint32_t)e.w : (uint32_t)tv.S;
+        const uint32_t s = have ? (uint32_t)e.w : (uint32_t)tv.S, d = line_threshold(ix, e.z, acc_base_m1);
         const uint4 rh = tv.rank_hdr[s];
         const bool scan = have && rh.w != 0u;
         uint32_t plane;
-        const uint32_t code = follow_lines(ix, have && !scan ? kCodeOpen : kCodeNone, s, (uint32_t)e.z, (uint32_t)e.y, tv.S, plane);
+        const uint32_t code = follow_lines(ix, have && !scan ? kCodeOpen : kCodeNone, s, d, (uint32_t)e.y, tv.S, plane);
         const bool hit = code < kCodeOpen;
         int32_t ans = hit ? (ix.line_rows() ? (int32_t)(code & row_mask) : ix.step_row[ix.hdr[s].z + (code & row_mask)]) : -1;
         st[1] += (uint32_t)__builtin_popcountll(__ballot(hit && plane > 1u));
@@ -54,8 +54,7 @@ __global__ __launch_bounds__(kLineThreads) void k_line_select(TableView tv, Inde
         if (scanned) {
             st[3] += (uint32_t)__builtin_popcountll(scanned);
             const uint4 none = make_uint4(0u, 0u, 0u, 0u);
-            const int32_t am = q.min_acc[have ? e.x : 0];
-            const int32_t row = ranked_first_fit<false>(tv, scan ? rh : none, am, (uint32_t)e.y);
+            const int32_t row = ranked_first_fit<false>(tv, scan ? rh : none, e.z, (uint32_t)e.y);
             ans = scan ? row : ans;
         }
         st[4] += (uint32_t)__builtin_popcountll(__ballot(have && ans < 0));
@@ -73,7 +72,6 @@ __global__ __launch_bounds__(kLineThreads) void k_line_select(TableView tv, Inde
         lds_barrier();
         const uint32_t waiting = l_count;
         if (waiting >= kLineDrain) finish_all(waiting);
-        uint32_t slice[kLineQueries], thr[kLineQueries], lim[kLineQueries];
         const bool whole = aligned && base + tile <= q.n;
         v4i f[4][kGroups];
         if (whole) {   // (every byte is used once: non-temporal)
@@ -95,28 +93,26 @@ __global__ __launch_bounds__(kLineThreads) void k_line_select(TableView tv, Inde
                     f[2][g][e] = in ? q.min_acc[i] : 0; f[3][g][e] = in ? q.bidx[i] : -1;
                 }
         }
-#pragma unroll
-        for (int g = 0; g < kGroups; ++g)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint32_t t = (uint32_t)f[0][g][e], b = (uint32_t)f[3][g][e];
-                const bool ok = (t < (uint32_t)tv.T) & (b < (uint32_t)tv.B) & (f[1][g][e] >= 0);   // (others: the empty slice)
-                slice[4 * g + e] = ok ? t * (uint32_t)tv.B + b : (uint32_t)tv.S;
-                thr[4 * g + e] = line_threshold(ix, f[2][g][e], acc_base_m1);
-                lim[4 * g + e] = (uint32_t)f[1][g][e];
-            }
-        __syncthreads();   // the fields of the whole tile are there: from here on lines only
+        // the fields of the whole tile are there: from here on lines only
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
             if (!mine(g)) continue;
             const int64_t i = base + g * 4 * kLineThreads + tid * 4;
             v4i r;
             uint64_t m[4];
-            uint32_t total = 0;
+            uint32_t total = 0, slice[4], thr[4], lim[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int k = 4 * g + e;
-                const uint32_t code = lookup_lines<false>(ix.lines, slice[k] * kLineBytes, thr[k], lim[k], row_mask);
+                const uint32_t t = (uint32_t)f[0][g][e], b = (uint32_t)f[3][g][e];
+                const bool ok = (t < (uint32_t)tv.T) & (b < (uint32_t)tv.B) & (f[1][g][e] >= 0);   // (others: the empty slice)
+                slice[e] = ok ? t * (uint32_t)tv.B + b : (uint32_t)tv.S;
+                thr[e] = line_threshold(ix, f[2][g][e], acc_base_m1);
+                lim[e] = (uint32_t)f[1][g][e];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t code = lookup_lines<false>(ix.lines, slice[e] * kLineBytes, thr[e], lim[e], row_mask);
                 r[e] = code < kCodeOpen ? (int32_t)(code & row_mask) : -1;
                 m[e] = __ballot(code >= kCodeOpen && code < kCodeNone);
                 total += (uint32_t)__builtin_popcountll(m[e]);
@@ -127,8 +123,7 @@ __global__ __launch_bounds__(kLineThreads) void k_line_select(TableView tv, Inde
                 at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int k = 4 * g + e;
-                    if ((m[e] >> lane) & 1u) l_open[at + lanes_below(m[e])] = v4i{(int32_t)(i + e), (int32_t)lim[k], (int32_t)thr[k], (int32_t)slice[k]};
+                    if ((m[e] >> lane) & 1u) l_open[at + lanes_below(m[e])] = v4i{(int32_t)(i + e), (int32_t)lim[e], f[2][g][e], (int32_t)slice[e]};
                     at += (uint32_t)__builtin_popcountll(m[e]);
                 }
                 st[0] += total;
@@ -136,7 +131,7 @@ __global__ __launch_bounds__(kLineThreads) void k_line_select(TableView tv, Inde
             if (!ix.line_rows()) {   // entries name steps
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (r[e] >= 0) r[e] = ix.step_row[ix.hdr[slice[4 * g + e]].z + (uint32_t)r[e]];
+                    if (r[e] >= 0) r[e] = ix.step_row[ix.hdr[slice[e]].z + (uint32_t)r[e]];
             }
             if (whole) {
                 __builtin_nontemporal_store(r, (v4i *)(q.out + i));
