@@ -568,9 +568,12 @@ bool mirror_pays(const IndexShape &x, int64_t n)
 {
     return x.room > 0 && n > 350000 && 50.0 * x.outside + 2300.0 * x.open + 1.5e6 / (double)n < 4.7;
 }
-// ... and where it is not, from how many queries on a tile at a time is ahead of a lane per query (8000 slices, 900,000 queries 13.6 and 14.8, 1.05M
-// 15.5 and 15.9; 64M queries, binned by group of tasks whose bodies fit one LDS, 729, so 459).
-constexpr int64_t kLineQueries = 900000;
+// ... and where it is not, from how many queries on a tile at a time is ahead of a lane per query.  us, a lane per query / a tile at a time, for
+// 600,000 / 900,000 / 1.3M / 1.6M / 2.5M / 5M queries, arrays of up to three calls (of 5M no more) in the last-level cache: 1000 tasks of 100
+// variants on average 10.3 / 12.6, 12.4 / 14.1, 16.2 / 17.7, 18.9 / 19.1, 25.7 / 26.7, 60 / 46; 400 of 60 9.3 / 10.8, 11.9 / 12.6, 15.6 / 16.3, 18.3 / 17.6, 25.0 /
+// 24.9, 58 / 44; 100 of 200 8.7 / 10.6, 11.3 / 12.1, 15.4 / 15.9, 18.2 / 17.2, 24.3 / 24.5, 55 / 46; 2000 of 20 8.4 / 9.9, 9.9 / 11.4, 12.9 / 15.8, 15.2 / 16.5, 20.3 /
+// 25.0, 48 / 43.  (64M queries on 8000 slices, binned by group of tasks whose bodies fit one LDS, 684, so 453.)
+constexpr int64_t kTileQueries = 1500000;
 // With suggestions (b null), and in two tiers (a the Active one, which all queries visit), whether a lane per query straight from memory is
 // ahead of the mirror.  Both are a start and a time per query, here in us and us per million; the crossing moves with the steps per slice (fewer
 // steps: more queries without an answer, each of them a drain and a second tier for the mirror), with the share of the bodies outside and
@@ -626,7 +629,7 @@ bool memory_pays(const IndexShape &a, const IndexShape *b, bool workers, bool cl
 hipError_t launch_select(infaas_sel *h, const QueryView &q, int32_t *park, hipStream_t st, const LaunchEvents *ev = nullptr)
 {
     const IndexShape x = shape_of(h);
-    h->last_route = mirror_pays(x, q.n) ? INFAAS_SEL_ROUTE_MIRROR : q.n >= kLineQueries ? INFAAS_SEL_ROUTE_TILES : INFAAS_SEL_ROUTE_MEMORY;
+    h->last_route = mirror_pays(x, q.n) ? INFAAS_SEL_ROUTE_MIRROR : q.n >= kTileQueries ? INFAAS_SEL_ROUTE_TILES : INFAAS_SEL_ROUTE_MEMORY;
     if (h->last_route == INFAAS_SEL_ROUTE_MIRROR) return launch_index_select(h->tv, h->ix, q, park, h->index_lds_bytes, h->num_cus, st, ev);
     if (h->last_route == INFAAS_SEL_ROUTE_TILES) return launch_line_select(h->tv, h->ix, q, h->num_cus, st, ev);
     return launch_direct_select(h->tv, h->ix, q, false, h->num_cus, st, ev);

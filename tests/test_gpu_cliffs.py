@@ -85,7 +85,7 @@ def test_cliff_tables_a_tile_at_a_time(oracle_lib, kind):
     q = query_args(workloads.make_queries(1, n=60_000))
     sel = make_selector(tb, engine=2)
     many = Repeated(sel, sel.select, q, [oracle_lib.select(*table_args(tb), *q)])
-    for n, route in ((899_999, MEMORY), (900_000, TILES), (1_234_567, TILES)):
+    for n, route in ((1_499_999, MEMORY), (1_500_000, TILES), (2_234_567, TILES)):
         many.check(n, route, kind)
         info = sel.info()
         assert info["lookup_scanned"] > 1000

@@ -73,7 +73,7 @@ def test_both_sides_of_the_limit(oracle_lib, kind):
     assert (sel.info()["index_groups"] > 1) == (kind in ("groups", "few_groups", "no_mirror"))
     assert sel.info()["lookup_route"] == 0
     many = Repeated(sel, sel.select, qs, [oracle_lib.select(*table_args(tb), *qs)])
-    limit = many.last_from_memory(1_500_001)
+    limit = many.last_from_memory(2_000_001)
     many.check(limit, MEMORY, kind)
     info = sel.info()
     assert info["lookup_parked"] == limit and info["lookup_global_body"] > limit // 4

@@ -1,12 +1,11 @@
-"""The group-by-group selection: tables whose staircase index does not fit one compute unit's LDS
-have their tasks dealt to groups that do, and batches of a million queries or more are binned by
-group, looked up with one group's index in LDS per workgroup, and put back into query order.  Every
-answer is compared with the CPU oracle."""
+"""Tables whose staircase index takes more than twice one compute unit's LDS have their tasks dealt to groups, each with a
+region of the index and counters of its own; large batches on them go a tile of queries per workgroup at a time, a line
+of memory per query.  Every answer is compared with the CPU oracle."""
 import numpy as np
 import pytest
 
 import workloads
-from gpu_util import gpu_select, make_selector, query_args, table_args, to_dev
+from gpu_util import MEMORY, TILES, gpu_select, make_selector, query_args, table_args, to_dev
 from test_gpu_parity import _assert_equal_everywhere, _staircase_table, _table
 
 pytestmark = pytest.mark.gpu
@@ -22,7 +21,7 @@ def test_groups_ragged_unaligned_and_invalid_queries(oracle_lib):
     (unknown task, bad batch index, negative bound) mixed in."""
     import torch
     tb = workloads.make_table(3)
-    n = 1_300_001
+    n = 2_100_001
     q = workloads.make_queries(3, n=n)
     rng = np.random.default_rng(31)
     task, slo, acc, bidx = (x.copy() for x in query_args(q))
@@ -42,10 +41,11 @@ def test_groups_ragged_unaligned_and_invalid_queries(oracle_lib):
         sel.select(*dev, out, n=n)
         torch.cuda.synchronize()
         _assert_equal_everywhere(out.cpu().numpy(), want, f"groups, arrays shifted by {shift}")
-    # exactly one tile, one query more, one less than the threshold of the path (which then is not taken)
-    for m in (1 << 20, (1 << 20) + 1, (1 << 20) - 1, 16384 * 65):
+    # whole tiles for every workgroup, one query more and one less, the least size of the path, and one less (which does not go there)
+    for m in (8192 * 256, 8192 * 256 + 1, 8192 * 256 - 1, 1_500_000, 1_499_999):
         got = gpu_select(sel, task[:m], slo[:m], acc[:m], bidx[:m])
         _assert_equal_everywhere(got, want[:m], f"groups, N={m}")
+        assert sel.info()["lookup_route"] == (TILES if m >= 1_500_000 else MEMORY)
     sel.destroy()
 
 
@@ -54,13 +54,13 @@ def test_groups_follow_load_reports(oracle_lib):
     next batch sees the new load."""
     tb = workloads.make_table(3)
     sel = make_selector(tb, engine=0)
-    sel.reserve(1_500_000)
+    sel.reserve(1_600_000)
     queue = tb.queue_us.copy()
     for step in range(3):
         up = workloads.make_load_update(3, tb.V, chunk=step + 1, fraction=0.3)
         sel.update_load(to_dev(up.variant_idx), to_dev(up.queue_us))
         oracle_lib.update_load(queue, up.variant_idx, up.queue_us)
-        q = workloads.make_queries(3, n=1_500_000, chunk=step + 1)
+        q = workloads.make_queries(3, n=1_600_000, chunk=step + 1)
         _say(f"groups after report {step}")
         got = gpu_select(sel, *query_args(q))
         want = oracle_lib.select(*table_args(tb, queue), *query_args(q))
@@ -75,7 +75,7 @@ def test_groups_with_overflowing_regions_long_and_missing_staircases(oracle_lib)
     with 300 steps (more than the index keeps: rank-ordered scan), one whose accuracies span more
     than 16 bits (no index at all) and two without variants.  A load report then slows the first
     rows down: every staircase grows to 40 steps, far more than the groups' regions hold, so most
-    slices are stored behind the regions and answered from global memory; a second report restores
+    slices are stored behind the regions; a second report restores
     half of the tasks."""
     rng = np.random.default_rng(77)
     T0, n0 = 12_000, 40
@@ -95,7 +95,7 @@ def test_groups_with_overflowing_regions_long_and_missing_staircases(oracle_lib)
     info = sel.info()
     _say(f"groups, staircases: groups={info['index_groups']} bytes={info['index_bytes']} truncated={info['index_truncated']}")
     assert info["index_groups"] >= 4 and info["index_truncated"] >= 21
-    n = 1_200_000
+    n = 1_600_000
     qt = rng.integers(0, T, n)
     special = rng.random(n) < 0.08
     qt[special] = T0 + rng.integers(0, 23, int(special.sum()))
@@ -112,6 +112,7 @@ def test_groups_with_overflowing_regions_long_and_missing_staircases(oracle_lib)
         _assert_equal_everywhere(got, want, label)
         assert len(np.unique(want)) > 5000
         info = sel.info()
+        assert info["lookup_route"] == TILES
         _say(f"{label}: parked {info['lookup_parked']} second {info['lookup_second_body']} "
              f"memory {info['lookup_global_body']} scanned {info['lookup_scanned']} none {info['lookup_unanswered']}")
         return info
@@ -134,12 +135,11 @@ def test_groups_with_overflowing_regions_long_and_missing_staircases(oracle_lib)
 
 
 def test_groups_in_a_graph(oracle_lib):
-    """The group-by-group call allocates nothing once its scratch exists: captured into a HIP graph
-    with the load report in front of it and replayed with new inputs."""
+    """A tile at a time, with the load report in front of it, captured into a HIP graph and replayed with new inputs."""
     import torch
     from test_gpu_graph import _capture, _fill
     tb = workloads.make_table(3)
-    n = 1_100_000
+    n = 1_600_000
     sel = make_selector(tb, engine=0)
     sel.reserve(n)
     qs = [workloads.make_queries(3, n=n, chunk=c) for c in range(2)]

@@ -58,6 +58,6 @@ def test_tables_that_the_mirror_does_not_pay_for(oracle_lib, call, kind):
     qs = (rng.integers(0, tb.num_tasks, q.N).astype(np.int32), *query_args(q)[1:3], rng.integers(0, tb.B, q.N).astype(np.int32))
     sel, want = _handle(oracle_lib, call, tb, 3, qs)
     many = Repeated(sel, getattr(sel, call), qs, want)
-    for n in (899_999, 900_000, 3_000_001):
-        many.check(n, TILES if call == "select" and n >= 900_000 else MEMORY, f"{call} {kind}")
+    for n in (1_499_999, 1_500_000, 3_000_001):
+        many.check(n, TILES if call == "select" and n >= 1_500_000 else MEMORY, f"{call} {kind}")
     sel.destroy()
