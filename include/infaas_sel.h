@@ -57,11 +57,11 @@ enum {
 
 /* infaas_sel_config.flags, bits 0-3: which search runs inside infaas_sel_select. */
 enum {
-    /* Default: the staircase index (per slice, the variants no cheaper variant dominates; a
-     * query is two binary searches and a bit-set intersection), mirrored in one compute unit's
-     * LDS when it fits; when it does not, or the batch is small, queries read it from global memory.  Queries the index cannot decide
-     * (its per-slice capacity was exceeded) are finished by a rank-ordered scan inside the same
-     * kernel, so results never depend on the engine.  While more than half of the slices exceed the
+    /* Default: the staircase index (per slice, the variants no cheaper variant dominates).  Where one compute
+     * unit's LDS holds it, or nearly, and the batch is large, it is mirrored there, and a query is two
+     * binary searches and a bit-set intersection; else a query reads a line of 16 variants from global
+     * memory.  Queries the index cannot decide (its per-slice capacity was exceeded) are finished in rank
+     * order inside the same kernel, so results never depend on the engine.  While more than half of the slices exceed the
      * capacity, slices are searched in rank order through levels of running extremes instead. */
     INFAAS_SEL_ENGINE_AUTO = 0,
     /* Exhaustive scan only: queries bucketed by (task, batch) slice, slice staged in LDS,
@@ -474,7 +474,7 @@ enum {
     INFAAS_SEL_K_SCAN_WIDE = 5,  /* scan engine: device-wide path for large slices */
     INFAAS_SEL_K_FINISH_WIDE = 6,/* scan engine: decode the device-wide minima */
     INFAAS_SEL_K_INDEX_BUILD = 7,/* staircase index (re)build */
-    INFAAS_SEL_K_INDEX_SELECT = 8,/* staircase index lookup, one lane per query */
+    INFAAS_SEL_K_INDEX_SELECT = 8,/* staircase index lookup, whichever way (INFAAS_SEL_ROUTE_*) */
     INFAAS_SEL_K_UPDATE_STATE = 9,/* state report (given, or derived from the instances' states): masks of the rank-ordered columns */
     INFAAS_SEL_K_WORKER_REPORT = 10,/* utilisation and instance-load report */
     INFAAS_SEL_K_WORKER_TABLES = 11,/* worker of every variant */
@@ -510,15 +510,15 @@ typedef struct {
     int32_t max_segment;        /* most variants in one task */
     int32_t lds_segment_limit;  /* effective value */
     int32_t wide_segments;      /* tasks handled by the device-wide scan path */
-    int32_t index_in_lds;       /* 1 when the lookup kernel mirrors the index in LDS (all of it, or
+    int32_t index_in_lds;       /* 1 when there is a lookup through a mirror of the index in LDS (of all of it, or
                                    as many slices as fit; the others are read from global memory) */
     int32_t index_truncated;    /* slices whose staircase was cut at its capacity or not stored */
     int32_t index_max_steps;    /* longest staircase of any slice (as stored) */
     int32_t index_hot_rows;     /* steps per slice whose caller row is kept beside the index in LDS */
     int64_t index_bytes;        /* size of the staircase index (as of the latest build a selection has run behind) */
     int64_t index_steps;        /* steps over all slices */
-    int64_t table_bytes;        /* device bytes of the variant store and of the levels and sorted blocks that slices
-                                   are searched through in rank order */
+    int64_t table_bytes;        /* device bytes of the variant store, of the levels and sorted blocks that slices
+                                   are searched through in rank order, and of the lines (512 bytes per slice) */
     int64_t scratch_bytes;      /* device bytes of scratch currently reserved */
     /* The most recent index lookup on this handle (of a state-aware call in two launches: the
      * Inactive tier's): the queries that were set aside, and what became of them.  By lookup_route:
@@ -533,9 +533,8 @@ typedef struct {
     int64_t lookup_global_body; /* ... answered by a first group read from global memory (slice not in LDS) */
     int64_t lookup_scanned;     /* ... sent through the rank-ordered scan of the slice */
     int64_t lookup_unanswered;  /* ... that ended without a feasible variant */
-    int32_t index_groups;       /* 1: one LDS holds (part of) the whole index; more: the tasks are dealt to this many
-                                   groups whose staircases fit one LDS each, and calls of a million queries or more
-                                   read one line of memory per query */
+    int32_t index_groups;       /* more than 1: the index takes more than twice one compute unit's LDS, and its tasks are
+                                   dealt to this many groups, each with a region of the index of its own */
     int32_t lookup_route;       /* INFAAS_SEL_ROUTE_*: how the most recent selection was looked up */
 } infaas_sel_info;
 int infaas_sel_get_info(infaas_sel_t *h, infaas_sel_info *out);

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_util import DeviceQueries, make_selector, query_args, table_args, to_dev
+from gpu_util import MEMORY, MIRROR, DeviceQueries, make_selector, query_args, table_args, to_dev
 from test_gpu_parity import _random_queries, _random_table, _staircase_queries, _staircase_table
 
 pytestmark = pytest.mark.gpu
@@ -129,9 +129,9 @@ def test_case1_state_and_load_reports(oracle_lib):
 
 
 def test_case1_config3_and_config2(oracle_lib):
-    """Configuration 3's table (most slices outside LDS: suggestions from the index copies in global
-    memory) with 2M queries, and configuration 2 at its full 16M queries: every element."""
-    for cfg, n in ((3, 2_000_000), (2, None)):
+    """Configuration 3's table (most slices outside LDS: straight from memory) with 2M queries, and
+    configuration 2 at its full 16M queries (through the mirrors): every element."""
+    for cfg, n, route in ((3, 2_000_000, MEMORY), (2, None, MIRROR)):
         tb = workloads.make_table(cfg)
         st = workloads.make_states(cfg, tb.V)
         q = workloads.make_queries(cfg, n=n)
@@ -139,6 +139,7 @@ def test_case1_config3_and_config2(oracle_lib):
         sel.load_states(st.state, st.load_us)
         var, tier, sug = _check(oracle_lib, sel, tb, st.state, st.load_us, query_args(q), f"config{cfg}")
         assert ((var < 0) & (sug >= 0)).sum() > 10_000
+        assert sel.info()["lookup_route"] == route
         sel.destroy()
 
 

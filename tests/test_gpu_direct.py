@@ -244,8 +244,8 @@ LENGTHS = [1, 6, 7, 8, 9, 15, 16, 17, 23, 24, 25, 30, 31, 32, 38, 39, 61, 62, 63
 
 @pytest.mark.parametrize("steps", LENGTHS)
 def test_bodies_of_every_length(oracle_lib, steps):
-    """Six slices, whose bodies fit L1, so that every lane searches them by itself: bounds that meet each key exactly, miss it by
-    one, meet all or none."""
+    """Six slices: bounds that meet each key exactly, miss it by one, meet all or none.  Straight from memory and, where the index holds
+    the slices completely, in their bodies in the mirror."""
     tb = _staircase_table(3, steps)
     rows = np.arange(tb.V)
     acc = np.concatenate([tb.acc_bp[rows] + d for d in (-1, 0, 1)] + [np.full(tb.V, x) for x in (-2**31, 2**31 - 1)])
@@ -259,16 +259,20 @@ def test_bodies_of_every_length(oracle_lib, steps):
     sel = make_selector(tb, engine=2)
     _assert_equal_everywhere(gpu_select(sel, *q), want, f"{steps} steps")
     assert (want >= 0).any() and (want < 0).any()
+    if steps <= 62:
+        Repeated(sel, sel.select, q, [want]).check(400_001, MIRROR, f"{steps} steps")
+        closest = Repeated(sel, sel.select_closest, q, oracle_lib.select_closest(*table_args(tb), *q))
+        closest.check(closest.least_beyond(400_001, 2_000_000, MIRROR), MIRROR, f"{steps} steps, closest")
     assert _pool_bytes(sel) <= 24 * 1024
     sel.destroy()
 
 
 @pytest.mark.parametrize("steps", LENGTHS)
 def test_many_bodies_of_every_length(oracle_lib, steps):
-    """Four lanes read a body's keys, eight each, where the bodies are more than L1 holds: staircases that end in front of, at and
-    behind every lane's share, in the first body and in the second, and bounds that meet a key exactly, miss it by one, meet all
-    or none.  Batches that give a wavefront 16, 32 and 64 queries; every call, half of the tasks in either tier (whose
-    own staircases have as many steps); and the same on tables as small as in the test above."""
+    """Staircases that end in front of, at and behind every lane's share of a line, and bounds that meet a key exactly, miss it by one,
+    meet all or none, on tables as small as in the test above and on ones whose lines are more than L1 holds.  Batches that give a
+    wavefront 16, 32 and 64 queries; every call, half of the tasks in either tier (whose own staircases have as many steps); where
+    the index holds the small tables' slices completely, through the mirrors too."""
     rng = np.random.default_rng([71, steps])
     body = sum(14 * ((k + 2) // 2 * 2) for k in (min(steps, 31), min(steps, 62) - 31) if k > 0)
     for half, large in ((2, False), (-(-110_000 // (2 * body)), True)):
@@ -289,7 +293,7 @@ def test_many_bodies_of_every_length(oracle_lib, steps):
         want = oracle_lib.select(*table_args(tb), *q)
         closest = oracle_lib.select_closest(*table_args(tb), *q)
         assert (want >= 0).any() and (want < 0).any()
-        for size in (3001, 50_001, 74_001, 90_001):   # (suggestions turn to the lookup kernel above 75,000 where slices have second bodies)
+        for size in (3001, 50_001, 74_001, 90_001):
             cut = tuple(x[:size] for x in q)
             _assert_equal_everywhere(gpu_select(sel, *cut), want[:size], f"{steps} steps N={size}")
             for g, w in zip(gpu_select_closest(sel, *cut), closest):
@@ -303,6 +307,9 @@ def test_many_bodies_of_every_length(oracle_lib, steps):
                 many = tuple(np.tile(x, 2)[:size] for x in q)
                 for g, w in zip(call(sel, *many), want):
                     _assert_equal_everywhere(g, np.tile(w, 2)[:size], f"{steps} steps {call.__name__} N={size}")
+            if not large and steps <= 62:
+                method = sel.select_tiered if call is gpu_select_tiered else sel.select_tiered_closest
+                Repeated(sel, method, q, want).check(6_000_001, MIRROR, f"{steps} steps {call.__name__}")
         assert (_pool_bytes(sel) > 96 * 1024) == large
         sel.destroy()
 

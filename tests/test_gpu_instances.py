@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_util import make_selector, query_args, table_args, to_dev
+from gpu_util import MIRROR, Repeated, make_selector, query_args, table_args, to_dev
 from test_gpu_parity import _random_queries, _random_table
 from test_gpu_workers import _random_cluster, cluster_args, gpu_select_workers, load_cluster
 
@@ -173,7 +173,7 @@ def test_workers_from_the_state_derivation(oracle_lib, B):
     sel.load_states(state, load)
     load_cluster(sel, (variant_hw, worker_hw, util, inst_variant, inst_worker, iload))
     sel.load_instance_states(ist)
-    q = _random_queries(rng, 6, B, 300_001, span=50)   # more than the two tables' limits: through the LDS mirrors too
+    q = _random_queries(rng, 6, B, 5001, span=50)   # every other turn so many of them that they go through the LDS mirrors
 
     def states():
         idx = rng.permutation(I)[:max(1, I // 3)].astype(np.int32)
@@ -200,7 +200,10 @@ def test_workers_from_the_state_derivation(oracle_lib, B):
                                     (workers, loads), (states, loads), (loads, states), (loads, workers))):
         for report in reports:
             report()
-        some = q if turn % 2 else tuple(x[:5001] for x in q)
-        _check(oracle_lib, sel, tb, load, (variant_hw, worker_hw, util, inst_variant, inst_worker, iload), ist, some, f"turn {turn}",
-               queue=queue)
+        cl = (variant_hw, worker_hw, util, inst_variant, inst_worker, iload)
+        if turn % 2 == 0:
+            _check(oracle_lib, sel, tb, load, cl, ist, q, f"turn {turn}", queue=queue)
+        else:
+            want = oracle_lib.select_instances(*table_args(tb, queue), load, *cl, ist, *q)
+            Repeated(sel, sel.select_workers, q, want).check(4_000_001, MIRROR, f"turn {turn}")
     sel.destroy()

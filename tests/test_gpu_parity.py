@@ -207,7 +207,7 @@ def _staircase_queries(rng, tb, n_queries, n, lat0=100_000):
 def test_long_staircases(oracle_lib, engine, steps):
     """Slices whose staircase fills one index body exactly (31), needs the second one (32..62), or
     exceeds the index capacity (63, 300: what the bodies leave open is finished in rank order).  Both straight
-    from memory and, in _compare, through the lookup kernel's mirror."""
+    from memory and, in _compare, through the lookup kernel's mirror or (63, 300) a tile at a time."""
     rng = np.random.default_rng(steps)
     tb = _staircase_table(5, steps)
     qs = _staircase_queries(rng, tb, 40_000, steps)

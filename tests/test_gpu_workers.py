@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_util import DeviceQueries, make_selector, query_args, table_args, to_dev
+from gpu_util import MEMORY, DeviceQueries, make_selector, query_args, table_args, to_dev
 from test_gpu_parity import _random_queries, _random_table, _staircase_queries, _staircase_table
 
 pytestmark = pytest.mark.gpu
@@ -207,7 +207,7 @@ def test_workers_config2_every_query(oracle_lib):
 
 def test_workers_config3_every_query(oracle_lib):
     """Config 3's table (1,000 tasks, 8,000 slices: only part of either index fits in LDS, so both
-    tiers also answer from the copies in global memory) with 4M queries: variant, tier and worker of
+    tiers are answered straight from memory) with 4M queries: variant, tier and worker of
     every query against the oracle."""
     cfg, n = 3, 4_000_000
     tb = workloads.make_table(cfg)
@@ -222,7 +222,7 @@ def test_workers_config3_every_query(oracle_lib):
     want = oracle_lib.select_workers(*table_args(tb), st.state, st.load_us, *cluster_args(wk), *query_args(q))
     for g, w in zip(got, want):
         assert np.array_equal(g, w)
-    assert sel.info()["lookup_global_body"] > 0
+    assert sel.info()["lookup_global_body"] > 0 and sel.info()["lookup_route"] == MEMORY
     assert all((want[1] == t).sum() > 1000 for t in (0, 1, 2))
     assert np.array_equal(got[0] >= 0, got[1] > 0) and np.array_equal(got[0] >= 0, got[2] >= 0)
     assert (tb.task_id[got[0][got[0] >= 0]] == q.task[got[0] >= 0]).all()
