@@ -1230,13 +1230,16 @@ int tiered_impl(infaas_sel_t *h, int64_t N, const int32_t *d_task, const int32_t
     hipStream_t st = (hipStream_t)hip_stream;
     // One kernel against two mirrors and two launches.
     const IndexShape xa = shape_of(h), xb = shape_of(h->inactive);
-    const bool direct = memory_pays(xa, &xb, workers, closest, N);
-    // The lists are allocated for direct calls too: the limits follow the index, and the same call after a report
-    // may need them where nothing can be allocated (under capture, after an eager call to warm up).  A direct call
-    // that is itself captured does without.
+    bool direct = memory_pays(xa, &xb, workers, closest, N);
+    // The lists are allocated for direct calls too: the choice follows the index, and the same call after a report
+    // may need them where nothing can be allocated (under capture, after an eager call to warm up).  A call that is
+    // itself captured and finds none does without.
     const int64_t most = std::min(N, kMaxTierPass);
     int rc = INFAAS_SEL_OK;
-    if (!open_there(h, most, closest) && !(direct && is_captured(st))) rc = ensure_open(h, most, closest);
+    if (!open_there(h, most, closest)) {
+        if (is_captured(st)) direct = true;
+        else rc = ensure_open(h, most, closest);
+    }
     if (rc == INFAAS_SEL_OK && workers) rc = refresh_workers(h, st);
     if (rc != INFAAS_SEL_OK) return rc;
     // The Active tier's lookup writes all result arrays and lists the valid queries it could not

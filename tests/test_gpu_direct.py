@@ -194,16 +194,20 @@ def test_suggestions_around_their_own_limit(oracle_lib):
     sel.destroy()
 
 
-def test_a_small_call_captured_without_warm_up(oracle_lib):
-    """A call that needs no lists may be captured before any other; its replays answer, and the eager call behind
-    them allocates the lists."""
+@pytest.mark.parametrize("n", [3001, 400_001 * 15])
+def test_a_call_captured_without_warm_up(oracle_lib, n):
+    """A call may be captured before any other: it goes straight from memory, which needs no lists, at a size too that would go
+    through the mirrors.  Its replays answer, and the eager call behind them allocates the lists."""
     import torch
     rng = np.random.default_rng(4)
     tb = _random_table(rng, 9, np.full(9, 40), 3)
     state, load = rng.integers(0, 4, tb.V).astype(np.int32), rng.integers(0, 50_000, tb.V).astype(np.int32)
-    n = 3001
+    times = 1 if n < 10_000 else 15
+    n //= times
     sets = [_random_queries(rng, 9, 3, n) for _ in range(3)]
-    want = [oracle_lib.select_case1(*table_args(tb), state, load, *q) for q in sets]
+    want = [[np.tile(w, times) for w in oracle_lib.select_case1(*table_args(tb), state, load, *q)] for q in sets]
+    sets = [[np.tile(x, times) for x in q] for q in sets]
+    n *= times
     loaded = make_selector(tb, engine=0)          # (so that the kernel's code is on the device)
     loaded.load_states(state, load)
     gpu_case1(loaded, *sets[0])
@@ -216,7 +220,7 @@ def test_a_small_call_captured_without_warm_up(oracle_lib):
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         sel.select_tiered_closest(*dq, *out)
-    assert sel.info()["scratch_bytes"] == before
+    assert sel.info()["scratch_bytes"] == before and sel.info()["lookup_route"] == MEMORY
     for rnd in range(4):
         for d, x in zip(dq, sets[rnd % 3]):
             d.copy_(torch.from_numpy(x))
@@ -229,6 +233,9 @@ def test_a_small_call_captured_without_warm_up(oracle_lib):
     sel.select_tiered_closest(*dq, *out)
     torch.cuda.synchronize()
     assert sel.info()["scratch_bytes"] >= before + 32 * n
+    assert sel.info()["lookup_route"] == (MEMORY if n < 10_000 else MIRROR)
+    for g, w in zip(out, want[rnd % 3]):
+        _assert_equal_everywhere(g.cpu().numpy(), w, "eager")
     loaded.destroy()
     sel.destroy()
 
